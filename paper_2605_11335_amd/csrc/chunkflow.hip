@@ -362,12 +362,13 @@ int prof_resolve(cf_ctx* c) {
     if (c->prof_pending.empty()) return CF_OK;
     CF_HIP(c, hipDeviceSynchronize());
     if (c->ktimes.empty()) {
-        c->ktimes.resize(2 * K_COUNT);
-        for (int i = 0; i < 2 * K_COUNT; ++i) {
+        static const char* const tile_name[GEMM_TILES] = {"/256x256", "/128x128", "/128x256"};
+        c->ktimes.resize(GEMM_TILES * K_COUNT);
+        for (int i = 0; i < GEMM_TILES * K_COUNT; ++i) {
             memset(&c->ktimes[i], 0, sizeof(cf_kernel_time));
             const bool gemm = strncmp(kKidName[i % K_COUNT], "gemm_", 5) == 0;
             snprintf(c->ktimes[i].name, sizeof c->ktimes[i].name, "%s%s", kKidName[i % K_COUNT],
-                     gemm ? (i < K_COUNT ? "/256x256" : "/128x128") : "");
+                     gemm ? tile_name[i / K_COUNT] : "");
         }
     }
     for (auto& pe : c->prof_pending) {
@@ -939,7 +940,8 @@ int cf_plan_linear(int32_t m_rows, int32_t n_features, int32_t* tile_rows) {
         return cf_fail(nullptr, CF_ERR_ARG, "cf_plan_linear: positive sizes and a result pointer are required");
     GemmArgs g{};
     g.M = m_rows; g.n0 = 0; g.n1 = n_features; g.N = n_features;
-    *tile_rows = gemm_tile(g) == 0 ? 256 : 128;
+    g.K = 3072;                          // the widths this is asked for; the choice hardly depends on it
+    *tile_rows = gemm_tile(g) == GEMM_256x256 ? 256 : 128;
     return CF_OK;
 }
 

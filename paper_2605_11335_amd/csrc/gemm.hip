@@ -1,437 +1,9 @@
-// bf16 MFMA GEMM for the block's linear layers (App. B: the projection and MLP terms):
-//   out[m, n] = epilogue( sum_k A[m, k] * W[n, k] + bias[n] ),  fp32 accumulation.
-// A is the activation matrix [M, K] (row-major, bf16); W is a linear weight stored
-// [out_features, in_features] inside the block's weight blob, so both operands are
-// K-contiguous and one launch can cover any panel [n0, n1) of output features -- the unit
-// in which streamed weights become usable chunk by chunk (Sec. 3.2).
-//
-// Tiling: a workgroup of 4 waves owns a BM x BN output tile; each wave owns a
-// (BM/2) x (BN/2) quadrant built from 32x32x16 bf16 MFMAs.  The MFMA "A" operand is the
-// weight fragment and the "B" operand the activation fragment, so an accumulator lane holds
-// one token row and 4 consecutive output features per register quad: epilogues then load
-// bias/gate and store results 4 features at a time.  K is consumed in slabs of 64 that are
-// copied global -> LDS directly (no register staging), double-buffered; 16-byte chunks of each
-// 128-byte LDS row are XOR-swizzled so that the fragment reads of consecutive rows spread over
-// all banks.  The k-steps are software-pipelined: LDS fragment reads of step s+1 and the
-// slab hand-over barrier run behind the MFMAs of step s.
-#include <type_traits>
+// Host side of the linear layers: argument checks, the choice of the tile, dispatch; and the matrix-core rate
+// diagnostics.  The kernels themselves are in gemm_kernel.h.
+#include <algorithm>
 
 #include "common.h"
 #include "kernels.h"
-
-namespace {
-
-constexpr int EPI_SPLIT_GELU_ERF = 2;  // kernel variant of EPI_SPLIT_GELU with the erf form of the activation
-constexpr int BK = 64;                 // K slab (bf16 elements) = 128 bytes per LDS row
-constexpr int STAGES = 2;              // slabs resident in LDS: one being multiplied, one in flight
-constexpr int ROWB = BK * 2;           // bytes per LDS row
-constexpr int CHUNKS = BK / 8;         // 16-byte chunks per LDS row
-constexpr int KSTEPS = BK / 16;        // MFMA k-steps per slab
-
-// slot of chunk c in row `row` is c ^ swz(row): conflict-free for 16-byte fragment reads of
-// consecutive rows on a 32-bank (8 lanes per phase) as well as a 64-bank (16 lanes) LDS
-__device__ __forceinline__ int swz(int row) { return ((row >> 1) & 7) ^ ((row & 1) << 2); }
-
-// 16 bytes per lane from global memory straight into LDS: lane l's data lands at lds + 16*l
-// (`lds` must be wave-uniform).
-__device__ __forceinline__ void lds_load16(const void* gptr, void* lds) {
-    __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)gptr,
-                                     (void __attribute__((address_space(3)))*)lds, 16, 0, 0);
-}
-
-// The same through a buffer resource: the address is base + voff (per lane) + soff (uniform), and
-// lanes whose offset lies past the resource's size fetch zeros, which takes care of ragged tile
-// edges.  The memory pipeline takes these a little faster than loads with a 64-bit address per lane.
-__device__ __forceinline__ void lds_bload16(__amdgpu_buffer_rsrc_t rsrc, uint32_t voff, uint32_t soff, void* lds) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (void __attribute__((address_space(3)))*)lds, 16, voff, soff, 0, 0);
-}
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint64_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)(bytes > 0xffffffffull ? 0xffffffffu : (uint32_t)bytes), 0x00020000);
-}
-
-// Slab hand-over: this wave's global->LDS loads (the next slab) have landed and its LDS reads
-// (the last fragments of the current slab) have returned; after the barrier that holds for the
-// whole workgroup, so the next slab may be read and the current one overwritten.
-__device__ __forceinline__ void slab_handover() {
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-// One workgroup's tile of one problem: workgroup `bid` of the `nblk` that problem owns.
-template <int BM, int BN, int EPI>
-__device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, uint32_t bid, uint32_t nblk) {
-    constexpr int WM = BM / 2, WN = BN / 2;        // wave quadrant
-    constexpr int MT = WM / 32, NT = WN / 32;      // 32x32 MFMA tiles per wave
-    constexpr int A_LOADS = BM * CHUNKS / 256;     // 16-byte global loads per thread per slab
-    constexpr int W_LOADS = BN * CHUNKS / 256;
-    constexpr int RPL = 1024 / ROWB;               // LDS rows written by one wave-load
-    constexpr int A_STAGE = BM * ROWB, W_STAGE = BN * ROWB;
-
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    char* const sA = smem;                         // [STAGES][BM][ROWB] activations
-    char* const sW = smem + STAGES * A_STAGE;      // [STAGES][BN][ROWB] weights
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wm0 = (wave & 1) * WM, wn0 = (wave >> 1) * WN;
-    const int li = lane & 31, lg = lane >> 5;
-
-    // logical tile: XCD-contiguous id, then groups of GM row-tiles walked feature-tile-major
-    const int tiles_m = (g.M + BM - 1) / BM;
-    const int tiles_n = (g.n1 - g.n0 + BN - 1) / BN;
-    const uint32_t lid = xcd_contiguous_id(bid, nblk);
-    // row-tile groups of about 8, all of one size: a short last group would walk every weight tile once more
-    const int n_groups = max(1, (tiles_m + 4) / 8);
-    const int GM = (tiles_m + n_groups - 1) / n_groups;
-    const int group = lid / (GM * tiles_n);
-    const int first_m = group * GM;
-    const int gsz = min(tiles_m - first_m, GM);
-    const int tm = first_m + (lid % (GM * tiles_n)) % gsz;
-    const int tn = (lid % (GM * tiles_n)) / gsz;
-    const int m0 = tm * BM;
-    const int n0 = g.n0 + tn * BN;
-
-    // Slab copies go global -> LDS directly (no register staging).  One such load writes the
-    // wave's 64 x 16 bytes to consecutive LDS addresses, i.e. RPL rows; which 16-byte chunk of
-    // its row a lane fetches is chosen so that the chunk lands in its swizzled slot.
-    const int uw = __builtin_amdgcn_readfirstlane(wave);
-    uint32_t a_voff[A_LOADS], w_voff[W_LOADS];   // byte offsets from the tile's first row
-    uint64_t w_src[W_LOADS];                     // blob offsets, for the tile that holds the resident/streamed split
-#pragma unroll
-    for (int j = 0; j < A_LOADS; ++j) {
-        const int row = (j * 4 + uw) * RPL + lane / CHUNKS;
-        const int c = (lane % CHUNKS) ^ swz(row);
-        a_voff[j] = (uint32_t)row * (uint32_t)g.lda * 2u + c * 16;
-    }
-#pragma unroll
-    for (int j = 0; j < W_LOADS; ++j) {
-        const int row = (j * 4 + uw) * RPL + lane / CHUNKS;
-        const int c = (lane % CHUNKS) ^ swz(row);
-        w_voff[j] = (uint32_t)row * (uint32_t)g.K * 2u + c * 16;
-        w_src[j] = g.w_off + ((uint64_t)min(n0 + row, g.N - 1) * g.K + c * 8) * 2;
-    }
-    // does the byte where the blob switches buffers fall inside this tile's weight rows?
-    const uint64_t t_begin = g.w_off + (uint64_t)n0 * g.K * 2, t_end = g.w_off + (uint64_t)min(n0 + BN, g.N) * g.K * 2;
-    const bool straddle = g.W.split > t_begin && g.W.split < t_end;
-    // resources that end with the tile's last valid row: the rows of a ragged tile beyond it read zeros
-    const __amdgpu_buffer_rsrc_t a_rsrc = make_rsrc(g.A + (size_t)m0 * g.lda, ((uint64_t)(g.M - 1 - m0) * g.lda + g.K) * 2);
-    const __amdgpu_buffer_rsrc_t w_rsrc = make_rsrc(wv_ptr(g.W, t_begin), t_end - t_begin);
-
-    floatx16 acc[NT][MT];
-#pragma unroll
-    for (int i = 0; i < NT; ++i)
-#pragma unroll
-        for (int j = 0; j < MT; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-    // LDS byte offsets of this lane's fragment rows (row*ROWB) and their swizzle keys
-    int a_off[MT], a_key[MT], w_off[NT], w_key[NT];
-#pragma unroll
-    for (int j = 0; j < MT; ++j) { const int row = wm0 + j * 32 + li; a_off[j] = row * ROWB; a_key[j] = swz(row); }
-#pragma unroll
-    for (int i = 0; i < NT; ++i) { const int row = wn0 + i * 32 + li; w_off[i] = row * ROWB; w_key[i] = swz(row); }
-
-    const int KT = g.K / BK;
-    bf16x8 fa[2][MT], fw[2][NT];
-
-    // slab kt_ -> stage kt_&1
-    auto issue_slab = [&](auto slow, int kt_) {
-        const int k0 = kt_ * BK * 2, st = kt_ & 1;
-        char* dA = sA + st * A_STAGE + uw * 1024;
-        char* dW = sW + st * W_STAGE + uw * 1024;
-#pragma unroll
-        for (int j = 0; j < A_LOADS; ++j) lds_bload16(a_rsrc, a_voff[j], k0, dA + j * 4096);
-#pragma unroll
-        for (int j = 0; j < W_LOADS; ++j) {
-            if (decltype(slow)::value) lds_load16(wv_ptr(g.W, w_src[j] + k0), dW + j * 4096);
-            else lds_bload16(w_rsrc, w_voff[j], k0, dW + j * 4096);
-        }
-    };
-    auto issue_one = [&](auto slow, int kt_, int q) {        // q-th load of slab kt_ (A loads first)
-        const int k0 = kt_ * BK * 2, st = kt_ & 1;
-        if (q < A_LOADS) {
-            lds_bload16(a_rsrc, a_voff[q], k0, sA + st * A_STAGE + uw * 1024 + q * 4096);
-        } else if (q < A_LOADS + W_LOADS) {
-            const int j = q - A_LOADS;
-            if (decltype(slow)::value) lds_load16(wv_ptr(g.W, w_src[j] + k0), sW + st * W_STAGE + uw * 1024 + j * 4096);
-            else lds_bload16(w_rsrc, w_voff[j], k0, sW + st * W_STAGE + uw * 1024 + j * 4096);
-        }
-    };
-    auto load_frags = [&](int buf, const char* cA, const char* cW, int kk) {
-        const int c = kk * 2 + lg;
-#pragma unroll
-        for (int j = 0; j < MT; ++j) fa[buf][j] = *(const bf16x8*)(cA + a_off[j] + ((c ^ a_key[j]) << 4));
-#pragma unroll
-        for (int i = 0; i < NT; ++i) fw[buf][i] = *(const bf16x8*)(cW + w_off[i] + ((c ^ w_key[i]) << 4));
-    };
-    // One slab = KSTEPS k-steps, software-pipelined: the fragments of step s+1 are read from LDS
-    // while the MFMAs of step s run.  The hand-over to the next slab sits before the slab's last
-    // step: its barrier, the first fragment reads of the next slab and the issue of the slab after
-    // that all hide behind that step's MFMAs.
-    auto slab = [&](auto slow, auto handover, auto issue, int kt) {
-        const char* cA = sA + (kt & 1) * A_STAGE;
-        const char* cW = sW + (kt & 1) * W_STAGE;
-        const char* nA = sA + ((kt + 1) & 1) * A_STAGE;
-        const char* nW = sW + ((kt + 1) & 1) * W_STAGE;
-#pragma unroll
-        for (int kk = 0; kk < KSTEPS; ++kk) {
-            const int cur = kk & 1, nxt = cur ^ 1;
-            const bool last = kk + 1 == KSTEPS;
-            if (!last) {
-                load_frags(nxt, cA, cW, kk + 1);
-            } else if (decltype(handover)::value) {
-                __builtin_amdgcn_sched_barrier(0);     // keep the previous step's MFMAs above the barrier
-                slab_handover();                       // slab kt+1 landed; slab kt fully read
-                __builtin_amdgcn_sched_barrier(0);
-                load_frags(nxt, nA, nW, 0);
-            }
-            if (last && decltype(issue)::value) {
-                // the loads of slab kt+2 go out between this step's MFMAs, in this order
-                constexpr int LPM = (A_LOADS + W_LOADS + MT * NT - 1) / (MT * NT);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int q = 0; q < MT * NT; ++q) {
-                    acc[q / MT][q % MT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[cur][q / MT], fa[cur][q % MT],
-                                                                                  acc[q / MT][q % MT], 0, 0, 0);
-#pragma unroll
-                    for (int u = 0; u < LPM; ++u) issue_one(slow, kt + 2, q * LPM + u);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < NT; ++i)
-#pragma unroll
-                    for (int j = 0; j < MT; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[cur][i], fa[cur][j], acc[i][j], 0, 0, 0);
-                if (!last || decltype(handover)::value) {
-                    // fragment reads go out two per MFMA at the head of the step
-#pragma unroll
-                    for (int q = 0; q < (MT + NT) / 2; ++q) {
-                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-                    }
-                    __builtin_amdgcn_sched_group_barrier(0x008, MT * NT - (MT + NT) / 2, 0);
-                }
-            }
-        }
-    };
-    using T_ = std::true_type;
-    using F_ = std::false_type;
-    auto run = [&](auto slow) {
-        issue_slab(slow, 0);
-        slab_handover();
-        if (KT > 1) issue_slab(slow, 1);
-        load_frags(0, sA, sW, 0);
-        int kt = 0;
-        for (; kt + 2 < KT; ++kt) slab(slow, T_{}, T_{}, kt);
-        if (kt + 1 < KT) { slab(slow, T_{}, F_{}, kt); ++kt; }
-        slab(slow, F_{}, F_{}, kt);
-    };
-    if (straddle) run(T_{}); else run(F_{});
-
-    // ---- epilogue.  In the accumulators a lane owns one token row and 4 consecutive features per
-    // register quad.  Bias / GELU / gate are applied there, then each wave transposes its quadrant
-    // through its own slice of LDS so that global stores are 16 bytes per lane with 16 (or 8)
-    // consecutive lanes covering one contiguous row segment.
-    constexpr bool OUT_BF16 = (EPI != EPI_GATE_RESID);
-    constexpr bool ACT_ERF = (EPI == EPI_SPLIT_GELU_ERF);
-    constexpr int PASSES = OUT_BF16 ? 1 : 2;               // fp32 rows are staged in two column halves
-    constexpr int NTP = NT / PASSES;                       // 32-column tiles per pass
-    constexpr int ELT = OUT_BF16 ? 2 : 4;
-    constexpr int RB = NTP * 32 * ELT;                     // staged row bytes (= WN * 2 either way)
-    constexpr int PITCH = RB + (OUT_BF16 ? 16 : 32);       // padded: conflict-free quad writes
-    constexpr int CPR = RB / 16, RPI = 64 / CPR;           // 16-byte chunks per row, rows per store
-    static_assert(4 * WM * PITCH <= 160 * 1024, "staging exceeds LDS");
-    {   // the epilogue is a scope of its own: its lane coordinates shadow the main loop's
-        // lane coordinates are derived afresh (lane from the wave's bit count, wave from its scalar copy)
-        // rather than kept in vector registers across the main loop
-        const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), wave = uw;
-        const int wm0 = (wave & 1) * WM, wn0 = (wave >> 1) * WN;
-        const int li = lane & 31, lg = lane >> 5;
-        // Bias of the wave's features, in accumulator order: 4 consecutive features per (feature tile, register
-        // quad).  Fetched in one go: taken one by one in the epilogue, each would cost a memory round trip.
-        uint32x2 bias_raw[NT][4];
-#pragma unroll
-        for (int i = 0; i < NT; ++i)
-#pragma unroll
-            for (int vb = 0; vb < 4; ++vb) bias_raw[i][vb] = uint32x2{0u, 0u};
-        if (g.has_bias) {
-#pragma unroll
-            for (int i = 0; i < NT; ++i)
-#pragma unroll
-                for (int vb = 0; vb < 4; ++vb) {
-                    const int n = min(n0 + wn0 + i * 32 + vb * 8 + lg * 4, g.N - 4);
-                    bias_raw[i][vb] = *(const uint32x2*)wv_ptr(g.W, g.bias_off + 2ull * n);
-                }
-        }
-        slab_handover();                       // every wave is done reading the slabs; the bias loads flew meanwhile
-        char* const stg = smem + wave * (WM * PITCH);
-#pragma unroll
-        for (int p = 0; p < PASSES; ++p) {
-#pragma unroll
-            for (int ii = 0; ii < NTP; ++ii) {
-                const int i = p * NTP + ii;
-#pragma unroll
-                for (int vb = 0; vb < 4; ++vb) {
-                    const int n = min(n0 + wn0 + i * 32 + vb * 8 + lg * 4, g.N - 4);
-                    const uint32x2 bb = bias_raw[i][vb];
-                    const float b[4] = {__uint_as_float(bb.x << 16), __uint_as_float(bb.x & 0xffff0000u),
-                                        __uint_as_float(bb.y << 16), __uint_as_float(bb.y & 0xffff0000u)};
-                    const bool act = OUT_BF16 && n >= g.n_split;
-#pragma unroll
-                    for (int j = 0; j < MT; ++j) {
-                        float v[4];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) v[e] = acc[i][j][vb * 4 + e] + b[e];
-                        char* dst = stg + (j * 32 + li) * PITCH + (ii * 32 + vb * 8 + lg * 4) * ELT;
-                        if (OUT_BF16) {
-                            if (act) {
-#pragma unroll
-                                for (int e = 0; e < 4; ++e) v[e] = ACT_ERF ? gelu_erf_f32(v[e]) : gelu_tanh_f32(v[e]);
-                            }
-                            bf16x4 o;
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) o[e] = (bf16)v[e];
-                            *(bf16x4*)dst = o;
-                        } else {
-                            *(float4*)dst = make_float4(v[0], v[1], v[2], v[3]);
-                        }
-                    }
-                }
-            }
-            // coalesced write-out of this pass
-            const int col = (lane % CPR) * (16 / ELT);                         // first column of the lane's chunk
-            const int n = n0 + wn0 + p * (NTP * 32) + col;
-            if constexpr (OUT_BF16) {
-#pragma unroll
-                for (int r = 0; r < WM / RPI; ++r) {
-                    const int row = r * RPI + lane / CPR;
-                    const int m = m0 + wm0 + row;
-                    const uint4 val = *(const uint4*)(stg + row * PITCH + (lane % CPR) * 16);
-                    if (m < g.M && n < g.n1) {
-                        bf16* dst = n < g.n_split ? g.out0 + (size_t)m * g.ld0 + n
-                                                  : g.out1 + (size_t)m * g.ld1 + g.col1_off + (n - g.n_split);
-                        *(uint4*)dst = val;
-                    }
-                }
-            } else {
-                // y = resid + gate * (...), the product rounded before the sum; the gate belongs to the row's
-                // sample.  The residual rows of UB stores are fetched together: taken one by one, each store
-                // would wait out a memory round trip of its own.  Lanes outside the problem read a valid
-                // address (row M-1, column 0) and store nothing.
-                constexpr int UB = 8;
-                static_assert((WM / RPI) % UB == 0, "write-out batches");
-                const bool n_ok = n < g.n1;
-                const int nc = n_ok ? n : 0;
-                const bool has_gate = g.gate != nullptr;
-                const float* const gate_p = has_gate ? g.gate : g.resid;       // a readable address either way
-                const long gate_bs = has_gate ? g.gate_bs : 0;
-                auto write_out = [&](auto per_sample) {
-                    constexpr bool PS = decltype(per_sample)::value;
-                    floatx4 gate_c = {1.f, 1.f, 1.f, 1.f};
-                    if (!PS && has_gate) gate_c = *(const floatx4*)(gate_p + nc);
-#pragma unroll
-                    for (int r0 = 0; r0 < WM / RPI; r0 += UB) {
-                        floatx4 rr[UB], gt[UB];                // native vectors: arrays of them stay in registers
-                        size_t y_off[UB];
-                        bool ok[UB];
-#pragma unroll
-                        for (int u = 0; u < UB; ++u) {
-                            const int row = (r0 + u) * RPI + lane / CPR;
-                            const int m = m0 + wm0 + row;
-                            ok[u] = n_ok && m < g.M;
-                            const int mm = min(m, g.M - 1);
-                            int b = 0, i = mm;
-                            if (PS) { b = mm / g.rows_per_sample; i = mm - b * g.rows_per_sample; }
-                            rr[u] = *(const floatx4*)(g.resid + (size_t)b * g.resid_bs + (size_t)i * g.ldy + nc);
-                            if (PS) {
-                                const floatx4 t = *(const floatx4*)(gate_p + (size_t)b * gate_bs + nc);
-                                gt[u] = has_gate ? t : gate_c;
-                            } else {
-                                gt[u] = gate_c;
-                            }
-                            y_off[u] = (size_t)b * g.y_bs + (size_t)i * g.ldy + nc;
-                        }
-#pragma unroll
-                        for (int u = 0; u < UB; ++u) {
-                            const int row = (r0 + u) * RPI + lane / CPR;
-                            const floatx4 val = *(const floatx4*)(stg + row * PITCH + (lane % CPR) * 16);
-                            floatx4 o;
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) o[e] = __fadd_rn(rr[u][e], __fmul_rn(gt[u][e], val[e]));
-                            if (ok[u]) *(floatx4*)(g.y + y_off[u]) = o;
-                        }
-                    }
-                };
-                if (g.rows_per_sample) write_out(std::true_type{}); else write_out(std::false_type{});
-            }
-        }
-    }
-}
-
-template <int BM, int BN, int EPI>
-__global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g) {
-    gemm_tile_body<BM, BN, EPI>(g, blockIdx.x, gridDim.x);
-}
-
-// Two independent problems of one tile shape and epilogue in one launch (the text and image streams
-// of a double-stream block, App. B): a small problem's workgroups ride along with the large one's
-// instead of holding the chip for the length of their K loop.  The first problem's share of the grid
-// is padded to a multiple of 8 so that both keep the block-index-to-XCD correspondence.
-struct GemmPair {
-    GemmArgs g[2];
-    uint32_t tiles0, tiles0_pad;
-};
-template <int BM, int BN, int EPI>
-__global__ __launch_bounds__(256) void gemm_pair_kernel(GemmPair p) {
-    if (blockIdx.x < p.tiles0) gemm_tile_body<BM, BN, EPI>(p.g[0], blockIdx.x, p.tiles0);
-    else if (blockIdx.x >= p.tiles0_pad) gemm_tile_body<BM, BN, EPI>(p.g[1], blockIdx.x - p.tiles0_pad, gridDim.x - p.tiles0_pad);
-}
-
-template <int BM, int BN, int EPI>
-size_t gemm_smem() {
-    const size_t stage_bytes = (size_t)STAGES * (BM + BN) * ROWB;
-    const size_t epi_bytes = 4ull * (BM / 2) * (BN + (EPI != EPI_GATE_RESID ? 16 : 32));   // 4 x WM x PITCH
-    return stage_bytes > epi_bytes ? stage_bytes : epi_bytes;
-}
-
-template <int BM, int BN, int EPI>
-hipError_t launch(const GemmArgs& g, hipStream_t s) {
-    const int tiles_m = (g.M + BM - 1) / BM;
-    const int tiles_n = (g.n1 - g.n0 + BN - 1) / BN;
-    const size_t smem = gemm_smem<BM, BN, EPI>();
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)gemm_bf16_kernel<BM, BN, EPI>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
-    hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, EPI>), dim3(tiles_m * tiles_n), dim3(256), smem, s, g);
-    return hipGetLastError();
-}
-
-template <int BM, int BN, int EPI>
-hipError_t launch_pair(const GemmArgs& g0, const GemmArgs& g1, hipStream_t s) {
-    auto tiles = [](const GemmArgs& g) { return (uint32_t)(((g.M + BM - 1) / BM) * ((g.n1 - g.n0 + BN - 1) / BN)); };
-    GemmPair p;
-    p.g[0] = g0;
-    p.g[1] = g1;
-    p.tiles0 = tiles(g0);
-    p.tiles0_pad = (p.tiles0 + 7u) & ~7u;
-    const size_t smem = gemm_smem<BM, BN, EPI>();
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)gemm_pair_kernel<BM, BN, EPI>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
-    hipLaunchKernelGGL((gemm_pair_kernel<BM, BN, EPI>), dim3(p.tiles0_pad + tiles(g1)), dim3(256), smem, s, p);
-    return hipGetLastError();
-}
-
-}  // namespace
 
 const char* gemm_check(const GemmArgs& g) {
     if (g.M <= 0 || g.N <= 0 || g.K <= 0) return "gemm: empty shape";
@@ -460,11 +32,8 @@ const char* gemm_check(const GemmArgs& g) {
     return nullptr;
 }
 
-// Tile shape for a launch: 0 = 256x256, 1 = 128x128.  The big tile has the best arithmetic
-// intensity but needs enough tiles to cover the 256 CUs; estimated cost = rounds x tile area /
-// relative efficiency of the shape (128x128 runs two workgroups per CU).  A 256-token x 128-feature
-// tile looked better than 128x128 with operands hot in the last-level cache but was the slowest of
-// the three inside a block, where every weight byte is read once, cold; it is not built.
+// How a launch over n features fills the chip, for cutting a streamed layer into panels: estimated with the two
+// square tiles only (cost = rounds x tile area / relative efficiency of the shape).
 namespace {
 // cost of a launch over n output features in units of one round of 256x256 tiles on all CUs
 void tile_costs(int M, long n, double* c256, double* c128) {
@@ -476,14 +45,49 @@ void tile_costs(int M, long n, double* c256, double* c128) {
 }
 }  // namespace
 
-int gemm_tile(const GemmArgs& g) {
-    double c256, c128;
-    tile_costs(g.M, g.n1 - g.n0, &c256, &c128);
-    return c256 <= c128 ? 0 : 1;
+// Tile shape for a launch.  The larger a tile, the fewer bytes a CU has to take in per FLOP, but the fewer
+// workgroups there are and the longer the last round of them.  Estimated time in us = rounds x (slabs x time
+// per slab + fixed part), fitted to layers of 64 to 13640 tokens and K = 512 to 15360 with weights read cold
+// (one MI355X): a slab takes a lone 256x256 workgroup per CU 1.05 us on a nearly empty chip and 1.35 on a full
+// one, a 128x256 one 0.76 to 0.88, 128x128 0.55 alone and 1.07 for the two a CU holds.
+namespace {
+struct TileCost { int bm, bn, per_cu; double lone, full, fixed; };      // us per slab of a CU's workgroups: few CUs busy | chip full
+constexpr TileCost kTileCost[GEMM_TILES] = {
+    {256, 256, 1, 1.05, 1.35, 9.0},
+    {128, 128, 2, 0.55, 1.07, 4.5},
+    {128, 256, 1, 0.76, 0.88, 6.0},
+};
+double tile_time(const TileCost& t, long tiles, int K) {
+    const double slabs = (K + 63) / 64;
+    const long slots = 256L * t.per_cu, rest = tiles % slots;
+    double us = (double)(tiles / slots) * (slabs * t.full + t.fixed);
+    if (rest) {
+        // the last round: a CU with one workgroup where it could hold two works off its slab alone
+        const double busy = (double)std::min(rest, 256L) / 256.0;
+        const double slab = rest > 256 ? t.full : t.per_cu > 1 ? t.lone : t.lone + (t.full - t.lone) * busy;
+        us += slabs * slab + t.fixed;
+    }
+    return us;
 }
+int best_tile(const GemmArgs* const (&g)[2]) {
+    int best = 0;
+    double best_us = 0;
+    for (int i = 0; i < GEMM_TILES; ++i) {
+        const TileCost& t = kTileCost[i];
+        long tiles = 0;
+        for (const GemmArgs* p : g)
+            if (p) tiles += (long)((p->M + t.bm - 1) / t.bm) * ((p->n1 - p->n0 + t.bn - 1) / t.bn);
+        const double us = tile_time(t, tiles, g[1] ? std::max(g[0]->K, g[1]->K) : g[0]->K);
+        if (i == 0 || us < best_us) best = i, best_us = us;
+    }
+    return best;
+}
+}  // namespace
+
+int gemm_tile(const GemmArgs& g) { return best_tile({&g, nullptr}); }
 
 // How well a launch over n output features uses the chip: work in rounds of 256x256 tiles divided
-// by the estimated cost of the tile shape gemm_tile would pick (1 = whole rounds of the big tile).
+// by the estimated cost of the better square tile (1 = whole rounds of the big tile).
 double gemm_fill(int M, int n) {
     double c256, c128;
     tile_costs(M, n, &c256, &c128);
@@ -616,30 +220,24 @@ hipError_t mix_rate_launch(int iters, int waves, int reads16, int valu, int exps
     return hipErrorInvalidValue;
 }
 
-hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) {
-    const int t = gemm_tile(g);
+namespace {
+hipError_t dispatch(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s) {
     // the erf form of the activation costs some forty VALU operations per element: it gets kernels
     // of its own rather than a run-time choice inside the tanh one
-    if (g.epi == EPI_SPLIT_GELU && g.act_erf)
-        return t == 0 ? launch<256, 256, EPI_SPLIT_GELU_ERF>(g, s) : launch<128, 128, EPI_SPLIT_GELU_ERF>(g, s);
-    if (g.epi == EPI_SPLIT_GELU) return t == 0 ? launch<256, 256, EPI_SPLIT_GELU>(g, s) : launch<128, 128, EPI_SPLIT_GELU>(g, s);
-    return t == 0 ? launch<256, 256, EPI_GATE_RESID>(g, s) : launch<128, 128, EPI_GATE_RESID>(g, s);
+    if (g.epi == EPI_GATE_RESID) return gemm_launch_gate_resid(tile, g, second, s);
+    return g.act_erf ? gemm_launch_split_gelu_erf(tile, g, second, s) : gemm_launch_split_gelu(tile, g, second, s);
 }
+}  // namespace
 
-// Tile shape both problems of a pair run with, or -1 if they cannot share a launch (different
-// epilogues).  Shapes that would pick different tiles alone take the larger problem's choice.
+hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) { return dispatch(gemm_tile(g), g, nullptr, s); }
+
+// Tile shape both problems of a pair run with, or -1 if they cannot share a launch (different epilogues).
 int gemm_pair_tile(const GemmArgs& g0, const GemmArgs& g1) {
     if (g0.epi != g1.epi || g0.act_erf != g1.act_erf) return -1;
-    const GemmArgs& big = (double)g0.M * (g0.n1 - g0.n0) >= (double)g1.M * (g1.n1 - g1.n0) ? g0 : g1;
-    return gemm_tile(big);
+    return best_tile({&g0, &g1});
 }
 
 hipError_t gemm_launch_pair(const GemmArgs& g0, const GemmArgs& g1, hipStream_t s) {
     const int t = gemm_pair_tile(g0, g1);
-    if (t < 0) return hipErrorInvalidValue;
-    if (g0.epi == EPI_SPLIT_GELU && g0.act_erf)
-        return t == 0 ? launch_pair<256, 256, EPI_SPLIT_GELU_ERF>(g0, g1, s) : launch_pair<128, 128, EPI_SPLIT_GELU_ERF>(g0, g1, s);
-    if (g0.epi == EPI_SPLIT_GELU)
-        return t == 0 ? launch_pair<256, 256, EPI_SPLIT_GELU>(g0, g1, s) : launch_pair<128, 128, EPI_SPLIT_GELU>(g0, g1, s);
-    return t == 0 ? launch_pair<256, 256, EPI_GATE_RESID>(g0, g1, s) : launch_pair<128, 128, EPI_GATE_RESID>(g0, g1, s);
+    return t < 0 ? hipErrorInvalidValue : dispatch(t, g0, &g1, s);
 }

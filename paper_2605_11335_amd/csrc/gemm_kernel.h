@@ -1,0 +1,461 @@
+// bf16 MFMA GEMM for the block's linear layers (App. B: the projection and MLP terms):
+//   out[m, n] = epilogue( sum_k A[m, k] * W[n, k] + bias[n] ),  fp32 accumulation.
+// A is the activation matrix [M, K] (row-major, bf16); W is a linear weight stored
+// [out_features, in_features] inside the block's weight blob, so both operands are
+// K-contiguous and one launch can cover any panel [n0, n1) of output features -- the unit
+// in which streamed weights become usable chunk by chunk (Sec. 3.2).
+//
+// Tiling: a workgroup of 4 waves owns a BM x BN output tile; each wave owns a
+// (BM/2) x (BN/2) quadrant built from 32x32x16 bf16 MFMAs.  The MFMA "A" operand is the
+// weight fragment and the "B" operand the activation fragment, so an accumulator lane holds
+// one token row and 4 consecutive output features per register quad: epilogues then load
+// bias/gate and store results 4 features at a time.  K is consumed in slabs of 64 that are
+// copied global -> LDS directly (no register staging) into two stages; 16-byte chunks of each
+// 128-byte LDS row are XOR-swizzled so that the fragment reads of consecutive rows spread over
+// all banks.
+//
+// What bounds the loop is the rate at which a CU's L1 takes in the operands (32 bytes per clock at the
+// matrix cores' full rate on the 256 x 256 tile, against some 38 that the path moves with nothing else to
+// do), so the copies have to be on their way all the time and evenly.  A slab is therefore worked off
+// in four quadrant phases, (activation half, weight half) = (0,0) (0,1) (1,1) (1,0): each phase needs one
+// half-tile that the one before did not, reads it into registers a phase ahead, and the half-tile's LDS
+// space is refilled for the slab after next as soon as all waves have read it.  Two hand-overs per slab
+// (barriers that leave the four youngest half-tiles in flight) instead of one that waits for everything:
+// 8192-cubed 837 -> 762 us, 13640 x 9216 x 3072 651 -> 603 us, 13640 x 3072 x 14336 1169 -> 971 us
+// (the time per slab of a full chip 1.52 -> 1.33 us).
+#pragma once
+#include <type_traits>
+
+#include "common.h"
+#include "kernels.h"
+
+namespace {
+
+constexpr int EPI_SPLIT_GELU_ERF = 2;  // kernel variant of EPI_SPLIT_GELU with the erf form of the activation
+constexpr int BK = 64;                 // K slab (bf16 elements) = 128 bytes per LDS row
+constexpr int STAGES = 2;              // slabs resident in LDS: one being multiplied, one in flight
+constexpr int ROWB = BK * 2;           // bytes per LDS row
+constexpr int CHUNKS = BK / 8;         // 16-byte chunks per LDS row
+constexpr int KSTEPS = BK / 16;        // MFMA k-steps per slab
+
+// slot of chunk c in row `row` is c ^ swz(row): conflict-free for 16-byte fragment reads of
+// consecutive rows on a 32-bank (8 lanes per phase) as well as a 64-bank (16 lanes) LDS
+__device__ __forceinline__ int swz(int row) { return ((row >> 1) & 7) ^ ((row & 1) << 2); }
+
+// 16 bytes per lane from global memory straight into LDS: lane l's data lands at lds + 16*l
+// (`lds` must be wave-uniform).
+__device__ __forceinline__ void lds_load16(const void* gptr, void* lds) {
+    __builtin_amdgcn_global_load_lds((const void __attribute__((address_space(1)))*)gptr,
+                                     (void __attribute__((address_space(3)))*)lds, 16, 0, 0);
+}
+
+// The same through a buffer resource: the address is base + voff (per lane) + soff (uniform), and
+// lanes whose offset lies past the resource's size fetch zeros, which takes care of ragged tile
+// edges.  The memory pipeline takes these a little faster than loads with a 64-bit address per lane.
+__device__ __forceinline__ void lds_bload16(__amdgpu_buffer_rsrc_t rsrc, uint32_t voff, uint32_t soff, void* lds) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (void __attribute__((address_space(3)))*)lds, 16, voff, soff, 0, 0);
+}
+__device__ __forceinline__ uint32_t rsrc_bytes(uint64_t bytes) { return bytes > 0xffffffffull ? 0xffffffffu : (uint32_t)bytes; }
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00020000);
+}
+
+// Slab hand-over: this wave's global->LDS loads (the next slab) have landed and its LDS reads
+// (the last fragments of the current slab) have returned; after the barrier that holds for the
+// whole workgroup, so the next slab may be read and the current one overwritten.
+__device__ __forceinline__ void slab_handover() {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// The same where the N youngest of this wave's loads may still be in flight.
+typedef __attribute__((address_space(3))) const bf16x8 lds_frag;
+template <int N>
+__device__ __forceinline__ void handover() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (0 << 8) | ((N >> 4) << 14));
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+template <int BM, int BN, int EPI>
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx16 (&acc)[BN / 64][BM / 64], int m0, int n0, int uw, char* smem) {
+    constexpr int WM = BM / 2, WN = BN / 2;        // wave quadrant
+    constexpr int MT = WM / 32, NT = WN / 32;      // 32x32 MFMA tiles per wave
+    // ---- epilogue.  In the accumulators a lane owns one token row and 4 consecutive features per
+    // register quad.  Bias / GELU / gate are applied there, then each wave transposes its quadrant
+    // through its own slice of LDS so that global stores are 16 bytes per lane with 16 (or 8)
+    // consecutive lanes covering one contiguous row segment.
+    constexpr bool OUT_BF16 = (EPI != EPI_GATE_RESID);
+    constexpr bool ACT_ERF = (EPI == EPI_SPLIT_GELU_ERF);
+    constexpr int PASSES = OUT_BF16 || NT == 1 ? 1 : 2;    // fp32 rows are staged in two column halves
+    constexpr int NTP = NT / PASSES;                       // 32-column tiles per pass
+    constexpr int ELT = OUT_BF16 ? 2 : 4;
+    constexpr int RB = NTP * 32 * ELT;                     // staged row bytes
+    constexpr int PITCH = RB + (OUT_BF16 ? 16 : 32);       // padded: conflict-free quad writes
+    constexpr int CPR = RB / 16, RPI = 64 / CPR;           // 16-byte chunks per row, rows per store
+    static_assert(4 * WM * PITCH <= 160 * 1024, "staging exceeds LDS");
+    {
+        // lane coordinates are derived afresh (lane from the wave's bit count, wave from its scalar copy)
+        // rather than kept in vector registers across the main loop
+        const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), wave = uw;
+        const int wm0 = (wave & 1) * WM, wn0 = (wave >> 1) * WN;
+        const int li = lane & 31, lg = lane >> 5;
+        // Bias of the wave's features, in accumulator order: 4 consecutive features per (feature tile, register
+        // quad).  Fetched in one go: taken one by one in the epilogue, each would cost a memory round trip.
+        uint32x2 bias_raw[NT][4];
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int vb = 0; vb < 4; ++vb) bias_raw[i][vb] = uint32x2{0u, 0u};
+        if (g.has_bias) {
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+#pragma unroll
+                for (int vb = 0; vb < 4; ++vb) {
+                    const int n = min(n0 + wn0 + i * 32 + vb * 8 + lg * 4, g.N - 4);
+                    bias_raw[i][vb] = *(const uint32x2*)wv_ptr(g.W, g.bias_off + 2ull * n);
+                }
+        }
+        slab_handover();                       // every wave is done reading the slabs; the bias loads flew meanwhile
+        char* const stg = smem + wave * (WM * PITCH);
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+#pragma unroll
+            for (int ii = 0; ii < NTP; ++ii) {
+                const int i = p * NTP + ii;
+#pragma unroll
+                for (int vb = 0; vb < 4; ++vb) {
+                    const int n = min(n0 + wn0 + i * 32 + vb * 8 + lg * 4, g.N - 4);
+                    const uint32x2 bb = bias_raw[i][vb];
+                    const float b[4] = {__uint_as_float(bb.x << 16), __uint_as_float(bb.x & 0xffff0000u),
+                                        __uint_as_float(bb.y << 16), __uint_as_float(bb.y & 0xffff0000u)};
+                    const bool act = OUT_BF16 && n >= g.n_split;
+#pragma unroll
+                    for (int j = 0; j < MT; ++j) {
+                        float v[4];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) v[e] = acc[i][j][vb * 4 + e] + b[e];
+                        char* dst = stg + (j * 32 + li) * PITCH + (ii * 32 + vb * 8 + lg * 4) * ELT;
+                        if (OUT_BF16) {
+                            if (act) {
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) v[e] = ACT_ERF ? gelu_erf_f32(v[e]) : gelu_tanh_f32(v[e]);
+                            }
+                            bf16x4 o;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) o[e] = (bf16)v[e];
+                            *(bf16x4*)dst = o;
+                        } else {
+                            *(float4*)dst = make_float4(v[0], v[1], v[2], v[3]);
+                        }
+                    }
+                }
+            }
+            // coalesced write-out of this pass
+            const int col = (lane % CPR) * (16 / ELT);                         // first column of the lane's chunk
+            const int n = n0 + wn0 + p * (NTP * 32) + col;
+            if constexpr (OUT_BF16) {
+#pragma unroll
+                for (int r = 0; r < WM / RPI; ++r) {
+                    const int row = r * RPI + lane / CPR;
+                    const int m = m0 + wm0 + row;
+                    const uint4 val = *(const uint4*)(stg + row * PITCH + (lane % CPR) * 16);
+                    if (m < g.M && n < g.n1) {
+                        bf16* dst = n < g.n_split ? g.out0 + (size_t)m * g.ld0 + n
+                                                  : g.out1 + (size_t)m * g.ld1 + g.col1_off + (n - g.n_split);
+                        *(uint4*)dst = val;
+                    }
+                }
+            } else {
+                // y = resid + gate * (...), the product rounded before the sum; the gate belongs to the row's
+                // sample.  The residual rows of UB stores are fetched together: taken one by one, each store
+                // would wait out a memory round trip of its own.  Lanes outside the problem read a valid
+                // address (row M-1, column 0) and store nothing.
+                constexpr int UB = WM / RPI < 8 ? WM / RPI : 8;
+                static_assert((WM / RPI) % UB == 0, "write-out batches");
+                const bool n_ok = n < g.n1;
+                const int nc = n_ok ? n : 0;
+                const bool has_gate = g.gate != nullptr;
+                const float* const gate_p = has_gate ? g.gate : g.resid;       // a readable address either way
+                const long gate_bs = has_gate ? g.gate_bs : 0;
+                auto write_out = [&](auto per_sample) {
+                    constexpr bool PS = decltype(per_sample)::value;
+                    floatx4 gate_c = {1.f, 1.f, 1.f, 1.f};
+                    if (!PS && has_gate) gate_c = *(const floatx4*)(gate_p + nc);
+#pragma unroll
+                    for (int r0 = 0; r0 < WM / RPI; r0 += UB) {
+                        floatx4 rr[UB], gt[UB];                // native vectors: arrays of them stay in registers
+                        size_t y_off[UB];
+                        bool ok[UB];
+#pragma unroll
+                        for (int u = 0; u < UB; ++u) {
+                            const int row = (r0 + u) * RPI + lane / CPR;
+                            const int m = m0 + wm0 + row;
+                            ok[u] = n_ok && m < g.M;
+                            const int mm = min(m, g.M - 1);
+                            int b = 0, i = mm;
+                            if (PS) { b = mm / g.rows_per_sample; i = mm - b * g.rows_per_sample; }
+                            rr[u] = *(const floatx4*)(g.resid + (size_t)b * g.resid_bs + (size_t)i * g.ldy + nc);
+                            if (PS) {
+                                const floatx4 t = *(const floatx4*)(gate_p + (size_t)b * gate_bs + nc);
+                                gt[u] = has_gate ? t : gate_c;
+                            } else {
+                                gt[u] = gate_c;
+                            }
+                            y_off[u] = (size_t)b * g.y_bs + (size_t)i * g.ldy + nc;
+                        }
+#pragma unroll
+                        for (int u = 0; u < UB; ++u) {
+                            const int row = (r0 + u) * RPI + lane / CPR;
+                            const floatx4 val = *(const floatx4*)(stg + row * PITCH + (lane % CPR) * 16);
+                            floatx4 o;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) o[e] = __fadd_rn(rr[u][e], __fmul_rn(gt[u][e], val[e]));
+                            if (ok[u]) *(floatx4*)(g.y + y_off[u]) = o;
+                        }
+                    }
+                };
+                if (g.rows_per_sample) write_out(std::true_type{}); else write_out(std::false_type{});
+            }
+        }
+    }
+}
+
+// One tile of one problem: tokens m0.., features n0...  STRADDLE: the byte where the blob switches buffers falls
+// inside the tile's weight rows (at most one tile column of a launch), so each lane picks its base.
+template <int BM, int BN, int EPI, bool STRADDLE>
+__device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0) {
+    constexpr int WM = BM / 2, WN = BN / 2;        // wave quadrant
+    constexpr int MT = WM / 32, NT = WN / 32;      // 32x32 MFMA tiles per wave
+    constexpr int MH = MT / 2, NH = NT / 2;        // of which one half-tile of an operand feeds this many
+    constexpr int GA = BM / 32, GW = BN / 32;      // 8-row units of a half-tile per wave row (column)
+    constexpr int LA = GA / 2, LW = GW / 2;        // wave-loads (1 KiB = one unit each) per wave and half-tile
+    constexpr int A_STAGE = BM * ROWB, W_STAGE = BN * ROWB;
+
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    char* const sA = smem;                         // [STAGES][BM][ROWB] activations
+    char* const sW = smem + STAGES * A_STAGE;      // [STAGES][BN][ROWB] weights
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int wm0 = (wave & 1) * WM, wn0 = (wave >> 1) * WN;
+    const int li = lane & 31, lg = lane >> 5;
+
+    // Slab copies go global -> LDS directly (no register staging).  One such load writes the
+    // wave's 64 x 16 bytes to consecutive LDS addresses, i.e. 8 rows (a unit); which 16-byte chunk of
+    // its row a lane fetches is chosen so that the chunk lands in its swizzled slot.  A half-tile is the
+    // rows that the waves' h-th halves cover: unit (j*4 + wave) of it is unit `unit(..)` of the tile.
+    const int uw = __builtin_amdgcn_readfirstlane(wave);
+    auto unit = [](int G, int h, int idx) { return (idx / G) * 2 * G + h * G + idx % G; };
+    uint32_t a_voff[2][LA], w_voff[2][LW];         // byte offsets from the tile's first row
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int j = 0; j < LA; ++j) {
+            const int row = unit(GA, h, j * 4 + uw) * 8 + lane / CHUNKS;
+            a_voff[h][j] = (uint32_t)row * (uint32_t)g.lda * 2u + ((lane % CHUNKS) ^ swz(row)) * 16;
+        }
+#pragma unroll
+        for (int j = 0; j < LW; ++j) {
+            const int row = unit(GW, h, j * 4 + uw) * 8 + lane / CHUNKS;
+            w_voff[h][j] = (uint32_t)row * (uint32_t)g.K * 2u + ((lane % CHUNKS) ^ swz(row)) * 16;
+        }
+    }
+    const uint64_t t_begin = g.w_off + (uint64_t)n0 * g.K * 2, t_end = g.w_off + (uint64_t)min(n0 + BN, g.N) * g.K * 2;
+    // resources that end with the tile's last valid row: the rows of a ragged tile beyond it read zeros
+    const void* const a_base = g.A + (size_t)m0 * g.lda;
+    const void* const w_base = wv_ptr(g.W, t_begin);
+    const uint32_t a_bytes = rsrc_bytes(((uint64_t)(g.M - 1 - m0) * g.lda + g.K) * 2), w_bytes = rsrc_bytes(t_end - t_begin);
+
+    floatx16 acc[NT][MT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = 0; j < MT; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+    // LDS address of this lane's fragment of k-step kk in row 0 of its quadrant; rows 32 apart share the swizzle
+    lds_frag *a_frag[KSTEPS], *w_frag[KSTEPS];
+#pragma unroll
+    for (int kk = 0; kk < KSTEPS; ++kk) {
+        const int c = ((kk * 2 + lg) ^ swz(li)) << 4;
+        a_frag[kk] = (lds_frag*)(sA + (wm0 + li) * ROWB + c);
+        w_frag[kk] = (lds_frag*)(sW + (wn0 + li) * ROWB + c);
+    }
+
+    const int KT = g.K / BK;
+    bf16x8 fa[2][MH][KSTEPS], fw[2][NH][KSTEPS];
+
+    // Slab kt's copies into stage st.  Past the last slab the resources are empty: the copies of the two slabs that do
+    // not exist fetch nothing, so the loop needs no tail and its wait counts never change.
+    struct Src { __amdgpu_buffer_rsrc_t a, w; uint32_t k0; bool on; };
+    auto source = [&](int kt) {
+        const bool on = kt < KT;
+        return Src{make_rsrc(a_base, on ? a_bytes : 0u), make_rsrc(w_base, on ? w_bytes : 0u), on ? (uint32_t)kt * (BK * 2) : 0u, on};
+    };
+    auto issue_a = [&](auto st, auto h, const Src& src, int q) {
+        lds_bload16(src.a, a_voff[h.value][q], src.k0, sA + st.value * A_STAGE + unit(GA, h.value, q * 4) * 1024 + uw * 1024);
+    };
+    auto issue_w = [&](auto st, auto h, const Src& src, int q) {
+        char* const dst = sW + st.value * W_STAGE + unit(GW, h.value, q * 4) * 1024 + uw * 1024;
+        if (STRADDLE && src.on) {                  // rows past the matrix read the tile's first bytes; they are never stored
+            const uint64_t o = (uint64_t)w_voff[h.value][q] + src.k0;
+            lds_load16(wv_ptr(g.W, t_begin + (o < t_end - t_begin ? o : 0)), dst);
+        } else {
+            lds_bload16(src.w, w_voff[h.value][q], src.k0, dst);
+        }
+    };
+    // r-th of the MH (NH) * KSTEPS fragments of a half-tile
+    auto read_a = [&](auto st, auto h, int r) {
+        fa[h.value][r / KSTEPS][r % KSTEPS] =
+            a_frag[r % KSTEPS][(st.value * A_STAGE + (h.value * MH + r / KSTEPS) * 32 * ROWB) / 16];
+    };
+    auto read_w = [&](auto st, auto h, auto buf, int r) {
+        fw[buf.value][r / KSTEPS][r % KSTEPS] =
+            w_frag[r % KSTEPS][(st.value * W_STAGE + (h.value * NH + r / KSTEPS) * 32 * ROWB) / 16];
+    };
+    // One phase: the MFMAs of activation half ha with weight half hb (held in fw[buf]), with fragment reads for the
+    // phases to come between the first of them and slab copies between the last
+    auto phase = [&](auto ha, auto hb, auto buf, int n_reads, auto read, int n_issues, auto issue) __attribute__((always_inline)) {
+        constexpr int NM = KSTEPS * NH * MH;
+        int r = 0, u = 0;
+#pragma unroll
+        for (int q = 0; q < NM; ++q) {
+            const int kk = q / (NH * MH), i = (q / MH) % NH, j = q % MH;
+            acc[hb.value * NH + i][ha.value * MH + j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                fw[buf.value][i][kk], fa[ha.value][j][kk], acc[hb.value * NH + i][ha.value * MH + j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            for (; r * NM < n_reads * 2 * (q + 1) && r < n_reads; ++r) read(r);
+            for (; u * NM < n_issues * (q + 1) && u < n_issues; ++u) issue(u);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using T_ = std::true_type;
+    using F_ = std::false_type;
+    // One slab of stage st: quadrant phases (0,0) (0,1) (1,1) (1,0).  At each hand-over every wave's loads of the two
+    // half-tiles about to be read have landed and its reads of the two before have returned, so those are refilled.
+    // What may still be in flight there: the four half-tiles issued after them.
+    auto slab = [&](auto st, int kt) __attribute__((always_inline)) {
+        using SN = std::integral_constant<int, decltype(st)::value ^ 1>;
+        const Src src = source(kt + 2);
+        handover<2 * (LA + LW)>();
+        phase(I0{}, I0{}, st, NH * KSTEPS, [&](int r) { read_w(st, I1{}, SN{}, r); }, LA, [&](int u) { issue_a(st, I0{}, src, u); });
+        phase(I0{}, I1{}, SN{}, MH * KSTEPS, [&](int r) { read_a(st, I1{}, r); }, LW, [&](int u) { issue_w(st, I0{}, src, u); });
+        handover<2 * (LA + LW)>();
+        phase(I1{}, I1{}, SN{}, MH * KSTEPS, [&](int r) { read_a(SN{}, I0{}, r); }, LW, [&](int u) { issue_w(st, I1{}, src, u); });
+        phase(I1{}, I0{}, st, NH * KSTEPS, [&](int r) { read_w(SN{}, I0{}, SN{}, r); }, LA, [&](int u) { issue_a(st, I1{}, src, u); });
+    };
+    auto issue_slab = [&](auto st, int kt) {
+        const Src src = source(kt);
+#pragma unroll
+        for (int q = 0; q < LA; ++q) issue_a(st, I0{}, src, q);
+#pragma unroll
+        for (int q = 0; q < LW; ++q) issue_w(st, I0{}, src, q);
+#pragma unroll
+        for (int q = 0; q < LW; ++q) issue_w(st, I1{}, src, q);
+#pragma unroll
+        for (int q = 0; q < LA; ++q) issue_a(st, I1{}, src, q);
+    };
+    issue_slab(I0{}, 0);
+    issue_slab(I1{}, 1);
+    handover<3 * (LA + LW)>();
+#pragma unroll
+    for (int r = 0; r < MH * KSTEPS; ++r) read_a(I0{}, I0{}, r);
+#pragma unroll
+    for (int r = 0; r < NH * KSTEPS; ++r) read_w(I0{}, I0{}, I0{}, r);
+    for (int kt = 0; kt < KT; kt += 2) {           // an odd last slab is followed by one of zeros
+        slab(I0{}, kt);
+        slab(I1{}, kt + 1);
+    }
+
+    gemm_epilogue<BM, BN, EPI>(g, acc, m0, n0, uw, smem);
+}
+
+// Workgroup `bid` of the `nblk` that problem owns.
+template <int BM, int BN, int EPI>
+__device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, uint32_t bid, uint32_t nblk) {
+    // logical tile: XCD-contiguous id, then groups of GM row-tiles walked feature-tile-major
+    const int tiles_m = (g.M + BM - 1) / BM;
+    const int tiles_n = (g.n1 - g.n0 + BN - 1) / BN;
+    const uint32_t lid = xcd_contiguous_id(bid, nblk);
+    // row-tile groups of about 8, all of one size: a short last group would walk every weight tile once more
+    const int n_groups = max(1, (tiles_m + 4) / 8);
+    const int GM = (tiles_m + n_groups - 1) / n_groups;
+    const int group = lid / (GM * tiles_n);
+    const int first_m = group * GM;
+    const int gsz = min(tiles_m - first_m, GM);
+    const int m0 = (first_m + (lid % (GM * tiles_n)) % gsz) * BM;
+    const int n0 = g.n0 + (lid % (GM * tiles_n)) / gsz * BN;
+    const uint64_t t_begin = g.w_off + (uint64_t)n0 * g.K * 2, t_end = g.w_off + (uint64_t)min(n0 + BN, g.N) * g.K * 2;
+    if (g.W.split > t_begin && g.W.split < t_end) gemm_tile_run<BM, BN, EPI, true>(g, m0, n0);
+    else gemm_tile_run<BM, BN, EPI, false>(g, m0, n0);
+}
+
+template <int BM, int BN, int EPI>
+__global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g) {
+    gemm_tile_body<BM, BN, EPI>(g, blockIdx.x, gridDim.x);
+}
+
+// Two independent problems of one tile shape and epilogue in one launch (the text and image streams
+// of a double-stream block, App. B): a small problem's workgroups ride along with the large one's
+// instead of holding the chip for the length of their K loop.  The first problem's share of the grid
+// is padded to a multiple of 8 so that both keep the block-index-to-XCD correspondence.
+struct GemmPair {
+    GemmArgs g[2];
+    uint32_t tiles0, tiles0_pad;
+};
+template <int BM, int BN, int EPI>
+__global__ __launch_bounds__(256) void gemm_pair_kernel(GemmPair p) {
+    if (blockIdx.x < p.tiles0) gemm_tile_body<BM, BN, EPI>(p.g[0], blockIdx.x, p.tiles0);
+    else if (blockIdx.x >= p.tiles0_pad) gemm_tile_body<BM, BN, EPI>(p.g[1], blockIdx.x - p.tiles0_pad, gridDim.x - p.tiles0_pad);
+}
+
+template <int BM, int BN, int EPI>
+constexpr size_t gemm_smem() {
+    constexpr int WM = BM / 2, WN = BN / 2;
+    constexpr int staged_row = EPI != EPI_GATE_RESID ? WN * 2 + 16 : (WN > 32 ? WN * 2 : WN * 4) + 32;     // the epilogue's PITCH
+    constexpr size_t loop = (size_t)STAGES * (BM + BN) * ROWB, epi = 4ull * WM * staged_row;
+    return loop > epi ? loop : epi;
+}
+
+template <class Kernel>
+hipError_t allow_smem(Kernel kernel, size_t smem) {
+    return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+}
+
+template <int BM, int BN, int EPI>
+hipError_t launch(const GemmArgs& g, const GemmArgs* second, hipStream_t s) {
+    auto tiles = [](const GemmArgs& p) { return (uint32_t)(((p.M + BM - 1) / BM) * ((p.n1 - p.n0 + BN - 1) / BN)); };
+    constexpr size_t smem = gemm_smem<BM, BN, EPI>();
+    if (!second) {
+        static const hipError_t allowed = allow_smem(gemm_bf16_kernel<BM, BN, EPI>, smem);
+        if (allowed != hipSuccess) return allowed;
+        hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, EPI>), dim3(tiles(g)), dim3(256), smem, s, g);
+    } else {
+        static const hipError_t allowed = allow_smem(gemm_pair_kernel<BM, BN, EPI>, smem);
+        if (allowed != hipSuccess) return allowed;
+        GemmPair p;
+        p.g[0] = g;
+        p.g[1] = *second;
+        p.tiles0 = tiles(g);
+        p.tiles0_pad = (p.tiles0 + 7u) & ~7u;
+        hipLaunchKernelGGL((gemm_pair_kernel<BM, BN, EPI>), dim3(p.tiles0_pad + tiles(*second)), dim3(256), smem, s, p);
+    }
+    return hipGetLastError();
+}
+
+// one problem, or two in one launch, with the given tile shape
+template <int EPI>
+hipError_t launch_tile(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s) {
+    switch (tile) {
+        case GEMM_256x256: return launch<256, 256, EPI>(g, second, s);
+        case GEMM_128x128: return launch<128, 128, EPI>(g, second, s);
+        case GEMM_128x256: return launch<128, 256, EPI>(g, second, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace

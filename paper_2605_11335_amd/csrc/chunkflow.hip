@@ -362,7 +362,7 @@ int prof_resolve(cf_ctx* c) {
     if (c->prof_pending.empty()) return CF_OK;
     CF_HIP(c, hipDeviceSynchronize());
     if (c->ktimes.empty()) {
-        static const char* const tile_name[GEMM_TILES] = {"/256x256", "/128x128", "/128x256"};
+        static const char* const tile_name[GEMM_TILES] = {"/256x256", "/128x128", "/128x256", "/128x64", "/64x64"};
         c->ktimes.resize(GEMM_TILES * K_COUNT);
         for (int i = 0; i < GEMM_TILES * K_COUNT; ++i) {
             memset(&c->ktimes[i], 0, sizeof(cf_kernel_time));

@@ -49,13 +49,16 @@ void tile_costs(int M, long n, double* c256, double* c128) {
 // workgroups there are and the longer the last round of them.  Estimated time in us = rounds x (slabs x time
 // per slab + fixed part), fitted to layers of 64 to 13640 tokens and K = 512 to 15360 with weights read cold
 // (one MI355X): a slab takes a lone 256x256 workgroup per CU 1.05 us on a nearly empty chip and 1.35 on a full
-// one, a 128x256 one 0.76 to 0.88, 128x128 0.55 alone and 1.07 for the two a CU holds.
+// one, a 128x256 one 0.76 to 0.88, 128x128 0.55 alone and 1.07 for the two a CU holds,
+// 128x64 0.43 and 0.92, 64x64 0.30 and 0.51.
 namespace {
 struct TileCost { int bm, bn, per_cu; double lone, full, fixed; };      // us per slab of a CU's workgroups: few CUs busy | chip full
 constexpr TileCost kTileCost[GEMM_TILES] = {
     {256, 256, 1, 1.05, 1.35, 9.0},
     {128, 128, 2, 0.55, 1.07, 4.5},
     {128, 256, 1, 0.76, 0.88, 6.0},
+    {128, 64, 2, 0.43, 0.92, 3.5},
+    {64, 64, 2, 0.30, 0.51, 3.0},
 };
 double tile_time(const TileCost& t, long tiles, int K) {
     const double slabs = (K + 63) / 64;

@@ -374,8 +374,129 @@ __device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0)
     gemm_epilogue<BM, BN, EPI>(g, acc, m0, n0, uw, smem);
 }
 
+// The same for small tiles, which are for layers with too few large ones to give every CU a workgroup: there the time is
+// the serial walk over K, slab by slab.  A wave holds all fragments of a slab, double-buffered in registers, so a slab's
+// stage is free as soon as it has been read and S stages keep S - 1 slabs on their way, which covers the latency of
+// weights read cold; one hand-over per slab.  A lone 64x64 workgroup takes 0.30 us per slab (LDS traffic and the
+// hand-over; six more stages change nothing, two fewer cost a fifth), 128x64 0.43, against 0.55 of the 128x128 tile.
+// 576 x 3072 x 12288: 164 us with the former loop, 111 with the 128x128 tile above, 85 with 128x64 (240 workgroups);
+// 64 x 3072 x 12288: 166, 102, 63 with 64x64; 512 x 512 x 2560: 31.4, 20.5, 12.2.
+template <int BM, int BN, int S, int EPI>
+__device__ __forceinline__ void gemm_ring_run(const GemmArgs& g, int m0, int n0) {
+    constexpr int WM = BM / 2, WN = BN / 2;        // wave quadrant
+    constexpr int MT = WM / 32, NT = WN / 32;      // 32x32 MFMA tiles per wave
+    constexpr int LA = BM / 32, LW = BN / 32, L = LA + LW;     // wave-loads (8 rows each) per wave and slab
+    constexpr int STAGE = (BM + BN) * ROWB;
+
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int uw = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 31, lg = lane >> 5;
+    const int wm0 = (uw & 1) * WM, wn0 = (uw >> 1) * WN;
+
+    uint32_t a_voff[LA], w_voff[LW];               // byte offsets from the tile's first row
+#pragma unroll
+    for (int j = 0; j < LA; ++j) {
+        const int row = (j * 4 + uw) * 8 + lane / CHUNKS;
+        a_voff[j] = (uint32_t)row * (uint32_t)g.lda * 2u + ((lane % CHUNKS) ^ swz(row)) * 16;
+    }
+#pragma unroll
+    for (int j = 0; j < LW; ++j) {
+        const int row = (j * 4 + uw) * 8 + lane / CHUNKS;
+        w_voff[j] = (uint32_t)row * (uint32_t)g.K * 2u + ((lane % CHUNKS) ^ swz(row)) * 16;
+    }
+    const uint64_t t_begin = g.w_off + (uint64_t)n0 * g.K * 2, t_end = g.w_off + (uint64_t)min(n0 + BN, g.N) * g.K * 2;
+    const bool straddle = g.W.split > t_begin && g.W.split < t_end;
+    const void* const a_base = g.A + (size_t)m0 * g.lda;
+    const void* const w_base = wv_ptr(g.W, t_begin);
+    const uint32_t a_bytes = rsrc_bytes(((uint64_t)(g.M - 1 - m0) * g.lda + g.K) * 2), w_bytes = rsrc_bytes(t_end - t_begin);
+
+    floatx16 acc[NT][MT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = 0; j < MT; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+    lds_frag *a_frag[KSTEPS], *w_frag[KSTEPS];
+#pragma unroll
+    for (int kk = 0; kk < KSTEPS; ++kk) {
+        const int c = ((kk * 2 + lg) ^ swz(li)) << 4;
+        a_frag[kk] = (lds_frag*)(smem + (wm0 + li) * ROWB + c);
+        w_frag[kk] = (lds_frag*)(smem + BM * ROWB + (wn0 + li) * ROWB + c);
+    }
+    const int KT = g.K / BK;
+    bf16x8 fa[2][MT][KSTEPS], fw[2][NT][KSTEPS];
+
+    struct Src { __amdgpu_buffer_rsrc_t a, w; uint32_t k0; bool on; };
+    auto source = [&](int kt) {
+        const bool on = kt < KT;
+        return Src{make_rsrc(a_base, on ? a_bytes : 0u), make_rsrc(w_base, on ? w_bytes : 0u), on ? (uint32_t)kt * (BK * 2) : 0u, on};
+    };
+    auto issue = [&](const Src& src, int stage, int q) {       // q-th of L copies of a slab into the stage at byte `stage`
+        char* const dst = smem + stage + uw * 1024 + q * 4096;
+        if (q < LA) {
+            lds_bload16(src.a, a_voff[q < LA ? q : 0], src.k0, dst);
+        } else {
+            const uint32_t vo = w_voff[q < LA ? 0 : q - LA];
+            if (straddle && src.on) {              // rows past the matrix read the tile's first bytes; they are never stored
+                const uint64_t o = (uint64_t)vo + src.k0;
+                lds_load16(wv_ptr(g.W, t_begin + (o < t_end - t_begin ? o : 0)), dst);
+            } else {
+                lds_bload16(src.w, vo, src.k0, dst);
+            }
+        }
+    };
+    auto read = [&](auto buf, int stage, int r) {              // r-th of (MT + NT) * KSTEPS fragments, k-step by k-step
+        const int kk = r / (MT + NT), t = r % (MT + NT);
+        if (t < MT) fa[buf.value][t][kk] = a_frag[kk][(stage + t * 32 * ROWB) / 16];
+        else fw[buf.value][t - MT][kk] = w_frag[kk][(stage + (t - MT) * 32 * ROWB) / 16];
+    };
+    auto slab = [&](auto buf, int kt, int here, int next) __attribute__((always_inline)) {
+        using Other = std::integral_constant<int, decltype(buf)::value ^ 1>;
+        constexpr int NM = KSTEPS * NT * MT, NR = KSTEPS * (MT + NT);
+        const Src src = source(kt + S);
+        handover<(S - 2) * L>();               // slab kt + 1 has landed; slab kt is in every wave's registers
+        int r = 0, u = 0;
+#pragma unroll
+        for (int q = 0; q < NM; ++q) {
+            const int kk = q / (NT * MT), i = (q / MT) % NT, j = q % MT;
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[buf.value][i][kk], fa[buf.value][j][kk], acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            for (; u * NM < L * (q + 1) && u < L; ++u) issue(src, here, u);
+            for (; r * NM < NR * (q + 1) && r < NR; ++r) read(Other{}, next, r);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+#pragma unroll
+    for (int st = 0; st < S; ++st) {
+        const Src src = source(st);
+#pragma unroll
+        for (int q = 0; q < L; ++q) issue(src, st * STAGE, q);
+    }
+    handover<(S - 1) * L>();
+#pragma unroll
+    for (int r = 0; r < KSTEPS * (MT + NT); ++r) read(I0{}, 0, r);
+    int here = 0;
+    auto after = [&](int st) { return st == (S - 1) * STAGE ? 0 : st + STAGE; };
+    for (int kt = 0; kt < KT; kt += 2) {           // an odd last slab is followed by one of zeros
+        int next = after(here);
+        slab(I0{}, kt, here, next);
+        here = next;
+        next = after(here);
+        slab(I1{}, kt + 1, here, next);
+        here = next;
+    }
+    gemm_epilogue<BM, BN, EPI>(g, acc, m0, n0, uw, smem);
+}
+
 // Workgroup `bid` of the `nblk` that problem owns.
-template <int BM, int BN, int EPI>
+// S: stages of the ring loop, 0 = the quadrant-phase loop (two stages).
+template <int BM, int BN, int S, int EPI>
 __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, uint32_t bid, uint32_t nblk) {
     // logical tile: XCD-contiguous id, then groups of GM row-tiles walked feature-tile-major
     const int tiles_m = (g.M + BM - 1) / BM;
@@ -389,14 +510,18 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, uint32_t bid, 
     const int gsz = min(tiles_m - first_m, GM);
     const int m0 = (first_m + (lid % (GM * tiles_n)) % gsz) * BM;
     const int n0 = g.n0 + (lid % (GM * tiles_n)) / gsz * BN;
-    const uint64_t t_begin = g.w_off + (uint64_t)n0 * g.K * 2, t_end = g.w_off + (uint64_t)min(n0 + BN, g.N) * g.K * 2;
-    if (g.W.split > t_begin && g.W.split < t_end) gemm_tile_run<BM, BN, EPI, true>(g, m0, n0);
-    else gemm_tile_run<BM, BN, EPI, false>(g, m0, n0);
+    if constexpr (S > 0) {
+        gemm_ring_run<BM, BN, S, EPI>(g, m0, n0);
+    } else {
+        const uint64_t t_begin = g.w_off + (uint64_t)n0 * g.K * 2, t_end = g.w_off + (uint64_t)min(n0 + BN, g.N) * g.K * 2;
+        if (g.W.split > t_begin && g.W.split < t_end) gemm_tile_run<BM, BN, EPI, true>(g, m0, n0);
+        else gemm_tile_run<BM, BN, EPI, false>(g, m0, n0);
+    }
 }
 
-template <int BM, int BN, int EPI>
+template <int BM, int BN, int S, int EPI>
 __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g) {
-    gemm_tile_body<BM, BN, EPI>(g, blockIdx.x, gridDim.x);
+    gemm_tile_body<BM, BN, S, EPI>(g, blockIdx.x, gridDim.x);
 }
 
 // Two independent problems of one tile shape and epilogue in one launch (the text and image streams
@@ -407,17 +532,17 @@ struct GemmPair {
     GemmArgs g[2];
     uint32_t tiles0, tiles0_pad;
 };
-template <int BM, int BN, int EPI>
+template <int BM, int BN, int S, int EPI>
 __global__ __launch_bounds__(256) void gemm_pair_kernel(GemmPair p) {
-    if (blockIdx.x < p.tiles0) gemm_tile_body<BM, BN, EPI>(p.g[0], blockIdx.x, p.tiles0);
-    else if (blockIdx.x >= p.tiles0_pad) gemm_tile_body<BM, BN, EPI>(p.g[1], blockIdx.x - p.tiles0_pad, gridDim.x - p.tiles0_pad);
+    if (blockIdx.x < p.tiles0) gemm_tile_body<BM, BN, S, EPI>(p.g[0], blockIdx.x, p.tiles0);
+    else if (blockIdx.x >= p.tiles0_pad) gemm_tile_body<BM, BN, S, EPI>(p.g[1], blockIdx.x - p.tiles0_pad, gridDim.x - p.tiles0_pad);
 }
 
-template <int BM, int BN, int EPI>
+template <int BM, int BN, int S, int EPI>
 constexpr size_t gemm_smem() {
     constexpr int WM = BM / 2, WN = BN / 2;
     constexpr int staged_row = EPI != EPI_GATE_RESID ? WN * 2 + 16 : (WN > 32 ? WN * 2 : WN * 4) + 32;     // the epilogue's PITCH
-    constexpr size_t loop = (size_t)STAGES * (BM + BN) * ROWB, epi = 4ull * WM * staged_row;
+    constexpr size_t loop = (size_t)(S > 0 ? S : STAGES) * (BM + BN) * ROWB, epi = 4ull * WM * staged_row;
     return loop > epi ? loop : epi;
 }
 
@@ -426,23 +551,23 @@ hipError_t allow_smem(Kernel kernel, size_t smem) {
     return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
 }
 
-template <int BM, int BN, int EPI>
+template <int BM, int BN, int S, int EPI>
 hipError_t launch(const GemmArgs& g, const GemmArgs* second, hipStream_t s) {
     auto tiles = [](const GemmArgs& p) { return (uint32_t)(((p.M + BM - 1) / BM) * ((p.n1 - p.n0 + BN - 1) / BN)); };
-    constexpr size_t smem = gemm_smem<BM, BN, EPI>();
+    constexpr size_t smem = gemm_smem<BM, BN, S, EPI>();
     if (!second) {
-        static const hipError_t allowed = allow_smem(gemm_bf16_kernel<BM, BN, EPI>, smem);
+        static const hipError_t allowed = allow_smem(gemm_bf16_kernel<BM, BN, S, EPI>, smem);
         if (allowed != hipSuccess) return allowed;
-        hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, EPI>), dim3(tiles(g)), dim3(256), smem, s, g);
+        hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, S, EPI>), dim3(tiles(g)), dim3(256), smem, s, g);
     } else {
-        static const hipError_t allowed = allow_smem(gemm_pair_kernel<BM, BN, EPI>, smem);
+        static const hipError_t allowed = allow_smem(gemm_pair_kernel<BM, BN, S, EPI>, smem);
         if (allowed != hipSuccess) return allowed;
         GemmPair p;
         p.g[0] = g;
         p.g[1] = *second;
         p.tiles0 = tiles(g);
         p.tiles0_pad = (p.tiles0 + 7u) & ~7u;
-        hipLaunchKernelGGL((gemm_pair_kernel<BM, BN, EPI>), dim3(p.tiles0_pad + tiles(*second)), dim3(256), smem, s, p);
+        hipLaunchKernelGGL((gemm_pair_kernel<BM, BN, S, EPI>), dim3(p.tiles0_pad + tiles(*second)), dim3(256), smem, s, p);
     }
     return hipGetLastError();
 }
@@ -451,9 +576,11 @@ hipError_t launch(const GemmArgs& g, const GemmArgs* second, hipStream_t s) {
 template <int EPI>
 hipError_t launch_tile(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s) {
     switch (tile) {
-        case GEMM_256x256: return launch<256, 256, EPI>(g, second, s);
-        case GEMM_128x128: return launch<128, 128, EPI>(g, second, s);
-        case GEMM_128x256: return launch<128, 256, EPI>(g, second, s);
+        case GEMM_256x256: return launch<256, 256, 0, EPI>(g, second, s);
+        case GEMM_128x128: return launch<128, 128, 0, EPI>(g, second, s);
+        case GEMM_128x256: return launch<128, 256, 0, EPI>(g, second, s);
+        case GEMM_128x64: return launch<128, 64, 3, EPI>(g, second, s);        // 72 and 80 KB of LDS: two workgroups per CU
+        case GEMM_64x64: return launch<64, 64, 5, EPI>(g, second, s);
         default: return hipErrorInvalidValue;
     }
 }

@@ -28,7 +28,7 @@ struct GemmArgs {
     int rows_per_sample; long gate_bs, resid_bs, y_bs;
 };
 const char* gemm_check(const GemmArgs& g);
-enum { GEMM_256x256 = 0, GEMM_128x128 = 1, GEMM_128x256 = 2, GEMM_TILES = 3 };     // tokens x features
+enum { GEMM_256x256 = 0, GEMM_128x128 = 1, GEMM_128x256 = 2, GEMM_128x64 = 3, GEMM_64x64 = 4, GEMM_TILES = 5 };     // tokens x features
 int gemm_tile(const GemmArgs& g);      // tile gemm_launch will use
 double gemm_fill(int M, int n);        // share of the launched rounds of workgroups that n features x M tokens fill
 hipError_t gemm_launch(const GemmArgs& g, hipStream_t s);

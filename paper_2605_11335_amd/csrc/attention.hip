@@ -14,6 +14,7 @@
 // B-operand layout of the second contraction (8 consecutive k per lane), so P^T is a pure
 // register repack.  V is kept transposed in HBM ([head, d, key]) so that its A-operand rows
 // are contiguous 16-byte reads as well.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -34,6 +35,40 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, ui
 constexpr int BKV = 64;    // keys per tile
 
 __device__ __forceinline__ float max3f(float a, float b, float c) { return __builtin_fmaxf(__builtin_fmaxf(a, b), c); }
+
+// Output row of query q of head h, times inv: lane = query, value(d, 4*vb + e) = column d*32 + vb*8 + lg*4 + e.
+template <int HD, class Value>
+__device__ __forceinline__ void store_rows(const AttnArgs& a, int h, int q, int lg, Value&& value, float inv) {
+    if (q >= a.nq) return;
+    const int hps = a.hps ? a.hps : a.H;            // heads per sample of a batch
+    const int b = h / hps, hh = h % hps;
+    bf16* op;
+    if (a.scatter) {
+        // the second exchange by the stores themselves: this rank's positions go to the projection operand,
+        // the others to the send buffer (in ascending position order, as the receiver expects them)
+        const TokenMap& m = a.map;
+        if (q >= m.pos0 && q < m.pos0 + m.len0) {
+            op = a.dst0 + (size_t)b * a.bs0 + (size_t)(q - m.pos0) * a.ld + (a.h0 + hh) * HD;
+        } else if (q >= m.pos1 && q < m.pos1 + m.len1) {
+            op = a.dst1 + (size_t)b * a.bs1 + (size_t)(q - m.pos1) * a.ld + (a.h0 + hh) * HD;
+        } else {
+            const int ri = q - (q >= m.pos0 + m.len0 ? m.len0 : 0) - (q >= m.pos1 + m.len1 ? m.len1 : 0);
+            op = a.send ? a.send + (size_t)b * a.send_bs + ((size_t)hh * (m.n_total - m.n_local) + ri) * HD : nullptr;
+        }
+    } else {
+        op = a.O + (size_t)b * a.o_bs + (size_t)hh * a.o_hs + (size_t)q * a.o_qs;
+    }
+    if (!op) return;
+#pragma unroll
+    for (int d = 0; d < HD / 32; ++d)
+#pragma unroll
+        for (int vb = 0; vb < 4; ++vb) {
+            bf16x4 w;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[e] = (bf16)(value(d, vb * 4 + e) * inv);
+            *(bf16x4*)(op + d * 32 + vb * 8 + lg * 4) = w;
+        }
+}
 
 // NW waves of 32 queries each per workgroup: 4 (two workgroups per CU), 7 or 8 (one per CU).
 template <int HD, int NW>
@@ -56,7 +91,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_kernel(AttnArgs a) {
 
     const int nqt = (a.nq + BQ - 1) / BQ;
     const uint32_t lid = xcd_contiguous_id(blockIdx.x, gridDim.x);
-    const int h = lid / nqt, qt = lid % nqt;
+    const int hs = lid / nqt, qt = lid % nqt;
+    const int h = hs / a.splits, part = hs % a.splits;       // head, and which part of the keys
     const int q0 = qt * BQ + wave * 32;
 
     // K swizzle: 256-byte rows (HD=128) rotate over 16 chunk slots, 128-byte rows over 8
@@ -115,7 +151,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_kernel(AttnArgs a) {
     // key row fed to MFMA row i: swap bits 2 and 3 of i
     const int krow = (lj & 0x13) | ((lj & 4) << 1) | ((lj & 8) >> 1);
 
-    const int NT = (a.nk + BKV - 1) / BKV;
+    const int T0 = part * a.part_tiles, NT = min((a.nk + BKV - 1) / BKV, T0 + a.part_tiles);     // this workgroup's tiles
     int out_of_range = 0;                       // wave-uniform: a fast tile met scores it could not take
 
     // One tile.  The LDS buffer is a compile-time constant so that fragment addresses are a per-lane
@@ -284,10 +320,10 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_kernel(AttnArgs a) {
             for (int v = 0; v < 16; ++v) o[d][v] = 0.f;
         mc = -INFINITY;
         l_run = 0.f;
-        issue_tile(0, 0);
+        issue_tile(T0, 0);
         __syncthreads();                        // (waits for the LDS-DMA, then the barrier)
-        tile(0, std::integral_constant<int, 0>{}, std::true_type{});
-        for (int t = 1; t < NT; t += 2) {
+        tile(T0, std::integral_constant<int, 0>{}, std::true_type{});
+        for (int t = T0 + 1; t < NT; t += 2) {
             tile(t, std::integral_constant<int, 1>{}, tracking_c);
             if (t + 1 < NT) tile(t + 1, std::integral_constant<int, 0>{}, tracking_c);
         }
@@ -296,41 +332,58 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_kernel(AttnArgs a) {
     // the K/V tiles are the workgroup's: if any wave met a tile out of range, all of them go again
     if (__syncthreads_or(out_of_range)) sweep(std::true_type{});
 
-    // ---- normalise and store: lane = query, register quad = 4 consecutive d
     const float l_tot = l_run + __shfl_xor(l_run, 32);
-    const float inv = 1.0f / l_tot;
-    const int q = q0 + lj;
-    if (q < a.nq) {
-        const int hps = a.hps ? a.hps : a.H;            // heads per sample of a batch
-        const int b = h / hps, hh = h % hps;
-        bf16* op;
-        if (a.scatter) {
-            // the second exchange by the stores themselves: this rank's positions go to the projection operand,
-            // the others to the send buffer (in ascending position order, as the receiver expects them)
-            const TokenMap& m = a.map;
-            if (q >= m.pos0 && q < m.pos0 + m.len0) {
-                op = a.dst0 + (size_t)b * a.bs0 + (size_t)(q - m.pos0) * a.ld + (a.h0 + hh) * HD;
-            } else if (q >= m.pos1 && q < m.pos1 + m.len1) {
-                op = a.dst1 + (size_t)b * a.bs1 + (size_t)(q - m.pos1) * a.ld + (a.h0 + hh) * HD;
-            } else {
-                const int ri = q - (q >= m.pos0 + m.len0 ? m.len0 : 0) - (q >= m.pos1 + m.len1 ? m.len1 : 0);
-                op = a.send ? a.send + (size_t)b * a.send_bs + ((size_t)hh * (m.n_total - m.n_local) + ri) * HD : nullptr;
-            }
-        } else {
-            op = a.O + (size_t)b * a.o_bs + (size_t)hh * a.o_hs + (size_t)q * a.o_qs;
+    if (a.splits > 1) {
+        // part of the keys only: O^T, the reference it is taken against and the row sum go to the scratch buffer as they
+        // lie in registers, 1 KiB per store
+        if (q0 < a.nq) {
+            const size_t tile32 = ((size_t)part * a.H + h) * ((a.nq + 31) / 32) + q0 / 32;
+            float* const po = a.part_o + tile32 * (32 * HD);
+#pragma unroll
+            for (int d = 0; d < DT; ++d)
+#pragma unroll
+                for (int vb = 0; vb < 4; ++vb) {
+                    const floatx4 v = {o[d][vb * 4], o[d][vb * 4 + 1], o[d][vb * 4 + 2], o[d][vb * 4 + 3]};
+                    *(floatx4*)(po + (d * 4 + vb) * 256 + lane * 4) = v;
+                }
+            if (lg == 0) *(float2*)(a.part_ml + tile32 * 64 + lj * 2) = make_float2(mc, l_tot);
         }
-        if (op) {
-#pragma unroll
-        for (int d = 0; d < DT; ++d)
-#pragma unroll
-            for (int vb = 0; vb < 4; ++vb) {
-                bf16x4 w;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) w[e] = (bf16)(o[d][vb * 4 + e] * inv);
-                *(bf16x4*)(op + d * 32 + vb * 8 + lg * 4) = w;
-            }
-        }
+        return;
     }
+    store_rows<HD>(a, h, q0 + lj, lg, [&](int d, int v) { return o[d][v]; }, 1.0f / l_tot);
+}
+
+// Puts the parts of the keys together: a wave per 32 queries of a head, lanes as in attn_fwd_kernel, parts in order.
+// Bound by the partial results it reads (3 heads x 4608 queries in four parts: 28 MB).
+template <int HD>
+__global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
+    constexpr int DT = HD / 32;
+    const int lane = threadIdx.x & 63, lj = lane & 31, lg = lane >> 5;
+    const int n32 = (a.nq + 31) / 32;
+    const int w = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (w >= a.H * n32) return;
+    const int h = w / n32, q0 = (w % n32) * 32;
+    const size_t part_stride = (size_t)a.H * n32, tile32 = (size_t)h * n32 + q0 / 32;
+    float m = -INFINITY;
+    for (int p = 0; p < a.splits; ++p) m = fmaxf(m, a.part_ml[(p * part_stride + tile32) * 64 + lj * 2]);
+    floatx4 o[DT * 4];
+#pragma unroll
+    for (int i = 0; i < DT * 4; ++i) o[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+    float l = 0.f;
+    for (int p = 0; p < a.splits; ++p) {
+        const float2 ml = *(const float2*)(a.part_ml + (p * part_stride + tile32) * 64 + lj * 2);
+        const float* const po = a.part_o + (p * part_stride + tile32) * (32 * HD);
+        floatx4 v[DT * 4];
+#pragma unroll
+        for (int i = 0; i < DT * 4; ++i) v[i] = *(const floatx4*)(po + i * 256 + lane * 4);
+        const float e = __builtin_amdgcn_exp2f(ml.x - m);
+        l = fmaf(ml.y, e, l);
+#pragma unroll
+        for (int i = 0; i < DT * 4; ++i)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) o[i][c] = fmaf(v[i][c], e, o[i][c]);
+    }
+    store_rows<HD>(a, h, q0 + lj, lg, [&](int d, int v) { return o[d * 4 + v / 4][v % 4]; }, 1.0f / l);
 }
 
 template <int HD, int NW>
@@ -344,7 +397,7 @@ hipError_t launch(const AttnArgs& a, hipStream_t s) {
         attr_set = true;
     }
     const int nqt = (a.nq + 32 * NW - 1) / (32 * NW);
-    hipLaunchKernelGGL((attn_fwd_kernel<HD, NW>), dim3(nqt * a.H), dim3(64 * NW), smem, s, a);
+    hipLaunchKernelGGL((attn_fwd_kernel<HD, NW>), dim3(nqt * a.H * a.splits), dim3(64 * NW), smem, s, a);
     return hipGetLastError();
 }
 
@@ -380,7 +433,10 @@ const char* attn_check(const AttnArgs& a) {
         if (((uintptr_t)a.O % 8) || (a.o_hs % 4) || (a.o_qs % 4) || (a.o_bs % 4)) return "attention: output must be 8-byte aligned";
     }
     if (a.hps < 0 || (a.hps && a.H % a.hps)) return "attention: H must be whole samples of hps heads";
-    if ((long)((a.nq + 127) / 128) * a.H > 0x7fffffffL) return "attention: grid too large";
+    if ((long)((a.nq + 127) / 128) * a.H * std::max(1, a.splits) > 0x7fffffffL) return "attention: grid too large";
+    if (a.splits > 1 && (!a.part_o || !a.part_ml || (((uintptr_t)a.part_o | (uintptr_t)a.part_ml) % 16) ||
+                         a.part_tiles < 1 || (long)(a.splits - 1) * a.part_tiles * BKV >= a.nk || (long)a.splits * a.part_tiles * BKV < a.nk))
+        return "attention: bad split of the keys";
     return nullptr;
 }
 
@@ -398,10 +454,11 @@ const char* attn_check(const AttnArgs& a) {
 // 4; very long sweeps whose 7- and 8-wave grids need the same number of generations to 7; the rest to 8.
 // Heights 5 and 6 were built once and never won: three SIMDs share the work of four.
 int attn_waves(const AttnArgs& a) {
+    const int splits = std::max(1, a.splits);
     // a grid that cannot even give every CU one 4-wave workgroup is spread as widely as possible
-    if ((long)((a.nq + 127) / 128) * a.H <= 256) return 4;
-    const double tiles = (double)((a.nk + BKV - 1) / BKV);
-    auto items = [&](int nw) { return (long)((a.nq + 32 * nw - 1) / (32 * nw)) * a.H; };
+    if ((long)((a.nq + 127) / 128) * a.H * splits <= 256) return 4;
+    const double tiles = splits > 1 ? a.part_tiles : (double)((a.nk + BKV - 1) / BKV);
+    auto items = [&](int nw) { return (long)((a.nq + 32 * nw - 1) / (32 * nw)) * a.H * splits; };
     auto generations = [](long n, long slots) { return (double)((n + slots - 1) / slots); };
     const double c8 = generations(items(8), 256) * (tiles + 2.5);
     const double c7 = generations(items(7), 256) * (0.96 * tiles + 9.0);
@@ -414,7 +471,47 @@ int attn_waves(const AttnArgs& a) {
     return best;
 }
 
+// Parts the keys of a launch are cut into.  Few heads over a short sequence (a Ulysses rank's share at degree 4 or 8)
+// are a few dozen workgroups that each sweep all keys; cut into parts they fill the chip, at the price of writing the
+// partial results and merging them.  Estimated time in us for 128-wide heads: a tile takes a 4-wave workgroup 0.97 alone
+// on its CU and 1.7 beside another, the merge 10 us and one pass over the partial results at 4 TB/s (3 heads x 4608: 72 us
+// whole, 51 in two or four parts; 12 heads x 2640: 51 us whole, 58 in two).  A function of one sample's heads and lengths
+// only, so that a sample's result does not depend on the batch it is part of.
+int attn_splits(int heads, int nq, int nk, int hd) {
+    const long items = (long)((nq + 127) / 128) * heads;
+    const int tiles = (nk + BKV - 1) / BKV;
+    int best = 1;
+    double best_us = 0;
+    for (int s = 1; s <= 8 && tiles >= 2 * s; ++s) {
+        const int per = (tiles + s - 1) / s;
+        if ((tiles + per - 1) / per != s) continue;
+        const long wgs = items * s;
+        if (s > 1 && wgs > 512) break;
+        double us = (wgs <= 256 ? 0.97 * per : 1.7 * per * (double)((wgs + 511) / 512)) * (hd == 64 ? 0.55 : 1.0) + 3.0;
+        if (s > 1) us += 10.0 + 4.0 * s * (double)heads * nq * hd / 4e6;
+        if (s == 1 || us < 0.95 * best_us) best = s, best_us = us;
+    }
+    return best;
+}
+
+uint64_t attn_part_floats(int heads, int nq, int hd, int splits) {
+    return splits > 1 ? (uint64_t)splits * heads * ((nq + 31) / 32) * 32 * (hd + 2) : 0;
+}
+
+void attn_set_split(AttnArgs* a, int splits, float* scratch) {
+    const int tiles = (a->nk + BKV - 1) / BKV;
+    a->splits = std::max(1, splits);
+    a->part_tiles = (tiles + a->splits - 1) / a->splits;
+    a->part_o = scratch;
+    a->part_ml = scratch ? scratch + (uint64_t)a->splits * a->H * ((a->nq + 31) / 32) * 32 * a->hd : nullptr;
+}
+
 hipError_t attn_launch(const AttnArgs& a, hipStream_t s) {
     const int nw = attn_waves(a);
-    return a.hd == 128 ? launch_nw<128>(nw, a, s) : launch_nw<64>(nw, a, s);
+    const hipError_t e = a.hd == 128 ? launch_nw<128>(nw, a, s) : launch_nw<64>(nw, a, s);
+    if (e != hipSuccess || a.splits == 1) return e;
+    const dim3 grid((a.H * ((a.nq + 31) / 32) + 3) / 4);
+    if (a.hd == 128) hipLaunchKernelGGL(attn_merge_kernel<128>, grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(attn_merge_kernel<64>, grid, dim3(256), 0, s, a);
+    return hipGetLastError();
 }

@@ -115,12 +115,23 @@ struct Ws {
     float *x1 = nullptr, *x2 = nullptr;
     bf16* up = nullptr;        // [n_local, f]
     bf16 *ckv = nullptr, *cQ = nullptr, *cK = nullptr, *cVt = nullptr;
+    float* part = nullptr;     // partial results of layers cut along their sum, live between two launches only
     uint64_t total = 0;
 };
 
 inline int n_pad_of(int n) { return (n + 63) / 64 * 64; }
 
 inline int batch_of(const cf_model_desc& m) { return m.batch > 0 ? m.batch : 1; }
+
+// parts of K in a residual layer of K input features: the two streams of a double-stream block, which normally share a
+// launch, are cut alike
+inline int sum_splits(const cf_model_desc& m, int kind, int K) {
+    const int nl = m.n_total / m.sp_degree, tl = kind == CF_DOUBLE_STREAM ? m.n_txt_total / m.sp_degree : 0;
+    return gemm_splits(nl - tl, tl, m.d, K);
+}
+// parts of the keys in the joint attention and in the cross-attention
+inline int self_splits(const cf_model_desc& m) { return attn_splits(m.n_heads / m.sp_degree, m.n_total, m.n_total, m.head_dim); }
+inline int cross_splits(const cf_model_desc& m) { return attn_splits(m.n_heads, m.n_total / m.sp_degree, m.l_ctx, m.head_dim); }
 
 // every per-token buffer holds the whole batch, sample after sample
 Ws carve(const cf_model_desc& m, int kind, char* base) {
@@ -149,6 +160,14 @@ Ws carve(const cf_model_desc& m, int kind, char* base) {
         w.cK = (bf16*)take(2ull * lc * d);
         w.cVt = (bf16*)take(2ull * B * d * n_pad_of(m.l_ctx));
     }
+    uint64_t part = attn_part_floats((int)hl, m.n_total, m.head_dim, self_splits(m));
+    if (kind == CF_DIT_CROSS)
+        part = std::max(part, attn_part_floats((int)(B * m.n_heads), m.n_total / m.sp_degree, m.head_dim, cross_splits(m)));
+    for (int k : {(int)(kind == CF_SINGLE_STREAM ? d + f : f), (int)d}) {
+        const int parts = sum_splits(m, kind, k);
+        if (parts > 1) part = std::max(part, parts * nl * d);
+    }
+    w.part = (float*)take(4 * part);
     w.total = off;
     return w;
 }
@@ -529,6 +548,7 @@ int run_linear(Fwd& F, int kid, const std::string& wname, const std::string& bna
     g.N = (int)w.rows;
     g.K = (int)w.cols;
     if (g.epi == EPI_SPLIT_GELU && g.n_split > g.N) g.n_split = g.N;
+    if (g.epi == EPI_GATE_RESID) gemm_set_split(&g, sum_splits(F.c->d, F.c->P(F.block).kind, g.K), F.ws.part);
     return panels(F, w, g.M, [&](int r0, int r1) -> int {
         GemmArgs p = g;
         p.n0 = r0;
@@ -565,6 +585,9 @@ int run_linear_pair(Fwd& F, int kid, const std::string (&wname)[2], const std::s
         g[i].n0 = 0;
         g[i].n1 = g[i].N;
         if (g[i].epi == EPI_SPLIT_GELU && g[i].n_split > g[i].N) g[i].n_split = g[i].N;
+        if (g[i].epi == EPI_GATE_RESID)      // both are in flight together: the second's parts follow the first's
+            gemm_set_split(&g[i], sum_splits(c->d, c->P(F.block).kind, g[i].K),
+                           F.ws.part + (i ? (size_t)g[0].ksplits * g[0].M * g[0].N : 0));
     }
     const int tile = pair ? gemm_pair_tile(g[0], g[1]) : -1;
     if (tile < 0) {
@@ -681,6 +704,7 @@ int run_joint_attention(Fwd& F, const RelayoutArgs* parts, int n_parts, const At
         a.ld = out.ld; a.h0 = h0;
         a.send = (bf16*)io->send_attn; a.send_bs = (long)peer_bs;
     }
+    attn_set_split(&a, self_splits(m), F.ws.part);
     if (const char* msg = attn_check(a)) return cf_fail(c, CF_ERR_ARG, "%s", msg);
     {
         ProfScope ps(c, F.s, K_ATTN, 4.0 * B * hl * (double)m.n_total * m.n_total * hd, 0);
@@ -1338,6 +1362,7 @@ int cf_op_attention(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, ui
     a.Q = (const bf16*)Q; a.K = (const bf16*)K; a.Vt = (const bf16*)Vt; a.O = (bf16*)O;
     a.o_hs = (long)nq * hd; a.o_qs = hd; a.H = H; a.nq = nq; a.nk = nk; a.nk_pad = nk_pad; a.hd = hd;
     a.scale = 1.0f / sqrtf((float)hd);
+    attn_set_split(&a, 1, nullptr);
     if (const char* msg = attn_check(a)) return cf_fail(nullptr, CF_ERR_ARG, "%s", msg);
     hipError_t e = attn_launch(a, (hipStream_t)stream);
     return e == hipSuccess ? CF_OK : cf_fail(nullptr, CF_ERR_HIP, "attention launch: %s", hipGetErrorString(e));
@@ -1497,6 +1522,7 @@ int fwd_dit(Fwd& F) {
         AttnArgs a{};
         a.Q = w.cQ; a.K = w.cK; a.Vt = w.cVt; a.O = w.c; a.o_hs = hd; a.o_qs = d; a.o_bs = dense;
         a.H = B * H; a.hps = H; a.nq = nl; a.nk = lc; a.nk_pad = lpad; a.hd = hd; a.scale = 1.0f / sqrtf((float)hd);
+        attn_set_split(&a, cross_splits(m), w.part);
         if (const char* msg = attn_check(a)) return cf_fail(c, CF_ERR_ARG, "%s", msg);
         ProfScope ps(c, F.s, K_CROSS_ATTN, 4.0 * B * H * (double)nl * lc * hd, 0);
         CF_HIP(c, attn_launch(a, F.s));

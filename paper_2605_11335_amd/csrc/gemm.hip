@@ -24,6 +24,9 @@ const char* gemm_check(const GemmArgs& g) {
         if (!g.resid || !g.y || (g.ldy % 4) || ((uintptr_t)g.y % 16) || ((uintptr_t)g.resid % 16)) return "gemm: bad residual/output";
         if (g.gate && ((uintptr_t)g.gate % 16)) return "gemm: gate must be 16-byte aligned";
         if (g.rows_per_sample < 0 || (g.rows_per_sample && g.M % g.rows_per_sample)) return "gemm: M must be whole samples";
+        if (g.ksplits > 1 && (!g.part || ((uintptr_t)g.part % 16) || g.part_slabs < 1 || (g.ksplits - 1) * g.part_slabs >= g.K / 64 ||
+                              g.ksplits * g.part_slabs < g.K / 64))
+            return "gemm: bad split of K";
         if (g.rows_per_sample && ((g.gate_bs % 4) || (g.resid_bs % 4) || (g.y_bs % 4) || g.gate_bs < 0 || g.resid_bs < 0 || g.y_bs < 0))
             return "gemm: sample strides must be non-negative multiples of 4 elements";
     } else {
@@ -65,29 +68,71 @@ double tile_time(const TileCost& t, long tiles, int K) {
     const long slots = 256L * t.per_cu, rest = tiles % slots;
     double us = (double)(tiles / slots) * (slabs * t.full + t.fixed);
     if (rest) {
-        // the last round: a CU with one workgroup where it could hold two works off its slab alone
-        const double busy = (double)std::min(rest, 256L) / 256.0;
-        const double slab = rest > 256 ? t.full : t.per_cu > 1 ? t.lone : t.lone + (t.full - t.lone) * busy;
+        // The last round.  A CU with one workgroup where it could hold two works off its slab alone; where some CUs hold
+        // two, those decide, at 0.7 of a full chip's time per slab if they are few (1320 x 3072 x 14336, 264 workgroups of
+        // 128x128: 0.76 us) and all of it from 70 % on.
+        double slab;
+        if (rest > 256) slab = t.full * (0.7 + 0.3 * std::min(1.0, (double)(rest - 256) / 179.0));
+        else if (t.per_cu > 1) slab = t.lone;
+        else slab = t.lone + (t.full - t.lone) * (double)rest / 256.0;
         us += slabs * slab + t.fixed;
     }
     return us;
 }
-int best_tile(const GemmArgs* const (&g)[2]) {
-    int best = 0;
+int best_tile(const GemmArgs* const (&g)[2], double* time = nullptr) {
+    int best = -1;
     double best_us = 0;
     for (int i = 0; i < GEMM_TILES; ++i) {
+        if (i == GEMM_256x256 && g[1] && g[1]->ksplits > 1) continue;        // not built: registers
         const TileCost& t = kTileCost[i];
         long tiles = 0;
+        int K = 0;                       // the longest walk
         for (const GemmArgs* p : g)
-            if (p) tiles += (long)((p->M + t.bm - 1) / t.bm) * ((p->n1 - p->n0 + t.bn - 1) / t.bn);
-        const double us = tile_time(t, tiles, g[1] ? std::max(g[0]->K, g[1]->K) : g[0]->K);
-        if (i == 0 || us < best_us) best = i, best_us = us;
+            if (p) {
+                tiles += (long)((p->M + t.bm - 1) / t.bm) * ((p->n1 - p->n0 + t.bn - 1) / t.bn) * std::max(1, p->ksplits);
+                K = std::max(K, p->ksplits > 1 ? p->part_slabs * 64 : p->K);
+            }
+        const double us = tile_time(t, tiles, K);
+        if (best < 0 || us < best_us) best = i, best_us = us;
     }
+    if (time) *time = best_us;
     return best;
 }
 }  // namespace
 
 int gemm_tile(const GemmArgs& g) { return best_tile({&g, nullptr}); }
+
+// Parts K is cut into.  A layer with few outputs and a long sum (the MLP-out layers of a short sequence or of a rank at
+// degree 4 or 8) has few tiles whatever their shape: cut, its workgroups multiply, each with a share of the walk.  The price
+// is writing the partial sums and a second kernel that adds them, in the order of the parts, and applies the epilogue:
+// 6 us and two passes over them at 4 TB/s.  Taken where the estimate promises a tenth.  A function of one sample's tokens and
+// the whole layer only, so that results depend neither on the batch nor on the panels a streamed layer is cut into.
+int gemm_splits(int rows, int rows2, int N, int K) {
+    GemmArgs g{}, g2{};
+    g.M = rows; g.N = g.n1 = N; g.K = K;
+    g2 = g;
+    g2.M = rows2;
+    const int slabs = K / 64;
+    int best = 1;
+    double best_us = 0;
+    for (int parts = 1; parts <= 8 && slabs >= 8 * parts; ++parts) {
+        gemm_set_split(&g, parts, nullptr);
+        if (g.ksplits != parts) continue;
+        gemm_set_split(&g2, parts, nullptr);
+        double us;
+        best_tile({&g, rows2 > 0 ? &g2 : nullptr}, &us);
+        if (parts > 1) us += 6.0 + 2.0 * 4.0 * parts * (double)(rows + rows2) * N / 4e6;
+        if (parts == 1 || us < (best == 1 ? 0.9 : 1.0) * best_us) best = parts, best_us = us;
+    }
+    return best;
+}
+
+void gemm_set_split(GemmArgs* g, int splits, float* part) {
+    const int slabs = g->K / 64;
+    g->part_slabs = splits > 1 ? (slabs + splits - 1) / splits : slabs;
+    g->ksplits = splits > 1 ? (slabs + g->part_slabs - 1) / g->part_slabs : 1;
+    g->part = part;
+}
 
 // How well a launch over n output features uses the chip: work in rounds of 256x256 tiles divided
 // by the estimated cost of the better square tile (1 = whole rounds of the big tile).
@@ -223,20 +268,64 @@ hipError_t mix_rate_launch(int iters, int waves, int reads16, int valu, int exps
     return hipErrorInvalidValue;
 }
 
+// The parts of one or two cut layers added up in order, and the epilogue of gemm_kernel.h: y = resid + gate * (sum + bias).
+// A thread per 4 features of a token.  Bound by the partial sums it reads (1320 x 3072 in three parts: 49 MB).
 namespace {
+struct ReduceArgs { GemmArgs g[2]; uint32_t blocks0; };
+__global__ __launch_bounds__(256) void gemm_reduce_kernel(ReduceArgs a) {
+    const bool second = blockIdx.x >= a.blocks0;
+    const GemmArgs& g = a.g[second];
+    const int quads = (g.n1 - g.n0) / 4;
+    const long q = (long)(blockIdx.x - (second ? a.blocks0 : 0)) * 256 + threadIdx.x;
+    if (q >= (long)g.M * quads) return;
+    const int m = q / quads, n = g.n0 + (q % quads) * 4;
+    const float* p = g.part + (size_t)m * g.N + n;
+    floatx4 v = *(const floatx4*)p;
+    for (int s = 1; s < g.ksplits; ++s) {
+        const floatx4 t = *(const floatx4*)(p + (size_t)s * g.M * g.N);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] += t[e];
+    }
+    if (g.has_bias) {
+        const uint32x2 b = *(const uint32x2*)wv_ptr(g.W, g.bias_off + 2ull * n);
+        v[0] += __uint_as_float(b.x << 16); v[1] += __uint_as_float(b.x & 0xffff0000u);
+        v[2] += __uint_as_float(b.y << 16); v[3] += __uint_as_float(b.y & 0xffff0000u);
+    }
+    int smp = 0, i = m;
+    if (g.rows_per_sample) { smp = m / g.rows_per_sample; i = m - smp * g.rows_per_sample; }
+    const floatx4 r = *(const floatx4*)(g.resid + (size_t)smp * g.resid_bs + (size_t)i * g.ldy + n);
+    floatx4 gt = {1.f, 1.f, 1.f, 1.f};
+    if (g.gate) gt = *(const floatx4*)(g.gate + (size_t)smp * g.gate_bs + n);
+    floatx4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = __fadd_rn(r[e], __fmul_rn(gt[e], v[e]));
+    *(floatx4*)(g.y + (size_t)smp * g.y_bs + (size_t)i * g.ldy + n) = o;
+}
+
+// one or two layers; those with a cut sum go through their parts
 hipError_t dispatch(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s) {
     // the erf form of the activation costs some forty VALU operations per element: it gets kernels
     // of its own rather than a run-time choice inside the tanh one
-    if (g.epi == EPI_GATE_RESID) return gemm_launch_gate_resid(tile, g, second, s);
-    return g.act_erf ? gemm_launch_split_gelu_erf(tile, g, second, s) : gemm_launch_split_gelu(tile, g, second, s);
+    if (g.epi != EPI_GATE_RESID) return g.act_erf ? gemm_launch_split_gelu_erf(tile, g, second, s) : gemm_launch_split_gelu(tile, g, second, s);
+    if (g.ksplits <= 1) return gemm_launch_gate_resid(tile, g, second, s);
+    const hipError_t e = gemm_launch_partial(tile, g, second, s);
+    if (e != hipSuccess) return e;
+    auto blocks = [](const GemmArgs& p) { return (uint32_t)(((long)p.M * ((p.n1 - p.n0) / 4) + 255) / 256); };
+    ReduceArgs a{};
+    a.g[0] = g;
+    a.blocks0 = blocks(g);
+    if (second) a.g[1] = *second;
+    hipLaunchKernelGGL(gemm_reduce_kernel, dim3(a.blocks0 + (second ? blocks(*second) : 0)), dim3(256), 0, s, a);
+    return hipGetLastError();
 }
 }  // namespace
 
 hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) { return dispatch(gemm_tile(g), g, nullptr, s); }
 
-// Tile shape both problems of a pair run with, or -1 if they cannot share a launch (different epilogues).
+// Tile shape both problems of a pair run with, or -1 if they cannot share a launch (different epilogues, or only one with
+// its sum in parts).
 int gemm_pair_tile(const GemmArgs& g0, const GemmArgs& g1) {
-    if (g0.epi != g1.epi || g0.act_erf != g1.act_erf) return -1;
+    if (g0.epi != g1.epi || g0.act_erf != g1.act_erf || (g0.ksplits > 1) != (g1.ksplits > 1)) return -1;
     return best_tile({&g0, &g1});
 }
 

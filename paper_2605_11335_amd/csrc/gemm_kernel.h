@@ -32,6 +32,7 @@
 namespace {
 
 constexpr int EPI_SPLIT_GELU_ERF = 2;  // kernel variant of EPI_SPLIT_GELU with the erf form of the activation
+constexpr int EPI_PARTIAL = 3;         // kernel variant of EPI_GATE_RESID that stores the sums of one part of K, nothing added
 constexpr int BK = 64;                 // K slab (bf16 elements) = 128 bytes per LDS row
 constexpr int STAGES = 2;              // slabs resident in LDS: one being multiplied, one in flight
 constexpr int ROWB = BK * 2;           // bytes per LDS row
@@ -78,14 +79,14 @@ __device__ __forceinline__ void handover() {
 }
 
 template <int BM, int BN, int EPI>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx16 (&acc)[BN / 64][BM / 64], int m0, int n0, int uw, char* smem) {
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx16 (&acc)[BN / 64][BM / 64], int m0, int n0, int part, int uw, char* smem) {
     constexpr int WM = BM / 2, WN = BN / 2;        // wave quadrant
     constexpr int MT = WM / 32, NT = WN / 32;      // 32x32 MFMA tiles per wave
     // ---- epilogue.  In the accumulators a lane owns one token row and 4 consecutive features per
     // register quad.  Bias / GELU / gate are applied there, then each wave transposes its quadrant
     // through its own slice of LDS so that global stores are 16 bytes per lane with 16 (or 8)
     // consecutive lanes covering one contiguous row segment.
-    constexpr bool OUT_BF16 = (EPI != EPI_GATE_RESID);
+    constexpr bool OUT_BF16 = (EPI != EPI_GATE_RESID && EPI != EPI_PARTIAL);
     constexpr bool ACT_ERF = (EPI == EPI_SPLIT_GELU_ERF);
     constexpr int PASSES = OUT_BF16 || NT == 1 ? 1 : 2;    // fp32 rows are staged in two column halves
     constexpr int NTP = NT / PASSES;                       // 32-column tiles per pass
@@ -107,7 +108,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx16 (&acc)
         for (int i = 0; i < NT; ++i)
 #pragma unroll
             for (int vb = 0; vb < 4; ++vb) bias_raw[i][vb] = uint32x2{0u, 0u};
-        if (g.has_bias) {
+        if (EPI != EPI_PARTIAL && g.has_bias) {
 #pragma unroll
             for (int i = 0; i < NT; ++i)
 #pragma unroll
@@ -165,6 +166,15 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx16 (&acc)
                                                   : g.out1 + (size_t)m * g.ld1 + g.col1_off + (n - g.n_split);
                         *(uint4*)dst = val;
                     }
+                }
+            } else if constexpr (EPI == EPI_PARTIAL) {
+                float* const out = g.part + (size_t)part * g.M * g.N;
+#pragma unroll
+                for (int r = 0; r < WM / RPI; ++r) {
+                    const int row = r * RPI + lane / CPR;
+                    const int m = m0 + wm0 + row;
+                    const floatx4 val = *(const floatx4*)(stg + row * PITCH + (lane % CPR) * 16);
+                    if (m < g.M && n < g.n1) *(floatx4*)(out + (size_t)m * g.N + n) = val;
                 }
             } else {
                 // y = resid + gate * (...), the product rounded before the sum; the gate belongs to the row's
@@ -224,7 +234,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx16 (&acc)
 // One tile of one problem: tokens m0.., features n0...  STRADDLE: the byte where the blob switches buffers falls
 // inside the tile's weight rows (at most one tile column of a launch), so each lane picks its base.
 template <int BM, int BN, int EPI, bool STRADDLE>
-__device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0) {
+__device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0, int part) {
     constexpr int WM = BM / 2, WN = BN / 2;        // wave quadrant
     constexpr int MT = WM / 32, NT = WN / 32;      // 32x32 MFMA tiles per wave
     constexpr int MH = MT / 2, NH = NT / 2;        // of which one half-tile of an operand feeds this many
@@ -284,7 +294,9 @@ __device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0)
         w_frag[kk] = (lds_frag*)(sW + (wn0 + li) * ROWB + c);
     }
 
-    const int KT = g.K / BK;
+    // slabs of this workgroup: all, or those of its part
+    const int kt0 = EPI == EPI_PARTIAL ? part * g.part_slabs : 0;
+    const int KT = EPI == EPI_PARTIAL ? min(g.part_slabs, g.K / BK - kt0) : g.K / BK;
     bf16x8 fa[2][MH][KSTEPS], fw[2][NH][KSTEPS];
 
     // Slab kt's copies into stage st.  Past the last slab the resources are empty: the copies of the two slabs that do
@@ -292,7 +304,7 @@ __device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0)
     struct Src { __amdgpu_buffer_rsrc_t a, w; uint32_t k0; bool on; };
     auto source = [&](int kt) {
         const bool on = kt < KT;
-        return Src{make_rsrc(a_base, on ? a_bytes : 0u), make_rsrc(w_base, on ? w_bytes : 0u), on ? (uint32_t)kt * (BK * 2) : 0u, on};
+        return Src{make_rsrc(a_base, on ? a_bytes : 0u), make_rsrc(w_base, on ? w_bytes : 0u), on ? (uint32_t)(kt0 + kt) * (BK * 2) : 0u, on};
     };
     auto issue_a = [&](auto st, auto h, const Src& src, int q) {
         lds_bload16(src.a, a_voff[h.value][q], src.k0, sA + st.value * A_STAGE + unit(GA, h.value, q * 4) * 1024 + uw * 1024);
@@ -371,7 +383,7 @@ __device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0)
         slab(I1{}, kt + 1);
     }
 
-    gemm_epilogue<BM, BN, EPI>(g, acc, m0, n0, uw, smem);
+    gemm_epilogue<BM, BN, EPI>(g, acc, m0, n0, part, uw, smem);
 }
 
 // The same for small tiles, which are for layers with too few large ones to give every CU a workgroup: there the time is
@@ -382,7 +394,7 @@ __device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0)
 // 576 x 3072 x 12288: 164 us with the former loop, 111 with the 128x128 tile above, 85 with 128x64 (240 workgroups);
 // 64 x 3072 x 12288: 166, 102, 63 with 64x64; 512 x 512 x 2560: 31.4, 20.5, 12.2.
 template <int BM, int BN, int S, int EPI>
-__device__ __forceinline__ void gemm_ring_run(const GemmArgs& g, int m0, int n0) {
+__device__ __forceinline__ void gemm_ring_run(const GemmArgs& g, int m0, int n0, int part) {
     constexpr int WM = BM / 2, WN = BN / 2;        // wave quadrant
     constexpr int MT = WM / 32, NT = WN / 32;      // 32x32 MFMA tiles per wave
     constexpr int LA = BM / 32, LW = BN / 32, L = LA + LW;     // wave-loads (8 rows each) per wave and slab
@@ -427,13 +439,15 @@ __device__ __forceinline__ void gemm_ring_run(const GemmArgs& g, int m0, int n0)
         a_frag[kk] = (lds_frag*)(smem + (wm0 + li) * ROWB + c);
         w_frag[kk] = (lds_frag*)(smem + BM * ROWB + (wn0 + li) * ROWB + c);
     }
-    const int KT = g.K / BK;
+    // slabs of this workgroup: all, or those of its part
+    const int kt0 = EPI == EPI_PARTIAL ? part * g.part_slabs : 0;
+    const int KT = EPI == EPI_PARTIAL ? min(g.part_slabs, g.K / BK - kt0) : g.K / BK;
     bf16x8 fa[2][MT][KSTEPS], fw[2][NT][KSTEPS];
 
     struct Src { __amdgpu_buffer_rsrc_t a, w; uint32_t k0; bool on; };
     auto source = [&](int kt) {
         const bool on = kt < KT;
-        return Src{make_rsrc(a_base, on ? a_bytes : 0u), make_rsrc(w_base, on ? w_bytes : 0u), on ? (uint32_t)kt * (BK * 2) : 0u, on};
+        return Src{make_rsrc(a_base, on ? a_bytes : 0u), make_rsrc(w_base, on ? w_bytes : 0u), on ? (uint32_t)(kt0 + kt) * (BK * 2) : 0u, on};
     };
     auto issue = [&](const Src& src, int stage, int q) {       // q-th of L copies of a slab into the stage at byte `stage`
         char* const dst = smem + stage + uw * 1024 + q * 4096;
@@ -491,17 +505,18 @@ __device__ __forceinline__ void gemm_ring_run(const GemmArgs& g, int m0, int n0)
         slab(I1{}, kt + 1, here, next);
         here = next;
     }
-    gemm_epilogue<BM, BN, EPI>(g, acc, m0, n0, uw, smem);
+    gemm_epilogue<BM, BN, EPI>(g, acc, m0, n0, part, uw, smem);
 }
 
-// Workgroup `bid` of the `nblk` that problem owns.
-// S: stages of the ring loop, 0 = the quadrant-phase loop (two stages).
+// Workgroup `bid` of the `nblk` that problem owns.  S: stages of the ring loop, 0 = the quadrant-phase loop (two stages).
 template <int BM, int BN, int S, int EPI>
 __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, uint32_t bid, uint32_t nblk) {
-    // logical tile: XCD-contiguous id, then groups of GM row-tiles walked feature-tile-major
+    // logical tile: XCD-contiguous id, then (part of K by part of K) groups of GM row-tiles walked feature-tile-major
     const int tiles_m = (g.M + BM - 1) / BM;
     const int tiles_n = (g.n1 - g.n0 + BN - 1) / BN;
-    const uint32_t lid = xcd_contiguous_id(bid, nblk);
+    uint32_t lid = xcd_contiguous_id(bid, nblk);
+    const int part = EPI == EPI_PARTIAL ? lid / (tiles_m * tiles_n) : 0;
+    lid -= part * (tiles_m * tiles_n);
     // row-tile groups of about 8, all of one size: a short last group would walk every weight tile once more
     const int n_groups = max(1, (tiles_m + 4) / 8);
     const int GM = (tiles_m + n_groups - 1) / n_groups;
@@ -511,11 +526,11 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, uint32_t bid, 
     const int m0 = (first_m + (lid % (GM * tiles_n)) % gsz) * BM;
     const int n0 = g.n0 + (lid % (GM * tiles_n)) / gsz * BN;
     if constexpr (S > 0) {
-        gemm_ring_run<BM, BN, S, EPI>(g, m0, n0);
+        gemm_ring_run<BM, BN, S, EPI>(g, m0, n0, part);
     } else {
         const uint64_t t_begin = g.w_off + (uint64_t)n0 * g.K * 2, t_end = g.w_off + (uint64_t)min(n0 + BN, g.N) * g.K * 2;
-        if (g.W.split > t_begin && g.W.split < t_end) gemm_tile_run<BM, BN, EPI, true>(g, m0, n0);
-        else gemm_tile_run<BM, BN, EPI, false>(g, m0, n0);
+        if (g.W.split > t_begin && g.W.split < t_end) gemm_tile_run<BM, BN, EPI, true>(g, m0, n0, part);
+        else gemm_tile_run<BM, BN, EPI, false>(g, m0, n0, part);
     }
 }
 
@@ -541,7 +556,7 @@ __global__ __launch_bounds__(256) void gemm_pair_kernel(GemmPair p) {
 template <int BM, int BN, int S, int EPI>
 constexpr size_t gemm_smem() {
     constexpr int WM = BM / 2, WN = BN / 2;
-    constexpr int staged_row = EPI != EPI_GATE_RESID ? WN * 2 + 16 : (WN > 32 ? WN * 2 : WN * 4) + 32;     // the epilogue's PITCH
+    constexpr int staged_row = EPI != EPI_GATE_RESID && EPI != EPI_PARTIAL ? WN * 2 + 16 : (WN > 32 ? WN * 2 : WN * 4) + 32;     // the epilogue's PITCH
     constexpr size_t loop = (size_t)(S > 0 ? S : STAGES) * (BM + BN) * ROWB, epi = 4ull * WM * staged_row;
     return loop > epi ? loop : epi;
 }
@@ -553,12 +568,16 @@ hipError_t allow_smem(Kernel kernel, size_t smem) {
 
 template <int BM, int BN, int S, int EPI>
 hipError_t launch(const GemmArgs& g, const GemmArgs* second, hipStream_t s) {
-    auto tiles = [](const GemmArgs& p) { return (uint32_t)(((p.M + BM - 1) / BM) * ((p.n1 - p.n0 + BN - 1) / BN)); };
+    auto tiles = [](const GemmArgs& p) {
+        return (uint32_t)(((p.M + BM - 1) / BM) * ((p.n1 - p.n0 + BN - 1) / BN)) * (EPI == EPI_PARTIAL ? p.ksplits : 1);
+    };
     constexpr size_t smem = gemm_smem<BM, BN, S, EPI>();
     if (!second) {
         static const hipError_t allowed = allow_smem(gemm_bf16_kernel<BM, BN, S, EPI>, smem);
         if (allowed != hipSuccess) return allowed;
         hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, S, EPI>), dim3(tiles(g)), dim3(256), smem, s, g);
+    } else if constexpr (BM * BN == 65536 && EPI == EPI_PARTIAL) {
+        return hipErrorInvalidValue;               // does not fit the registers; gemm_pair_tile never asks for it
     } else {
         static const hipError_t allowed = allow_smem(gemm_pair_kernel<BM, BN, S, EPI>, smem);
         if (allowed != hipSuccess) return allowed;

@@ -26,7 +26,13 @@ struct GemmArgs {
     // sample b = m / rows_per_sample; it uses gate + b*gate_bs and sits at b*resid_bs + i*ldy in resid,
     // b*y_bs + i*ldy in y (strides in elements).  rows_per_sample = 0: one sample, strides unused.
     int rows_per_sample; long gate_bs, resid_bs, y_bs;
+    // EPI_GATE_RESID with the sum over K cut into ksplits parts of part_slabs 64-wide slabs each (gemm_set_split), computed
+    // by workgroups of their own into part[ksplits][M][N] and put together by a second kernel; 0 or 1 = whole.
+    int ksplits, part_slabs;
+    float* part;
 };
+int gemm_splits(int rows, int rows2, int N, int K);      // parts to cut K into, for one sample's tokens (rows2: of a second layer in the launch)
+void gemm_set_split(GemmArgs* g, int splits, float* part);
 const char* gemm_check(const GemmArgs& g);
 enum { GEMM_256x256 = 0, GEMM_128x128 = 1, GEMM_128x256 = 2, GEMM_128x64 = 3, GEMM_64x64 = 4, GEMM_TILES = 5 };     // tokens x features
 int gemm_tile(const GemmArgs& g);      // tile gemm_launch will use
@@ -36,6 +42,7 @@ hipError_t gemm_launch(const GemmArgs& g, hipStream_t s);
 hipError_t gemm_launch_split_gelu(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s);
 hipError_t gemm_launch_split_gelu_erf(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s);
 hipError_t gemm_launch_gate_resid(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s);
+hipError_t gemm_launch_partial(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s);     // the parts of a cut sum only
 hipError_t mfma_rate_launch(int iters, int random_operands, float* out, hipStream_t s);   // diagnostic: MFMAs on registers only
 // diagnostic: MFMAs sharing the SIMD with LDS fragment reads and VALU work (see gemm.hip for the supported mixes)
 hipError_t mix_rate_launch(int iters, int waves, int reads16, int valu, int exps, float* out, hipStream_t s);
@@ -69,7 +76,14 @@ struct AttnArgs {
     bf16 *dst0, *dst1, *send;
     int ld, h0;
     long bs0, bs1, send_bs;
+    // The keys in `splits` parts of part_tiles 64-key tiles each (attn_set_split), merged by a second kernel; 1 = whole.
+    // Scratch, float: part_o [splits][H][ceil(nq/32)][32 * hd] in register order, part_ml [..][32] (reference, row sum).
+    int splits, part_tiles;
+    float *part_o, *part_ml;
 };
+int attn_splits(int heads, int nq, int nk, int hd);      // parts to cut the keys into, for one sample's heads
+uint64_t attn_part_floats(int heads, int nq, int hd, int splits);      // scratch for all samples' heads; 0 if splits is 1
+void attn_set_split(AttnArgs* a, int splits, float* scratch);          // after H, nq, nk and hd are set
 const char* attn_check(const AttnArgs& a);
 hipError_t attn_launch(const AttnArgs& a, hipStream_t s);
 int attn_waves(const AttnArgs& a);      // waves per workgroup attn_launch takes (host arithmetic only)

@@ -70,10 +70,37 @@ __device__ __forceinline__ void store_rows(const AttnArgs& a, int h, int q, int 
         }
 }
 
-// NW waves of 32 queries each per workgroup: 4 (two workgroups per CU), 7 or 8 (one per CU).
-template <int HD, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void attn_fwd_kernel(AttnArgs a) {
-    constexpr int BQ = 32 * NW;
+// What a sweep holds after some of its tiles, as it lies in registers: O^T a KiB per store and wave, then reference and
+// row sum of every lane.  A workgroup's state is state_floats<HD, NW>() long.
+template <int HD>
+__device__ __forceinline__ void store_state(float* to, int wave, int lane, const floatx16 (&o)[HD / 32], float mc, float l_run) {
+    float* const p = to + wave * (64 * (HD / 2 + 2));
+#pragma unroll
+    for (int i = 0; i < HD / 8; ++i) {
+        const floatx4 v = {o[i / 4][i % 4 * 4], o[i / 4][i % 4 * 4 + 1], o[i / 4][i % 4 * 4 + 2], o[i / 4][i % 4 * 4 + 3]};
+        *(floatx4*)(p + i * 256 + lane * 4) = v;
+    }
+    *(float2*)(p + HD / 8 * 256 + lane * 2) = make_float2(mc, l_run);
+}
+template <int HD>
+__device__ __forceinline__ void load_state(const float* from, int wave, int lane, floatx16 (&o)[HD / 32], float& mc, float& l_run) {
+    const float* const p = from + wave * (64 * (HD / 2 + 2));
+#pragma unroll
+    for (int i = 0; i < HD / 8; ++i) {
+        const floatx4 v = *(const floatx4*)(p + i * 256 + lane * 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[i / 4][i % 4 * 4 + e] = v[e];
+    }
+    const float2 ml = *(const float2*)(p + HD / 8 * 256 + lane * 2);
+    mc = ml.x;
+    l_run = ml.y;
+}
+
+// One sweep of a workgroup (NW waves of 32 queries each, the wave's first at q0) over the key tiles [T0, T1) of head h.
+// `from`: not NULL = go on from the state another workgroup left there after the tiles before T0 (store_state).
+// finish(o, mc, l) gets O^T, the reference it is taken against and the lane's row sum.
+template <int HD, int NW, class Finish>
+__device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int T0, int T1, const float* from, Finish&& finish) {
     constexpr int KCH = HD / 8;                 // 16-byte chunks per K row
     constexpr int KROW = HD * 2;                // bytes per K row in LDS
     constexpr int KL = BKV * KCH / 64, VL = HD * 8 / 64;   // wave-loads (1 KiB each) per K / V^T tile
@@ -88,12 +115,6 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_kernel(AttnArgs a) {
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lj = lane & 31, lg = lane >> 5;
-
-    const int nqt = (a.nq + BQ - 1) / BQ;
-    const uint32_t lid = xcd_contiguous_id(blockIdx.x, gridDim.x);
-    const int hs = lid / nqt, qt = lid % nqt;
-    const int h = hs / a.splits, part = hs % a.splits;       // head, and which part of the keys
-    const int q0 = qt * BQ + wave * 32;
 
     // K swizzle: 256-byte rows (HD=128) rotate over 16 chunk slots, 128-byte rows over 8
     auto kswz = [](int key) { return HD == 128 ? (key & 15) : (((key >> 1) & 7) ^ ((key & 1) << 2)); };
@@ -151,7 +172,6 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_kernel(AttnArgs a) {
     // key row fed to MFMA row i: swap bits 2 and 3 of i
     const int krow = (lj & 0x13) | ((lj & 4) << 1) | ((lj & 8) >> 1);
 
-    const int T0 = part * a.part_tiles, NT = min((a.nk + BKV - 1) / BKV, T0 + a.part_tiles);     // this workgroup's tiles
     int out_of_range = 0;                       // wave-uniform: a fast tile met scores it could not take
 
     // One tile.  The LDS buffer is a compile-time constant so that fragment addresses are a per-lane
@@ -169,7 +189,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_kernel(AttnArgs a) {
     auto tile = [&](int t, auto buf_c, auto tracking_c) __attribute__((always_inline)) {
         constexpr int buf = decltype(buf_c)::value;
         constexpr bool tracking = decltype(tracking_c)::value;
-        if (t + 1 < NT) issue_tile(t + 1, buf ^ 1);
+        if (t + 1 < T1) issue_tile(t + 1, buf ^ 1);
         const char* cK = sK + buf * K_TILE;
         const char* cV = sV + buf * V_TILE;
 
@@ -312,45 +332,124 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_kernel(AttnArgs a) {
 
         __syncthreads();                        // tile t+1 has landed, tile t may be overwritten
     };
-    // One sweep over the keys: the first tile always tracks (it sets the reference), the others in pairs.
+    // One sweep: the first tile tracks (it sets the reference) unless the state is inherited, the others go in pairs.
     auto sweep = [&](auto tracking_c) __attribute__((always_inline)) {
+        int t = T0;
+        if (from) {
+            load_state<HD>(from, wave, lane, o, mc, l_run);
+            issue_tile(t, 1);
+            __syncthreads();                    // (waits for the LDS-DMA, then the barrier)
+        } else {
 #pragma unroll
-        for (int d = 0; d < DT; ++d)
+            for (int d = 0; d < DT; ++d)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) o[d][v] = 0.f;
-        mc = -INFINITY;
-        l_run = 0.f;
-        issue_tile(T0, 0);
-        __syncthreads();                        // (waits for the LDS-DMA, then the barrier)
-        tile(T0, std::integral_constant<int, 0>{}, std::true_type{});
-        for (int t = T0 + 1; t < NT; t += 2) {
+                for (int v = 0; v < 16; ++v) o[d][v] = 0.f;
+            mc = -INFINITY;
+            l_run = 0.f;
+            issue_tile(t, 0);
+            __syncthreads();
+            tile(t, std::integral_constant<int, 0>{}, std::true_type{});
+            ++t;
+        }
+        for (; t < T1; t += 2) {
             tile(t, std::integral_constant<int, 1>{}, tracking_c);
-            if (t + 1 < NT) tile(t + 1, std::integral_constant<int, 0>{}, tracking_c);
+            if (t + 1 < T1) tile(t + 1, std::integral_constant<int, 0>{}, tracking_c);
         }
     };
     sweep(std::false_type{});
     // the K/V tiles are the workgroup's: if any wave met a tile out of range, all of them go again
     if (__syncthreads_or(out_of_range)) sweep(std::true_type{});
+    finish(o, mc, l_run);
+}
 
-    const float l_tot = l_run + __shfl_xor(l_run, 32);
-    if (a.splits > 1) {
-        // part of the keys only: O^T, the reference it is taken against and the row sum go to the scratch buffer as they
-        // lie in registers, 1 KiB per store
-        if (q0 < a.nq) {
-            const size_t tile32 = ((size_t)part * a.H + h) * ((a.nq + 31) / 32) + q0 / 32;
-            float* const po = a.part_o + tile32 * (32 * HD);
+// NW waves of 32 queries each per workgroup: 4 (two workgroups per CU), 7 or 8 (one per CU).
+template <int HD, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void attn_fwd_kernel(AttnArgs a) {
+    constexpr int BQ = 32 * NW, DT = HD / 32;
+    const int nqt = (a.nq + BQ - 1) / BQ;
+    const uint32_t lid = xcd_contiguous_id(blockIdx.x, gridDim.x);
+    const int hs = lid / nqt, qt = lid % nqt;
+    const int h = hs / a.splits, part = hs % a.splits;       // head, and which part of the keys
+    const int lane = threadIdx.x & 63, lj = lane & 31, lg = lane >> 5;
+    const int q0 = qt * BQ + (threadIdx.x >> 6) * 32;
+    const int T0 = part * a.part_tiles, T1 = min((a.nk + BKV - 1) / BKV, T0 + a.part_tiles);
+    attn_sweep<HD, NW>(a, h, q0, T0, T1, nullptr, [&](floatx16 (&o)[DT], float mc, float l_run) {
+        const float l_tot = l_run + __shfl_xor(l_run, 32);
+        if (a.splits > 1) {
+            // part of the keys only: O^T, the reference it is taken against and the row sum go to the scratch buffer as they
+            // lie in registers, 1 KiB per store
+            if (q0 < a.nq) {
+                const size_t tile32 = ((size_t)part * a.H + h) * ((a.nq + 31) / 32) + q0 / 32;
+                float* const po = a.part_o + tile32 * (32 * HD);
 #pragma unroll
-            for (int d = 0; d < DT; ++d)
+                for (int d = 0; d < DT; ++d)
 #pragma unroll
-                for (int vb = 0; vb < 4; ++vb) {
-                    const floatx4 v = {o[d][vb * 4], o[d][vb * 4 + 1], o[d][vb * 4 + 2], o[d][vb * 4 + 3]};
-                    *(floatx4*)(po + (d * 4 + vb) * 256 + lane * 4) = v;
-                }
-            if (lg == 0) *(float2*)(a.part_ml + tile32 * 64 + lj * 2) = make_float2(mc, l_tot);
+                    for (int vb = 0; vb < 4; ++vb) {
+                        const floatx4 v = {o[d][vb * 4], o[d][vb * 4 + 1], o[d][vb * 4 + 2], o[d][vb * 4 + 3]};
+                        *(floatx4*)(po + (d * 4 + vb) * 256 + lane * 4) = v;
+                    }
+                if (lg == 0) *(float2*)(a.part_ml + tile32 * 64 + lj * 2) = make_float2(mc, l_tot);
+            }
+            return;
         }
-        return;
+        store_rows<HD>(a, h, q0 + lj, lg, [&](int d, int v) { return o[d][v]; }, 1.0f / l_tot);
+    });
+}
+
+// The same work dealt out evenly: a grid that takes 5.02 generations of workgroups pays for six, so here one workgroup per
+// CU stays and every XCD gets the same number of key tiles.  The unit is a group of 32 query tiles, one per CU of an XCD,
+// swept in step (they share K and V tiles through the XCD's L2); XCD x of 8 takes the x-th eighth of the groups' key tiles
+// laid end to end.  Where an eighth ends inside a group, XCD x sweeps the group's first tiles -- before anything else -- and
+// leaves the state of every sweep in memory, and XCD x + 1 goes on from there after its own groups, a generation or more
+// later: the same tiles in the same order, so the same bits as one sweep.  Should the state not be there when it is needed
+// (its workgroup has not been given a CU for kWaitTicks), the sweep starts over from the first tile.
+// 12 heads x 27280 x 128: 3.91 ms, 4.38 in six generations of 7-wave workgroups (the slowest XCD decides: their clocks differ
+// by 3 %); 48 heads x 4608: 464 us, 467 in four.
+constexpr unsigned long long kWaitTicks = 2000000;       // 20 ms of the 100 MHz counter
+template <int HD>
+__global__ __launch_bounds__(512, 2) void attn_even_kernel(AttnArgs a) {
+    constexpr int NW = 8, BQ = 32 * NW, DT = HD / 32;
+    __shared__ int ready;
+    const int lane = threadIdx.x & 63, lj = lane & 31, lg = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
+    const int nqt = (a.nq + BQ - 1) / BQ, items = nqt * a.H, NT = (a.nk + BKV - 1) / BKV;
+    const long total = (long)((items + 31) / 32) * NT, u0 = total * x / 8, u1 = total * (x + 1) / 8;
+    const int g0 = (int)(u0 / NT), t0 = (int)(u0 % NT), g1 = (int)(u1 / NT), t1 = (int)(u1 % NT);     // g1 > g0: see attn_even
+    // steps: the head of group g1 (left for XCD x + 1), the whole groups, the rest of group g0
+    const int first_whole = t0 ? g0 + 1 : g0, n_steps = 1 + (g1 - first_whole) + 1;
+    for (int step = 0; step < n_steps; ++step) {
+        const bool leave = step == 0, take = step == n_steps - 1;
+        if ((leave && !t1) || (take && !t0)) continue;
+        const int item = (leave ? g1 : take ? g0 : first_whole + step - 1) * 32 + j;
+        if (item >= items) continue;
+        const float* from = nullptr;
+        if (take) {
+            if (threadIdx.x == 0) {
+                uint32_t* const f = a.even_flags + (x - 1) * 32 + j;
+                const unsigned long long give_up = __builtin_amdgcn_s_memrealtime() + kWaitTicks;
+                int r;
+                while (!(r = __hip_atomic_load(f, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) == 1u) && __builtin_amdgcn_s_memrealtime() < give_up)
+                    __builtin_amdgcn_s_sleep(16);
+                ready = r;
+            }
+            __syncthreads();                   // orders every wave behind thread 0's acquire
+            if (ready) from = a.even_state + ((size_t)(x - 1) * 32 + j) * (NW * 64 * (HD / 2 + 2));
+        }
+        const int h = item / nqt, q0 = item % nqt * BQ + wave * 32;
+        attn_sweep<HD, NW>(a, h, q0, from ? t0 : 0, leave ? t1 : NT, from, [&](floatx16 (&o)[DT], float mc, float l_run) {
+            if (leave) {
+                store_state<HD>(a.even_state + ((size_t)x * 32 + j) * (NW * 64 * (HD / 2 + 2)), wave, lane, o, mc, l_run);
+                // One release per workgroup, by thread 0 behind the barrier: it writes back the XCD's whole L2.  By every wave
+                // it cost 57 us.
+                __syncthreads();
+                if (threadIdx.x == 0) __hip_atomic_store(a.even_flags + x * 32 + j, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            } else {
+                const float l_tot = l_run + __shfl_xor(l_run, 32);
+                store_rows<HD>(a, h, q0 + lj, lg, [&](int d, int v) { return o[d][v]; }, 1.0f / l_tot);
+            }
+        });
     }
-    store_rows<HD>(a, h, q0 + lj, lg, [&](int d, int v) { return o[d][v]; }, 1.0f / l_tot);
 }
 
 // Puts the parts of the keys together: a wave per 32 queries of a head, lanes as in attn_fwd_kernel, parts in order.
@@ -437,6 +536,8 @@ const char* attn_check(const AttnArgs& a) {
     if (a.splits > 1 && (!a.part_o || !a.part_ml || (((uintptr_t)a.part_o | (uintptr_t)a.part_ml) % 16) ||
                          a.part_tiles < 1 || (long)(a.splits - 1) * a.part_tiles * BKV >= a.nk || (long)a.splits * a.part_tiles * BKV < a.nk))
         return "attention: bad split of the keys";
+    if (a.even_state && (a.splits > 1 || !a.even_flags || ((uintptr_t)a.even_state % 16) || a.hd != 128 || (long)((a.nq + 255) / 256) * a.H <= 7 * 32))
+        return "attention: launch cannot be dealt out evenly";
     return nullptr;
 }
 
@@ -453,10 +554,8 @@ const char* attn_check(const AttnArgs& a) {
 // Short sweeps (cross-attention to a few hundred keys) and grids that end on a half-empty generation go to
 // 4; very long sweeps whose 7- and 8-wave grids need the same number of generations to 7; the rest to 8.
 // Heights 5 and 6 were built once and never won: three SIMDs share the work of four.
-int attn_waves(const AttnArgs& a) {
+static int waves_and_cost(const AttnArgs& a, double* cost) {
     const int splits = std::max(1, a.splits);
-    // a grid that cannot even give every CU one 4-wave workgroup is spread as widely as possible
-    if ((long)((a.nq + 127) / 128) * a.H * splits <= 256) return 4;
     const double tiles = splits > 1 ? a.part_tiles : (double)((a.nk + BKV - 1) / BKV);
     auto items = [&](int nw) { return (long)((a.nq + 32 * nw - 1) / (32 * nw)) * a.H * splits; };
     auto generations = [](long n, long slots) { return (double)((n + slots - 1) / slots); };
@@ -468,7 +567,15 @@ int attn_waves(const AttnArgs& a) {
     double best_cost = c8;
     if (c7 < best_cost - 1e-9) { best = 7; best_cost = c7; }
     if (c4 < best_cost - 1e-9) { best = 4; best_cost = c4; }
+    // a grid that cannot even give every CU one 4-wave workgroup is spread as widely as possible
+    if (items(4) <= 256) { best = 4; best_cost = c4; }
+    *cost = best_cost;
     return best;
+}
+
+int attn_waves(const AttnArgs& a) {
+    double cost;
+    return waves_and_cost(a, &cost);
 }
 
 // Parts the keys of a launch are cut into.  Few heads over a short sequence (a Ulysses rank's share at degree 4 or 8)
@@ -506,7 +613,38 @@ void attn_set_split(AttnArgs* a, int splits, float* scratch) {
     a->part_ml = scratch ? scratch + (uint64_t)a->splits * a->H * ((a->nq + 31) / 32) * 32 * a->hd : nullptr;
 }
 
+// Is the launch worth dealing out evenly?  In the units above, groups of 32 query tiles: an eighth of the groups per XCD,
+// a fixed part per sweep (one more of them where an eighth ends inside a group) and about 15 for leaving (17 us, most of it
+// the L2 write-back) and fetching the states.  At least eight groups: a workgroup's share must cover a whole sweep, or three of them would queue up in one.
+// 128-wide heads only: a CU holds two 8-wave workgroups of the 64-wide kernel, which one evenly dealt workgroup does not match
+// (8 heads x 30950 x 64: 2.70 against 2.36 ms).
+uint64_t attn_even_floats(int H, int nq, int nk, int hd, int splits) {
+    const long groups = ((long)((nq + 255) / 256) * H + 31) / 32;
+    if (splits > 1 || groups < 8 || hd != 128) return 0;
+    AttnArgs a{};
+    a.H = H; a.nq = nq; a.nk = nk; a.hd = hd; a.splits = 1;
+    double plain;
+    waves_and_cost(a, &plain);
+    const double tiles = (double)((nk + BKV - 1) / BKV), even = groups / 8.0 * (tiles + 2.5) + 2.5 + 15.0;
+    return even < 0.96 * plain ? (uint64_t)256 * 512 * (hd / 2 + 2) : 0;
+}
+
+void attn_set_even(AttnArgs* a, float* state, uint32_t* flags) {
+    const bool on = state && flags && attn_even_floats(a->H, a->nq, a->nk, a->hd, a->splits) > 0;
+    a->even_state = on ? state : nullptr;
+    a->even_flags = on ? flags : nullptr;
+}
+
+static hipError_t launch_even(const AttnArgs& a, hipStream_t s) {
+    const size_t smem = 2 * (BKV * 128 * 2 + 128 * 128);
+    static const hipError_t allowed = hipFuncSetAttribute((const void*)attn_even_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (allowed != hipSuccess) return allowed;
+    hipLaunchKernelGGL(attn_even_kernel<128>, dim3(256), dim3(512), smem, s, a);
+    return hipGetLastError();
+}
+
 hipError_t attn_launch(const AttnArgs& a, hipStream_t s) {
+    if (a.even_state) return launch_even(a, s);
     const int nw = attn_waves(a);
     const hipError_t e = a.hd == 128 ? launch_nw<128>(nw, a, s) : launch_nw<64>(nw, a, s);
     if (e != hipSuccess || a.splits == 1) return e;

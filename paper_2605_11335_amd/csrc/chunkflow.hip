@@ -115,6 +115,7 @@ struct Ws {
     float *x1 = nullptr, *x2 = nullptr;
     bf16* up = nullptr;        // [n_local, f]
     bf16 *ckv = nullptr, *cQ = nullptr, *cK = nullptr, *cVt = nullptr;
+    uint32_t* flags = nullptr; // ATTN_FLAGS words
     float* part = nullptr;     // partial results of layers cut along their sum, live between two launches only
     uint64_t total = 0;
 };
@@ -167,7 +168,9 @@ Ws carve(const cf_model_desc& m, int kind, char* base) {
         const int parts = sum_splits(m, kind, k);
         if (parts > 1) part = std::max(part, parts * nl * d);
     }
-    w.part = (float*)take(4 * part);
+    const uint64_t even = attn_even_floats((int)hl, m.n_total, m.n_total, m.head_dim, self_splits(m));
+    if (even) w.flags = (uint32_t*)take(4 * ATTN_FLAGS);
+    w.part = (float*)take(4 * std::max(part, even));
     w.total = off;
     return w;
 }
@@ -684,7 +687,7 @@ int run_joint_attention(Fwd& F, const RelayoutArgs* parts, int n_parts, const At
         ProfScope ps(c, F.s, K_RELAYOUT, 0, bytes);
         CF_HIP(c, pre_attention_launch(pb, n_parts, P > 1 ? (const bf16*)io->peer_q + b * peer_bs : nullptr,
                                        P > 1 ? (const bf16*)io->peer_k + b * peer_bs : nullptr,
-                                       P > 1 ? (const bf16*)io->peer_v + b * peer_bs : nullptr, pa, F.s));
+                                       P > 1 ? (const bf16*)io->peer_v + b * peer_bs : nullptr, pa, F.ws.flags, F.s));
     }
     CF_TRY(emulate_collectives(F, 3));
     AttnArgs a{};
@@ -705,6 +708,7 @@ int run_joint_attention(Fwd& F, const RelayoutArgs* parts, int n_parts, const At
         a.send = (bf16*)io->send_attn; a.send_bs = (long)peer_bs;
     }
     attn_set_split(&a, self_splits(m), F.ws.part);
+    attn_set_even(&a, F.ws.part, F.ws.flags);
     if (const char* msg = attn_check(a)) return cf_fail(c, CF_ERR_ARG, "%s", msg);
     {
         ProfScope ps(c, F.s, K_ATTN, 4.0 * B * hl * (double)m.n_total * m.n_total * hd, 0);

@@ -334,12 +334,15 @@ struct PreAttnArgs {
     int n_parts;
     const bf16 *peer_q, *peer_k, *peer_v;      // may be NULL (sp_degree 1, or projection-only use)
     PeerAttnArgs pa;
+    uint32_t* zero;                            // ATTN_FLAGS words to clear, or NULL
     int seg[7];                                // end of each segment: qk0, vt0, qk1, vt1, peer_qk, peer_vt, peer_attn
 };
 
+static_assert(ATTN_FLAGS == 256, "one word per thread of a workgroup");
 __global__ __launch_bounds__(256) void pre_attention_kernel(PreAttnArgs a) {
     __shared__ uint16_t tile[64 * (128 + 2)];
     const int b = blockIdx.x;
+    if (b == 0 && a.zero) a.zero[threadIdx.x] = 0;
     int lo = 0;
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
@@ -424,12 +427,13 @@ hipError_t ln_affine_launch(const float* x, const WView& W, uint64_t w_off, uint
 }
 
 hipError_t pre_attention_launch(const RelayoutArgs* parts, int n_parts, const bf16* peer_q, const bf16* peer_k,
-                                const bf16* peer_v, const PeerAttnArgs& pa, hipStream_t s) {
+                                const bf16* peer_v, const PeerAttnArgs& pa, uint32_t* zero, hipStream_t s) {
     if (n_parts < 1 || n_parts > 2) return hipErrorInvalidValue;
     PreAttnArgs a{};
     a.n_parts = n_parts;
     a.peer_q = peer_q; a.peer_k = peer_k; a.peer_v = peer_v;
     a.pa = pa;
+    a.zero = zero;
     int end = 0;
     for (int p = 0; p < 2; ++p) {
         if (p < n_parts) {
@@ -466,7 +470,7 @@ hipError_t pre_attention_launch(const RelayoutArgs* parts, int n_parts, const bf
 }
 
 hipError_t relayout_launch(const RelayoutArgs& r, hipStream_t s) {
-    return pre_attention_launch(&r, 1, nullptr, nullptr, nullptr, PeerAttnArgs{}, s);
+    return pre_attention_launch(&r, 1, nullptr, nullptr, nullptr, PeerAttnArgs{}, nullptr, s);
 }
 
 hipError_t checksum_launch(const void* data, uint64_t bytes, uint64_t first_word, uint64_t* out, hipStream_t s) {

@@ -80,10 +80,17 @@ struct AttnArgs {
     // Scratch, float: part_o [splits][H][ceil(nq/32)][32 * hd] in register order, part_ml [..][32] (reference, row sum).
     int splits, part_tiles;
     float *part_o, *part_ml;
+    // The whole launch dealt out evenly over the XCDs (attn_set_even); NULL = one workgroup per query tile.  Scratch: the
+    // states of 256 sweeps, and 256 flags that must be zero when the launch starts.
+    float* even_state;
+    uint32_t* even_flags;
 };
 int attn_splits(int heads, int nq, int nk, int hd);      // parts to cut the keys into, for one sample's heads
 uint64_t attn_part_floats(int heads, int nq, int hd, int splits);      // scratch for all samples' heads; 0 if splits is 1
 void attn_set_split(AttnArgs* a, int splits, float* scratch);          // after H, nq, nk and hd are set
+uint64_t attn_even_floats(int H, int nq, int nk, int hd, int splits);  // scratch of a launch worth dealing out evenly, else 0
+void attn_set_even(AttnArgs* a, float* state, uint32_t* flags);        // after attn_set_split; does nothing where it does not pay
+constexpr int ATTN_FLAGS = 256;
 const char* attn_check(const AttnArgs& a);
 hipError_t attn_launch(const AttnArgs& a, hipStream_t s);
 int attn_waves(const AttnArgs& a);      // waves per workgroup attn_launch takes (host arithmetic only)
@@ -131,8 +138,9 @@ struct PeerAttnArgs {
 // One launch for everything that does not depend on attention itself: the relayout of up to two parts (one per
 // stream), when given the peer rows (what the first exchange delivers) placed at the remote positions of
 // parts[0]'s operands (q, k copied; v transposed), and the peer attention rows of the second exchange.
+// zero: ATTN_FLAGS words to clear for the attention launch that follows, or NULL.
 hipError_t pre_attention_launch(const RelayoutArgs* parts, int n_parts, const bf16* peer_q, const bf16* peer_k,
-                                const bf16* peer_v, const PeerAttnArgs& pa, hipStream_t s);
+                                const bf16* peer_v, const PeerAttnArgs& pa, uint32_t* zero, hipStream_t s);
 
 hipError_t checksum_launch(const void* data, uint64_t bytes, uint64_t first_word, uint64_t* out, hipStream_t s);
 hipError_t f32_to_bf16_launch(const float* src, bf16* dst, size_t n, hipStream_t s);

@@ -25,7 +25,7 @@ def forward(cfg, params, inputs):
 
 
 # query tiles of 256: 12 x 24 heads = 9 groups of 32 exactly; 11 x 24 (one sample, or two of 12 heads) = 8 groups and a quarter
-@pytest.mark.parametrize("n,heads,hd,batch,sharp", [(2850, 24, 128, 1, 1.0), (2760, 24, 128, 1, 1.0), (2760, 12, 128, 2, 1.0), (2760, 12, 128, 2, 20.0)])
+@pytest.mark.parametrize("n,heads,hd,batch,sharp", [(2850, 24, 128, 1, 1.0), (2760, 24, 128, 1, 1.0), (2760, 12, 128, 2, 1.0), (2760, 24, 128, 1, 20.0)])
 def test_dealt_out_evenly(n, heads, hd, batch, sharp):
     cfg = wl.BlockConfig("even", wl.KIND_SINGLE, n_blocks=1, d=heads * hd, n_heads=heads, head_dim=hd, f=256, n_total=n, n_chunks=3, batch=batch)
     params, inputs = wl.gen_block_params(cfg, 0), wl.gen_block_inputs(cfg, 0)
@@ -40,6 +40,6 @@ def test_dealt_out_evenly(n, heads, hd, batch, sharp):
         rows = np.sort(np.random.default_rng(b).choice(n, 200, replace=False))
         ref = ob.block_forward(one, params, x, rows=rows)["y"]
         print(f"sample {b}: rel_l2={rel_l2(y[b][rows], ref):.3e}", flush=True)
-        # a logit of standard deviation 20 moves by 0.05 when q and k are rounded to bf16, and its weight by as many per cent:
-        # with sharp logits only the bits above are held tightly
+        # a logit of standard deviation 20 moves by 0.05 when q and k are rounded to bf16, and its weight by as many per cent;
+        # tiles then go out of the fast softmax's range, and each part of a sweep is repeated by the workgroup that has it
         assert rel_l2(y[b][rows], ref) <= (1e-2 if sharp == 1.0 else 5e-2)

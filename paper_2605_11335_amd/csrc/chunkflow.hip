@@ -528,15 +528,37 @@ int run_modvec(Fwd& F, const std::string& wname, const std::string& bname, const
     });
 }
 
-// `rows` rows of the whole batch, rows_per_sample of them per sample (0: one sample); sample b is read at
-// x + b*x_bs and modulated with shift + b*mod_bs, scale + b*mod_bs
-int run_ln_mod(Fwd& F, const float* x, const float* shift, const float* scale, bf16* out, int rows, int rows_per_sample,
-               long x_bs, long mod_bs) {
-    if (rows <= 0) return CF_OK;
-    ProfScope ps(F.c, F.s, K_LN, 0, 6.0 * rows * F.c->d.d);
-    CF_HIP(F.c, ln_modulate_launch(x, shift, scale, out, rows, F.c->d.d, F.c->d.d, rows_per_sample, x_bs, mod_bs, F.s));
+// Two modulation matrices of one shape (the streams of a double-stream block): one launch when neither needs a chunk that has
+// not been waited for yet, otherwise each in its own panels.
+int run_modvec_pair(Fwd& F, const std::string (&wname)[2], const std::string (&bname)[2], const float* t, float* const (&out)[2], long out_bs) {
+    cf_ctx* c = F.c;
+    const TensorDesc *w[2], *b[2];
+    const int have = std::max(c->waited_upto, c->P(F.block).n_res_chunks - 1);
+    bool pair = true;
+    for (int i = 0; i < 2; ++i) {
+        w[i] = &T(F, wname[i]);
+        b[i] = &T(F, bname[i]);
+        if ((int)((std::max(w[i]->off + w[i]->bytes(), b[i]->off + b[i]->bytes()) - 1) / c->chunk_bytes) > have) pair = false;
+    }
+    if (!pair) {
+        for (int i = 0; i < 2; ++i) CF_TRY(run_modvec(F, wname[i], bname[i], t, out[i], out_bs));
+        return CF_OK;
+    }
+    const int B = batch_of(c->d), n = (int)w[0]->rows, K = (int)w[0]->cols;
+    ProfScope ps(c, F.s, K_MODVEC, 4.0 * B * n * K, 4.0 * n * K);
+    CF_HIP(c, modvec_launch(F.W, w[0]->off, b[0]->off, t, out[0], 0, n, K, B, out_bs, F.s, w[1]->off, b[1]->off, out[1]));
     return CF_OK;
 }
+
+int run_ln_mod(Fwd& F, const LnArgs* parts, int n_parts) {
+    int rows = 0;
+    for (int i = 0; i < n_parts; ++i) rows += parts[i].rows;
+    if (rows <= 0) return CF_OK;
+    ProfScope ps(F.c, F.s, K_LN, 0, 6.0 * rows * F.c->d.d);
+    CF_HIP(F.c, ln_modulate_launch(parts, n_parts, F.c->d.d, F.s));
+    return CF_OK;
+}
+int run_ln_mod(Fwd& F, const LnArgs& a) { return run_ln_mod(F, &a, 1); }
 
 // out-feature panels of one linear layer; `g` carries everything but the panel and the weights
 int run_linear(Fwd& F, int kid, const std::string& wname, const std::string& bname, GemmArgs g) {
@@ -757,7 +779,7 @@ int fwd_single(Fwd& F) {
     const long mod_bs = 3L * d, xs = x_stride(io, (long)nl * d);
     CF_TRY(run_modvec(F, "w_mod", "b_mod", io->temb, F.ws.mod, mod_bs));
     const float *shift = F.ws.mod, *scale = F.ws.mod + d, *gate = F.ws.mod + 2 * d;
-    CF_TRY(run_ln_mod(F, io->x, shift, scale, F.ws.xn, rows, rps, xs, mod_bs));
+    CF_TRY(run_ln_mod(F, LnArgs{io->x, shift, scale, F.ws.xn, rows, rps, xs, mod_bs}));
     if (m.qk_rmsnorm) { CF_TRY(need(F, T(F, "q_norm"))); CF_TRY(need(F, T(F, "k_norm"))); }
     GemmArgs g{};
     g.A = F.ws.xn; g.lda = d; g.M = rows; g.epi = EPI_SPLIT_GELU;
@@ -1375,7 +1397,8 @@ int cf_op_attention(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, ui
 int cf_op_ln_modulate(const float* x, const float* shift, const float* scale, uint16_t* xn, int32_t rows, int32_t d,
                       void* stream) {
     if (!x || !shift || !scale || !xn) return cf_fail(nullptr, CF_ERR_ARG, "null operand");
-    hipError_t e = ln_modulate_launch(x, shift, scale, (bf16*)xn, rows, d, d, 0, 0, 0, (hipStream_t)stream);
+    const LnArgs a{x, shift, scale, (bf16*)xn, rows, 0, 0, 0};
+    hipError_t e = ln_modulate_launch(&a, 1, d, (hipStream_t)stream);
     return e == hipSuccess ? CF_OK : cf_fail(nullptr, CF_ERR_ARG, "ln_modulate: %s", hipGetErrorString(e));
 }
 
@@ -1487,7 +1510,7 @@ int fwd_dit(Fwd& F) {
     const float *sh1 = w.mod, *sc1 = w.mod + d, *g1 = w.mod + 2 * d, *sh2 = w.mod + 3 * d, *sc2 = w.mod + 4 * d,
                 *g2 = w.mod + 5 * d;
     // self-attention
-    CF_TRY(run_ln_mod(F, io->x, sh1, sc1, w.xn, rows, rps, xs, mod_bs));
+    CF_TRY(run_ln_mod(F, LnArgs{io->x, sh1, sc1, w.xn, rows, rps, xs, mod_bs}));
     if (m.qk_rmsnorm) { CF_TRY(need(F, T(F, "q_norm"))); CF_TRY(need(F, T(F, "k_norm"))); }
     CF_TRY(run_linear(F, K_QKV, "w_qkv", "b_qkv", plain_linear(w.xn, d, rows, w.qkv, 3 * d)));
     RelayoutArgs r = relayout_for(F, w.qkv, nl, 0, "q_norm", "k_norm");
@@ -1519,8 +1542,8 @@ int fwd_dit(Fwd& F) {
         rk.map = identity_map(lc); rk.Q = nullptr; rk.K = w.cK + (size_t)b * lc * d; rk.Vt = w.cVt + (size_t)b * d * lpad;
         rk.n_pad = lpad;
         ProfScope ps(c, F.s, K_RELAYOUT, 0, 2.0 * 2 * ((double)nl * d + 2.0 * lc * d));
-        CF_HIP(c, relayout_launch(rq, F.s));
-        CF_HIP(c, relayout_launch(rk, F.s));
+        const RelayoutArgs both[2] = {rq, rk};
+        CF_HIP(c, pre_attention_launch(both, 2, nullptr, nullptr, nullptr, PeerAttnArgs{}, nullptr, F.s));
     }
     {
         AttnArgs a{};
@@ -1533,7 +1556,7 @@ int fwd_dit(Fwd& F) {
     }
     CF_TRY(run_linear(F, K_CROSS_OUT, "w_co", "b_co", resid_linear(w.c, d, rows, w.x1, nullptr, w.x2, d)));
     // FFN
-    CF_TRY(run_ln_mod(F, w.x2, sh2, sc2, w.xn, rows, rps, dense, mod_bs));
+    CF_TRY(run_ln_mod(F, LnArgs{w.x2, sh2, sc2, w.xn, rows, rps, dense, mod_bs}));
     CF_TRY(run_linear(F, K_UP, "w_up", "b_up", gelu_linear(w.xn, d, rows, w.up, f)));
     return run_linear(F, K_DOWN, "w_down", "b_down", batched(resid_linear(w.up, f, rows, w.x2, g2, io->y, d), B, nl, mod_bs, dense, xs));
 }
@@ -1557,10 +1580,15 @@ int fwd_double(Fwd& F) {
     const long xs[2] = {x_txt_stride(io, (long)per[0] * d), x_stride(io, (long)per[1] * d)};
     const long dense[2] = {(long)per[0] * d, (long)per[1] * d};
     const long mod_bs = 12L * d;
-    for (int s = 0; s < 2; ++s) CF_TRY(run_modvec(F, nm(st[s], "w_mod"), nm(st[s], "b_mod"), io->temb, w.mod + 6 * d * s, mod_bs));
+    {
+        const std::string wn[2] = {nm(st[0], "w_mod"), nm(st[1], "w_mod")}, bn[2] = {nm(st[0], "b_mod"), nm(st[1], "b_mod")};
+        float* const out[2] = {w.mod, w.mod + 6 * d};
+        CF_TRY(run_modvec_pair(F, wn, bn, io->temb, out, mod_bs));
+    }
     auto mod = [&](int s, int i) { return w.mod + 6 * d * s + i * d; };
-    for (int s = 0; s < 2; ++s)
-        CF_TRY(run_ln_mod(F, xin[s], mod(s, 0), mod(s, 1), w.xn + (size_t)row0[s] * d, rows[s], rps[s], xs[s], mod_bs));
+    LnArgs ln[2];
+    for (int s = 0; s < 2; ++s) ln[s] = LnArgs{xin[s], mod(s, 0), mod(s, 1), w.xn + (size_t)row0[s] * d, rows[s], rps[s], xs[s], mod_bs};
+    CF_TRY(run_ln_mod(F, ln, 2));
     RelayoutArgs parts[2];
     auto names = [&](const char* t, std::string (&out)[2]) { out[0] = nm(st[0], t); out[1] = nm(st[1], t); };
     std::string wn[2], bn[2];
@@ -1586,7 +1614,8 @@ int fwd_double(Fwd& F) {
         CF_TRY(run_linear_pair(F, K_OUT, wn, bn, g));
     }
     for (int s = 0; s < 2; ++s)
-        CF_TRY(run_ln_mod(F, w.x1 + (size_t)row0[s] * d, mod(s, 3), mod(s, 4), w.xn + (size_t)row0[s] * d, rows[s], rps[s], dense[s], mod_bs));
+        ln[s] = LnArgs{w.x1 + (size_t)row0[s] * d, mod(s, 3), mod(s, 4), w.xn + (size_t)row0[s] * d, rows[s], rps[s], dense[s], mod_bs};
+    CF_TRY(run_ln_mod(F, ln, 2));
     {
         GemmArgs g[2];
         for (int s = 0; s < 2; ++s) g[s] = gelu_linear(w.xn + (size_t)row0[s] * d, d, rows[s], w.up + (size_t)row0[s] * f, f);

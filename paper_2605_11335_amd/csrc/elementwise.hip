@@ -48,8 +48,10 @@ constexpr int MV_ROWS = 4;
 // at the bandwidth of the weight matrix.  A lane whose step lies past the end re-reads the row's last
 // chunk and adds nothing.
 template <int U>
-__global__ __launch_bounds__(256) void modvec_kernel(WView W, uint64_t w_off, uint64_t b_off, const float* __restrict__ t,
-                                                     float* __restrict__ m, int n0, int n1, int K, long m_bs) {
+__global__ __launch_bounds__(256) void modvec_kernel(WView W, uint64_t w_off, uint64_t b_off, uint64_t w_off2, uint64_t b_off2,
+                                                     const float* __restrict__ t, float* __restrict__ m, float* __restrict__ m2,
+                                                     int n0, int n1, int K, long m_bs) {
+    if (blockIdx.z) { w_off = w_off2; b_off = b_off2; m = m2; }      // the second matrix of a launch
     t += (size_t)blockIdx.y * K;                 // one sample of the batch per grid row
     m += (size_t)blockIdx.y * m_bs;
     const int lane = threadIdx.x & 63;
@@ -97,20 +99,22 @@ __global__ __launch_bounds__(256) void modvec_kernel(WView W, uint64_t w_off, ui
 }
 
 // ---------------------------------------------------------------------------------------------
-// LayerNorm over d (no affine, biased variance, eps 1e-6) then modulate or affine; wave per row
+// LayerNorm over d (no affine, biased variance, eps 1e-6) then modulate or affine; wave per row.  Workgroups from blocks0 on
+// have the second of a launch's two parts.
+struct LnPair { LnArgs part[2]; int blocks0; };
 template <int NJ, bool AFFINE>
-__global__ __launch_bounds__(256) void ln_kernel(const float* __restrict__ x, const float* __restrict__ shift,
-                                                 const float* __restrict__ scale, WView W, uint64_t w_off,
-                                                 uint64_t b_off, bf16* __restrict__ out, int rows, int d, int ld_out,
-                                                 int rows_per_sample, long x_bs, long mod_bs) {
+__global__ __launch_bounds__(256) void ln_kernel(LnPair p, WView W, uint64_t w_off, uint64_t b_off, int d) {
+    const LnArgs& a = p.part[(int)blockIdx.x >= p.blocks0];
     const int lane = threadIdx.x & 63;
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= rows) return;
+    const int row = ((int)blockIdx.x - ((int)blockIdx.x >= p.blocks0 ? p.blocks0 : 0)) * 4 + (threadIdx.x >> 6);
+    if (row >= a.rows) return;
     // a batch stacks samples along the rows: each has its own modulation vectors and may sit at its own stride
     int smp = 0, ri = row;
-    if (rows_per_sample) { smp = row / rows_per_sample; ri = row - smp * rows_per_sample; }
-    const float* xr = x + (size_t)smp * x_bs + (size_t)ri * d;
-    if (!AFFINE) { shift += (size_t)smp * mod_bs; scale += (size_t)smp * mod_bs; }
+    if (a.rows_per_sample) { smp = row / a.rows_per_sample; ri = row - smp * a.rows_per_sample; }
+    const float* __restrict__ xr = a.x + (size_t)smp * a.x_bs + (size_t)ri * d;
+    const float *__restrict__ shift = a.shift, *__restrict__ scale = a.scale;
+    bf16* __restrict__ out = a.xn;
+    if (!AFFINE) { shift += (size_t)smp * a.mod_bs; scale += (size_t)smp * a.mod_bs; }
     float4 v[NJ];
     float s = 0.f;
 #pragma unroll
@@ -157,18 +161,25 @@ __global__ __launch_bounds__(256) void ln_kernel(const float* __restrict__ x, co
         o[1] = (bf16)(v[j].y * rstd * a[1] + b[1]);
         o[2] = (bf16)(v[j].z * rstd * a[2] + b[2]);
         o[3] = (bf16)(v[j].w * rstd * a[3] + b[3]);
-        *(bf16x4*)(out + (size_t)row * ld_out + c) = o;
+        *(bf16x4*)(out + (size_t)row * d + c) = o;
     }
 }
 
 template <bool AFFINE>
-hipError_t ln_dispatch(const float* x, const float* shift, const float* scale, const WView& W, uint64_t w_off,
-                       uint64_t b_off, bf16* out, int rows, int d, int ld_out, int rows_per_sample, long x_bs, long mod_bs,
-                       hipStream_t s) {
-    if (rows <= 0) return hipSuccess;
-    if (d % 256 || d > 4096 || rows_per_sample < 0 || (x_bs % 4) || (mod_bs % 4)) return hipErrorInvalidValue;
-    const dim3 grid((rows + 3) / 4), blk(256);
-#define CF_LN_CASE(NJ) case NJ: hipLaunchKernelGGL((ln_kernel<NJ, AFFINE>), grid, blk, 0, s, x, shift, scale, W, w_off, b_off, out, rows, d, ld_out, rows_per_sample, x_bs, mod_bs); break;
+hipError_t ln_dispatch(const LnArgs* parts, int n_parts, const WView& W, uint64_t w_off, uint64_t b_off, int d, hipStream_t s) {
+    LnPair p{};
+    int blocks = 0;
+    for (int i = 0; i < n_parts; ++i) {
+        const LnArgs& a = parts[i];
+        if (a.rows_per_sample < 0 || (a.x_bs % 4) || (a.mod_bs % 4)) return hipErrorInvalidValue;
+        p.part[i] = a;
+        blocks += a.rows > 0 ? (a.rows + 3) / 4 : 0;
+        if (i == 0) p.blocks0 = blocks;
+    }
+    if (blocks == 0) return hipSuccess;
+    if (d % 256 || d > 4096) return hipErrorInvalidValue;
+    const dim3 grid(blocks), blk(256);
+#define CF_LN_CASE(NJ) case NJ: hipLaunchKernelGGL((ln_kernel<NJ, AFFINE>), grid, blk, 0, s, p, W, w_off, b_off, d); break;
     switch (d / 256) {
         CF_LN_CASE(1) CF_LN_CASE(2) CF_LN_CASE(3) CF_LN_CASE(4) CF_LN_CASE(6) CF_LN_CASE(8) CF_LN_CASE(12) CF_LN_CASE(16)
         default: return hipErrorInvalidValue;
@@ -179,108 +190,122 @@ hipError_t ln_dispatch(const float* x, const float* shift, const float* scale, c
 
 // ---------------------------------------------------------------------------------------------
 // q,k: optional per-head RMSNorm, then head-major placement (own heads) or send buffers (others).
-// v of other heads: send buffer.  A group of hd/8 lanes owns one (row, tensor, head) vector.
+// v of other heads: send buffer.  A wave takes one of q, k, v of one row; a group of hd/8 of its lanes owns a head's vector.
+// Everything between HBM and HBM is index arithmetic here: with a flat item index taken apart by 64-bit divisions (three per
+// 16 bytes) the kernel ran at 3.6-4.2 TB/s.
 __device__ __forceinline__ void qk_relayout_part(const RelayoutArgs& r, int bid, int nblk) {
-    const int lph = r.hd / 8;                       // lanes per head vector
-    const int vec_per_blk = 256 / lph;
-    const long n_vec = (long)r.rows * 3 * r.n_heads;
-    const int sub = threadIdx.x % lph;
-    for (long vi = (long)bid * vec_per_blk + threadIdx.x / lph; vi < n_vec; vi += (long)nblk * vec_per_blk) {
-        const int hh = vi % r.n_heads;
-        const int tns = (vi / r.n_heads) % 3;       // 0 q, 1 k, 2 v
-        const int row = vi / (3 * r.n_heads);
+    const int lane = threadIdx.x & 63;
+    const int lph = r.hd / 8, lsh = r.hd == 128 ? 4 : 3;        // lanes per head vector
+    const int vpw = 64 >> lsh, grp = lane >> lsh, sub = lane & (lph - 1);
+    float w[2][8];
+    if (r.has_norm) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) unpack8(*(const uint32x4*)wv_ptr(r.W, (t ? r.kn_off : r.qn_off) + sub * 16), w[t]);
+    }
+    const int n_other = r.n_heads - r.h_local;
+    for (uint32_t item = (uint32_t)bid * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); item < (uint32_t)r.rows * 3u; item += (uint32_t)nblk * 4u) {
+        const int row = item / 3u, tns = item % 3u;             // 0 q, 1 k, 2 v
         const int col = tns == 0 ? r.col_q : (tns == 1 ? r.col_k : r.col_v);
-        const bool own = hh >= r.h0 && hh < r.h0 + r.h_local;
-        bf16* dst;
+        bf16* const send = tns == 0 ? r.send_q : (tns == 1 ? r.send_k : r.send_v);
+        if (col < 0 || (tns == 2 && (!send || n_other == 0))) continue;      // own v goes through the transposing part
         const int lrow = r.row0 + row;
-        if (own) {
-            if (tns == 2) continue;                 // own v goes through the transposing kernel
-            bf16* base = tns == 0 ? r.Q : r.K;
-            dst = base + ((size_t)(hh - r.h0) * r.map.n_total + local_pos(r.map, lrow)) * r.hd;
-        } else {
-            bf16* base = tns == 0 ? r.send_q : (tns == 1 ? r.send_k : r.send_v);
-            if (!base) continue;
-            const int ho = hh < r.h0 ? hh : hh - r.h_local;
-            dst = base + ((size_t)ho * r.map.n_local + lrow) * r.hd;
+        bf16* const own_dst = (tns == 0 ? r.Q : r.K) + (size_t)local_pos(r.map, lrow) * r.hd + sub * 8;
+        const size_t own_hs = (size_t)r.map.n_total * r.hd, send_hs = (size_t)r.map.n_local * r.hd;
+        bf16* const send_dst = send + (size_t)lrow * r.hd + sub * 8;
+        const bf16* const src = r.src + (size_t)row * r.ld + col + sub * 8;
+        const bool turn = r.rope_cos && tns < 2;
+        float4 cs = make_float4(1.f, 1.f, 1.f, 1.f), sn = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (turn) {          // this lane's 8 elements are pairs sub*4 .. sub*4+3 of the head vector, for every head
+            const size_t ro = (size_t)lrow * (r.hd / 2) + sub * 4;
+            cs = *(const float4*)(r.rope_cos + ro);
+            sn = *(const float4*)(r.rope_sin + ro);
         }
-        if (col < 0) continue;
-        uint4 u = *(const uint4*)(r.src + (size_t)row * r.ld + col + hh * r.hd + sub * 8);
-        if ((r.has_norm || r.rope_cos) && tns < 2) {
-            float f[8];
-            unpack8(u, f);
-            if (r.has_norm) {
-                float ss = 0.f;
+        for (int h4 = 0; h4 < r.n_heads; h4 += 4 * vpw) {        // four vectors of a lane group in flight
+            uint32x4 u[4];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) ss += f[e] * f[e];
-                for (int o = lph >> 1; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
-                const float rs = rsqrtf(ss / r.hd + 1e-6f);
-                const uint4 wu = *(const uint4*)wv_ptr(r.W, (tns == 0 ? r.qn_off : r.kn_off) + sub * 16);
-                float w[8];
-                unpack8(wu, w);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) f[e] = f[e] * rs * w[e];
+            for (int q = 0; q < 4; ++q) {
+                u[q] = *(const uint32x4*)(src + min(h4 + q * vpw + grp, r.n_heads - 1) * r.hd);
             }
-            if (r.rope_cos) {
-                // this lane's 8 elements are pairs sub*4 .. sub*4+3 of the head vector
-                const size_t ro = (size_t)lrow * (r.hd / 2) + sub * 4;
-                const float4 cs = *(const float4*)(r.rope_cos + ro), sn = *(const float4*)(r.rope_sin + ro);
-                const float c[4] = {cs.x, cs.y, cs.z, cs.w}, s4[4] = {sn.x, sn.y, sn.z, sn.w};
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float a = f[2 * e], b = f[2 * e + 1];
-                    f[2 * e] = a * c[e] - b * s4[e];
-                    f[2 * e + 1] = a * s4[e] + b * c[e];
+            for (int q = 0; q < 4; ++q) {
+                const int hh = h4 + q * vpw + grp;
+                if (hh >= r.n_heads) continue;
+                const bool own = hh >= r.h0 && hh < r.h0 + r.h_local;
+                if (own ? tns == 2 : !send) continue;
+                bf16* const dst = own ? own_dst + (hh - r.h0) * own_hs : send_dst + (hh < r.h0 ? hh : hh - r.h_local) * send_hs;
+                if (tns == 2 || !(r.has_norm || turn)) {
+                    *(uint32x4*)dst = u[q];
+                    continue;
                 }
-            }
-            bf16x8 o8;
+                float f[8];
+                unpack8(u[q], f);
+                if (r.has_norm) {
+                    float ss = 0.f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) o8[e] = (bf16)f[e];
-            *(bf16x8*)(dst + sub * 8) = o8;
-        } else {
-            *(uint4*)(dst + sub * 8) = u;
+                    for (int e = 0; e < 8; ++e) ss += f[e] * f[e];
+                    for (int o = lph >> 1; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
+                    const float rs = rsqrtf(ss / r.hd + 1e-6f);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) f[e] = f[e] * rs * (tns ? w[1][e] : w[0][e]);
+                }
+                if (turn) {
+                    const float c[4] = {cs.x, cs.y, cs.z, cs.w}, s4[4] = {sn.x, sn.y, sn.z, sn.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float a = f[2 * e], b = f[2 * e + 1];
+                        f[2 * e] = a * c[e] - b * s4[e];
+                        f[2 * e + 1] = a * s4[e] + b * c[e];
+                    }
+                }
+                bf16x8 o8;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o8[e] = (bf16)f[e];
+                *(bf16x8*)dst = o8;
+            }
         }
     }
 }
 
-// [token, hd] rows of one head -> Vt[head, d, position] (keys contiguous).  64 tokens per block.
-// src element (h, i, d) at src + h*src_hs + i*src_rs + d; i counts local rows (remote=0) or
-// remote rows (remote=1) and maps to its position in the joint sequence.
-__device__ __forceinline__ void v_transpose_part(uint16_t* tile, int bx, int h, const bf16* __restrict__ src, long src_hs,
-                                                 long src_rs, int n_rows, int row0, bf16* __restrict__ Vt, int hd, int n_pad,
-                                                 const TokenMap& map, int remote) {
-    const int i0 = bx * 64;
-    const int stride = hd + 2;
-    const int cpr = hd / 8;
-    for (int q = threadIdx.x; q < 64 * cpr; q += 256) {
-        const int tr = q / cpr, c = q % cpr;
-        uint4 u = make_uint4(0, 0, 0, 0);
-        if (i0 + tr < n_rows) u = *(const uint4*)(src + (size_t)h * src_hs + (size_t)(i0 + tr) * src_rs + c * 8);
-        uint32_t* t32 = (uint32_t*)(tile + tr * stride + c * 8);   // stride even: 4-byte aligned
-        t32[0] = u.x; t32[1] = u.y; t32[2] = u.z; t32[3] = u.w;
-    }
-    __syncthreads();
-    // each thread: one d row, 8 consecutive tokens
-    for (int q = threadIdx.x; q < hd * 8; q += 256) {
-        const int dd = q >> 3, tg = (q & 7) * 8;
-        if (i0 + tg >= n_rows) continue;
-        const int i_first = row0 + i0 + tg;
-        const int p_first = remote ? remote_pos(map, i_first) : local_pos(map, i_first);
-        const int cnt = min(8, n_rows - (i0 + tg));
-        const int i_last = i_first + cnt - 1;
-        const int p_last = remote ? remote_pos(map, i_last) : local_pos(map, i_last);
-        bf16* drow = Vt + ((size_t)h * hd + dd) * n_pad;
-        if (cnt == 8 && p_last - p_first == 7 && (p_first & 7) == 0) {
-            uint16_t e[8];
+// [token, hd] rows of one head -> Vt[head, d, position] (keys contiguous).  src element (h, i, d) at
+// src + h*src_hs + i*src_rs + d; i counts local rows (remote=0) or remote rows (remote=1) and maps to its position in the
+// joint sequence.  A lane turns 8 tokens x 8 elements round in its registers: it reads 16 bytes of eight tokens and writes
+// 16 bytes (8 positions) of eight rows of Vt; the 64 lanes of a wave are 8 token groups x 8 element groups, so both sides
+// touch whole 128-byte lines.  A workgroup takes V_TOKENS(hd) tokens of all hd elements.
+__host__ __device__ __forceinline__ int v_tokens(int hd) { return hd == 128 ? 128 : 256; }
+__device__ __forceinline__ void v_transpose_part(int bx, int h, const bf16* __restrict__ src, long src_hs, long src_rs, int n_rows,
+                                                 int row0, bf16* __restrict__ Vt, int hd, int n_pad, const TokenMap& map, int remote) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int c = (lane & 7) + (hd == 128 ? (wave & 1) * 8 : 0);                             // 8-element group
+    const int i0 = bx * v_tokens(hd) + (hd == 128 ? wave >> 1 : wave) * 64 + (lane >> 3) * 8;    // first token
+    const int cnt = min(8, n_rows - i0);
+    if (cnt > 0) {
+        uint32x4 u[8];
+        const bf16* const p = src + (size_t)h * src_hs + (size_t)i0 * src_rs + c * 8;
 #pragma unroll
-            for (int k = 0; k < 8; ++k) e[k] = tile[(tg + k) * stride + dd];
-            uint4 u;
-            u.x = e[0] | ((uint32_t)e[1] << 16); u.y = e[2] | ((uint32_t)e[3] << 16);
-            u.z = e[4] | ((uint32_t)e[5] << 16); u.w = e[6] | ((uint32_t)e[7] << 16);
-            *(uint4*)(drow + p_first) = u;
+        for (int k = 0; k < 8; ++k) u[k] = *(const uint32x4*)(p + (size_t)min(k, cnt - 1) * src_rs);
+        const int i_first = row0 + i0, i_last = i_first + cnt - 1;
+        const int p_first = remote ? remote_pos(map, i_first) : local_pos(map, i_first);
+        const int p_last = remote ? remote_pos(map, i_last) : local_pos(map, i_last);
+        const bool line = cnt == 8 && p_last - p_first == 7 && (p_first & 7) == 0;
+        uint16_t* const vh = (uint16_t*)Vt + (size_t)h * hd * n_pad;         // a head's rows: 32-bit offsets from here
+        const uint32_t o0 = (uint32_t)(c * 8) * (uint32_t)n_pad;
+        if (line) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {                        // element c*8 + e of the eight tokens
+                uint32x4 t;
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    t[k] = __builtin_amdgcn_perm(u[2 * k + 1][e >> 1], u[2 * k][e >> 1], e & 1 ? 0x07060302u : 0x05040100u);
+                *(uint32x4*)(vh + (o0 + (uint32_t)e * (uint32_t)n_pad + (uint32_t)p_first)) = t;
+            }
         } else {
-            for (int k = 0; k < cnt; ++k) {
-                const int p = remote ? remote_pos(map, i_first + k) : local_pos(map, i_first + k);
-                ((uint16_t*)drow)[p] = tile[(tg + k) * stride + dd];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                if (k >= cnt) break;
+                const uint32_t pos = remote ? remote_pos(map, i_first + k) : local_pos(map, i_first + k);
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    vh[o0 + (uint32_t)e * (uint32_t)n_pad + pos] = (uint16_t)(u[k][e >> 1] >> (16 * (e & 1)));
             }
         }
     }
@@ -293,36 +318,44 @@ __device__ __forceinline__ void v_transpose_part(uint16_t* tile, int bx, int h, 
     }
 }
 
-// peer q/k rows -> head-major operands at the remote positions (16-byte chunk copies)
-__device__ __forceinline__ void peer_qk_part(int bid, int nblk, const bf16* __restrict__ pq, const bf16* __restrict__ pk,
+// peer q/k rows -> head-major operands at the remote positions: a workgroup copies PEER_PIECES 16-byte pieces of one head of
+// one tensor
+constexpr int PEER_PIECES = 256 * 8;
+__device__ __forceinline__ void peer_qk_part(int bid, int blocks_per_head, const bf16* __restrict__ pq, const bf16* __restrict__ pk,
                                              bf16* __restrict__ Q, bf16* __restrict__ K, int h_local, int hd, const TokenMap& map) {
-    const int cpr = hd / 8;
-    const int n_rem = map.n_total - map.n_local;
-    const long total = 2L * h_local * n_rem * cpr;
-    for (long q = (long)bid * 256 + threadIdx.x; q < total; q += (long)nblk * 256) {
-        const int c = q % cpr;
-        long rest = q / cpr;
-        const int i = rest % n_rem; rest /= n_rem;
-        const int h = rest % h_local;
-        const int tns = rest / h_local;
-        const bf16* s = (tns ? pk : pq) + ((size_t)h * n_rem + i) * hd + c * 8;
-        bf16* d = (tns ? K : Q) + ((size_t)h * map.n_total + remote_pos(map, i)) * hd + c * 8;
-        *(uint4*)d = *(const uint4*)s;
+    const int lsh = hd == 128 ? 4 : 3, n_rem = map.n_total - map.n_local;
+    const int th = bid / blocks_per_head, h = th % h_local;
+    const bf16* const s = (th >= h_local ? pk : pq) + (size_t)h * n_rem * hd;
+    bf16* const d = (th >= h_local ? K : Q) + (size_t)h * map.n_total * hd;
+    const int first = (bid % blocks_per_head) * PEER_PIECES + threadIdx.x, total = n_rem << lsh;
+    uint32x4 u[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        u[q] = *(const uint32x4*)(s + (size_t)min(first + q * 256, total - 1) * 8);      // (loads behind branches each take registers of their own)
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const int piece = first + q * 256;
+        if (piece < total) *(uint32x4*)(d + (size_t)remote_pos(map, piece >> lsh) * hd + (piece & ((1 << lsh) - 1)) * 8) = u[q];
     }
 }
 
 // attention rows of the other ranks' heads for this rank's tokens -> their columns of the projection operand
-__device__ __forceinline__ void peer_attn_part(int bid, int nblk, const PeerAttnArgs& p) {
-    const int cpr = p.hd / 8, n_other = p.n_heads - p.h_local;
-    const long total = (long)p.map.n_local * n_other * cpr;
-    for (long q = (long)bid * 256 + threadIdx.x; q < total; q += (long)nblk * 256) {
-        const int c = q % cpr;
-        long rest = q / cpr;
-        const int ho = rest % n_other;
-        const int i = rest / n_other;
+__device__ __forceinline__ void peer_attn_part(int bid, const PeerAttnArgs& p) {
+    const int lsh = p.hd == 128 ? 4 : 3;
+    const uint32_t n_other = p.n_heads - p.h_local, total = ((uint32_t)p.map.n_local * n_other) << lsh;
+    const uint32_t first = (uint32_t)bid * PEER_PIECES + threadIdx.x;
+    uint32x4 u[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        u[q] = *(const uint32x4*)(p.peer_attn + (size_t)min(first + q * 256, total - 1) * 8);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const uint32_t piece = first + q * 256;
+        if (piece >= total) continue;
+        const int i = (piece >> lsh) / n_other, ho = (piece >> lsh) % n_other;
         const int hh = ho < p.h0 ? ho : ho + p.h_local;
-        bf16* row = i < p.map.len0 ? p.dst + (size_t)i * p.ld : p.dst1 + (size_t)(i - p.map.len0) * p.ld;
-        *(uint4*)(row + hh * p.hd + c * 8) = *(const uint4*)(p.peer_attn + ((size_t)i * n_other + ho) * p.hd + c * 8);
+        bf16* const row = i < p.map.len0 ? p.dst + (size_t)i * p.ld : p.dst1 + (size_t)(i - p.map.len0) * p.ld;
+        *(uint32x4*)(row + hh * p.hd + (piece & ((1u << lsh) - 1)) * 8) = u[q];
     }
 }
 
@@ -340,7 +373,6 @@ struct PreAttnArgs {
 
 static_assert(ATTN_FLAGS == 256, "one word per thread of a workgroup");
 __global__ __launch_bounds__(256) void pre_attention_kernel(PreAttnArgs a) {
-    __shared__ uint16_t tile[64 * (128 + 2)];
     const int b = blockIdx.x;
     if (b == 0 && a.zero) a.zero[threadIdx.x] = 0;
     int lo = 0;
@@ -351,8 +383,8 @@ __global__ __launch_bounds__(256) void pre_attention_kernel(PreAttnArgs a) {
         if (b < a.seg[2 * p]) { qk_relayout_part(r, b - lo, a.seg[2 * p] - lo); return; }
         lo = a.seg[2 * p];
         if (b < a.seg[2 * p + 1]) {
-            const int nbx = (r.rows + 63) / 64, i = b - lo;
-            v_transpose_part(tile, i % nbx, i / nbx, r.src + r.col_v + (size_t)r.h0 * r.hd, (long)r.hd, (long)r.ld, r.rows,
+            const int nbx = (r.rows + v_tokens(r.hd) - 1) / v_tokens(r.hd), i = b - lo;
+            v_transpose_part(i % nbx, i / nbx, r.src + r.col_v + (size_t)r.h0 * r.hd, (long)r.hd, (long)r.ld, r.rows,
                              r.row0, r.Vt, r.hd, r.n_pad, r.map, 0);
             return;
         }
@@ -360,16 +392,16 @@ __global__ __launch_bounds__(256) void pre_attention_kernel(PreAttnArgs a) {
     }
     const RelayoutArgs& r0 = a.part[0];
     const int n_rem = r0.map.n_total - r0.map.n_local;
-    if (b < a.seg[4]) { peer_qk_part(b - lo, a.seg[4] - lo, a.peer_q, a.peer_k, r0.Q, r0.K, r0.h_local, r0.hd, r0.map); return; }
+    if (b < a.seg[4]) { peer_qk_part(b - lo, (a.seg[4] - lo) / (2 * r0.h_local), a.peer_q, a.peer_k, r0.Q, r0.K, r0.h_local, r0.hd, r0.map); return; }
     lo = a.seg[4];
     if (b < a.seg[5]) {
-        const int nbx = (n_rem + 63) / 64, i = b - lo;
-        v_transpose_part(tile, i % nbx, i / nbx, a.peer_v, (long)n_rem * r0.hd, (long)r0.hd, n_rem, 0, r0.Vt, r0.hd, r0.n_pad,
+        const int nbx = (n_rem + v_tokens(r0.hd) - 1) / v_tokens(r0.hd), i = b - lo;
+        v_transpose_part(i % nbx, i / nbx, a.peer_v, (long)n_rem * r0.hd, (long)r0.hd, n_rem, 0, r0.Vt, r0.hd, r0.n_pad,
                          r0.map, 1);
         return;
     }
     lo = a.seg[5];
-    if (b < a.seg[6]) peer_attn_part(b - lo, a.seg[6] - lo, a.pa);
+    if (b < a.seg[6]) peer_attn_part(b - lo, a.pa);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -401,12 +433,12 @@ inline int grid_for(long items, int per_block, int cap = 256 * 16) {
 }  // namespace
 
 hipError_t modvec_launch(const WView& W, uint64_t w_off, uint64_t b_off, const float* t, float* m, int n0, int n1,
-                         int K, int batch, long m_bs, hipStream_t s) {
+                         int K, int batch, long m_bs, hipStream_t s, uint64_t w_off2, uint64_t b_off2, float* m2) {
     if (n1 <= n0) return hipSuccess;
     if (K % 8 || batch < 1 || batch > 65535) return hipErrorInvalidValue;
-    const dim3 grid((n1 - n0 + 4 * MV_ROWS - 1) / (4 * MV_ROWS), batch);
+    const dim3 grid((n1 - n0 + 4 * MV_ROWS - 1) / (4 * MV_ROWS), batch, w_off2 ? 2 : 1);
     const int steps = (K / 8 + 63) / 64;         // steps of a lane's walk over K; taken 3 or 4 at a time
-#define CF_MV_CASE(U) hipLaunchKernelGGL(modvec_kernel<U>, grid, dim3(256), 0, s, W, w_off, b_off, t, m, n0, n1, K, m_bs)
+#define CF_MV_CASE(U) hipLaunchKernelGGL(modvec_kernel<U>, grid, dim3(256), 0, s, W, w_off, b_off, w_off2, b_off2, t, m, m2, n0, n1, K, m_bs)
     if (steps == 1) CF_MV_CASE(1);
     else if (steps == 2) CF_MV_CASE(2);
     else if (steps % 3 == 0) CF_MV_CASE(3);
@@ -415,15 +447,15 @@ hipError_t modvec_launch(const WView& W, uint64_t w_off, uint64_t b_off, const f
     return hipGetLastError();
 }
 
-hipError_t ln_modulate_launch(const float* x, const float* shift, const float* scale, bf16* xn, int rows, int d,
-                              int ld_out, int rows_per_sample, long x_bs, long mod_bs, hipStream_t s) {
-    WView none{nullptr, nullptr, 0};
-    return ln_dispatch<false>(x, shift, scale, none, 0, 0, xn, rows, d, ld_out, rows_per_sample, x_bs, mod_bs, s);
+hipError_t ln_modulate_launch(const LnArgs* parts, int n_parts, int d, hipStream_t s) {
+    if (n_parts < 1 || n_parts > 2) return hipErrorInvalidValue;
+    return ln_dispatch<false>(parts, n_parts, WView{nullptr, nullptr, 0}, 0, 0, d, s);
 }
 
 hipError_t ln_affine_launch(const float* x, const WView& W, uint64_t w_off, uint64_t b_off, bf16* xn, int rows, int d,
                             hipStream_t s) {
-    return ln_dispatch<true>(x, nullptr, nullptr, W, w_off, b_off, xn, rows, d, d, 0, 0, 0, s);
+    const LnArgs a{x, nullptr, nullptr, xn, rows, 0, 0, 0};
+    return ln_dispatch<true>(&a, 1, W, w_off, b_off, d, s);
 }
 
 hipError_t pre_attention_launch(const RelayoutArgs* parts, int n_parts, const bf16* peer_q, const bf16* peer_k,
@@ -440,9 +472,10 @@ hipError_t pre_attention_launch(const RelayoutArgs* parts, int n_parts, const bf
             const RelayoutArgs& r = parts[p];
             if (r.hd != 64 && r.hd != 128) return hipErrorInvalidValue;
             a.part[p] = r;
-            if (r.rows > 0) end += grid_for((long)r.rows * 3 * r.n_heads, 256 / (r.hd / 8));
+            if (r.rows > (1 << 29)) return hipErrorInvalidValue;             // 32-bit item indices
+            if (r.rows > 0) end += grid_for((long)r.rows * 3, 4, 1 << 16);     // a wave per tensor of a row
             a.seg[2 * p] = end;
-            if (r.rows > 0 && r.col_v >= 0 && r.Vt) end += ((r.rows + 63) / 64) * r.h_local;
+            if (r.rows > 0 && r.col_v >= 0 && r.Vt) end += ((r.rows + v_tokens(r.hd) - 1) / v_tokens(r.hd)) * r.h_local;
             a.seg[2 * p + 1] = end;
         } else {
             a.seg[2 * p] = a.seg[2 * p + 1] = end;
@@ -451,9 +484,10 @@ hipError_t pre_attention_launch(const RelayoutArgs* parts, int n_parts, const bf
     const RelayoutArgs& r0 = parts[0];
     const int n_rem = r0.map.n_total - r0.map.n_local;
     if (peer_q && peer_k && peer_v && n_rem > 0) {
-        end += grid_for(2L * r0.h_local * n_rem * (r0.hd / 8), 256);
+        if ((long)n_rem * (r0.hd / 8) > (1L << 30)) return hipErrorInvalidValue;
+        end += 2 * r0.h_local * (int)(((long)n_rem * (r0.hd / 8) + PEER_PIECES - 1) / PEER_PIECES);
         a.seg[4] = end;
-        end += ((n_rem + 63) / 64) * r0.h_local;
+        end += ((n_rem + v_tokens(r0.hd) - 1) / v_tokens(r0.hd)) * r0.h_local;
         a.seg[5] = end;
     } else {
         a.seg[4] = a.seg[5] = end;
@@ -461,16 +495,14 @@ hipError_t pre_attention_launch(const RelayoutArgs* parts, int n_parts, const bf
     if (pa.peer_attn && pa.n_heads > pa.h_local && pa.map.n_local > 0) {
         if ((pa.hd != 64 && pa.hd != 128) || !pa.dst || (pa.ld % 8)) return hipErrorInvalidValue;
         if (!a.pa.dst1) a.pa.dst1 = pa.dst + (size_t)pa.map.len0 * pa.ld;
-        end += grid_for((long)pa.map.n_local * (pa.n_heads - pa.h_local) * (pa.hd / 8), 256);
+        const long pieces = (long)pa.map.n_local * (pa.n_heads - pa.h_local) * (pa.hd / 8);
+        if (pieces > (1L << 31)) return hipErrorInvalidValue;
+        end += (int)((pieces + PEER_PIECES - 1) / PEER_PIECES);
     }
     a.seg[6] = end;
     if (end == 0) return hipSuccess;
     hipLaunchKernelGGL(pre_attention_kernel, dim3(end), dim3(256), 0, s, a);
     return hipGetLastError();
-}
-
-hipError_t relayout_launch(const RelayoutArgs& r, hipStream_t s) {
-    return pre_attention_launch(&r, 1, nullptr, nullptr, nullptr, PeerAttnArgs{}, nullptr, s);
 }
 
 hipError_t checksum_launch(const void* data, uint64_t bytes, uint64_t first_word, uint64_t* out, hipStream_t s) {

@@ -95,16 +95,24 @@ const char* attn_check(const AttnArgs& a);
 hipError_t attn_launch(const AttnArgs& a, hipStream_t s);
 int attn_waves(const AttnArgs& a);      // waves per workgroup attn_launch takes (host arithmetic only)
 
-// m[b][n] = sum_k W[n,k] t[b][k] + bias[n]  (fp32 out), rows [n0, n1), for `batch` vectors t + b*K -> m + b*m_bs
+// m[b][n] = sum_k W[n,k] t[b][k] + bias[n]  (fp32 out), rows [n0, n1), for `batch` vectors t + b*K -> m + b*m_bs.
+// w_off2 != 0: a second matrix of the same shape (bias at b_off2) in the same launch, its result at m2.
 hipError_t modvec_launch(const WView& W, uint64_t w_off, uint64_t b_off, const float* t, float* m,
-                         int n0, int n1, int K, int batch, long m_bs, hipStream_t s);
+                         int n0, int n1, int K, int batch, long m_bs, hipStream_t s, uint64_t w_off2 = 0, uint64_t b_off2 = 0,
+                         float* m2 = nullptr);
 
 // xn = LN(x) * (1 + scale) + shift  (fp32 in, bf16 out); with ln_w/ln_b (blob offsets, has_affine)
 // instead: xn = LN(x) * w + b.
 // Row r of a batch is row r % rows_per_sample of sample b = r / rows_per_sample: read at x + b*x_bs, modulated
-// with shift + b*mod_bs, scale + b*mod_bs; written densely to xn + r*ld_out.
-hipError_t ln_modulate_launch(const float* x, const float* shift, const float* scale, bf16* xn,
-                              int rows, int d, int ld_out, int rows_per_sample, long x_bs, long mod_bs, hipStream_t s);
+// with shift + b*mod_bs, scale + b*mod_bs; written densely to xn + r*ld_out.  rows_per_sample = 0: one sample.
+struct LnArgs {
+    const float *x, *shift, *scale;
+    bf16* xn;
+    int rows, rows_per_sample;
+    long x_bs, mod_bs;
+};
+// one or two (the streams of a double-stream block) in one launch, rows of width d
+hipError_t ln_modulate_launch(const LnArgs* parts, int n_parts, int d, hipStream_t s);
 hipError_t ln_affine_launch(const float* x, const WView& W, uint64_t w_off, uint64_t b_off, bf16* xn,
                             int rows, int d, hipStream_t s);
 
@@ -123,7 +131,6 @@ struct RelayoutArgs {
     int n_pad;
     bf16 *send_q, *send_k, *send_v;   // [n_heads - h_local, n_local, hd] (may be NULL)
 };
-hipError_t relayout_launch(const RelayoutArgs& r, hipStream_t s);
 
 // What this rank receives from the second exchange (Sec. 2.1): the attention output of the other ranks' heads for
 // its own tokens, peer_attn [n_local, n_heads - h_local, hd], copied into the columns of those heads in the

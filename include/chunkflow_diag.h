@@ -22,8 +22,8 @@ extern "C" {
 int cf_plan_attention(int32_t H, int32_t nq, int32_t nk, int32_t head_dim, int32_t* waves_per_workgroup);
 
 /* Host-only view of the tile a linear layer over m_rows tokens and n_features output features is
- * launched with (the GEMMs of App. B), for a layer of 3072 input features: *tile_rows receives 256 (256 x 256
- * tiles, one workgroup per CU) or 128 (a smaller tile).  The big tile has the better arithmetic intensity; a
+ * launched with (the GEMMs of App. B), for a layer of 3072 input features: *tile_rows receives 256 (256 or 192
+ * tokens x 256 features, one workgroup per CU) or 128 (a smaller tile).  The big tile has the better arithmetic intensity; a
  * smaller one is taken where the big one would leave most CUs without a tile.  No GPU is touched.
  * CF_ERR_ARG: non-positive sizes, NULL result. */
 int cf_plan_linear(int32_t m_rows, int32_t n_features, int32_t* tile_rows);

@@ -124,19 +124,30 @@ inline int n_pad_of(int n) { return (n + 63) / 64 * 64; }
 
 inline int batch_of(const cf_model_desc& m) { return m.batch > 0 ? m.batch : 1; }
 
-// parts of K in a residual layer of K input features: the two streams of a double-stream block, which normally share a
-// launch, are cut alike
-inline int sum_splits(const cf_model_desc& m, int kind, int K) {
-    const int nl = m.n_total / m.sp_degree, tl = kind == CF_DOUBLE_STREAM ? m.n_txt_total / m.sp_degree : 0;
-    return gemm_splits(nl - tl, tl, m.d, K);
+// How the launches of a block kind are cut, and the scratch that takes.
+void plan_cuts(Plan* p, const cf_model_desc& m) {
+    const int P = m.sp_degree, hl = m.n_heads / P, nl = m.n_total / P, B = batch_of(m), hd = m.head_dim;
+    p->self_splits = attn_splits(hl, m.n_total, m.n_total, hd);
+    p->even_floats = attn_even_floats(B * hl, m.n_total, m.n_total, hd, p->self_splits);
+    uint64_t part = std::max(p->even_floats, attn_part_floats(B * hl, m.n_total, hd, p->self_splits));
+    if (p->kind == CF_DIT_CROSS) {
+        p->cross_splits = attn_splits(m.n_heads, nl, m.l_ctx, hd);
+        part = std::max(part, attn_part_floats(B * m.n_heads, nl, hd, p->cross_splits));
+    }
+    // residual layers: the two streams of a double-stream block, which normally share a launch, are cut alike
+    const int tl = p->kind == CF_DOUBLE_STREAM ? m.n_txt_total / P : 0;
+    const int k_mlp = p->kind == CF_SINGLE_STREAM ? m.d + m.f : m.f;
+    p->sum_splits_d = gemm_splits(nl - tl, tl, m.d, m.d);
+    p->sum_splits_mlp = gemm_splits(nl - tl, tl, m.d, k_mlp);
+    const int most = std::max(p->sum_splits_d, p->sum_splits_mlp);
+    if (most > 1) part = std::max(part, (uint64_t)most * B * nl * m.d);
+    p->part_floats = part;
 }
-// parts of the keys in the joint attention and in the cross-attention
-inline int self_splits(const cf_model_desc& m) { return attn_splits(m.n_heads / m.sp_degree, m.n_total, m.n_total, m.head_dim); }
-inline int cross_splits(const cf_model_desc& m) { return attn_splits(m.n_heads, m.n_total / m.sp_degree, m.l_ctx, m.head_dim); }
 
 // every per-token buffer holds the whole batch, sample after sample
-Ws carve(const cf_model_desc& m, int kind, char* base) {
+Ws carve(const cf_model_desc& m, const Plan& p, char* base) {
     Ws w;
+    const int kind = p.kind;
     uint64_t off = 0;
     auto take = [&](uint64_t bytes) { char* p = base + off; off = align_up(off + bytes, 256); return p; };
     const uint64_t B = batch_of(m);
@@ -161,16 +172,8 @@ Ws carve(const cf_model_desc& m, int kind, char* base) {
         w.cK = (bf16*)take(2ull * lc * d);
         w.cVt = (bf16*)take(2ull * B * d * n_pad_of(m.l_ctx));
     }
-    uint64_t part = attn_part_floats((int)hl, m.n_total, m.head_dim, self_splits(m));
-    if (kind == CF_DIT_CROSS)
-        part = std::max(part, attn_part_floats((int)(B * m.n_heads), m.n_total / m.sp_degree, m.head_dim, cross_splits(m)));
-    for (int k : {(int)(kind == CF_SINGLE_STREAM ? d + f : f), (int)d}) {
-        const int parts = sum_splits(m, kind, k);
-        if (parts > 1) part = std::max(part, parts * nl * d);
-    }
-    const uint64_t even = attn_even_floats((int)hl, m.n_total, m.n_total, m.head_dim, self_splits(m));
-    if (even) w.flags = (uint32_t*)take(4 * ATTN_FLAGS);
-    w.part = (float*)take(4 * std::max(part, even));
+    if (p.even_floats) w.flags = (uint32_t*)take(4 * ATTN_FLAGS);
+    w.part = (float*)take(4 * p.part_floats);
     w.total = off;
     return w;
 }
@@ -384,7 +387,7 @@ int prof_resolve(cf_ctx* c) {
     if (c->prof_pending.empty()) return CF_OK;
     CF_HIP(c, hipDeviceSynchronize());
     if (c->ktimes.empty()) {
-        static const char* const tile_name[GEMM_TILES] = {"/256x256", "/128x128", "/128x256", "/128x64", "/64x64"};
+        static const char* const tile_name[GEMM_TILES] = {"/256x256", "/128x128", "/128x256", "/128x64", "/64x64", "/192x256"};
         c->ktimes.resize(GEMM_TILES * K_COUNT);
         for (int i = 0; i < GEMM_TILES * K_COUNT; ++i) {
             memset(&c->ktimes[i], 0, sizeof(cf_kernel_time));
@@ -560,6 +563,11 @@ int run_ln_mod(Fwd& F, const LnArgs* parts, int n_parts) {
 }
 int run_ln_mod(Fwd& F, const LnArgs& a) { return run_ln_mod(F, &a, 1); }
 
+int sum_splits(const Fwd& F, int K) {
+    const Plan& p = F.c->P(F.block);
+    return K == F.c->d.d ? p.sum_splits_d : p.sum_splits_mlp;
+}
+
 // out-feature panels of one linear layer; `g` carries everything but the panel and the weights
 int run_linear(Fwd& F, int kid, const std::string& wname, const std::string& bname, GemmArgs g) {
     if (g.M <= 0) return CF_OK;
@@ -573,7 +581,7 @@ int run_linear(Fwd& F, int kid, const std::string& wname, const std::string& bna
     g.N = (int)w.rows;
     g.K = (int)w.cols;
     if (g.epi == EPI_SPLIT_GELU && g.n_split > g.N) g.n_split = g.N;
-    if (g.epi == EPI_GATE_RESID) gemm_set_split(&g, sum_splits(F.c->d, F.c->P(F.block).kind, g.K), F.ws.part);
+    if (g.epi == EPI_GATE_RESID) gemm_set_split(&g, sum_splits(F, g.K), F.ws.part);
     return panels(F, w, g.M, [&](int r0, int r1) -> int {
         GemmArgs p = g;
         p.n0 = r0;
@@ -611,7 +619,7 @@ int run_linear_pair(Fwd& F, int kid, const std::string (&wname)[2], const std::s
         g[i].n1 = g[i].N;
         if (g[i].epi == EPI_SPLIT_GELU && g[i].n_split > g[i].N) g[i].n_split = g[i].N;
         if (g[i].epi == EPI_GATE_RESID)      // both are in flight together: the second's parts follow the first's
-            gemm_set_split(&g[i], sum_splits(c->d, c->P(F.block).kind, g[i].K),
+            gemm_set_split(&g[i], sum_splits(F, g[i].K),
                            F.ws.part + (i ? (size_t)g[0].ksplits * g[0].M * g[0].N : 0));
     }
     const int tile = pair ? gemm_pair_tile(g[0], g[1]) : -1;
@@ -729,7 +737,7 @@ int run_joint_attention(Fwd& F, const RelayoutArgs* parts, int n_parts, const At
         a.ld = out.ld; a.h0 = h0;
         a.send = (bf16*)io->send_attn; a.send_bs = (long)peer_bs;
     }
-    attn_set_split(&a, self_splits(m), F.ws.part);
+    attn_set_split(&a, c->P(F.block).self_splits, F.ws.part);
     attn_set_even(&a, F.ws.part, F.ws.flags);
     if (const char* msg = attn_check(a)) return cf_fail(c, CF_ERR_ARG, "%s", msg);
     {
@@ -834,7 +842,8 @@ void plan_model(cf_ctx* c) {
         Plan& p = c->plan[k];
         if (p.kind >= 0) continue;
         plan_layout(&p, c->d, k, c->chunk_bytes);
-        p.ws_bytes = carve(c->d, k, nullptr).total;
+        plan_cuts(&p, c->d);
+        p.ws_bytes = carve(c->d, p, nullptr).total;
         c->ws_bytes = std::max(c->ws_bytes, p.ws_bytes);
         c->max_chunks = std::max(c->max_chunks, p.n_chunks);
     }
@@ -991,7 +1000,8 @@ int cf_plan_linear(int32_t m_rows, int32_t n_features, int32_t* tile_rows) {
     GemmArgs g{};
     g.M = m_rows; g.n0 = 0; g.n1 = n_features; g.N = n_features;
     g.K = 3072;                          // the widths this is asked for; the choice hardly depends on it
-    *tile_rows = gemm_tile(g) == GEMM_256x256 ? 256 : 128;
+    const int t = gemm_tile(g);
+    *tile_rows = t == GEMM_256x256 || t == GEMM_192x256 ? 256 : 128;
     return CF_OK;
 }
 
@@ -1144,7 +1154,7 @@ int dit_block_fwd(cf_ctx* c, int32_t block, const cf_block_io* io, void* compute
     if (c->comm_stream && c->comm_bytes && c->fwd_count >= 2)
         CF_HIP(c, hipEventSynchronize(c->fwd_ev[(c->fwd_count - 2) % 4]));
 
-    Fwd F{c, block, (hipStream_t)compute_stream, view_of(c, block), io, carve(c->d, p.kind, (char*)io->workspace)};
+    Fwd F{c, block, (hipStream_t)compute_stream, view_of(c, block), io, carve(c->d, p, (char*)io->workspace)};
     c->waited_upto = p.n_res_chunks - 1;
     if (streamed && c->adaptive_waits && !c->pause_resume && c->hidden_kind[p.kind]) {
         // blocks of this kind have been finding their weights in place: wait once, for the last chunk, and
@@ -1549,7 +1559,7 @@ int fwd_dit(Fwd& F) {
         AttnArgs a{};
         a.Q = w.cQ; a.K = w.cK; a.Vt = w.cVt; a.O = w.c; a.o_hs = hd; a.o_qs = d; a.o_bs = dense;
         a.H = B * H; a.hps = H; a.nq = nl; a.nk = lc; a.nk_pad = lpad; a.hd = hd; a.scale = 1.0f / sqrtf((float)hd);
-        attn_set_split(&a, cross_splits(m), w.part);
+        attn_set_split(&a, c->P(F.block).cross_splits, w.part);
         if (const char* msg = attn_check(a)) return cf_fail(c, CF_ERR_ARG, "%s", msg);
         ProfScope ps(c, F.s, K_CROSS_ATTN, 4.0 * B * H * (double)nl * lc * hd, 0);
         CF_HIP(c, attn_launch(a, F.s));

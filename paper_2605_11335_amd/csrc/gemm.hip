@@ -53,7 +53,8 @@ void tile_costs(int M, long n, double* c256, double* c128) {
 // per slab + fixed part), fitted to layers of 64 to 13640 tokens and K = 512 to 15360 with weights read cold
 // (one MI355X): a slab takes a lone 256x256 workgroup per CU 1.05 us on a nearly empty chip and 1.35 on a full
 // one, a 128x256 one 0.76 to 0.88, 128x128 0.55 alone and 1.07 for the two a CU holds,
-// 128x64 0.43 and 0.92, 64x64 0.30 and 0.51.
+// 128x64 0.43 and 0.92, 64x64 0.30 and 0.51; 192x256, for grids that end a little past whole rounds of the big tile,
+// 0.85 to 1.05 (1531 x 12288 x 3072: 118 us in 384 tiles, 131 in 288 of 256x256 or 576 of 128x256).
 namespace {
 struct TileCost { int bm, bn, per_cu; double lone, full, fixed; };      // us per slab of a CU's workgroups: few CUs busy | chip full
 constexpr TileCost kTileCost[GEMM_TILES] = {
@@ -62,6 +63,7 @@ constexpr TileCost kTileCost[GEMM_TILES] = {
     {128, 256, 1, 0.76, 0.88, 6.0},
     {128, 64, 2, 0.43, 0.92, 3.5},
     {64, 64, 2, 0.30, 0.51, 3.0},
+    {192, 256, 1, 0.85, 1.05, 7.5},
 };
 double tile_time(const TileCost& t, long tiles, int K) {
     const double slabs = (K + 63) / 64;

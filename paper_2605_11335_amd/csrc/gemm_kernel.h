@@ -17,9 +17,10 @@
 // What bounds the loop is the rate at which a CU's L1 takes in the operands (32 bytes per clock at the
 // matrix cores' full rate on the 256 x 256 tile, against some 38 that the path moves with nothing else to
 // do), so the copies have to be on their way all the time and evenly.  A slab is therefore worked off
-// in four quadrant phases, (activation half, weight half) = (0,0) (0,1) (1,1) (1,0): each phase needs one
-// half-tile that the one before did not, reads it into registers a phase ahead, and the half-tile's LDS
-// space is refilled for the slab after next as soon as all waves have read it.  Two hand-overs per slab
+// in four quadrant phases, (activation half, weight half) = (0,0) (0,1) (1,1) (1,0) (six where the
+// activations go in thirds): each phase needs one half-tile that the one before did not, reads it into
+// registers a phase ahead, and the half-tile's LDS space is refilled for the slab after next as soon as all
+// waves have read it.  Two hand-overs per slab
 // (barriers that leave the four youngest half-tiles in flight) instead of one that waits for everything:
 // 8192-cubed 837 -> 762 us, 13640 x 9216 x 3072 651 -> 603 us, 13640 x 3072 x 14336 1169 -> 971 us
 // (the time per slab of a full chip 1.52 -> 1.33 us).
@@ -237,9 +238,11 @@ template <int BM, int BN, int EPI, bool STRADDLE>
 __device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0, int part) {
     constexpr int WM = BM / 2, WN = BN / 2;        // wave quadrant
     constexpr int MT = WM / 32, NT = WN / 32;      // 32x32 MFMA tiles per wave
-    constexpr int MH = MT / 2, NH = NT / 2;        // of which one half-tile of an operand feeds this many
-    constexpr int GA = BM / 32, GW = BN / 32;      // 8-row units of a half-tile per wave row (column)
-    constexpr int LA = GA / 2, LW = GW / 2;        // wave-loads (1 KiB = one unit each) per wave and half-tile
+    constexpr int PA = MT % 2 ? 3 : 2;             // the activations go in thirds or halves, the weights in halves
+    constexpr int MH = MT / PA, NH = NT / 2;       // MFMA tiles of a part
+    constexpr int GA = WM / PA / 8, GW = WN / 2 / 8;           // 8-row units of a part per wave row (column)
+    constexpr int LA = GA / 2, LW = GW / 2;        // wave-loads (1 KiB = one unit each) per wave and part
+    constexpr int L = PA * LA + 2 * LW;            // and per slab
     constexpr int A_STAGE = BM * ROWB, W_STAGE = BN * ROWB;
 
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -253,24 +256,25 @@ __device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0,
 
     // Slab copies go global -> LDS directly (no register staging).  One such load writes the
     // wave's 64 x 16 bytes to consecutive LDS addresses, i.e. 8 rows (a unit); which 16-byte chunk of
-    // its row a lane fetches is chosen so that the chunk lands in its swizzled slot.  A half-tile is the
-    // rows that the waves' h-th halves cover: unit (j*4 + wave) of it is unit `unit(..)` of the tile.
+    // its row a lane fetches is chosen so that the chunk lands in its swizzled slot.  Part h of an operand is the
+    // rows that the h-th parts of the waves' quadrants cover: unit (j*4 + wave) of it is unit `unit(..)` of the tile.
     const int uw = __builtin_amdgcn_readfirstlane(wave);
-    auto unit = [](int G, int h, int idx) { return (idx / G) * 2 * G + h * G + idx % G; };
-    uint32_t a_voff[2][LA], w_voff[2][LW];         // byte offsets from the tile's first row
+    auto unit = [](int G, int parts, int h, int idx) { return (idx / G) * parts * G + h * G + idx % G; };
+    uint32_t a_voff[PA][LA], w_voff[2][LW];        // byte offsets from the tile's first row
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int h = 0; h < PA; ++h)
 #pragma unroll
         for (int j = 0; j < LA; ++j) {
-            const int row = unit(GA, h, j * 4 + uw) * 8 + lane / CHUNKS;
+            const int row = unit(GA, PA, h, j * 4 + uw) * 8 + lane / CHUNKS;
             a_voff[h][j] = (uint32_t)row * (uint32_t)g.lda * 2u + ((lane % CHUNKS) ^ swz(row)) * 16;
         }
 #pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
         for (int j = 0; j < LW; ++j) {
-            const int row = unit(GW, h, j * 4 + uw) * 8 + lane / CHUNKS;
+            const int row = unit(GW, 2, h, j * 4 + uw) * 8 + lane / CHUNKS;
             w_voff[h][j] = (uint32_t)row * (uint32_t)g.K * 2u + ((lane % CHUNKS) ^ swz(row)) * 16;
         }
-    }
     const uint64_t t_begin = g.w_off + (uint64_t)n0 * g.K * 2, t_end = g.w_off + (uint64_t)min(n0 + BN, g.N) * g.K * 2;
     // resources that end with the tile's last valid row: the rows of a ragged tile beyond it read zeros
     const void* const a_base = g.A + (size_t)m0 * g.lda;
@@ -306,76 +310,100 @@ __device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0,
         const bool on = kt < KT;
         return Src{make_rsrc(a_base, on ? a_bytes : 0u), make_rsrc(w_base, on ? w_bytes : 0u), on ? (uint32_t)(kt0 + kt) * (BK * 2) : 0u, on};
     };
-    auto issue_a = [&](auto st, auto h, const Src& src, int q) {
-        lds_bload16(src.a, a_voff[h.value][q], src.k0, sA + st.value * A_STAGE + unit(GA, h.value, q * 4) * 1024 + uw * 1024);
+    auto issue_a = [&](auto st, int h, const Src& src, int q) {
+        lds_bload16(src.a, a_voff[h][q], src.k0, sA + st.value * A_STAGE + unit(GA, PA, h, q * 4 + uw) * 1024);
     };
-    auto issue_w = [&](auto st, auto h, const Src& src, int q) {
-        char* const dst = sW + st.value * W_STAGE + unit(GW, h.value, q * 4) * 1024 + uw * 1024;
+    auto issue_w = [&](auto st, int h, const Src& src, int q) {
+        char* const dst = sW + st.value * W_STAGE + unit(GW, 2, h, q * 4 + uw) * 1024;
         if (STRADDLE && src.on) {                  // rows past the matrix read the tile's first bytes; they are never stored
-            const uint64_t o = (uint64_t)w_voff[h.value][q] + src.k0;
+            const uint64_t o = (uint64_t)w_voff[h][q] + src.k0;
             lds_load16(wv_ptr(g.W, t_begin + (o < t_end - t_begin ? o : 0)), dst);
         } else {
-            lds_bload16(src.w, w_voff[h.value][q], src.k0, dst);
+            lds_bload16(src.w, w_voff[h][q], src.k0, dst);
         }
     };
-    // r-th of the MH (NH) * KSTEPS fragments of a half-tile
-    auto read_a = [&](auto st, auto h, int r) {
-        fa[h.value][r / KSTEPS][r % KSTEPS] =
+    // The copies of a slab in two groups: parts a0 w0, whose stage is free a slab and a half before, then w1 a1 (a2).
+    auto issue_first = [&](auto st, const Src& src, int q) {
+        if (q < LA) issue_a(st, 0, src, q); else issue_w(st, 0, src, q - LA);
+    };
+    auto issue_second = [&](auto st, const Src& src, int q) {
+        if (q < LW) issue_w(st, 1, src, q); else issue_a(st, 1 + (q - LW) / LA, src, (q - LW) % LA);
+    };
+    constexpr int L1 = LA + LW, L2 = L - L1;
+    // r-th of the MH (NH) * KSTEPS fragments of a part
+    auto read_a = [&](auto st, auto h, auto buf, int r) {
+        fa[buf.value][r / KSTEPS][r % KSTEPS] =
             a_frag[r % KSTEPS][(st.value * A_STAGE + (h.value * MH + r / KSTEPS) * 32 * ROWB) / 16];
     };
     auto read_w = [&](auto st, auto h, auto buf, int r) {
         fw[buf.value][r / KSTEPS][r % KSTEPS] =
             w_frag[r % KSTEPS][(st.value * W_STAGE + (h.value * NH + r / KSTEPS) * 32 * ROWB) / 16];
     };
-    // One phase: the MFMAs of activation half ha with weight half hb (held in fw[buf]), with fragment reads for the
-    // phases to come between the first of them and slab copies between the last
-    auto phase = [&](auto ha, auto hb, auto buf, int n_reads, auto read, int n_issues, auto issue) __attribute__((always_inline)) {
+    // One phase: the MFMAs of activation part ha (held in fa[ba]) with weight half hb (in fw[bw]), with fragment reads for
+    // the phases to come between the first of them and the copies [u0, u1) of a group spread over them
+    auto phase = [&](auto ha, auto ba, auto hb, auto bw, int n_reads, auto read, int u0, int u1, auto issue) __attribute__((always_inline)) {
         constexpr int NM = KSTEPS * NH * MH;
-        int r = 0, u = 0;
+        int r = 0, u = u0;
 #pragma unroll
         for (int q = 0; q < NM; ++q) {
             const int kk = q / (NH * MH), i = (q / MH) % NH, j = q % MH;
             acc[hb.value * NH + i][ha.value * MH + j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                fw[buf.value][i][kk], fa[ha.value][j][kk], acc[hb.value * NH + i][ha.value * MH + j], 0, 0, 0);
+                fw[bw.value][i][kk], fa[ba.value][j][kk], acc[hb.value * NH + i][ha.value * MH + j], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
             for (; r * NM < n_reads * 2 * (q + 1) && r < n_reads; ++r) read(r);
-            for (; u * NM < n_issues * (q + 1) && u < n_issues; ++u) issue(u);
+            for (; (u - u0) * NM < (u1 - u0) * (q + 1) && u < u1; ++u) issue(u);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
-    using T_ = std::true_type;
-    using F_ = std::false_type;
-    // One slab of stage st: quadrant phases (0,0) (0,1) (1,1) (1,0).  At each hand-over every wave's loads of the two
-    // half-tiles about to be read have landed and its reads of the two before have returned, so those are refilled.
-    // What may still be in flight there: the four half-tiles issued after them.
+    using I2 = std::integral_constant<int, 2>;
+    // One slab of stage (and parity) st, as the serpentine of its quadrant phases.  At each hand-over every wave's loads of
+    // the parts about to be read have landed and its reads of the ones before have returned, so those are refilled.  What
+    // may still be in flight there: one slab's worth of copies issued after them.
+    // Activation part a is in fragment buffer (parity * PA + a) & 1; weight half 0 in buffer `parity` where it is used to
+    // the slab's end (PA = 2), else in 0.
     auto slab = [&](auto st, int kt) __attribute__((always_inline)) {
-        using SN = std::integral_constant<int, decltype(st)::value ^ 1>;
+        constexpr int P = decltype(st)::value;
+        using SN = std::integral_constant<int, P ^ 1>;
+        using A0 = std::integral_constant<int, (P * PA) & 1>;
+        using A1 = std::integral_constant<int, (P * PA + 1) & 1>;
+        using NA = std::integral_constant<int, ((P ^ 1) * PA) & 1>;       // a0 of the next slab
+        using W0 = std::integral_constant<int, PA == 2 ? P : 0>;
+        using W1 = std::integral_constant<int, W0::value ^ 1>;
+        using NW = std::integral_constant<int, PA == 2 ? P ^ 1 : 0>;      // w0 of the next slab
         const Src src = source(kt + 2);
-        handover<2 * (LA + LW)>();
-        phase(I0{}, I0{}, st, NH * KSTEPS, [&](int r) { read_w(st, I1{}, SN{}, r); }, LA, [&](int u) { issue_a(st, I0{}, src, u); });
-        phase(I0{}, I1{}, SN{}, MH * KSTEPS, [&](int r) { read_a(st, I1{}, r); }, LW, [&](int u) { issue_w(st, I0{}, src, u); });
-        handover<2 * (LA + LW)>();
-        phase(I1{}, I1{}, SN{}, MH * KSTEPS, [&](int r) { read_a(SN{}, I0{}, r); }, LW, [&](int u) { issue_w(st, I1{}, src, u); });
-        phase(I1{}, I0{}, st, NH * KSTEPS, [&](int r) { read_w(SN{}, I0{}, SN{}, r); }, LA, [&](int u) { issue_a(st, I1{}, src, u); });
+        auto first = [&](int u) { issue_first(st, src, u); };
+        auto second = [&](int u) { issue_second(st, src, u); };
+        handover<L>();
+        if constexpr (PA == 2) {
+            phase(I0{}, A0{}, I0{}, W0{}, NH * KSTEPS, [&](int r) { read_w(st, I1{}, W1{}, r); }, 0, L1 / 2, first);
+            phase(I0{}, A0{}, I1{}, W1{}, MH * KSTEPS, [&](int r) { read_a(st, I1{}, A1{}, r); }, L1 / 2, L1, first);
+            handover<L>();
+            phase(I1{}, A1{}, I1{}, W1{}, MH * KSTEPS, [&](int r) { read_a(SN{}, I0{}, NA{}, r); }, 0, L2 / 2, second);
+            phase(I1{}, A1{}, I0{}, W0{}, NH * KSTEPS, [&](int r) { read_w(SN{}, I0{}, NW{}, r); }, L2 / 2, L2, second);
+        } else {
+            phase(I0{}, A0{}, I0{}, W0{}, NH * KSTEPS, [&](int r) { read_w(st, I1{}, W1{}, r); }, 0, L1 / 3, first);
+            phase(I0{}, A0{}, I1{}, W1{}, MH * KSTEPS, [&](int r) { read_a(st, I1{}, A1{}, r); }, L1 / 3, 2 * L1 / 3, first);
+            phase(I1{}, A1{}, I1{}, W1{}, MH * KSTEPS, [&](int r) { read_a(st, I2{}, A0{}, r); }, 2 * L1 / 3, L1, first);
+            handover<L>();
+            phase(I1{}, A1{}, I0{}, W0{}, 0, [](int) {}, 0, L2 / 3, second);
+            phase(I2{}, A0{}, I0{}, W0{}, MH * KSTEPS, [&](int r) { read_a(SN{}, I0{}, NA{}, r); }, L2 / 3, 2 * L2 / 3, second);
+            phase(I2{}, A0{}, I1{}, W1{}, NH * KSTEPS, [&](int r) { read_w(SN{}, I0{}, NW{}, r); }, 2 * L2 / 3, L2, second);
+        }
     };
     auto issue_slab = [&](auto st, int kt) {
         const Src src = source(kt);
 #pragma unroll
-        for (int q = 0; q < LA; ++q) issue_a(st, I0{}, src, q);
+        for (int q = 0; q < L1; ++q) issue_first(st, src, q);
 #pragma unroll
-        for (int q = 0; q < LW; ++q) issue_w(st, I0{}, src, q);
-#pragma unroll
-        for (int q = 0; q < LW; ++q) issue_w(st, I1{}, src, q);
-#pragma unroll
-        for (int q = 0; q < LA; ++q) issue_a(st, I1{}, src, q);
+        for (int q = 0; q < L2; ++q) issue_second(st, src, q);
     };
     issue_slab(I0{}, 0);
     issue_slab(I1{}, 1);
-    handover<3 * (LA + LW)>();
+    handover<2 * L - L1>();
 #pragma unroll
-    for (int r = 0; r < MH * KSTEPS; ++r) read_a(I0{}, I0{}, r);
+    for (int r = 0; r < MH * KSTEPS; ++r) read_a(I0{}, I0{}, I0{}, r);
 #pragma unroll
     for (int r = 0; r < NH * KSTEPS; ++r) read_w(I0{}, I0{}, I0{}, r);
     for (int kt = 0; kt < KT; kt += 2) {           // an odd last slab is followed by one of zeros
@@ -598,6 +626,7 @@ hipError_t launch_tile(int tile, const GemmArgs& g, const GemmArgs* second, hipS
         case GEMM_256x256: return launch<256, 256, 0, EPI>(g, second, s);
         case GEMM_128x128: return launch<128, 128, 0, EPI>(g, second, s);
         case GEMM_128x256: return launch<128, 256, 0, EPI>(g, second, s);
+        case GEMM_192x256: return launch<192, 256, 0, EPI>(g, second, s);
         case GEMM_128x64: return launch<128, 64, 3, EPI>(g, second, s);        // 72 and 80 KB of LDS: two workgroups per CU
         case GEMM_64x64: return launch<64, 64, 5, EPI>(g, second, s);
         default: return hipErrorInvalidValue;

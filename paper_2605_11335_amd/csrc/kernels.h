@@ -34,7 +34,7 @@ struct GemmArgs {
 int gemm_splits(int rows, int rows2, int N, int K);      // parts to cut K into, for one sample's tokens (rows2: of a second layer in the launch)
 void gemm_set_split(GemmArgs* g, int splits, float* part);
 const char* gemm_check(const GemmArgs& g);
-enum { GEMM_256x256 = 0, GEMM_128x128 = 1, GEMM_128x256 = 2, GEMM_128x64 = 3, GEMM_64x64 = 4, GEMM_TILES = 5 };     // tokens x features
+enum { GEMM_256x256 = 0, GEMM_128x128 = 1, GEMM_128x256 = 2, GEMM_128x64 = 3, GEMM_64x64 = 4, GEMM_192x256 = 5, GEMM_TILES = 6 };     // tokens x features
 int gemm_tile(const GemmArgs& g);      // tile gemm_launch will use
 double gemm_fill(int M, int n);        // share of the launched rounds of workgroups that n features x M tokens fill
 hipError_t gemm_launch(const GemmArgs& g, hipStream_t s);

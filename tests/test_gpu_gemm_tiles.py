@@ -1,4 +1,4 @@
-"""The tile shapes of the linear layers (256x256, 128x256, 128x128, 128x64, 64x64 tokens x features): which one a launch
+"""The tile shapes of the linear layers (256x256, 192x256, 128x256, 128x128, 128x64, 64x64 tokens x features): which one a launch
 takes depends on its size, the order of every sum does not, so the rows of a large launch equal, bit for bit, the same rows
 computed by launches of fewer tokens; and the large launch is right against the float64 product."""
 import math
@@ -40,7 +40,7 @@ def test_every_tile_shape_gives_the_same_bits(K):
     assert_bf16_close(host_bits(out), ob.gelu_tanh(z), extra_abs=2e-4)
     # fp32 sums of K products of size 0.05: each rounding is at most 2^-24 of a partial sum of size 0.05 sqrt(K)
     assert max_abs(y.cpu().numpy(), resid.cpu().numpy().astype(np.float64) + gate.cpu().numpy().astype(np.float64) * z) < 5e-5 * math.sqrt(K)
-    for m in (1, 63, 65, 200, 500, 1100):
+    for m in (1, 63, 65, 200, 500, 1100, 1900, 2250):
         o, v = layer(m)
         assert torch.equal(o, out[:m]) and torch.equal(v, y[:m]), m
     # the same features as panels of a few tiles each

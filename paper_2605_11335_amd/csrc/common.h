@@ -42,10 +42,10 @@ __device__ __forceinline__ uint32_t xcd_contiguous_id(uint32_t bid, uint32_t nb)
     return xcd < r ? xcd * (q + 1) + idx : r * (q + 1) + (xcd - r) * q + idx;
 }
 
-// x * sigmoid(2u), u = sqrt(2/pi) (x + 0.044715 x^3): the tanh form of GELU.
+// x * sigmoid(2u), u = sqrt(2/pi) (x + 0.044715 x^3): the tanh form of GELU.  exp(-2u) = exp2(x (a + b x^2)) with the factors
+// folded into a and b (an epilogue of 256 x 256 tiles evaluates it 256 times per lane: 1 % of 2304 x 21504 x 3072).
 __device__ __forceinline__ float gelu_tanh_f32(float x) {
-    const float u = 0.7978845608028654f * (x + 0.044715f * x * x * x);
-    const float en = __builtin_amdgcn_exp2f(u * -2.8853900817779268f);  // exp(-2u)
+    const float en = __builtin_amdgcn_exp2f(x * fmaf(x * x, -0.1029432407f, -2.302208198f));
     return x * __builtin_amdgcn_rcpf(1.0f + en);
 }
 

@@ -396,54 +396,83 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_kernel(AttnArgs a) {
     });
 }
 
-// The same work dealt out evenly: a grid that takes 5.02 generations of workgroups pays for six, so here one workgroup per
-// CU stays and every XCD gets the same number of key tiles.  The unit is a group of 32 query tiles, one per CU of an XCD,
-// swept in step (they share K and V tiles through the XCD's L2); XCD x of 8 takes the x-th eighth of the groups' key tiles
-// laid end to end.  Where an eighth ends inside a group, XCD x sweeps the group's first tiles -- before anything else -- and
-// leaves the state of every sweep in memory, and XCD x + 1 goes on from there after its own groups, a generation or more
-// later: the same tiles in the same order, so the same bits as one sweep.  Should the state not be there when it is needed
-// (its workgroup has not been given a CU for kWaitTicks), the sweep starts over from the first tile.
-// 12 heads x 27280 x 128: 3.91 ms, 4.38 in six generations of 7-wave workgroups (the slowest XCD decides: their clocks differ
-// by 3 %); 48 heads x 4608: 464 us, 467 in four.
+// The same work dealt out by the kernel itself: one workgroup per CU stays and takes one sweep after the other.  The unit is a
+// group of 32 query tiles, one per CU of an XCD, swept in step (they share K and V tiles through the XCD's L2); "lane" j is the
+// j-th tile of every group and the j-th CU of every XCD.  A sweep may be cut: the first tiles by one workgroup, which leaves
+// the sweep's state in memory, the rest later by another, of another XCD, from there -- the same tiles in the same order, so
+// the same bits as one sweep.  Should the state not be there when it is needed (its workgroup has not been given a CU for
+// kWaitTicks), the sweep starts over from the first tile.
+//
+// Two plans.  Even shares (even_units = 0), for a few generations: XCD x takes the x-th eighth of the groups' key tiles laid end
+// to end; where an eighth ends inside a group, XCD x sweeps the group's first tiles before anything else and XCD x + 1 goes on
+// after its own groups, a generation or more later.  12 heads x 27280 x 128: 3.91 ms, against 4.38 in six generations of 7-wave
+// workgroups for 5.72.
+// Taken as they come (even_units > 0), for many generations of long sweeps: the XCDs' clocks differ by +-3 %, and dealt out
+// alike the slowest decides (12 heads x 119056: XCDs done after 65.2 to 69.7 ms, now all after 66.6: 1306 TFLOP/s).  The
+// workgroups of a lane draw groups from a counter; the last even_last groups go in even_cuts pieces each, all first pieces
+// before all second ones, so that the end is ragged by a piece and not by a sweep.
 constexpr unsigned long long kWaitTicks = 2000000;       // 20 ms of the 100 MHz counter
 template <int HD>
 __global__ __launch_bounds__(512, 2) void attn_even_kernel(AttnArgs a) {
-    constexpr int NW = 8, BQ = 32 * NW, DT = HD / 32;
-    __shared__ int ready;
+    constexpr int NW = 8, BQ = 32 * NW, DT = HD / 32, STATE = NW * 64 * (HD / 2 + 2);
+    __shared__ int shared_word;
     const int lane = threadIdx.x & 63, lj = lane & 31, lg = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
     const int nqt = (a.nq + BQ - 1) / BQ, items = nqt * a.H, NT = (a.nk + BKV - 1) / BKV;
-    const long total = (long)((items + 31) / 32) * NT, u0 = total * x / 8, u1 = total * (x + 1) / 8;
-    const int g0 = (int)(u0 / NT), t0 = (int)(u0 % NT), g1 = (int)(u1 / NT), t1 = (int)(u1 % NT);     // g1 > g0: see attn_even
-    // steps: the head of group g1 (left for XCD x + 1), the whole groups, the rest of group g0
-    const int first_whole = t0 ? g0 + 1 : g0, n_steps = 1 + (g1 - first_whole) + 1;
-    for (int step = 0; step < n_steps; ++step) {
-        const bool leave = step == 0, take = step == n_steps - 1;
-        if ((leave && !t1) || (take && !t0)) continue;
-        const int item = (leave ? g1 : take ? g0 : first_whole + step - 1) * 32 + j;
+    const int groups = (items + 31) / 32;
+    const long total = (long)groups * NT, u0 = total * x / 8, u1 = total * (x + 1) / 8;
+    const int g0 = (int)(u0 / NT), t0 = (int)(u0 % NT), g1 = (int)(u1 / NT), t1 = (int)(u1 % NT);     // g1 > g0: at least 8 groups
+    // even shares, in steps: the head of group g1 (left for XCD x + 1), the whole groups, the rest of group g0
+    const int first_whole = t0 ? g0 + 1 : g0, n_steps = a.even_units ? a.even_units : 1 + (g1 - first_whole) + 1;
+    for (int step = 0;; ++step) {
+        int group, T0 = 0, T1 = NT, take = -1, leave = -1;      // take, leave: state slots, 32 lanes each
+        if (a.even_units) {
+            if (threadIdx.x == 0) shared_word = (int)__hip_atomic_fetch_add(a.even_flags + ATTN_FLAGS - 32 + j, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            const int u = __builtin_amdgcn_readfirstlane(shared_word);
+            __syncthreads();                   // the word is used again below
+            if (u >= n_steps) break;
+            const int whole = groups - a.even_last;
+            group = u;
+            if (u >= whole) {
+                const int c = (u - whole) / a.even_last, r = (u - whole) % a.even_last;
+                group = whole + r;
+                T0 = (int)((long)NT * c / a.even_cuts);
+                T1 = (int)((long)NT * (c + 1) / a.even_cuts);
+                if (c > 0) take = (c - 1) * a.even_last + r;
+                if (c + 1 < a.even_cuts) leave = c * a.even_last + r;
+            }
+        } else {
+            if (step >= n_steps) break;
+            group = first_whole + step - 1;
+            if (step == 0) { if (!t1) continue; group = g1; T1 = t1; leave = x; }
+            else if (step == n_steps - 1) { if (!t0) continue; group = g0; T0 = t0; take = x - 1; }
+        }
+        const int item = group * 32 + j;
         if (item >= items) continue;
         const float* from = nullptr;
-        if (take) {
+        if (take >= 0) {
             if (threadIdx.x == 0) {
-                uint32_t* const f = a.even_flags + (x - 1) * 32 + j;
+                uint32_t* const f = a.even_flags + take * 32 + j;
                 const unsigned long long give_up = __builtin_amdgcn_s_memrealtime() + kWaitTicks;
                 int r;
                 while (!(r = __hip_atomic_load(f, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) == 1u) && __builtin_amdgcn_s_memrealtime() < give_up)
                     __builtin_amdgcn_s_sleep(16);
-                ready = r;
+                shared_word = r;
             }
             __syncthreads();                   // orders every wave behind thread 0's acquire
-            if (ready) from = a.even_state + ((size_t)(x - 1) * 32 + j) * (NW * 64 * (HD / 2 + 2));
+            if (__builtin_amdgcn_readfirstlane(shared_word)) from = a.even_state + ((size_t)take * 32 + j) * STATE;
+            else T0 = 0;
         }
         const int h = item / nqt, q0 = item % nqt * BQ + wave * 32;
-        attn_sweep<HD, NW>(a, h, q0, from ? t0 : 0, leave ? t1 : NT, from, [&](floatx16 (&o)[DT], float mc, float l_run) {
-            if (leave) {
-                store_state<HD>(a.even_state + ((size_t)x * 32 + j) * (NW * 64 * (HD / 2 + 2)), wave, lane, o, mc, l_run);
+        attn_sweep<HD, NW>(a, h, q0, T0, T1, from, [&](floatx16 (&o)[DT], float mc, float l_run) {
+            if (leave >= 0) {
+                store_state<HD>(a.even_state + ((size_t)leave * 32 + j) * STATE, wave, lane, o, mc, l_run);
                 // One release per workgroup, by thread 0 behind the barrier: it writes back the XCD's whole L2.  By every wave
                 // it cost 57 us.
                 __syncthreads();
-                if (threadIdx.x == 0) __hip_atomic_store(a.even_flags + x * 32 + j, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+                if (threadIdx.x == 0) __hip_atomic_store(a.even_flags + leave * 32 + j, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
             } else {
                 const float l_tot = l_run + __shfl_xor(l_run, 32);
                 store_rows<HD>(a, h, q0 + lj, lg, [&](int d, int v) { return o[d][v]; }, 1.0f / l_tot);
@@ -537,7 +566,7 @@ const char* attn_check(const AttnArgs& a) {
                          a.part_tiles < 1 || (long)(a.splits - 1) * a.part_tiles * BKV >= a.nk || (long)a.splits * a.part_tiles * BKV < a.nk))
         return "attention: bad split of the keys";
     if (a.even_state && (a.splits > 1 || !a.even_flags || ((uintptr_t)a.even_state % 16) || a.hd != 128 || (long)((a.nq + 255) / 256) * a.H <= 7 * 32))
-        return "attention: launch cannot be dealt out evenly";
+        return "attention: launch cannot be dealt out by the kernel";
     return nullptr;
 }
 
@@ -613,26 +642,47 @@ void attn_set_split(AttnArgs* a, int splits, float* scratch) {
     a->part_ml = scratch ? scratch + (uint64_t)a->splits * a->H * ((a->nq + 31) / 32) * 32 * a->hd : nullptr;
 }
 
-// Is the launch worth dealing out evenly?  In the units above, groups of 32 query tiles: an eighth of the groups per XCD,
-// a fixed part per sweep (one more of them where an eighth ends inside a group) and about 15 for leaving (17 us, most of it
-// the L2 write-back) and fetching the states.  At least eight groups: a workgroup's share must cover a whole sweep, or three of them would queue up in one.
+// How the launch is dealt out: 0 = by the grid, 1 = even shares, 2 = taken as they come.  Estimated in the units above for
+// groups of 32 query tiles.  By the grid and in even shares the slowest XCD takes 3 % longer than the mean.  Even shares: an
+// eighth of the groups per XCD, a fixed part per sweep (one more of them where an eighth ends inside a group) and about 15 for
+// leaving (17 us, most of it the L2 write-back) and fetching the states.  As they come: 15 for each of the pieces an XCD takes
+// of the last kEvenLast groups, and half a piece of ragged end.  At least eight groups: a workgroup's even share must cover a
+// whole sweep, or three of them would queue up in one.
 // 128-wide heads only: a CU holds two 8-wave workgroups of the 64-wide kernel, which one evenly dealt workgroup does not match
 // (8 heads x 30950 x 64: 2.70 against 2.36 ms).
-uint64_t attn_even_floats(int H, int nq, int nk, int hd, int splits) {
+// Where the lines lie (us by the grid / even / drawn; the estimated even share of the grid's time in brackets): 48 heads x 4608
+// 491 / 459 / 500 (0.97), 48 x 6000 806 / 756 / 805 (0.97), 96 x 4608 889 / 892 / 937 (1.00), 8 x 24000 1898 / 1926 / 1966
+// (1.02), 24 x 13640 2114 / 1900 / 1927 (0.88), 24 x 20000 4072 / 3961 / 3999 (0.94), 4 x 60000 5952 / 5846 / 5889 (0.94: by the
+// grid 8-wave sweeps, whose time is estimated too high by up to 4 %), 12 x 119056 69.2 / - / 66.65 ms.  The last sweeps in four
+// pieces each; there, in two 66.96, in three 66.70.
+constexpr int kEvenLast = 8, kEvenCuts = 4;
+static int even_plan(int H, int nq, int nk, int hd, int splits) {
     const long groups = ((long)((nq + 255) / 256) * H + 31) / 32;
     if (splits > 1 || groups < 8 || hd != 128) return 0;
     AttnArgs a{};
     a.H = H; a.nq = nq; a.nk = nk; a.hd = hd; a.splits = 1;
     double plain;
-    waves_and_cost(a, &plain);
-    const double tiles = (double)((nk + BKV - 1) / BKV), even = groups / 8.0 * (tiles + 2.5) + 2.5 + 15.0;
-    return even < 0.96 * plain ? (uint64_t)256 * 512 * (hd / 2 + 2) : 0;
+    const int waves = waves_and_cost(a, &plain);
+    const double tiles = (double)((nk + BKV - 1) / BKV), sweeps = groups / 8.0 * (tiles + 2.5);
+    const double even = 1.03 * (sweeps + 2.5 + 15.0), drawn = sweeps + 15.0 * kEvenCuts + tiles / kEvenCuts / 2;
+    if (groups >= 3 * kEvenLast && drawn < 0.99 * even && drawn < 0.985 * 1.03 * plain) return 2;
+    return even < (waves == 8 ? 0.96 : 0.98) * 1.03 * plain ? 1 : 0;
+}
+
+uint64_t attn_even_floats(int H, int nq, int nk, int hd, int splits) {
+    const int plan = even_plan(H, nq, nk, hd, splits);
+    return plan ? (uint64_t)(plan == 2 ? kEvenLast * (kEvenCuts - 1) : 7) * 32 * 512 * (hd / 2 + 2) : 0;
 }
 
 void attn_set_even(AttnArgs* a, float* state, uint32_t* flags) {
-    const bool on = state && flags && attn_even_floats(a->H, a->nq, a->nk, a->hd, a->splits) > 0;
-    a->even_state = on ? state : nullptr;
-    a->even_flags = on ? flags : nullptr;
+    static_assert(kEvenLast * (kEvenCuts - 1) * 32 + 32 <= ATTN_FLAGS, "a flag per state and 32 counters");
+    const int plan = state && flags ? even_plan(a->H, a->nq, a->nk, a->hd, a->splits) : 0;
+    a->even_state = plan ? state : nullptr;
+    a->even_flags = plan ? flags : nullptr;
+    a->even_last = kEvenLast;
+    a->even_cuts = kEvenCuts;
+    const int groups = (int)(((long)((a->nq + 255) / 256) * a->H + 31) / 32);
+    a->even_units = plan == 2 ? groups - kEvenLast + kEvenLast * kEvenCuts : 0;
 }
 
 static hipError_t launch_even(const AttnArgs& a, hipStream_t s) {

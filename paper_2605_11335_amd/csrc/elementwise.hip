@@ -371,10 +371,10 @@ struct PreAttnArgs {
     int seg[7];                                // end of each segment: qk0, vt0, qk1, vt1, peer_qk, peer_vt, peer_attn
 };
 
-static_assert(ATTN_FLAGS == 256, "one word per thread of a workgroup");
 __global__ __launch_bounds__(256) void pre_attention_kernel(PreAttnArgs a) {
     const int b = blockIdx.x;
-    if (b == 0 && a.zero) a.zero[threadIdx.x] = 0;
+    if (b == 0 && a.zero)
+        for (int i = threadIdx.x; i < ATTN_FLAGS; i += 256) a.zero[i] = 0;
     int lo = 0;
 #pragma unroll
     for (int p = 0; p < 2; ++p) {

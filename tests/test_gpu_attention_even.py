@@ -1,6 +1,6 @@
-"""Attention dealt out evenly over the XCDs (a sweep that one workgroup begins and another ends): against the oracle, and the
-same bits as sweeps done by one workgroup each -- a batch large enough to be dealt out equals its samples run alone, which are
-too small for it."""
+"""Attention dealt out by the kernel (a sweep that one workgroup begins and another ends), in even shares and as the workgroups
+come for it: against the oracle, and the same bits as sweeps done by one workgroup each -- a batch large enough to be dealt out
+equals its samples run alone, which are too small for it (or, the long ones, are dealt out differently)."""
 import numpy as np
 import pytest
 
@@ -24,8 +24,10 @@ def forward(cfg, params, inputs):
         run.close()
 
 
-# query tiles of 256: 12 x 24 heads = 9 groups of 32 exactly; 11 x 24 (one sample, or two of 12 heads) = 8 groups and a quarter
-@pytest.mark.parametrize("n,heads,hd,batch,sharp", [(2850, 24, 128, 1, 1.0), (2760, 24, 128, 1, 1.0), (2760, 12, 128, 2, 1.0), (2760, 24, 128, 1, 20.0)])
+# query tiles of 256: 12 x 24 heads = 9 groups of 32 exactly; 11 x 24 (one sample, or two of 12 heads) = 8 groups and a quarter.
+# 353 x 6 = 66 groups and 6 tiles, of sweeps long enough to be drawn from a counter
+@pytest.mark.parametrize("n,heads,hd,batch,sharp", [(2850, 24, 128, 1, 1.0), (2760, 24, 128, 1, 1.0), (2760, 12, 128, 2, 1.0), (2760, 24, 128, 1, 20.0),
+                                                     (90200, 2, 128, 3, 1.0)])
 def test_dealt_out_evenly(n, heads, hd, batch, sharp):
     cfg = wl.BlockConfig("even", wl.KIND_SINGLE, n_blocks=1, d=heads * hd, n_heads=heads, head_dim=hd, f=256, n_total=n, n_chunks=3, batch=batch)
     params, inputs = wl.gen_block_params(cfg, 0), wl.gen_block_inputs(cfg, 0)

@@ -362,20 +362,22 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
     finish(o, mc, l_run);
 }
 
-// NW waves of 32 queries each per workgroup: 4 (two workgroups per CU), 7 or 8 (one per CU).
-template <int HD, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void attn_fwd_kernel(AttnArgs a) {
+// NW waves of 32 queries each per workgroup: 4 (two workgroups per CU), 7 or 8 (one per CU); for 64-wide heads twice as many,
+// held to the 128 registers that takes: at 129 a CU has one 7-wave workgroup and 8 heads x 20892 take 1.11 ms instead of 0.90.
+// PARTS: the keys are cut (a.splits > 1), the results go to scratch.
+template <int HD, int NW, bool PARTS>
+__global__ __launch_bounds__(64 * NW, HD == 64 ? 4 : 2) void attn_fwd_kernel(AttnArgs a) {
     constexpr int BQ = 32 * NW, DT = HD / 32;
     const int nqt = (a.nq + BQ - 1) / BQ;
     const uint32_t lid = xcd_contiguous_id(blockIdx.x, gridDim.x);
     const int hs = lid / nqt, qt = lid % nqt;
-    const int h = hs / a.splits, part = hs % a.splits;       // head, and which part of the keys
-    const int lane = threadIdx.x & 63, lj = lane & 31, lg = lane >> 5;
-    const int q0 = qt * BQ + (threadIdx.x >> 6) * 32;
-    const int T0 = part * a.part_tiles, T1 = min((a.nk + BKV - 1) / BKV, T0 + a.part_tiles);
+    const int h = PARTS ? hs / a.splits : hs, part = PARTS ? hs % a.splits : 0;       // head, and which part of the keys
+    const int q0 = qt * BQ + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 32;
+    const int NT = (a.nk + BKV - 1) / BKV, T0 = PARTS ? part * a.part_tiles : 0, T1 = PARTS ? min(NT, T0 + a.part_tiles) : NT;
     attn_sweep<HD, NW>(a, h, q0, T0, T1, nullptr, [&](floatx16 (&o)[DT], float mc, float l_run) {
+        const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0)), lj = lane & 31, lg = lane >> 5;
         const float l_tot = l_run + __shfl_xor(l_run, 32);
-        if (a.splits > 1) {
+        if constexpr (PARTS) {
             // part of the keys only: O^T, the reference it is taken against and the row sum go to the scratch buffer as they
             // lie in registers, 1 KiB per store
             if (q0 < a.nq) {
@@ -390,9 +392,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_fwd_kernel(AttnArgs a) {
                     }
                 if (lg == 0) *(float2*)(a.part_ml + tile32 * 64 + lj * 2) = make_float2(mc, l_tot);
             }
-            return;
+        } else {
+            store_rows<HD>(a, h, q0 + lj, lg, [&](int d, int v) { return o[d][v]; }, 1.0f / l_tot);
         }
-        store_rows<HD>(a, h, q0 + lj, lg, [&](int d, int v) { return o[d][v]; }, 1.0f / l_tot);
     });
 }
 
@@ -514,28 +516,32 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
     store_rows<HD>(a, h, q0 + lj, lg, [&](int d, int v) { return o[d * 4 + v / 4][v % 4]; }, 1.0f / l);
 }
 
-template <int HD, int NW>
+template <int HD, int NW, bool PARTS>
 hipError_t launch(const AttnArgs& a, hipStream_t s) {
     const size_t smem = 2 * (BKV * HD * 2 + HD * 128);
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)attn_fwd_kernel<HD, NW>,
+        hipError_t e = hipFuncSetAttribute((const void*)attn_fwd_kernel<HD, NW, PARTS>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
     const int nqt = (a.nq + 32 * NW - 1) / (32 * NW);
-    hipLaunchKernelGGL((attn_fwd_kernel<HD, NW>), dim3(nqt * a.H * a.splits), dim3(64 * NW), smem, s, a);
+    hipLaunchKernelGGL((attn_fwd_kernel<HD, NW, PARTS>), dim3(nqt * a.H * a.splits), dim3(64 * NW), smem, s, a);
     return hipGetLastError();
 }
 
-template <int HD>
+template <int HD, bool PARTS>
 hipError_t launch_nw(int nw, const AttnArgs& a, hipStream_t s) {
     switch (nw) {
-        case 7: return launch<HD, 7>(a, s);
-        case 8: return launch<HD, 8>(a, s);
-        default: return launch<HD, 4>(a, s);
+        case 7: return launch<HD, 7, PARTS>(a, s);
+        case 8: return launch<HD, 8, PARTS>(a, s);
+        default: return launch<HD, 4, PARTS>(a, s);
     }
+}
+template <int HD>
+hipError_t launch_nw(int nw, const AttnArgs& a, hipStream_t s) {
+    return a.splits > 1 ? launch_nw<HD, true>(nw, a, s) : launch_nw<HD, false>(nw, a, s);
 }
 
 }  // namespace
@@ -649,7 +655,7 @@ void attn_set_split(AttnArgs* a, int splits, float* scratch) {
 // of the last kEvenLast groups, and half a piece of ragged end.  At least eight groups: a workgroup's even share must cover a
 // whole sweep, or three of them would queue up in one.
 // 128-wide heads only: a CU holds two 8-wave workgroups of the 64-wide kernel, which one evenly dealt workgroup does not match
-// (8 heads x 30950 x 64: 2.70 against 2.36 ms).
+// (8 heads x 30950 x 64: 2.70 against 1.83 ms).
 // Where the lines lie (us by the grid / even / drawn; the estimated even share of the grid's time in brackets): 48 heads x 4608
 // 491 / 459 / 500 (0.97), 48 x 6000 806 / 756 / 805 (0.97), 96 x 4608 889 / 892 / 937 (1.00), 8 x 24000 1898 / 1926 / 1966
 // (1.02), 24 x 13640 2114 / 1900 / 1927 (0.88), 24 x 20000 4072 / 3961 / 3999 (0.94), 4 x 60000 5952 / 5846 / 5889 (0.94: by the

@@ -34,11 +34,11 @@ PEAK_LINK_GBS = 64.0           # PCIe Gen5 x16, one direction
 
 # HBM bytes per launch of the dominant kernel, from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs
 # scaled by a copy kernel of known size (see profiles/); None until measured for a workload.
-TRAFFIC = {("flux", "gemm_lin1/256x256"): 607860396,      # profiles/hbm_traffic_flux_kernels.md
-           ("flux", "gemm_lin2/128x128"): 528712950,
-           ("flux", "attention"): 66248782,               # profiles/hbm_traffic_attention_all_shares.md
-           ("wan", "attention"): 950651315,
-           ("hunyuan", "attention"): 11949446179}
+TRAFFIC = {("flux", "gemm_lin1/256x256"): 617400000,      # profiles/hbm_traffic_attention_all_shares.md
+           ("flux", "gemm_lin2/256x256"): 547800000,      # two parts and their reduction
+           ("flux", "attention"): 66300000,
+           ("wan", "attention"): 972200000,
+           ("hunyuan", "attention"): 12493300000}
 HEADLINE = "hunyuan"
 
 

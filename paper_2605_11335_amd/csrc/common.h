@@ -50,17 +50,19 @@ __device__ __forceinline__ float gelu_tanh_f32(float x) {
 }
 
 // x * Phi(x), the GELU the tanh form approximates, by the rational-times-Gaussian formula of Abramowitz & Stegun 7.1.26 for
-// erfc (absolute error below 1.5e-7, far under a bf16 ulp of the result):
+// erfc (absolute error below 1.5e-7, far under a bf16 ulp of a result of ordinary size):
 // erfc(z) = (a1 t + ... + a5 t^5) exp(-z^2), t = 1 / (1 + p z), z = |x| / sqrt 2 >= 0, and x Phi(x) = max(x, 0) - 0.5 |x| erfc(z):
-// nothing cancels in the negative tail.  Sixteen operations with the hardware's reciprocal and exponential (1 ulp each); with a
-// correctly rounded reciprocal and exp2f it was some sixty, 8 us more per generation of 256 x 256 tiles (1320 x 14336 x 3072:
-// 166 -> 150 us) and 9 % off where the result is below 1e-6 (now 0.4 %, the bf16 rounding).
+// nothing cancels in the negative tail, where the formula's relative error is what is left (0.4 % of the result at x = -6, 1 % at
+// -8, 3 % at -12: results of 6e-9, 5e-15 and 2e-32).  The factor |x| is held to 20, from where on erfc(z) is zero in fp32: an
+// infinite one would make +inf a NaN; a NaN still comes through erfc.  Seventeen operations with the hardware's reciprocal and
+// exponential (1 ulp each); with a correctly rounded reciprocal and exp2f it was some sixty, 8 us more per generation of
+// 256 x 256 tiles (1320 x 14336 x 3072: 166 -> 150 us).
 __device__ __forceinline__ float gelu_erf_f32(float x) {
     const float ax = fabsf(x), z = ax * 0.70710678118654752f;
     const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, z, 1.0f));
     const float poly = t * fmaf(t, fmaf(t, fmaf(t, fmaf(t, 1.061405429f, -1.453152027f), 1.421413741f), -0.284496736f), 0.254829592f);
     const float g = __builtin_amdgcn_exp2f(z * z * -1.4426950408889634f);     // exp(-z^2)
-    return fmaxf(x, 0.0f) - 0.5f * ax * (poly * g);
+    return fmaxf(x, 0.0f) - 0.5f * __builtin_amdgcn_fmed3f(ax, 0.0f, 20.0f) * (poly * g);
 }
 
 // splitmix64's output function: the per-word mixer of the streamed-bytes checksum.

@@ -63,6 +63,10 @@ class cf_sim_result(C.Structure):
                 ("resident_fraction", C.c_double)]
 
 
+class cf_attention_plan(C.Structure):
+    _fields_ = [("waves", C.c_int32), ("parts", C.c_int32), ("deal", C.c_int32)]
+
+
 class cf_tune_choice(C.Structure):
     _fields_ = [("chunk_bytes", C.c_uint64), ("r", C.c_double), ("feasible", C.c_int32), ("sim", cf_sim_result)]
 
@@ -76,8 +80,8 @@ CORE_EXPORTS = ["cf_create", "cf_destroy", "cf_last_error", "cf_blob_bytes", "cf
                 "cf_stats_reset", "cf_set_profiling", "cf_set_adaptive_waits", "cf_kernel_times", "cf_kernel_times_reset",
                 "cf_sync", "cf_op_checksum", "cf_op_checksum_noalloc"]
 #: what include/chunkflow_diag.h declares: single-kernel hooks, planner views, the matrix-core rate probe
-DIAG_EXPORTS = ["cf_plan_attention", "cf_plan_linear", "cf_op_linear", "cf_op_linear_residual", "cf_op_attention",
-                "cf_op_ln_modulate", "cf_op_modvec", "cf_op_mfma_rate", "cf_op_mix_rate"]
+DIAG_EXPORTS = ["cf_plan_attention", "cf_plan_block_attention", "cf_plan_linear", "cf_op_linear", "cf_op_linear_residual",
+                "cf_op_attention", "cf_op_attention_form", "cf_op_ln_modulate", "cf_op_modvec", "cf_op_mfma_rate", "cf_op_mix_rate"]
 EXPORTS = CORE_EXPORTS + DIAG_EXPORTS
 
 _lib = None
@@ -111,6 +115,7 @@ def lib() -> C.CDLL:
         _lib.cf_plan_panels.argtypes = [C.c_void_p, C.c_char_p, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p,
                                         C.POINTER(C.c_int32)]
         _lib.cf_plan_attention.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)]
+        _lib.cf_plan_block_attention.argtypes = [C.c_int32] * 5 + [C.POINTER(cf_attention_plan)]
         _lib.cf_plan_linear.argtypes = [C.c_int32, C.c_int32, C.POINTER(C.c_int32)]
         _lib.cf_register_block.argtypes = [C.c_void_p, C.c_int32, C.c_void_p, C.c_uint64]
         _lib.cf_set_block_kinds.argtypes = [C.c_void_p, C.c_void_p, C.c_int32]
@@ -135,6 +140,7 @@ def lib() -> C.CDLL:
                                                C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]
         _lib.cf_op_attention.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32,
                                          C.c_int32, C.c_int32, C.c_int32, C.c_void_p]
+        _lib.cf_op_attention_form.argtypes = [C.c_void_p] * 4 + [C.c_int32] * 8 + [C.c_void_p, C.c_uint64, C.c_void_p]
         _lib.cf_op_ln_modulate.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_void_p]
         _lib.cf_op_modvec.argtypes = [C.c_void_p, C.c_uint64, C.c_uint64, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_void_p]
         _lib.cf_op_mfma_rate.argtypes = [C.c_int32, C.c_int32, C.c_void_p, C.c_void_p]
@@ -371,6 +377,13 @@ def cf_plan_attention(H: int, nq: int, nk: int, head_dim: int) -> int:
     return out.value
 
 
+def cf_plan_block_attention(heads: int, batch: int, nq: int, nk: int, head_dim: int) -> cf_attention_plan:
+    """How a block launches attention over `heads` heads of each of `batch` samples (host arithmetic only)."""
+    out = cf_attention_plan()
+    _check(lib().cf_plan_block_attention(heads, batch, nq, nk, head_dim, C.byref(out)))
+    return out
+
+
 def cf_plan_linear(m_rows: int, n_features: int) -> int:
     """Tile height (256 or 128) a linear layer of this shape is launched with (host arithmetic only)."""
     out = C.c_int32()
@@ -393,6 +406,12 @@ def cf_op_linear_residual(A, blob, w_off, bias_off, M, N, K, resid, gate, y, lda
 
 def cf_op_attention(Q, K, Vt, O, H, nq, nk, nk_pad, hd, stream=None):
     _check(lib().cf_op_attention(_ptr(Q), _ptr(K), _ptr(Vt), _ptr(O), H, nq, nk, nk_pad, hd, _stream_handle(stream)))
+
+
+def cf_op_attention_form(Q, K, Vt, O, H, nq, nk, nk_pad, hd, scratch, parts=1, deal=0, no_wait=False, stream=None):
+    """Attention cut or dealt out as told; `scratch`: device tensor, its first 4096 bytes zero for a deal."""
+    _check(lib().cf_op_attention_form(_ptr(Q), _ptr(K), _ptr(Vt), _ptr(O), H, nq, nk, nk_pad, hd, parts, deal, int(no_wait), _ptr(scratch),
+                                      0 if scratch is None else scratch.numel() * scratch.element_size(), _stream_handle(stream)))
 
 
 def cf_op_ln_modulate(x, shift, scale, xn, rows, d, stream=None):

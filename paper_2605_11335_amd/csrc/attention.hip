@@ -458,8 +458,8 @@ __global__ __launch_bounds__(512, 2) void attn_even_kernel(AttnArgs a) {
             if (threadIdx.x == 0) {
                 uint32_t* const f = a.even_flags + take * 32 + j;
                 const unsigned long long give_up = __builtin_amdgcn_s_memrealtime() + kWaitTicks;
-                int r;
-                while (!(r = __hip_atomic_load(f, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) == 1u) && __builtin_amdgcn_s_memrealtime() < give_up)
+                int r = 0;
+                while (a.even_wait && !(r = __hip_atomic_load(f, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) == 1u) && __builtin_amdgcn_s_memrealtime() < give_up)
                     __builtin_amdgcn_s_sleep(16);
                 shared_word = r;
             }
@@ -662,7 +662,7 @@ void attn_set_split(AttnArgs* a, int splits, float* scratch) {
 // grid 8-wave sweeps, whose time is estimated too high by up to 4 %), 12 x 119056 69.2 / - / 66.65 ms.  The last sweeps in four
 // pieces each; there, in two 66.96, in three 66.70.
 constexpr int kEvenLast = 8, kEvenCuts = 4;
-static int even_plan(int H, int nq, int nk, int hd, int splits) {
+int attn_deal(int H, int nq, int nk, int hd, int splits) {
     const long groups = ((long)((nq + 255) / 256) * H + 31) / 32;
     if (splits > 1 || groups < 8 || hd != 128) return 0;
     AttnArgs a{};
@@ -675,20 +675,19 @@ static int even_plan(int H, int nq, int nk, int hd, int splits) {
     return even < (waves == 8 ? 0.96 : 0.98) * 1.03 * plain ? 1 : 0;
 }
 
-uint64_t attn_even_floats(int H, int nq, int nk, int hd, int splits) {
-    const int plan = even_plan(H, nq, nk, hd, splits);
-    return plan ? (uint64_t)(plan == 2 ? kEvenLast * (kEvenCuts - 1) : 7) * 32 * 512 * (hd / 2 + 2) : 0;
+uint64_t attn_deal_floats(int deal) {
+    return deal ? (uint64_t)(deal == 2 ? kEvenLast * (kEvenCuts - 1) : 7) * 32 * 512 * (128 / 2 + 2) : 0;
 }
 
-void attn_set_even(AttnArgs* a, float* state, uint32_t* flags) {
+void attn_set_deal(AttnArgs* a, int deal, float* state, uint32_t* flags) {
     static_assert(kEvenLast * (kEvenCuts - 1) * 32 + 32 <= ATTN_FLAGS, "a flag per state and 32 counters");
-    const int plan = state && flags ? even_plan(a->H, a->nq, a->nk, a->hd, a->splits) : 0;
-    a->even_state = plan ? state : nullptr;
-    a->even_flags = plan ? flags : nullptr;
+    a->even_state = deal ? state : nullptr;
+    a->even_flags = deal ? flags : nullptr;
     a->even_last = kEvenLast;
     a->even_cuts = kEvenCuts;
+    a->even_wait = 1;
     const int groups = (int)(((long)((a->nq + 255) / 256) * a->H + 31) / 32);
-    a->even_units = plan == 2 ? groups - kEvenLast + kEvenLast * kEvenCuts : 0;
+    a->even_units = deal == 2 ? groups - kEvenLast + kEvenLast * kEvenCuts : 0;
 }
 
 static hipError_t launch_even(const AttnArgs& a, hipStream_t s) {

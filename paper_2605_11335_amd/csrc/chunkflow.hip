@@ -128,8 +128,8 @@ inline int batch_of(const cf_model_desc& m) { return m.batch > 0 ? m.batch : 1; 
 void plan_cuts(Plan* p, const cf_model_desc& m) {
     const int P = m.sp_degree, hl = m.n_heads / P, nl = m.n_total / P, B = batch_of(m), hd = m.head_dim;
     p->self_splits = attn_splits(hl, m.n_total, m.n_total, hd);
-    p->even_floats = attn_even_floats(B * hl, m.n_total, m.n_total, hd, p->self_splits);
-    uint64_t part = std::max(p->even_floats, attn_part_floats(B * hl, m.n_total, hd, p->self_splits));
+    p->self_deal = attn_deal(B * hl, m.n_total, m.n_total, hd, p->self_splits);
+    uint64_t part = std::max(attn_deal_floats(p->self_deal), attn_part_floats(B * hl, m.n_total, hd, p->self_splits));
     if (p->kind == CF_DIT_CROSS) {
         p->cross_splits = attn_splits(m.n_heads, nl, m.l_ctx, hd);
         part = std::max(part, attn_part_floats(B * m.n_heads, nl, hd, p->cross_splits));
@@ -172,7 +172,7 @@ Ws carve(const cf_model_desc& m, const Plan& p, char* base) {
         w.cK = (bf16*)take(2ull * lc * d);
         w.cVt = (bf16*)take(2ull * B * d * n_pad_of(m.l_ctx));
     }
-    if (p.even_floats) w.flags = (uint32_t*)take(4 * ATTN_FLAGS);
+    if (p.self_deal) w.flags = (uint32_t*)take(4 * ATTN_FLAGS);
     w.part = (float*)take(4 * p.part_floats);
     w.total = off;
     return w;
@@ -738,7 +738,7 @@ int run_joint_attention(Fwd& F, const RelayoutArgs* parts, int n_parts, const At
         a.send = (bf16*)io->send_attn; a.send_bs = (long)peer_bs;
     }
     attn_set_split(&a, c->P(F.block).self_splits, F.ws.part);
-    attn_set_even(&a, F.ws.part, F.ws.flags);
+    attn_set_deal(&a, c->P(F.block).self_deal, F.ws.part, F.ws.flags);
     if (const char* msg = attn_check(a)) return cf_fail(c, CF_ERR_ARG, "%s", msg);
     {
         ProfScope ps(c, F.s, K_ATTN, 4.0 * B * hl * (double)m.n_total * m.n_total * hd, 0);
@@ -991,6 +991,18 @@ int cf_plan_attention(int32_t H, int32_t nq, int32_t nk, int32_t head_dim, int32
     AttnArgs a{};
     a.H = H; a.nq = nq; a.nk = nk; a.hd = head_dim;
     *waves_per_workgroup = attn_waves(a);
+    return CF_OK;
+}
+
+int cf_plan_block_attention(int32_t heads, int32_t batch, int32_t nq, int32_t nk, int32_t head_dim, cf_attention_plan* plan) {
+    if (heads <= 0 || batch <= 0 || (int64_t)heads * batch > 0x7fffffff || nq <= 0 || nk <= 0 || (head_dim != 64 && head_dim != 128) || !plan)
+        return cf_fail(nullptr, CF_ERR_ARG, "cf_plan_block_attention: positive sizes, head_dim 64 or 128 and a result pointer are required");
+    AttnArgs a{};
+    a.H = heads * batch; a.nq = nq; a.nk = nk; a.hd = head_dim;
+    attn_set_split(&a, attn_splits(heads, nq, nk, head_dim), nullptr);
+    plan->parts = a.splits;
+    plan->deal = attn_deal(a.H, nq, nk, head_dim, a.splits);
+    plan->waves = plan->deal ? 8 : attn_waves(a);
     return CF_OK;
 }
 
@@ -1399,6 +1411,25 @@ int cf_op_attention(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, ui
     a.o_hs = (long)nq * hd; a.o_qs = hd; a.H = H; a.nq = nq; a.nk = nk; a.nk_pad = nk_pad; a.hd = hd;
     a.scale = 1.0f / sqrtf((float)hd);
     attn_set_split(&a, 1, nullptr);
+    if (const char* msg = attn_check(a)) return cf_fail(nullptr, CF_ERR_ARG, "%s", msg);
+    hipError_t e = attn_launch(a, (hipStream_t)stream);
+    return e == hipSuccess ? CF_OK : cf_fail(nullptr, CF_ERR_HIP, "attention launch: %s", hipGetErrorString(e));
+}
+
+int cf_op_attention_form(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O, int32_t H, int32_t nq, int32_t nk,
+                         int32_t nk_pad, int32_t hd, int32_t parts, int32_t deal, int32_t no_wait, void* scratch, uint64_t scratch_bytes,
+                         void* stream) {
+    AttnArgs a{};
+    a.Q = (const bf16*)Q; a.K = (const bf16*)K; a.Vt = (const bf16*)Vt; a.O = (bf16*)O;
+    a.o_hs = (long)nq * hd; a.o_qs = hd; a.H = H; a.nq = nq; a.nk = nk; a.nk_pad = nk_pad; a.hd = hd;
+    if (parts < 1 || parts > 64 || deal < 0 || deal > 2 || (parts > 1 && deal)) return cf_fail(nullptr, CF_ERR_ARG, "attention: keys in up to 64 parts, or dealt out as 1 or 2");
+    if (const char* msg = attn_check(a)) return cf_fail(nullptr, CF_ERR_ARG, "%s", msg);       // the sizes, before they are computed with
+    a.scale = 1.0f / sqrtf((float)hd);
+    const uint64_t need = 4 * (deal ? ATTN_FLAGS + attn_deal_floats(deal) : attn_part_floats(H, nq, hd, parts));
+    if (need && (!scratch || scratch_bytes < need)) return cf_fail(nullptr, CF_ERR_ARG, "attention: this form needs %llu bytes of scratch", (unsigned long long)need);
+    attn_set_split(&a, parts, (float*)scratch);
+    attn_set_deal(&a, deal, (float*)scratch + ATTN_FLAGS, (uint32_t*)scratch);
+    a.even_wait = !no_wait;
     if (const char* msg = attn_check(a)) return cf_fail(nullptr, CF_ERR_ARG, "%s", msg);
     hipError_t e = attn_launch(a, (hipStream_t)stream);
     return e == hipSuccess ? CF_OK : cf_fail(nullptr, CF_ERR_HIP, "attention launch: %s", hipGetErrorString(e));

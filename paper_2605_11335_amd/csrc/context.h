@@ -56,9 +56,10 @@ struct Plan {
     uint64_t res_bytes = 0;
     uint64_t ws_bytes = 0;
     // how the block's launches are cut (functions of the model's sizes alone): parts of the keys in the joint and in the
-    // cross-attention, parts of K in residual layers with K = d and with the MLP-out layer's K; scratch for them in floats
-    int self_splits = 1, cross_splits = 1, sum_splits_d = 1, sum_splits_mlp = 1;
-    uint64_t even_floats = 0, part_floats = 0;
+    // cross-attention, how the joint attention's sweeps are dealt out (attn_deal), parts of K in residual layers with K = d and
+    // with the MLP-out layer's K; scratch for them in floats
+    int self_splits = 1, cross_splits = 1, self_deal = 0, sum_splits_d = 1, sum_splits_mlp = 1;
+    uint64_t part_floats = 0;
 };
 
 struct cf_ctx {

@@ -80,17 +80,19 @@ struct AttnArgs {
     // Scratch, float: part_o [splits][H][ceil(nq/32)][32 * hd] in register order, part_ml [..][32] (reference, row sum).
     int splits, part_tiles;
     float *part_o, *part_ml;
-    // Sweeps dealt out by the kernel (attn_set_even) instead of one workgroup per query tile; state NULL = no.  Scratch: the
-    // states of cut sweeps, and ATTN_FLAGS words that must be zero when the launch starts.
+    // Sweeps dealt out by the kernel (attn_set_deal) instead of one workgroup per query tile; state NULL = no.  Scratch: the
+    // states of cut sweeps, and ATTN_FLAGS words that must be zero when the launch starts.  even_wait: 0 = no state is ever
+    // waited for or taken, as when the wait runs out.
     float* even_state;
     uint32_t* even_flags;
-    int even_units, even_last, even_cuts;
+    int even_units, even_last, even_cuts, even_wait;
 };
 int attn_splits(int heads, int nq, int nk, int hd);      // parts to cut the keys into, for one sample's heads
 uint64_t attn_part_floats(int heads, int nq, int hd, int splits);      // scratch for all samples' heads; 0 if splits is 1
 void attn_set_split(AttnArgs* a, int splits, float* scratch);          // after H, nq, nk and hd are set
-uint64_t attn_even_floats(int H, int nq, int nk, int hd, int splits);  // scratch of a launch the kernel had better deal out, else 0
-void attn_set_even(AttnArgs* a, float* state, uint32_t* flags);        // after attn_set_split; does nothing where it does not pay
+int attn_deal(int H, int nq, int nk, int hd, int splits);              // how the sweeps of all samples' heads are dealt out: 0 by the grid, 1 even, 2 drawn
+uint64_t attn_deal_floats(int deal);                                   // scratch for the states of cut sweeps
+void attn_set_deal(AttnArgs* a, int deal, float* state, uint32_t* flags);      // after attn_set_split
 constexpr int ATTN_FLAGS = 1024;
 const char* attn_check(const AttnArgs& a);
 hipError_t attn_launch(const AttnArgs& a, hipStream_t s);

@@ -248,3 +248,25 @@ def test_no_alloc_checksum_rejects_oversize_and_misaligned_requests_before_touch
     assert lib.cf_op_checksum_noalloc(fake, 12, 0, fake, None) == B.CF_ERR_ARG
     assert lib.cf_op_checksum_noalloc(fake, 8, 0, None, None) == B.CF_ERR_ARG
     assert lib.cf_op_checksum_noalloc(C.c_void_p(4097), 8, 0, fake, None) == B.CF_ERR_ARG
+
+
+def test_block_attention_plans():
+    """How a block launches attention: the Flux-like share whole, by the grid; its share on eight GPUs with its keys in parts,
+    at any batch; the video shares dealt out by the kernel, evenly or drawn from a counter.  Bad requests for a form fail on
+    their arguments."""
+    def plan(*shape):
+        p = B.cf_plan_block_attention(*shape)
+        return p.waves, p.parts, p.deal
+    assert plan(12, 1, 4608, 4608, 128) == (8, 1, 0)
+    assert plan(12, 1, 27280, 27280, 128) == (8, 1, 1)
+    assert plan(12, 1, 119056, 119056, 128) == (8, 1, 2)
+    for batch in (1, 4):
+        assert B.cf_plan_block_attention(3, batch, 4608, 4608, 128).parts > 1
+    for bad in ((0, 1, 10, 10, 128), (1, 0, 10, 10, 128), (1, 1, 0, 10, 128), (1, 1, 10, 0, 128), (1, 1, 10, 10, 96), (1 << 20, 1 << 20, 10, 10, 64)):
+        with pytest.raises(B.ChunkflowError):
+            B.cf_plan_block_attention(*bad)
+    lib, p = B.lib(), C.c_void_p(4096)             # never dereferenced
+    for H, nq, nk, hd, parts, deal, nbytes in ((1, 64, 512, 128, 0, 0, 1 << 30), (1, 64, 512, 128, 65, 0, 1 << 30), (1, 64, 512, 128, 9, 0, 1 << 30),
+                                               (1, 64, 512, 128, 2, 1, 1 << 30), (1, 64, 512, 128, 1, 3, 1 << 30), (1, 64, 512, 128, 2, 0, 1000),
+                                               (12, 64, 512, 128, 1, 1, 1 << 30), (12, 4800, 512, 64, 1, 1, 1 << 30), (12, 4800, 512, 128, 1, 1, 4096)):
+        assert lib.cf_op_attention_form(p, p, p, p, H, nq, nk, nk, hd, parts, deal, 0, p, nbytes, None) == B.CF_ERR_ARG

@@ -33,6 +33,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, ui
 }
 
 constexpr int BKV = 64;    // keys per tile
+constexpr float kNoRef = -3.402823466e38f;     // reference of a query before its first score: finite, so that a tile, and with it
+                                               // a whole part of the keys, may hold nothing but -inf scores (weights of zero)
 
 __device__ __forceinline__ float max3f(float a, float b, float c) { return __builtin_fmaxf(__builtin_fmaxf(a, b), c); }
 
@@ -258,9 +260,9 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
                 const float a0 = max3f(m3[0], m3[1], m3[2]), a1 = max3f(m3[3], m3[4], m3[5]), a2 = max3f(m3[6], m3[7], m3[8]);
                 mx = max3f(max3f(a0, a1, a2), m3[9], m3[10]);
             }
-            mx = fmaxf(mx, __shfl_xor(mx, 32));         // every tile holds a key below nk: mx is finite
-            const float mc_new = fmaxf(mc, mx * c2);
-            const float alpha = __builtin_amdgcn_exp2f(mc - mc_new);             // 0 from mc = -inf
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float mc_new = fmaxf(mc, mx * c2);                             // -inf where all scores are: mc stays
+            const float alpha = __builtin_amdgcn_exp2f(mc - mc_new);             // 0 from kNoRef
             l_run *= alpha;
 #pragma unroll
             for (int d = 0; d < DT; ++d)
@@ -344,7 +346,7 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
             for (int d = 0; d < DT; ++d)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) o[d][v] = 0.f;
-            mc = -INFINITY;
+            mc = kNoRef;
             l_run = 0.f;
             issue_tile(t, 0);
             __syncthreads();

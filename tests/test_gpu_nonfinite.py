@@ -5,7 +5,8 @@ import torch
 
 import workload as wl
 from paper_2605_11335_amd import binding as B
-from tests.util import bits_to_f64, host_bits
+from tests.test_gpu_attention_forms import form, operands, reference, whole
+from tests.util import bits_to_f64, host_bits, max_abs, rel_l2
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -36,3 +37,23 @@ def test_activation_at_the_ends_of_the_range(erf):
         elif v <= -20.0 or v == 0.0:
             assert g == 0.0, (v, g)
     assert abs(got[-1][-1] - 0.8413447) < 2.0 ** -8
+
+
+# the first tile of the sequence, of each part in turn, of a part that holds no other key, the last (ragged) tile, and all but one
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("parts", [1, 2, 3, 5])
+@pytest.mark.parametrize("lo,hi", [(0, 64), (0, 192), (192, 256), (256, 384), (320, 384), (512, 577), (64, 577)])
+def test_tiles_of_scores_of_minus_infinity(hd, parts, lo, hi):
+    """Keys whose scores are all -inf have a weight of zero, wherever they lie."""
+    H, nq, nk = 2, 300, 577
+    rng = np.random.default_rng(hd + parts + lo)
+    q, k, v = (rng.normal(size=(H, n, hd)) for n in (nq, nk, nk))
+    q[:, :, 0] = np.abs(q[:, :, 0]) + 0.5
+    ops, values = operands(q, k, v)
+    ops[1][:, lo:hi, 0] = -128                     # the bits of -inf in bf16: 0xff80
+    got = bits_to_f64(whole(ops) if parts == 1 else form(ops, parts=parts))
+    values[1][:, lo:hi, 0] = -np.inf
+    ref = reference(values)
+    assert np.isfinite(ref).all() and np.isfinite(got).all()
+    print(f"rel_l2={rel_l2(got, ref):.3e}", flush=True)
+    assert rel_l2(got, ref) < 6e-3 and max_abs(got, ref) < 2e-2 * max(1.0, np.abs(ref).max())

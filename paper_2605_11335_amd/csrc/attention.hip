@@ -100,9 +100,10 @@ __device__ __forceinline__ void load_state(const float* from, int wave, int lane
 
 // One sweep of a workgroup (NW waves of 32 queries each, the wave's first at q0) over the key tiles [T0, T1) of head h.
 // `from`: not NULL = go on from the state another workgroup left there after the tiles before T0 (store_state).
-// finish(o, mc, l) gets O^T, the reference it is taken against and the lane's row sum.
-template <int HD, int NW, class Finish>
-__device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int T0, int T1, const float* from, Finish&& finish) {
+// repeat() is asked where a tile was out of the fast softmax's range: whether the sweep is to be repeated here; if not, finish
+// is not called.  finish(o, mc, l) gets O^T, the reference it is taken against and the lane's row sum.
+template <int HD, int NW, class Repeat, class Finish>
+__device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int T0, int T1, const float* from, Repeat&& repeat, Finish&& finish) {
     constexpr int KCH = HD / 8;                 // 16-byte chunks per K row
     constexpr int KROW = HD * 2;                // bytes per K row in LDS
     constexpr int KL = BKV * KCH / 64, VL = HD * 8 / 64;   // wave-loads (1 KiB each) per K / V^T tile
@@ -360,7 +361,10 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
     };
     sweep(std::false_type{});
     // the K/V tiles are the workgroup's: if any wave met a tile out of range, all of them go again
-    if (__syncthreads_or(out_of_range)) sweep(std::true_type{});
+    if (__syncthreads_or(out_of_range)) {
+        if (!repeat()) return;
+        sweep(std::true_type{});
+    }
     finish(o, mc, l_run);
 }
 
@@ -376,7 +380,7 @@ __global__ __launch_bounds__(64 * NW, HD == 64 ? 4 : 2) void attn_fwd_kernel(Att
     const int h = PARTS ? hs / a.splits : hs, part = PARTS ? hs % a.splits : 0;       // head, and which part of the keys
     const int q0 = qt * BQ + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 32;
     const int NT = (a.nk + BKV - 1) / BKV, T0 = PARTS ? part * a.part_tiles : 0, T1 = PARTS ? min(NT, T0 + a.part_tiles) : NT;
-    attn_sweep<HD, NW>(a, h, q0, T0, T1, nullptr, [&](floatx16 (&o)[DT], float mc, float l_run) {
+    attn_sweep<HD, NW>(a, h, q0, T0, T1, nullptr, [] { return true; }, [&](floatx16 (&o)[DT], float mc, float l_run) {
         const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0)), lj = lane & 31, lg = lane >> 5;
         const float l_tot = l_run + __shfl_xor(l_run, 32);
         if constexpr (PARTS) {
@@ -404,8 +408,10 @@ __global__ __launch_bounds__(64 * NW, HD == 64 ? 4 : 2) void attn_fwd_kernel(Att
 // group of 32 query tiles, one per CU of an XCD, swept in step (they share K and V tiles through the XCD's L2); "lane" j is the
 // j-th tile of every group and the j-th CU of every XCD.  A sweep may be cut: the first tiles by one workgroup, which leaves
 // the sweep's state in memory, the rest later by another, of another XCD, from there -- the same tiles in the same order, so
-// the same bits as one sweep.  Should the state not be there when it is needed (its workgroup has not been given a CU for
-// kWaitTicks), the sweep starts over from the first tile.
+// the same bits as one sweep of an 8-wave workgroup.  Should the state not be there when it is needed (its workgroup has not been given a CU for
+// kWaitTicks), the sweep starts over from the first tile.  Where a tile is out of the fast softmax's range no state is left,
+// only word of it (kUnfit), and the workgroup with the last piece takes the whole sweep, which it then repeats as one
+// workgroup would: the bits depend neither on the cut nor on what was waited for.
 //
 // Two plans.  Even shares (even_units = 0), for a few generations: XCD x takes the x-th eighth of the groups' key tiles laid end
 // to end; where an eighth ends inside a group, XCD x sweeps the group's first tiles before anything else and XCD x + 1 goes on
@@ -416,6 +422,7 @@ __global__ __launch_bounds__(64 * NW, HD == 64 ? 4 : 2) void attn_fwd_kernel(Att
 // workgroups of a lane draw groups from a counter; the last even_last groups go in even_cuts pieces each, all first pieces
 // before all second ones, so that the end is ragged by a piece and not by a sweep.
 constexpr unsigned long long kWaitTicks = 2000000;       // 20 ms of the 100 MHz counter
+enum : uint32_t { kStateLeft = 1, kUnfit = 2 };          // flag of a cut sweep; 0 = not there yet
 template <int HD>
 __global__ __launch_bounds__(512, 2) void attn_even_kernel(AttnArgs a) {
     constexpr int NW = 8, BQ = 32 * NW, DT = HD / 32, STATE = NW * 64 * (HD / 2 + 2);
@@ -460,28 +467,41 @@ __global__ __launch_bounds__(512, 2) void attn_even_kernel(AttnArgs a) {
             if (threadIdx.x == 0) {
                 uint32_t* const f = a.even_flags + take * 32 + j;
                 const unsigned long long give_up = __builtin_amdgcn_s_memrealtime() + kWaitTicks;
-                int r = 0;
-                while (a.even_wait && !(r = __hip_atomic_load(f, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) == 1u) && __builtin_amdgcn_s_memrealtime() < give_up)
+                uint32_t r = 0;
+                while (a.even_wait && !(r = __hip_atomic_load(f, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT)) && __builtin_amdgcn_s_memrealtime() < give_up)
                     __builtin_amdgcn_s_sleep(16);
-                shared_word = r;
+                shared_word = (int)r;
             }
             __syncthreads();                   // orders every wave behind thread 0's acquire
-            if (__builtin_amdgcn_readfirstlane(shared_word)) from = a.even_state + ((size_t)take * 32 + j) * STATE;
+            const uint32_t found = (uint32_t)__builtin_amdgcn_readfirstlane(shared_word);
+            if (found == kUnfit && leave >= 0) {
+                if (threadIdx.x == 0) __hip_atomic_store(a.even_flags + leave * 32 + j, (uint32_t)kUnfit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __syncthreads();               // the word is written again in the next step
+                continue;
+            }
+            if (found == kStateLeft) from = a.even_state + ((size_t)take * 32 + j) * STATE;
             else T0 = 0;
         }
         const int h = item / nqt, q0 = item % nqt * BQ + wave * 32;
-        attn_sweep<HD, NW>(a, h, q0, T0, T1, from, [&](floatx16 (&o)[DT], float mc, float l_run) {
-            if (leave >= 0) {
-                store_state<HD>(a.even_state + ((size_t)leave * 32 + j) * STATE, wave, lane, o, mc, l_run);
-                // One release per workgroup, by thread 0 behind the barrier: it writes back the XCD's whole L2.  By every wave
-                // it cost 57 us.
-                __syncthreads();
-                if (threadIdx.x == 0) __hip_atomic_store(a.even_flags + leave * 32 + j, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-            } else {
-                const float l_tot = l_run + __shfl_xor(l_run, 32);
-                store_rows<HD>(a, h, q0 + lj, lg, [&](int d, int v) { return o[d][v]; }, 1.0f / l_tot);
-            }
-        });
+        bool unfit;                            // a tile was out of range, and this workgroup has not all of the sweep
+        do {
+            unfit = false;
+            attn_sweep<HD, NW>(a, h, q0, T0, T1, from, [&] { unfit = leave >= 0 || from; return !unfit; }, [&](floatx16 (&o)[DT], float mc, float l_run) {
+                if (leave >= 0) {
+                    store_state<HD>(a.even_state + ((size_t)leave * 32 + j) * STATE, wave, lane, o, mc, l_run);
+                    // One release per workgroup, by thread 0 behind the barrier: it writes back the XCD's whole L2.  By every wave
+                    // it cost 57 us.
+                    __syncthreads();
+                    if (threadIdx.x == 0) __hip_atomic_store(a.even_flags + leave * 32 + j, (uint32_t)kStateLeft, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+                } else {
+                    const float l_tot = l_run + __shfl_xor(l_run, 32);
+                    store_rows<HD>(a, h, q0 + lj, lg, [&](int d, int v) { return o[d][v]; }, 1.0f / l_tot);
+                }
+            });
+            T0 = 0;
+            from = nullptr;
+        } while (unfit && leave < 0);
+        if (unfit && threadIdx.x == 0) __hip_atomic_store(a.even_flags + leave * 32 + j, (uint32_t)kUnfit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 

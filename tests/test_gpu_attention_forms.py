@@ -77,3 +77,28 @@ def test_dealt_out_sweeps_have_the_bits_of_whole_ones(H, nq, nk, deal):
     want = whole(ops)
     for no_wait in (False, True):
         assert np.array_equal(form(ops, deal=deal, no_wait=no_wait), want), no_wait
+
+
+# the scores of half of the heads leave the range of a sweep without a running maximum at one tile: in the first piece of a cut
+# sweep, in any later one, at the very end
+@pytest.mark.parametrize("H,nq,nk", [(12, 8400, 2030), (12, 4700, 2030), (12, 4800, 4800)])      # 13 groups, eighths cut inside; 8, in pieces if drawn
+@pytest.mark.parametrize("at", [0.02, 0.2, 0.4, 0.6, 0.8, 0.99])
+@pytest.mark.parametrize("deal", [1, 2])
+def test_dealt_out_sweeps_that_have_to_be_repeated(H, nq, nk, at, deal):
+    """A cut sweep is then repeated from its first tile, as a whole one is, whichever of its pieces found out."""
+    assert B.cf_plan_attention(H, nq, nk, 128) == 8            # a repeated sweep is a workgroup's: the same 256 queries
+    rng = np.random.default_rng(nk)
+    q, k, v = (rng.normal(size=(H, n, 128)) for n in (nq, nk, nk))
+    u = rng.normal(size=128)
+    u /= np.linalg.norm(u)
+    q += 4.0 * u
+    jump = int(at * nk) // 64 * 64
+    k[::2, jump:jump + 64] += 600.0 * u                        # 4 * 600 / sqrt(128) = 212 nats
+    ops, values = operands(q, k, v)
+    want = whole(ops)
+    rows = np.sort(rng.choice(nq, 100, replace=False))
+    got, ref = bits_to_f64(want)[:, rows], reference((values[0][:, rows], values[1], values[2]))
+    assert rel_l2(got, ref) < 6e-3
+    for no_wait in (False, True):
+        out = form(ops, deal=deal, no_wait=no_wait)
+        assert np.array_equal(out, want), (no_wait, int((out != want).sum()))

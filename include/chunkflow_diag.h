@@ -53,7 +53,8 @@ int cf_op_linear_residual(const uint16_t* A, int32_t lda, const void* blob, uint
 int cf_op_attention(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O,
                     int32_t H, int32_t nq, int32_t nk, int32_t nk_pad, int32_t hd, void* stream);
 /* The same in a form of the caller's choice, as a block may launch it: keys in `parts` parts, or (parts = 1) dealt out as
- * `deal` says; head width 128 and more than 7 * 32 query tiles of 256 for deal 1 and 2.  no_wait: a workgroup that would go on
+ * `deal` says; head width 128 and more than 7 * 32 query tiles of 256 for deal 1 and 2,
+ * more than 192 keys for deal 2.  no_wait: a workgroup that would go on
  * with a sweep begun by another does not find it, as if that one had not run in time.  scratch: 16-byte aligned;
  * parts * H * ceil(nq / 32) * 32 * (hd + 2) floats, or for a deal 4096 bytes that are ZERO followed by 24 * 32 * 512 * 66 floats. */
 int cf_op_attention_form(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O, int32_t H, int32_t nq, int32_t nk,

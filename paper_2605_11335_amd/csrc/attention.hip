@@ -595,6 +595,8 @@ const char* attn_check(const AttnArgs& a) {
         return "attention: bad split of the keys";
     if (a.even_state && (a.splits > 1 || !a.even_flags || ((uintptr_t)a.even_state % 16) || a.hd != 128 || (long)((a.nq + 255) / 256) * a.H <= 7 * 32))
         return "attention: launch cannot be dealt out by the kernel";
+    // a sweep works off its first tile whatever its end: an empty piece would count one twice
+    if (a.even_state && a.even_units && (a.nk + BKV - 1) / BKV < a.even_cuts) return "attention: too few keys to cut a sweep in pieces";
     return nullptr;
 }
 
@@ -693,7 +695,7 @@ int attn_deal(int H, int nq, int nk, int hd, int splits) {
     const int waves = waves_and_cost(a, &plain);
     const double tiles = (double)((nk + BKV - 1) / BKV), sweeps = groups / 8.0 * (tiles + 2.5);
     const double even = 1.03 * (sweeps + 2.5 + 15.0), drawn = sweeps + 15.0 * kEvenCuts + tiles / kEvenCuts / 2;
-    if (groups >= 3 * kEvenLast && drawn < 0.99 * even && drawn < 0.985 * 1.03 * plain) return 2;
+    if (groups >= 3 * kEvenLast && tiles >= kEvenCuts && drawn < 0.99 * even && drawn < 0.985 * 1.03 * plain) return 2;
     return even < (waves == 8 ? 0.96 : 0.98) * 1.03 * plain ? 1 : 0;
 }
 

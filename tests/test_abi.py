@@ -268,5 +268,7 @@ def test_block_attention_plans():
     lib, p = B.lib(), C.c_void_p(4096)             # never dereferenced
     for H, nq, nk, hd, parts, deal, nbytes in ((1, 64, 512, 128, 0, 0, 1 << 30), (1, 64, 512, 128, 65, 0, 1 << 30), (1, 64, 512, 128, 9, 0, 1 << 30),
                                                (1, 64, 512, 128, 2, 1, 1 << 30), (1, 64, 512, 128, 1, 3, 1 << 30), (1, 64, 512, 128, 2, 0, 1000),
-                                               (12, 64, 512, 128, 1, 1, 1 << 30), (12, 4800, 512, 64, 1, 1, 1 << 30), (12, 4800, 512, 128, 1, 1, 4096)):
+                                               (12, 64, 512, 128, 1, 1, 1 << 30), (12, 4800, 512, 64, 1, 1, 1 << 30), (12, 4800, 512, 128, 1, 1, 4096), (12, 4800, 192, 128, 1, 2, 1 << 30)):
         assert lib.cf_op_attention_form(p, p, p, p, H, nq, nk, nk, hd, parts, deal, 0, p, nbytes, None) == B.CF_ERR_ARG
+    # a drawn sweep is cut in four pieces of at least a tile, however many there are
+    assert all(plan(48, b, nq, nk, 128)[2] != 2 for b in (1, 16, 256) for nq in (4608, 119056) for nk in (1, 64, 128, 192))

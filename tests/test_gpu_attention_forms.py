@@ -67,8 +67,8 @@ def test_keys_in_parts(H, nq, nk, hd, parts, sharp):
     assert rel_l2(got[:, rows], ref) < 6e-3 and max_abs(got[:, rows], ref) < 2e-2 * max(1.0, np.abs(ref).max())
 
 
-# groups of 32 query tiles: 8 and a quarter, 9 exactly, 9 and a quarter; key counts of 75, 43 and 5 tiles, ragged
-@pytest.mark.parametrize("H,nq,nk", [(12, 4800, 4800), (24, 2850, 2750), (11, 6800, 300)])
+# groups of 32 query tiles: 8 and a quarter, 9 exactly, 9 and a quarter; key counts of 75, 43, 5 and 4 tiles, ragged
+@pytest.mark.parametrize("H,nq,nk", [(12, 4800, 4800), (24, 2850, 2750), (11, 6800, 300), (12, 4800, 200)])
 @pytest.mark.parametrize("deal", [1, 2])
 def test_dealt_out_sweeps_have_the_bits_of_whole_ones(H, nq, nk, deal):
     """Also where no workgroup ever finds the state that another left, and starts its sweep over."""

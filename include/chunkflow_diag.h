@@ -23,11 +23,12 @@ extern "C" {
 int cf_plan_attention(int32_t H, int32_t nq, int32_t nk, int32_t head_dim, int32_t* waves_per_workgroup);
 
 /* Host-only view of how a block launches attention, `heads` heads for each of `batch` samples: with its keys in
- * `parts` parts (1 = whole), computed by workgroups of their own and merged afterwards; dealt out by the grid (deal 0), by the kernel
- * in even shares (1) or as workgroups come for the next sweep (2), whole sweeps of 8-wave workgroups in either
- * case; in workgroups of `waves` waves.  The choice of parts looks at one sample alone.  No GPU is touched. */
+ * `parts` parts (1 = whole), computed by workgroups of their own and merged afterwards or (all_parts, where the
+ * batch fills the chip) by one workgroup after the other; dealt out by the grid (deal 0), by the kernel in even shares (1) or as
+ * workgroups come for the next sweep (2), whole sweeps of 8-wave workgroups in either case; in workgroups of `waves`
+ * waves.  The number of parts is a matter of one sample alone, and the bits of the result with it.  No GPU is touched. */
 typedef struct cf_attention_plan {
-    int32_t waves, parts, deal;
+    int32_t waves, parts, all_parts, deal;
 } cf_attention_plan;
 int cf_plan_block_attention(int32_t heads, int32_t batch, int32_t nq, int32_t nk, int32_t head_dim, cf_attention_plan* plan);
 
@@ -52,13 +53,13 @@ int cf_op_linear_residual(const uint16_t* A, int32_t lda, const void* blob, uint
  * O [H,nq,hd] (App. B attention term, no mask). */
 int cf_op_attention(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O,
                     int32_t H, int32_t nq, int32_t nk, int32_t nk_pad, int32_t hd, void* stream);
-/* The same in a form of the caller's choice, as a block may launch it: keys in `parts` parts, or (parts = 1) dealt out as
- * `deal` says; head width 128 and more than 7 * 32 query tiles of 256 for deal 1 and 2,
+/* The same in a form of the caller's choice, as a block may launch it: keys in `parts` parts, with all_parts those of
+ * a query tile in one workgroup, or (parts = 1) dealt out as `deal` says; head width 128 and more than 7 * 32 query tiles of 256 for deal 1 and 2,
  * more than 192 keys for deal 2.  no_wait: a workgroup that would go on
- * with a sweep begun by another does not find it, as if that one had not run in time.  scratch: 16-byte aligned;
- * parts * H * ceil(nq / 32) * 32 * (hd + 2) floats, or for a deal 4096 bytes that are ZERO followed by 24 * 32 * 512 * 66 floats. */
+ * with a sweep begun by another does not find it, as if that one had not run in time.  scratch: 16-byte aligned; none with
+ * all_parts, parts * H * ceil(nq / 32) * 32 * (hd + 2) floats, or for a deal 4096 bytes that are ZERO followed by 24 * 32 * 512 * 66 floats. */
 int cf_op_attention_form(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O, int32_t H, int32_t nq, int32_t nk,
-                         int32_t nk_pad, int32_t hd, int32_t parts, int32_t deal, int32_t no_wait, void* scratch, uint64_t scratch_bytes,
+                         int32_t nk_pad, int32_t hd, int32_t parts, int32_t all_parts, int32_t deal, int32_t no_wait, void* scratch, uint64_t scratch_bytes,
                          void* stream);
 /* xn = LayerNorm(x) * (1 + scale) + shift, bf16 out. */
 int cf_op_ln_modulate(const float* x, const float* shift, const float* scale, uint16_t* xn,

@@ -64,7 +64,7 @@ class cf_sim_result(C.Structure):
 
 
 class cf_attention_plan(C.Structure):
-    _fields_ = [("waves", C.c_int32), ("parts", C.c_int32), ("deal", C.c_int32)]
+    _fields_ = [("waves", C.c_int32), ("parts", C.c_int32), ("all_parts", C.c_int32), ("deal", C.c_int32)]
 
 
 class cf_tune_choice(C.Structure):
@@ -140,7 +140,7 @@ def lib() -> C.CDLL:
                                                C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]
         _lib.cf_op_attention.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32,
                                          C.c_int32, C.c_int32, C.c_int32, C.c_void_p]
-        _lib.cf_op_attention_form.argtypes = [C.c_void_p] * 4 + [C.c_int32] * 8 + [C.c_void_p, C.c_uint64, C.c_void_p]
+        _lib.cf_op_attention_form.argtypes = [C.c_void_p] * 4 + [C.c_int32] * 9 + [C.c_void_p, C.c_uint64, C.c_void_p]
         _lib.cf_op_ln_modulate.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_void_p]
         _lib.cf_op_modvec.argtypes = [C.c_void_p, C.c_uint64, C.c_uint64, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_void_p]
         _lib.cf_op_mfma_rate.argtypes = [C.c_int32, C.c_int32, C.c_void_p, C.c_void_p]
@@ -408,9 +408,9 @@ def cf_op_attention(Q, K, Vt, O, H, nq, nk, nk_pad, hd, stream=None):
     _check(lib().cf_op_attention(_ptr(Q), _ptr(K), _ptr(Vt), _ptr(O), H, nq, nk, nk_pad, hd, _stream_handle(stream)))
 
 
-def cf_op_attention_form(Q, K, Vt, O, H, nq, nk, nk_pad, hd, scratch, parts=1, deal=0, no_wait=False, stream=None):
+def cf_op_attention_form(Q, K, Vt, O, H, nq, nk, nk_pad, hd, scratch, parts=1, all_parts=False, deal=0, no_wait=False, stream=None):
     """Attention cut or dealt out as told; `scratch`: device tensor, its first 4096 bytes zero for a deal."""
-    _check(lib().cf_op_attention_form(_ptr(Q), _ptr(K), _ptr(Vt), _ptr(O), H, nq, nk, nk_pad, hd, parts, deal, int(no_wait), _ptr(scratch),
+    _check(lib().cf_op_attention_form(_ptr(Q), _ptr(K), _ptr(Vt), _ptr(O), H, nq, nk, nk_pad, hd, parts, int(all_parts), deal, int(no_wait), _ptr(scratch),
                                       0 if scratch is None else scratch.numel() * scratch.element_size(), _stream_handle(stream)))
 
 

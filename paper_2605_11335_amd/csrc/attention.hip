@@ -98,11 +98,27 @@ __device__ __forceinline__ void load_state(const float* from, int wave, int lane
     l_run = ml.y;
 }
 
+// A part of the keys joined to the ones before it, (m, l) and (mc, l_part) the references and row sums: both brought to the higher
+// reference.  One order and one rounding for the workgroup that has all parts and for the kernel that reads them.
+struct Joint {
+    float before, part;                        // factors
+    __device__ __forceinline__ float join(float sum, float o) const { return fmaf(o, part, __fmul_rn(sum, before)); }
+};
+__device__ __forceinline__ Joint join_part(float& m, float& l, float mc, float l_part) {
+    const float hi = fmaxf(m, mc);
+    const Joint f = {__builtin_amdgcn_exp2f(m - hi), __builtin_amdgcn_exp2f(mc - hi)};
+    l = f.join(l, l_part);
+    m = hi;
+    return f;
+}
+
 // One sweep of a workgroup (NW waves of 32 queries each, the wave's first at q0) over the key tiles [T0, T1) of head h.
 // `from`: not NULL = go on from the state another workgroup left there after the tiles before T0 (store_state).
 // repeat() is asked where a tile was out of the fast softmax's range: whether the sweep is to be repeated here; if not, finish
 // is not called.  finish(o, mc, l) gets O^T, the reference it is taken against and the lane's row sum.
-template <int HD, int NW, class Repeat, class Finish>
+// ALL_PARTS: the tiles are parts of a.part_tiles (an even number) one after the other, each swept as by a workgroup of its own
+// and joined to the ones before (join_part) in registers; the copies run on from part to part.
+template <int HD, int NW, bool ALL_PARTS, class Repeat, class Finish>
 __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int T0, int T1, const float* from, Repeat&& repeat, Finish&& finish) {
     constexpr int KCH = HD / 8;                 // 16-byte chunks per K row
     constexpr int KROW = HD * 2;                // bytes per K row in LDS
@@ -176,6 +192,7 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
     const int krow = (lj & 0x13) | ((lj & 4) << 1) | ((lj & 8) >> 1);
 
     int out_of_range = 0;                       // wave-uniform: a fast tile met scores it could not take
+    const int T_end = T1;                       // of the copies
 
     // One tile.  The LDS buffer is a compile-time constant so that fragment addresses are a per-lane
     // register plus an immediate.
@@ -192,7 +209,7 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
     auto tile = [&](int t, auto buf_c, auto tracking_c) __attribute__((always_inline)) {
         constexpr int buf = decltype(buf_c)::value;
         constexpr bool tracking = decltype(tracking_c)::value;
-        if (t + 1 < T1) issue_tile(t + 1, buf ^ 1);
+        if (t + 1 < T_end) issue_tile(t + 1, buf ^ 1);
         const char* cK = sK + buf * K_TILE;
         const char* cV = sV + buf * V_TILE;
 
@@ -336,7 +353,7 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
         __syncthreads();                        // tile t+1 has landed, tile t may be overwritten
     };
     // One sweep: the first tile tracks (it sets the reference) unless the state is inherited, the others go in pairs.
-    auto sweep = [&](auto tracking_c) __attribute__((always_inline)) {
+    auto sweep = [&](auto tracking_c, bool landed) __attribute__((always_inline)) {
         int t = T0;
         if (from) {
             load_state<HD>(from, wave, lane, o, mc, l_run);
@@ -349,8 +366,10 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
                 for (int v = 0; v < 16; ++v) o[d][v] = 0.f;
             mc = kNoRef;
             l_run = 0.f;
-            issue_tile(t, 0);
-            __syncthreads();
+            if (!landed) {
+                issue_tile(t, 0);
+                __syncthreads();
+            }
             tile(t, std::integral_constant<int, 0>{}, std::true_type{});
             ++t;
         }
@@ -359,33 +378,60 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
             if (t + 1 < T1) tile(t + 1, std::integral_constant<int, 0>{}, tracking_c);
         }
     };
-    sweep(std::false_type{});
-    // the K/V tiles are the workgroup's: if any wave met a tile out of range, all of them go again
-    if (__syncthreads_or(out_of_range)) {
-        if (!repeat()) return;
-        sweep(std::true_type{});
+    if constexpr (ALL_PARTS) {
+        floatx16 sum[DT];                       // the parts so far
+        float m_sum = kNoRef, l_sum = 0.f;
+#pragma unroll
+        for (int d = 0; d < DT; ++d)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sum[d][v] = 0.f;
+        for (int t0 = T0; t0 < T_end; t0 += a.part_tiles) {
+            T0 = t0;
+            T1 = min(T_end, t0 + a.part_tiles);
+            sweep(std::false_type{}, t0 > 0);
+            if (__syncthreads_or(out_of_range)) {
+                out_of_range = 0;
+                sweep(std::true_type{}, false);
+            }
+            const Joint f = join_part(m_sum, l_sum, mc, l_run + __shfl_xor(l_run, 32));
+#pragma unroll
+            for (int d = 0; d < DT; ++d)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) sum[d][v] = f.join(sum[d][v], o[d][v]);
+        }
+        finish(sum, m_sum, l_sum);
+    } else {
+        sweep(std::false_type{}, false);
+        // the K/V tiles are the workgroup's: if any wave met a tile out of range, all of them go again
+        if (__syncthreads_or(out_of_range)) {
+            if (!repeat()) return;
+            sweep(std::true_type{}, false);
+        }
+        finish(o, mc, l_run);
     }
-    finish(o, mc, l_run);
 }
 
 // NW waves of 32 queries each per workgroup: 4 (two workgroups per CU), 7 or 8 (one per CU); for 64-wide heads twice as many,
 // held to the 128 registers that takes: at 129 a CU has one 7-wave workgroup and 8 heads x 20892 take 1.11 ms instead of 0.90.
-// PARTS: the keys are cut (a.splits > 1), the results go to scratch.
-template <int HD, int NW, bool PARTS>
-__global__ __launch_bounds__(64 * NW, HD == 64 ? 4 : 2) void attn_fwd_kernel(AttnArgs a) {
+// PARTS: the keys are cut (a.splits > 1), each part for a workgroup of its own, the results go to scratch.  ALL_PARTS: cut alike,
+// and a workgroup has all parts of its queries, for which it holds a second O^T: 246 to 250 registers with 128-wide heads; 162 with
+// 64-wide ones, where three 4-wave workgroups then share a CU, which costs no time (32 heads x 4696: 198.4 us whole, 198.6).
+enum { WHOLE, PARTS, ALL_PARTS };
+template <int HD, int NW, int FORM>
+__global__ __launch_bounds__(64 * NW, HD == 64 ? (FORM == ALL_PARTS ? 3 : 4) : 2) void attn_fwd_kernel(AttnArgs a) {
     constexpr int BQ = 32 * NW, DT = HD / 32;
     const int nqt = (a.nq + BQ - 1) / BQ;
     const uint32_t lid = xcd_contiguous_id(blockIdx.x, gridDim.x);
     const int hs = lid / nqt, qt = lid % nqt;
-    const int h = PARTS ? hs / a.splits : hs, part = PARTS ? hs % a.splits : 0;       // head, and which part of the keys
+    const int h = FORM == PARTS ? hs / a.splits : hs, part = FORM == PARTS ? hs % a.splits : 0;       // head, and which part of the keys
     const int q0 = qt * BQ + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 32;
-    const int NT = (a.nk + BKV - 1) / BKV, T0 = PARTS ? part * a.part_tiles : 0, T1 = PARTS ? min(NT, T0 + a.part_tiles) : NT;
-    attn_sweep<HD, NW>(a, h, q0, T0, T1, nullptr, [] { return true; }, [&](floatx16 (&o)[DT], float mc, float l_run) {
+    const int NT = (a.nk + BKV - 1) / BKV;
+    const int T0 = FORM == PARTS ? part * a.part_tiles : 0, T1 = FORM == PARTS ? min(NT, T0 + a.part_tiles) : NT;
+    attn_sweep<HD, NW, FORM == ALL_PARTS>(a, h, q0, T0, T1, nullptr, [] { return true; }, [&](floatx16 (&o)[DT], float mc, float l_run) {
         const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0)), lj = lane & 31, lg = lane >> 5;
-        const float l_tot = l_run + __shfl_xor(l_run, 32);
-        if constexpr (PARTS) {
-            // part of the keys only: O^T, the reference it is taken against and the row sum go to the scratch buffer as they
-            // lie in registers, 1 KiB per store
+        const float l_tot = FORM == ALL_PARTS ? l_run : l_run + __shfl_xor(l_run, 32);
+        if constexpr (FORM == PARTS) {
+            // O^T, the reference it is taken against and the row sum as they lie in registers, 1 KiB per store
             if (q0 < a.nq) {
                 const size_t tile32 = ((size_t)part * a.H + h) * ((a.nq + 31) / 32) + q0 / 32;
                 float* const po = a.part_o + tile32 * (32 * HD);
@@ -486,7 +532,7 @@ __global__ __launch_bounds__(512, 2) void attn_even_kernel(AttnArgs a) {
         bool unfit;                            // a tile was out of range, and this workgroup has not all of the sweep
         do {
             unfit = false;
-            attn_sweep<HD, NW>(a, h, q0, T0, T1, from, [&] { unfit = leave >= 0 || from; return !unfit; }, [&](floatx16 (&o)[DT], float mc, float l_run) {
+            attn_sweep<HD, NW, false>(a, h, q0, T0, T1, from, [&] { unfit = leave >= 0 || from; return !unfit; }, [&](floatx16 (&o)[DT], float mc, float l_run) {
                 if (leave >= 0) {
                     store_state<HD>(a.even_state + ((size_t)leave * 32 + j) * STATE, wave, lane, o, mc, l_run);
                     // One release per workgroup, by thread 0 behind the barrier: it writes back the XCD's whole L2.  By every wave
@@ -516,54 +562,56 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
     if (w >= a.H * n32) return;
     const int h = w / n32, q0 = (w % n32) * 32;
     const size_t part_stride = (size_t)a.H * n32, tile32 = (size_t)h * n32 + q0 / 32;
-    float m = -INFINITY;
-    for (int p = 0; p < a.splits; ++p) m = fmaxf(m, a.part_ml[(p * part_stride + tile32) * 64 + lj * 2]);
+    float m = kNoRef, l = 0.f;
     floatx4 o[DT * 4];
 #pragma unroll
     for (int i = 0; i < DT * 4; ++i) o[i] = floatx4{0.f, 0.f, 0.f, 0.f};
-    float l = 0.f;
     for (int p = 0; p < a.splits; ++p) {
         const float2 ml = *(const float2*)(a.part_ml + (p * part_stride + tile32) * 64 + lj * 2);
         const float* const po = a.part_o + (p * part_stride + tile32) * (32 * HD);
         floatx4 v[DT * 4];
 #pragma unroll
         for (int i = 0; i < DT * 4; ++i) v[i] = *(const floatx4*)(po + i * 256 + lane * 4);
-        const float e = __builtin_amdgcn_exp2f(ml.x - m);
-        l = fmaf(ml.y, e, l);
+        const Joint f = join_part(m, l, ml.x, ml.y);
 #pragma unroll
         for (int i = 0; i < DT * 4; ++i)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) o[i][c] = fmaf(v[i][c], e, o[i][c]);
+            for (int c = 0; c < 4; ++c) o[i][c] = f.join(o[i][c], v[i][c]);
     }
     store_rows<HD>(a, h, q0 + lj, lg, [&](int d, int v) { return o[d * 4 + v / 4][v % 4]; }, 1.0f / l);
 }
 
-template <int HD, int NW, bool PARTS>
+template <int HD, int NW, int FORM>
 hipError_t launch(const AttnArgs& a, hipStream_t s) {
     const size_t smem = 2 * (BKV * HD * 2 + HD * 128);
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void*)attn_fwd_kernel<HD, NW, PARTS>,
+        hipError_t e = hipFuncSetAttribute((const void*)attn_fwd_kernel<HD, NW, FORM>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
     const int nqt = (a.nq + 32 * NW - 1) / (32 * NW);
-    hipLaunchKernelGGL((attn_fwd_kernel<HD, NW, PARTS>), dim3(nqt * a.H * a.splits), dim3(64 * NW), smem, s, a);
+    hipLaunchKernelGGL((attn_fwd_kernel<HD, NW, FORM>), dim3(nqt * a.H * (FORM == PARTS ? a.splits : 1)), dim3(64 * NW), smem, s, a);
     return hipGetLastError();
 }
 
-template <int HD, bool PARTS>
+template <int HD, int FORM>
 hipError_t launch_nw(int nw, const AttnArgs& a, hipStream_t s) {
     switch (nw) {
-        case 7: return launch<HD, 7, PARTS>(a, s);
-        case 8: return launch<HD, 8, PARTS>(a, s);
-        default: return launch<HD, 4, PARTS>(a, s);
+        case 7: return launch<HD, 7, FORM>(a, s);
+        case 8: return launch<HD, 8, FORM>(a, s);
+        default: return launch<HD, 4, FORM>(a, s);
     }
 }
 template <int HD>
 hipError_t launch_nw(int nw, const AttnArgs& a, hipStream_t s) {
-    return a.splits > 1 ? launch_nw<HD, true>(nw, a, s) : launch_nw<HD, false>(nw, a, s);
+    if (a.splits <= 1) return launch_nw<HD, WHOLE>(nw, a, s);
+    if (a.all_parts) {
+        if constexpr (HD == 64) return launch<HD, 4, ALL_PARTS>(a, s);
+        else return launch_nw<HD, ALL_PARTS>(nw, a, s);
+    }
+    return launch_nw<HD, PARTS>(nw, a, s);
 }
 
 }  // namespace
@@ -590,9 +638,11 @@ const char* attn_check(const AttnArgs& a) {
     }
     if (a.hps < 0 || (a.hps && a.H % a.hps)) return "attention: H must be whole samples of hps heads";
     if ((long)((a.nq + 127) / 128) * a.H * std::max(1, a.splits) > 0x7fffffffL) return "attention: grid too large";
-    if (a.splits > 1 && (!a.part_o || !a.part_ml || (((uintptr_t)a.part_o | (uintptr_t)a.part_ml) % 16) ||
-                         a.part_tiles < 1 || (long)(a.splits - 1) * a.part_tiles * BKV >= a.nk || (long)a.splits * a.part_tiles * BKV < a.nk))
+    if (a.splits > 1 && (a.part_tiles < 2 || (a.part_tiles & 1) || (long)(a.splits - 1) * a.part_tiles * BKV >= a.nk || (long)a.splits * a.part_tiles * BKV < a.nk))
         return "attention: bad split of the keys";
+    if (a.splits > 1 && !a.all_parts && (!a.part_o || !a.part_ml || (((uintptr_t)a.part_o | (uintptr_t)a.part_ml) % 16)))
+        return "attention: no scratch for the parts of the keys";
+    if (a.all_parts && a.splits < 2) return "attention: no parts for a workgroup to have all of";
     if (a.even_state && (a.splits > 1 || !a.even_flags || ((uintptr_t)a.even_state % 16) || a.hd != 128 || (long)((a.nq + 255) / 256) * a.H <= 7 * 32))
         return "attention: launch cannot be dealt out by the kernel";
     // a sweep works off its first tile whatever its end: an empty piece would count one twice
@@ -614,7 +664,7 @@ const char* attn_check(const AttnArgs& a) {
 // 4; very long sweeps whose 7- and 8-wave grids need the same number of generations to 7; the rest to 8.
 // Heights 5 and 6 were built once and never won: three SIMDs share the work of four.
 static int waves_and_cost(const AttnArgs& a, double* cost) {
-    const int splits = std::max(1, a.splits);
+    const int splits = a.all_parts ? 1 : std::max(1, a.splits);          // workgroups over one query tile
     const double tiles = splits > 1 ? a.part_tiles : (double)((a.nk + BKV - 1) / BKV);
     auto items = [&](int nw) { return (long)((a.nq + 32 * nw - 1) / (32 * nw)) * a.H * splits; };
     auto generations = [](long n, long slots) { return (double)((n + slots - 1) / slots); };
@@ -633,24 +683,29 @@ static int waves_and_cost(const AttnArgs& a, double* cost) {
 }
 
 int attn_waves(const AttnArgs& a) {
+    if (a.all_parts && a.hd == 64) return 4;       // see attn_fwd_kernel
     double cost;
     return waves_and_cost(a, &cost);
 }
+
+// Key tiles of a part: an even number, so that every part begins in the same one of the two tile buffers.
+static int tiles_per_part(int tiles, int parts) { return parts > 1 ? ((tiles + parts - 1) / parts + 1) & ~1 : tiles; }
 
 // Parts the keys of a launch are cut into.  Few heads over a short sequence (a Ulysses rank's share at degree 4 or 8)
 // are a few dozen workgroups that each sweep all keys; cut into parts they fill the chip, at the price of writing the
 // partial results and merging them.  Estimated time in us for 128-wide heads: a tile takes a 4-wave workgroup 0.97 alone
 // on its CU and 1.7 beside another, the merge 10 us and one pass over the partial results at 4 TB/s (3 heads x 4608: 72 us
 // whole, 51 in two or four parts; 12 heads x 2640: 51 us whole, 58 in two).  A function of one sample's heads and lengths
-// only, so that a sample's result does not depend on the batch it is part of.
+// only, so that a sample's result does not depend on the batch it is part of; parts of at least 6 tiles (8 with 64-wide heads),
+// so that a batch that fills the chip, and whose workgroups have all parts, loses no more than a few per cent by joining them.
 int attn_splits(int heads, int nq, int nk, int hd) {
     const long items = (long)((nq + 127) / 128) * heads;
-    const int tiles = (nk + BKV - 1) / BKV;
+    const int tiles = (nk + BKV - 1) / BKV, least = hd == 64 ? 8 : 6;
     int best = 1;
     double best_us = 0;
-    for (int s = 1; s <= 8 && tiles >= 2 * s; ++s) {
-        const int per = (tiles + s - 1) / s;
-        if ((tiles + per - 1) / per != s) continue;
+    for (int s = 1; s <= 8; ++s) {
+        const int per = tiles_per_part(tiles, s);
+        if (s > 1 && (per < least || (tiles + per - 1) / per != s)) continue;
         const long wgs = items * s;
         if (s > 1 && wgs > 512) break;
         double us = (wgs <= 256 ? 0.97 * per : 1.7 * per * (double)((wgs + 511) / 512)) * (hd == 64 ? 0.55 : 1.0) + 3.0;
@@ -660,6 +715,24 @@ int attn_splits(int heads, int nq, int nk, int hd) {
     return best;
 }
 
+// Whether a workgroup has all parts of its queries, for the heads of all samples together: where the query tiles alone fill the
+// chip, the parts only cost (12 heads x 4608 x 128, four samples: 115 us in one sweep, 136 in two parts and their merge, 115 with
+// both in one workgroup).  Estimated in us, n = 4-wave workgroups per CU: a tile takes each CU 0.97 + 0.25 n up to one of them and
+// 0.25 + 0.97 n from there on with 128-wide heads, 0.45 + 0.48 n and at least 0.68 with 64-wide ones; joining a part costs
+// half a tile, the merge 6 us and a pass over the partial results at 4 TB/s.  (3 heads x 4608 for 1, 2, 3, 4, 8 samples, in parts /
+// in one workgroup: 55/74, 78/81, 126/108, 146/126, 286/248; 3 x 2640: 34/46, 44/47, -, 65/54, 119/95; 2 x 4696 x 64 for 1, 4, 16:
+// 29/51, 64/75, 210/199.)
+bool attn_all_parts(int heads, int nq, int nk, int hd, int splits) {
+    if (splits <= 1) return false;
+    const double tiles = (nk + BKV - 1) / BKV, items = (double)((nq + 127) / 128) * heads;
+    auto sweeps = [&](double wgs, double t) {
+        const double n = wgs / 256.0;
+        return t * (hd == 64 ? std::max(0.68, 0.45 + 0.48 * n) : n <= 1.0 ? 0.97 + 0.25 * n : 0.25 + 0.97 * n);
+    };
+    const double parts = sweeps(items * splits, tiles_per_part((int)tiles, splits)) + 6.0 + 4.0 * splits * (double)heads * nq * hd / 4e6;
+    return sweeps(items, tiles + 0.5 * (splits - 1)) < parts;
+}
+
 uint64_t attn_part_floats(int heads, int nq, int hd, int splits) {
     return splits > 1 ? (uint64_t)splits * heads * ((nq + 31) / 32) * 32 * (hd + 2) : 0;
 }
@@ -667,7 +740,7 @@ uint64_t attn_part_floats(int heads, int nq, int hd, int splits) {
 void attn_set_split(AttnArgs* a, int splits, float* scratch) {
     const int tiles = (a->nk + BKV - 1) / BKV;
     a->splits = std::max(1, splits);
-    a->part_tiles = (tiles + a->splits - 1) / a->splits;
+    a->part_tiles = tiles_per_part(tiles, a->splits);
     a->part_o = scratch;
     a->part_ml = scratch ? scratch + (uint64_t)a->splits * a->H * ((a->nq + 31) / 32) * 32 * a->hd : nullptr;
 }
@@ -726,7 +799,7 @@ hipError_t attn_launch(const AttnArgs& a, hipStream_t s) {
     if (a.even_state) return launch_even(a, s);
     const int nw = attn_waves(a);
     const hipError_t e = a.hd == 128 ? launch_nw<128>(nw, a, s) : launch_nw<64>(nw, a, s);
-    if (e != hipSuccess || a.splits == 1) return e;
+    if (e != hipSuccess || a.splits <= 1 || a.all_parts) return e;
     const dim3 grid((a.H * ((a.nq + 31) / 32) + 3) / 4);
     if (a.hd == 128) hipLaunchKernelGGL(attn_merge_kernel<128>, grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL(attn_merge_kernel<64>, grid, dim3(256), 0, s, a);

@@ -128,11 +128,13 @@ inline int batch_of(const cf_model_desc& m) { return m.batch > 0 ? m.batch : 1; 
 void plan_cuts(Plan* p, const cf_model_desc& m) {
     const int P = m.sp_degree, hl = m.n_heads / P, nl = m.n_total / P, B = batch_of(m), hd = m.head_dim;
     p->self_splits = attn_splits(hl, m.n_total, m.n_total, hd);
+    p->self_all_parts = attn_all_parts(B * hl, m.n_total, m.n_total, hd, p->self_splits);
     p->self_deal = attn_deal(B * hl, m.n_total, m.n_total, hd, p->self_splits);
-    uint64_t part = std::max(attn_deal_floats(p->self_deal), attn_part_floats(B * hl, m.n_total, hd, p->self_splits));
+    uint64_t part = std::max(attn_deal_floats(p->self_deal), p->self_all_parts ? 0 : attn_part_floats(B * hl, m.n_total, hd, p->self_splits));
     if (p->kind == CF_DIT_CROSS) {
         p->cross_splits = attn_splits(m.n_heads, nl, m.l_ctx, hd);
-        part = std::max(part, attn_part_floats(B * m.n_heads, nl, hd, p->cross_splits));
+        p->cross_all_parts = attn_all_parts(B * m.n_heads, nl, m.l_ctx, hd, p->cross_splits);
+        if (!p->cross_all_parts) part = std::max(part, attn_part_floats(B * m.n_heads, nl, hd, p->cross_splits));
     }
     // residual layers: the two streams of a double-stream block, which normally share a launch, are cut alike
     const int tl = p->kind == CF_DOUBLE_STREAM ? m.n_txt_total / P : 0;
@@ -738,6 +740,7 @@ int run_joint_attention(Fwd& F, const RelayoutArgs* parts, int n_parts, const At
         a.send = (bf16*)io->send_attn; a.send_bs = (long)peer_bs;
     }
     attn_set_split(&a, c->P(F.block).self_splits, F.ws.part);
+    a.all_parts = c->P(F.block).self_all_parts;
     attn_set_deal(&a, c->P(F.block).self_deal, F.ws.part, F.ws.flags);
     if (const char* msg = attn_check(a)) return cf_fail(c, CF_ERR_ARG, "%s", msg);
     {
@@ -1001,6 +1004,7 @@ int cf_plan_block_attention(int32_t heads, int32_t batch, int32_t nq, int32_t nk
     a.H = heads * batch; a.nq = nq; a.nk = nk; a.hd = head_dim;
     attn_set_split(&a, attn_splits(heads, nq, nk, head_dim), nullptr);
     plan->parts = a.splits;
+    plan->all_parts = a.all_parts = attn_all_parts(a.H, nq, nk, head_dim, a.splits);
     plan->deal = attn_deal(a.H, nq, nk, head_dim, a.splits);
     plan->waves = plan->deal ? 8 : attn_waves(a);
     return CF_OK;
@@ -1417,7 +1421,7 @@ int cf_op_attention(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, ui
 }
 
 int cf_op_attention_form(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O, int32_t H, int32_t nq, int32_t nk,
-                         int32_t nk_pad, int32_t hd, int32_t parts, int32_t deal, int32_t no_wait, void* scratch, uint64_t scratch_bytes,
+                         int32_t nk_pad, int32_t hd, int32_t parts, int32_t all_parts, int32_t deal, int32_t no_wait, void* scratch, uint64_t scratch_bytes,
                          void* stream) {
     AttnArgs a{};
     a.Q = (const bf16*)Q; a.K = (const bf16*)K; a.Vt = (const bf16*)Vt; a.O = (bf16*)O;
@@ -1425,9 +1429,10 @@ int cf_op_attention_form(const uint16_t* Q, const uint16_t* K, const uint16_t* V
     if (parts < 1 || parts > 64 || deal < 0 || deal > 2 || (parts > 1 && deal)) return cf_fail(nullptr, CF_ERR_ARG, "attention: keys in up to 64 parts, or dealt out as 1 or 2");
     if (const char* msg = attn_check(a)) return cf_fail(nullptr, CF_ERR_ARG, "%s", msg);       // the sizes, before they are computed with
     a.scale = 1.0f / sqrtf((float)hd);
-    const uint64_t need = 4 * (deal ? ATTN_FLAGS + attn_deal_floats(deal) : attn_part_floats(H, nq, hd, parts));
+    const uint64_t need = 4 * (deal ? ATTN_FLAGS + attn_deal_floats(deal) : (all_parts ? 0 : attn_part_floats(H, nq, hd, parts)));
     if (need && (!scratch || scratch_bytes < need)) return cf_fail(nullptr, CF_ERR_ARG, "attention: this form needs %llu bytes of scratch", (unsigned long long)need);
     attn_set_split(&a, parts, (float*)scratch);
+    a.all_parts = all_parts != 0;
     attn_set_deal(&a, deal, (float*)scratch + ATTN_FLAGS, (uint32_t*)scratch);
     a.even_wait = !no_wait;
     if (const char* msg = attn_check(a)) return cf_fail(nullptr, CF_ERR_ARG, "%s", msg);
@@ -1591,6 +1596,7 @@ int fwd_dit(Fwd& F) {
         a.Q = w.cQ; a.K = w.cK; a.Vt = w.cVt; a.O = w.c; a.o_hs = hd; a.o_qs = d; a.o_bs = dense;
         a.H = B * H; a.hps = H; a.nq = nl; a.nk = lc; a.nk_pad = lpad; a.hd = hd; a.scale = 1.0f / sqrtf((float)hd);
         attn_set_split(&a, c->P(F.block).cross_splits, w.part);
+        a.all_parts = c->P(F.block).cross_all_parts;
         if (const char* msg = attn_check(a)) return cf_fail(c, CF_ERR_ARG, "%s", msg);
         ProfScope ps(c, F.s, K_CROSS_ATTN, 4.0 * B * H * (double)nl * lc * hd, 0);
         CF_HIP(c, attn_launch(a, F.s));

@@ -260,8 +260,11 @@ def test_block_attention_plans():
     assert plan(12, 1, 4608, 4608, 128) == (8, 1, 0)
     assert plan(12, 1, 27280, 27280, 128) == (8, 1, 1)
     assert plan(12, 1, 119056, 119056, 128) == (8, 1, 2)
-    for batch in (1, 4):
-        assert B.cf_plan_block_attention(3, batch, 4608, 4608, 128).parts > 1
+    for shape in ((3, 4608, 128), (3, 2640, 128), (1, 4696, 128), (1, 2264, 64)):
+        one = B.cf_plan_block_attention(shape[0], 1, shape[1], shape[1], shape[2])
+        many = B.cf_plan_block_attention(shape[0], 32, shape[1], shape[1], shape[2])
+        # as many parts (the bits depend on them), but a batch that fills the chip does not pay for workgroups of their own
+        assert many.parts == one.parts > 1 and many.all_parts and not one.all_parts, shape
     for bad in ((0, 1, 10, 10, 128), (1, 0, 10, 10, 128), (1, 1, 0, 10, 128), (1, 1, 10, 0, 128), (1, 1, 10, 10, 96), (1 << 20, 1 << 20, 10, 10, 64)):
         with pytest.raises(B.ChunkflowError):
             B.cf_plan_block_attention(*bad)
@@ -269,6 +272,6 @@ def test_block_attention_plans():
     for H, nq, nk, hd, parts, deal, nbytes in ((1, 64, 512, 128, 0, 0, 1 << 30), (1, 64, 512, 128, 65, 0, 1 << 30), (1, 64, 512, 128, 9, 0, 1 << 30),
                                                (1, 64, 512, 128, 2, 1, 1 << 30), (1, 64, 512, 128, 1, 3, 1 << 30), (1, 64, 512, 128, 2, 0, 1000),
                                                (12, 64, 512, 128, 1, 1, 1 << 30), (12, 4800, 512, 64, 1, 1, 1 << 30), (12, 4800, 512, 128, 1, 1, 4096), (12, 4800, 192, 128, 1, 2, 1 << 30)):
-        assert lib.cf_op_attention_form(p, p, p, p, H, nq, nk, nk, hd, parts, deal, 0, p, nbytes, None) == B.CF_ERR_ARG
+        assert lib.cf_op_attention_form(p, p, p, p, H, nq, nk, nk, hd, parts, 0, deal, 0, p, nbytes, None) == B.CF_ERR_ARG
     # a drawn sweep is cut in four pieces of at least a tile, however many there are
     assert all(plan(48, b, nq, nk, 128)[2] != 2 for b in (1, 16, 256) for nq in (4608, 119056) for nk in (1, 64, 128, 192))

@@ -30,13 +30,13 @@ def whole(ops):
     return host_bits(o)
 
 
-def form(ops, parts=1, deal=0, no_wait=False):
+def form(ops, parts=1, all_parts=False, deal=0, no_wait=False):
     q, k, vt, H, nq, nk, pad, hd = ops
     floats = parts * H * ((nq + 31) // 32) * 32 * (hd + 2) if parts > 1 else 24 * 32 * 512 * 66
     scratch = torch.full((FLAG_BYTES // 4 + floats,), float("nan"), device=DEV)
     scratch[:FLAG_BYTES // 4] = 0.0
     o = torch.zeros((H, nq, hd), dtype=torch.int16, device=DEV)
-    B.cf_op_attention_form(q, k, vt, o, H, nq, nk, pad, hd, scratch, parts, deal, no_wait)
+    B.cf_op_attention_form(q, k, vt, o, H, nq, nk, pad, hd, None if all_parts else scratch, parts, all_parts, deal, no_wait)
     torch.cuda.synchronize()
     return host_bits(o)
 
@@ -52,7 +52,7 @@ def reference(values):
 
 
 # parts that end inside, at and one key past a tile; a last part of one ragged tile; workgroups of 4, 7 and 8 waves
-@pytest.mark.parametrize("H,nq,nk,hd,parts", [(1, 1888, 1888, 64, 5), (2, 77, 2265, 64, 6), (3, 300, 513, 64, 3), (1, 33, 449, 128, 8),
+@pytest.mark.parametrize("H,nq,nk,hd,parts", [(1, 1888, 1888, 64, 5), (2, 77, 2265, 64, 6), (3, 300, 513, 64, 3), (1, 33, 449, 128, 4),
                                               (3, 1000, 1153, 128, 4), (2, 4500, 640, 128, 2), (8, 3500, 9000, 64, 2),
                                               (1, 27000, 17000, 128, 2), (1, 27000, 34000, 128, 2), (1, 27000, 34000, 64, 2)])
 @pytest.mark.parametrize("sharp", [1.0, 24.0])
@@ -61,6 +61,11 @@ def test_keys_in_parts(H, nq, nk, hd, parts, sharp):
     q, k, v = (rng.normal(size=(H, n, hd)) for n in (nq, nk, nk))
     ops, values = operands(q * np.sqrt(sharp), k * np.sqrt(sharp), v)
     got = bits_to_f64(form(ops, parts=parts))
+    if sharp == 1.0:      # a sweep repeated for scores out of range is a workgroup's, and the two forms may differ in its height
+        assert np.array_equal(form(ops, parts=parts, all_parts=True), form(ops, parts=parts))
+    else:
+        one = bits_to_f64(form(ops, parts=parts, all_parts=True))
+        assert rel_l2(one, got) < 3e-3
     rows = np.sort(rng.choice(nq, min(nq, 600), replace=False))
     ref = reference((values[0][:, rows], values[1], values[2]))
     print(f"rel_l2={rel_l2(got[:, rows], ref):.3e} max_abs={max_abs(got[:, rows], ref):.3e}", flush=True)

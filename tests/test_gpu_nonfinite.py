@@ -42,7 +42,7 @@ def test_activation_at_the_ends_of_the_range(erf):
 # the first tile of the sequence, of each part in turn, of a part that holds no other key, the last (ragged) tile, and all but one
 @pytest.mark.parametrize("hd", [64, 128])
 @pytest.mark.parametrize("parts", [1, 2, 3, 5])
-@pytest.mark.parametrize("lo,hi", [(0, 64), (0, 192), (192, 256), (256, 384), (320, 384), (512, 577), (64, 577)])
+@pytest.mark.parametrize("lo,hi", [(0, 64), (0, 192), (192, 256), (256, 384), (320, 384), (384, 448), (512, 577), (64, 577)])
 def test_tiles_of_scores_of_minus_infinity(hd, parts, lo, hi):
     """Keys whose scores are all -inf have a weight of zero, wherever they lie."""
     H, nq, nk = 2, 300, 577
@@ -55,5 +55,7 @@ def test_tiles_of_scores_of_minus_infinity(hd, parts, lo, hi):
     values[1][:, lo:hi, 0] = -np.inf
     ref = reference(values)
     assert np.isfinite(ref).all() and np.isfinite(got).all()
+    if parts > 1:
+        assert np.array_equal(form(ops, parts=parts, all_parts=True), form(ops, parts=parts))
     print(f"rel_l2={rel_l2(got, ref):.3e}", flush=True)
     assert rel_l2(got, ref) < 6e-3 and max_abs(got, ref) < 2e-2 * max(1.0, np.abs(ref).max())

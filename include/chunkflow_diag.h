@@ -39,6 +39,16 @@ int cf_plan_block_attention(int32_t heads, int32_t batch, int32_t nq, int32_t nk
  * CF_ERR_ARG: non-positive sizes, NULL result. */
 int cf_plan_linear(int32_t m_rows, int32_t n_features, int32_t* tile_rows);
 
+/* Host-only view of how a block launches a linear layer of k input features over `rows` tokens of each of `batch`
+ * samples (rows2 > 0: with a second layer over rows2 tokens in the same launch, as the streams of a double-stream block): its
+ * tile of tokens x features exactly.  residual: with the gated fp32 residual, whose sum over k may be cut into `parts` parts
+ * (a matter of one sample alone, and the bits with it); the tile is then that of the parts, and last_tile_* is not zero where
+ * the last part has a launch of its own, which puts the sum together.  No GPU is touched. */
+typedef struct cf_linear_plan {
+    int32_t tile_tokens, tile_features, parts, last_tile_tokens, last_tile_features;
+} cf_linear_plan;
+int cf_plan_block_linear(int32_t rows, int32_t rows2, int32_t batch, int32_t n_features, int32_t k, int32_t residual, cf_linear_plan* plan);
+
 /* ---- single kernels.  `blob` holds W (and bias) at the given byte offsets. */
 /* out[m,n] = A[m,:] . W[n,:] + bias[n]; features < n_split stored bf16 to out0[m*ld0+n], the rest
  * through GELU (tanh form, or erf form if gelu_erf) to out1[m*ld1 + n - n_split] (App. B linear layers). */
@@ -49,6 +59,11 @@ int cf_op_linear(const uint16_t* A, int32_t lda, const void* blob, uint64_t w_of
 int cf_op_linear_residual(const uint16_t* A, int32_t lda, const void* blob, uint64_t w_off, int64_t bias_off,
                           int32_t M, int32_t N, int32_t K, const float* resid, const float* gate,
                           float* y, void* stream);
+/* The same on tiles of the caller's choice (those of cf_plan_block_linear), with the sum over K in `parts` parts, put together by
+ * a kernel of its own or (last_joins) by the launch of the last part.  scratch: parts * M * N floats, 16-byte aligned. */
+int cf_op_linear_residual_form(const uint16_t* A, int32_t lda, const void* blob, uint64_t w_off, int64_t bias_off, int32_t M, int32_t N,
+                               int32_t K, const float* resid, const float* gate, float* y, int32_t tile_tokens, int32_t tile_features,
+                               int32_t parts, int32_t last_joins, void* scratch, uint64_t scratch_bytes, void* stream);
 /* O[h,q,:] = softmax(Q K^T / sqrt(hd)) V; Q [H,nq,hd], K [H,nk,hd], Vt [H,hd,nk_pad] (pad zero),
  * O [H,nq,hd] (App. B attention term, no mask). */
 int cf_op_attention(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O,

@@ -67,6 +67,10 @@ class cf_attention_plan(C.Structure):
     _fields_ = [("waves", C.c_int32), ("parts", C.c_int32), ("all_parts", C.c_int32), ("deal", C.c_int32)]
 
 
+class cf_linear_plan(C.Structure):
+    _fields_ = [(n, C.c_int32) for n in ("tile_tokens", "tile_features", "parts", "last_tile_tokens", "last_tile_features")]
+
+
 class cf_tune_choice(C.Structure):
     _fields_ = [("chunk_bytes", C.c_uint64), ("r", C.c_double), ("feasible", C.c_int32), ("sim", cf_sim_result)]
 
@@ -80,7 +84,7 @@ CORE_EXPORTS = ["cf_create", "cf_destroy", "cf_last_error", "cf_blob_bytes", "cf
                 "cf_stats_reset", "cf_set_profiling", "cf_set_adaptive_waits", "cf_kernel_times", "cf_kernel_times_reset",
                 "cf_sync", "cf_op_checksum", "cf_op_checksum_noalloc"]
 #: what include/chunkflow_diag.h declares: single-kernel hooks, planner views, the matrix-core rate probe
-DIAG_EXPORTS = ["cf_plan_attention", "cf_plan_block_attention", "cf_plan_linear", "cf_op_linear", "cf_op_linear_residual",
+DIAG_EXPORTS = ["cf_plan_attention", "cf_plan_block_attention", "cf_plan_linear", "cf_plan_block_linear", "cf_op_linear", "cf_op_linear_residual", "cf_op_linear_residual_form",
                 "cf_op_attention", "cf_op_attention_form", "cf_op_ln_modulate", "cf_op_modvec", "cf_op_mfma_rate", "cf_op_mix_rate"]
 EXPORTS = CORE_EXPORTS + DIAG_EXPORTS
 
@@ -117,6 +121,7 @@ def lib() -> C.CDLL:
         _lib.cf_plan_attention.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)]
         _lib.cf_plan_block_attention.argtypes = [C.c_int32] * 5 + [C.POINTER(cf_attention_plan)]
         _lib.cf_plan_linear.argtypes = [C.c_int32, C.c_int32, C.POINTER(C.c_int32)]
+        _lib.cf_plan_block_linear.argtypes = [C.c_int32] * 6 + [C.POINTER(cf_linear_plan)]
         _lib.cf_register_block.argtypes = [C.c_void_p, C.c_int32, C.c_void_p, C.c_uint64]
         _lib.cf_set_block_kinds.argtypes = [C.c_void_p, C.c_void_p, C.c_int32]
         _lib.cf_simulate.argtypes = [C.c_void_p, C.c_double, C.POINTER(cf_machine_t), C.POINTER(cf_sim_result)]
@@ -138,6 +143,9 @@ def lib() -> C.CDLL:
                                       C.c_int32, C.c_int32, C.c_void_p]
         _lib.cf_op_linear_residual.argtypes = [C.c_void_p, C.c_int32, C.c_void_p, C.c_uint64, C.c_int64, C.c_int32,
                                                C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]
+        _lib.cf_op_linear_residual_form.argtypes = [C.c_void_p, C.c_int32, C.c_void_p, C.c_uint64, C.c_int64, C.c_int32, C.c_int32, C.c_int32,
+                                                    C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_int32,
+                                                    C.c_void_p, C.c_uint64, C.c_void_p]
         _lib.cf_op_attention.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32,
                                          C.c_int32, C.c_int32, C.c_int32, C.c_void_p]
         _lib.cf_op_attention_form.argtypes = [C.c_void_p] * 4 + [C.c_int32] * 9 + [C.c_void_p, C.c_uint64, C.c_void_p]
@@ -391,6 +399,13 @@ def cf_plan_linear(m_rows: int, n_features: int) -> int:
     return out.value
 
 
+def cf_plan_block_linear(rows: int, n_features: int, k: int, residual: bool, rows2: int = 0, batch: int = 1) -> cf_linear_plan:
+    """How a block launches a linear layer of this shape (host arithmetic only)."""
+    out = cf_linear_plan()
+    _check(lib().cf_plan_block_linear(rows, rows2, batch, n_features, k, int(residual), C.byref(out)))
+    return out
+
+
 def cf_op_mfma_rate(iters: int, random_operands: bool, out, stream=None) -> None:
     _check(lib().cf_op_mfma_rate(iters, int(random_operands), _ptr(out), _stream_handle(stream)))
 
@@ -402,6 +417,13 @@ def cf_op_mix_rate(iters: int, waves: int, reads_per_16: int, valu_per_mfma: int
 def cf_op_linear_residual(A, blob, w_off, bias_off, M, N, K, resid, gate, y, lda=None, stream=None):
     _check(lib().cf_op_linear_residual(_ptr(A), K if lda is None else lda, _ptr(blob), w_off, bias_off, M, N, K,
                                        _ptr(resid), _ptr(gate), _ptr(y), _stream_handle(stream)))
+
+
+def cf_op_linear_residual_form(A, blob, w_off, bias_off, M, N, K, resid, gate, y, tile, parts=1, last_joins=False, scratch=None, stream=None):
+    """cf_op_linear_residual on the given (tokens, features) tile, its sum in parts."""
+    _check(lib().cf_op_linear_residual_form(_ptr(A), K, _ptr(blob), w_off, bias_off, M, N, K, _ptr(resid), _ptr(gate), _ptr(y), tile[0], tile[1],
+                                            parts, int(last_joins), _ptr(scratch),
+                                            0 if scratch is None else scratch.numel() * scratch.element_size(), _stream_handle(stream)))
 
 
 def cf_op_attention(Q, K, Vt, O, H, nq, nk, nk_pad, hd, stream=None):

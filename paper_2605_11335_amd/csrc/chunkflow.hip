@@ -369,7 +369,7 @@ hipEvent_t prof_event(cf_ctx* c) {
     return e;
 }
 
-// kid + K_COUNT * variant; variant = the GEMM's tile shape (gemm_tile)
+// kid + K_COUNT * variant; variant = the GEMM's tile shape (GemmPlan::tile)
 struct ProfScope {
     cf_ctx* c; hipStream_t s; ProfEntry pe; bool on;
     ProfScope(cf_ctx* c_, hipStream_t s_, int kid, double flops, double bytes, int variant = 0)
@@ -589,7 +589,7 @@ int run_linear(Fwd& F, int kid, const std::string& wname, const std::string& bna
         p.n0 = r0;
         p.n1 = r1;
         if (const char* msg = gemm_check(p)) return cf_fail(F.c, CF_ERR_ARG, "%s (%s)", msg, wname.c_str());
-        ProfScope ps(F.c, F.s, kid, 2.0 * p.M * (r1 - r0) * p.K, 0, gemm_tile(p));
+        ProfScope ps(F.c, F.s, kid, 2.0 * p.M * (r1 - r0) * p.K, 0, gemm_plan(p, nullptr).tile);
         CF_HIP(F.c, gemm_launch(p, F.s));
         return CF_OK;
     });
@@ -624,14 +624,13 @@ int run_linear_pair(Fwd& F, int kid, const std::string (&wname)[2], const std::s
             gemm_set_split(&g[i], sum_splits(F, g[i].K),
                            F.ws.part + (i ? (size_t)g[0].ksplits * g[0].M * g[0].N : 0));
     }
-    const int tile = pair ? gemm_pair_tile(g[0], g[1]) : -1;
-    if (tile < 0) {
+    if (!pair || !gemm_can_pair(g[0], g[1])) {
         CF_TRY(run_linear(F, kid, wname[0], bname[0], g_in[0]));
         return run_linear(F, kid, wname[1], bname[1], g_in[1]);
     }
     for (int i = 0; i < 2; ++i)
         if (const char* msg = gemm_check(g[i])) return cf_fail(c, CF_ERR_ARG, "%s (%s)", msg, wname[i].c_str());
-    ProfScope ps(c, F.s, kid, 2.0 * g[0].M * g[0].N * g[0].K + 2.0 * g[1].M * g[1].N * g[1].K, 0, tile);
+    ProfScope ps(c, F.s, kid, 2.0 * g[0].M * g[0].N * g[0].K + 2.0 * g[1].M * g[1].N * g[1].K, 0, gemm_plan(g[0], &g[1]).tile);
     CF_HIP(c, gemm_launch_pair(g[0], g[1], F.s));
     return CF_OK;
 }
@@ -1016,8 +1015,25 @@ int cf_plan_linear(int32_t m_rows, int32_t n_features, int32_t* tile_rows) {
     GemmArgs g{};
     g.M = m_rows; g.n0 = 0; g.n1 = n_features; g.N = n_features;
     g.K = 3072;                          // the widths this is asked for; the choice hardly depends on it
-    const int t = gemm_tile(g);
+    const int t = gemm_plan(g, nullptr).tile;
     *tile_rows = t == GEMM_256x256 || t == GEMM_192x256 ? 256 : 128;
+    return CF_OK;
+}
+
+int cf_plan_block_linear(int32_t rows, int32_t rows2, int32_t batch, int32_t n_features, int32_t k, int32_t residual, cf_linear_plan* plan) {
+    if (rows <= 0 || rows2 < 0 || batch <= 0 || ((int64_t)rows + rows2) * batch > 0x7fffffff || n_features <= 0 || k <= 0 || !plan)
+        return cf_fail(nullptr, CF_ERR_ARG, "cf_plan_block_linear: positive sizes and a result pointer are required");
+    GemmArgs g[2] = {};
+    const int parts = residual ? gemm_splits(rows, rows2, n_features, k) : 1;
+    for (int i = 0; i < 2; ++i) {
+        g[i].M = (i ? rows2 : rows) * batch; g[i].N = g[i].n1 = n_features; g[i].K = k;
+        gemm_set_split(&g[i], parts, nullptr);
+    }
+    const GemmPlan p = gemm_plan(g[0], rows2 ? &g[1] : nullptr);
+    plan->parts = g[0].ksplits;
+    gemm_tile_shape(p.tile, &plan->tile_tokens, &plan->tile_features);
+    plan->last_tile_tokens = plan->last_tile_features = 0;
+    if (p.last >= 0) gemm_tile_shape(p.last, &plan->last_tile_tokens, &plan->last_tile_features);
     return CF_OK;
 }
 
@@ -1406,6 +1422,30 @@ int cf_op_linear_residual(const uint16_t* A, int32_t lda, const void* blob, uint
     if (const char* msg = gemm_check(g)) return cf_fail(nullptr, CF_ERR_ARG, "%s", msg);
     hipError_t e = gemm_launch(g, (hipStream_t)stream);
     return e == hipSuccess ? CF_OK : cf_fail(nullptr, CF_ERR_HIP, "gemm launch: %s", hipGetErrorString(e));
+}
+
+int cf_op_linear_residual_form(const uint16_t* A, int32_t lda, const void* blob, uint64_t w_off, int64_t bias_off, int32_t M, int32_t N,
+                               int32_t K, const float* resid, const float* gate, float* y, int32_t tile_tokens, int32_t tile_features,
+                               int32_t parts, int32_t last_joins, void* scratch, uint64_t scratch_bytes, void* stream) {
+    if (!A || !blob) return cf_fail(nullptr, CF_ERR_ARG, "null operand");
+    GemmArgs g{};
+    g.A = (const bf16*)A; g.lda = lda; g.W = flat_view(blob); g.w_off = w_off;
+    g.has_bias = bias_off >= 0; g.bias_off = bias_off >= 0 ? (uint64_t)bias_off : 0;
+    g.M = M; g.N = N; g.K = K; g.n0 = 0; g.n1 = N; g.epi = EPI_GATE_RESID;
+    g.resid = resid; g.gate = gate; g.y = y; g.ldy = N;
+    if (const char* msg = gemm_check(g)) return cf_fail(nullptr, CF_ERR_ARG, "%s", msg);
+    int tile = 0, tokens = 0, features = 0;
+    for (; tile < GEMM_TILES; ++tile) {
+        gemm_tile_shape(tile, &tokens, &features);
+        if (tokens == tile_tokens && features == tile_features) break;
+    }
+    if (tile == GEMM_TILES) return cf_fail(nullptr, CF_ERR_ARG, "linear: no tile of %d tokens x %d features", tile_tokens, tile_features);
+    if (parts < 1 || parts > K / 64) return cf_fail(nullptr, CF_ERR_ARG, "linear: 1 to K / 64 parts");
+    gemm_set_split(&g, parts, (float*)scratch);
+    if (g.ksplits > 1 && (!scratch || scratch_bytes < 4ull * g.ksplits * M * N)) return cf_fail(nullptr, CF_ERR_ARG, "linear: too little scratch for the parts");
+    if (const char* msg = gemm_check(g)) return cf_fail(nullptr, CF_ERR_ARG, "%s", msg);
+    hipError_t e = gemm_launch_as(GemmPlan{tile, g.ksplits > 1 && last_joins ? tile : -1}, g, (hipStream_t)stream);
+    return e == hipSuccess ? CF_OK : cf_fail(nullptr, CF_ERR_HIP, "linear launch: %s", hipGetErrorString(e));
 }
 
 int cf_op_attention(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O, int32_t H, int32_t nq,

@@ -81,17 +81,20 @@ double tile_time(const TileCost& t, long tiles, int K) {
     }
     return us;
 }
-int best_tile(const GemmArgs* const (&g)[2], double* time = nullptr) {
+// What a launch covers of a cut sum: all its parts, all but the last, the last
+enum Share { ALL_OF_IT, BEFORE_LAST, LAST };
+int best_tile(const GemmArgs* const (&g)[2], Share share = ALL_OF_IT, double* time = nullptr) {
     int best = -1;
     double best_us = 0;
     for (int i = 0; i < GEMM_TILES; ++i) {
-        if (i == GEMM_256x256 && g[1] && g[1]->ksplits > 1) continue;        // not built: registers
+        if (i == GEMM_256x256 && g[1] && g[1]->ksplits > 1 && share != LAST) continue;        // not built: registers
         const TileCost& t = kTileCost[i];
         long tiles = 0;
         int K = 0;                       // the longest walk
         for (const GemmArgs* p : g)
             if (p) {
-                tiles += (long)((p->M + t.bm - 1) / t.bm) * ((p->n1 - p->n0 + t.bn - 1) / t.bn) * std::max(1, p->ksplits);
+                const int parts = p->ksplits <= 1 || share == LAST ? 1 : share == BEFORE_LAST ? p->ksplits - 1 : p->ksplits;
+                tiles += (long)((p->M + t.bm - 1) / t.bm) * ((p->n1 - p->n0 + t.bn - 1) / t.bn) * parts;
                 K = std::max(K, p->ksplits > 1 ? p->part_slabs * 64 : p->K);
             }
         const double us = tile_time(t, tiles, K);
@@ -102,7 +105,25 @@ int best_tile(const GemmArgs* const (&g)[2], double* time = nullptr) {
 }
 }  // namespace
 
-int gemm_tile(const GemmArgs& g) { return best_tile({&g, nullptr}); }
+// How a cut sum is put together: by a kernel of its own that reads all parts, or by the launch of its last part, which
+// follows that of the others and reads those alone: a pass over a partial result written and read less, a launch of workgroups
+// that may fill the chip badly more.  The passes run at 3.5 TB/s.  It pays where a batch fills the chip (9216 tokens x 3072 x 15360
+// in two parts: 778 us put together by the kernel, 700 by the last part; 4608 tokens: 373 and 350; 576 tokens: 78 and 106).
+GemmPlan gemm_plan(const GemmArgs& g, const GemmArgs* second) {
+    const GemmArgs* const both[2] = {&g, second};
+    double all, before, last, bytes = 0;
+    const GemmPlan one = {best_tile(both, ALL_OF_IT, &all), -1};
+    if (g.ksplits <= 1) return one;
+    const GemmPlan two = {best_tile(both, BEFORE_LAST, &before), best_tile(both, LAST, &last)};
+    for (const GemmArgs* p : both)
+        if (p) bytes += 4.0 * p->M * (p->n1 - p->n0);
+    return before + last + 3.0 + (g.ksplits + 1) * bytes / 3.5e6 < all + 6.0 + (g.ksplits + 2) * bytes / 3.5e6 ? two : one;
+}
+
+void gemm_tile_shape(int tile, int* tokens, int* features) {
+    *tokens = kTileCost[tile].bm;
+    *features = kTileCost[tile].bn;
+}
 
 // Parts K is cut into.  A layer with few outputs and a long sum (the MLP-out layers of a short sequence or of a rank at
 // degree 4 or 8) has few tiles whatever their shape: cut, its workgroups multiply, each with a share of the walk.  The price
@@ -110,6 +131,8 @@ int gemm_tile(const GemmArgs& g) { return best_tile({&g, nullptr}); }
 // 6 us and two passes over them at 4 TB/s.  Taken where the estimate promises a twentieth (2304 x 3072 x 15360 in two parts:
 // a Flux-like single-stream block 660 -> 645 us).  A function of one sample's tokens and
 // the whole layer only, so that results depend neither on the batch nor on the panels a streamed layer is cut into.
+// At most three parts, because a batch that fills the chip pays for each and gains nothing (576 tokens x 3072 x 15360 per sample,
+// one sample / eight of them in 1, 2, 3, 4, 5 parts: 103/347, 79/363, 83/395, 69/442, 72/485 us).
 int gemm_splits(int rows, int rows2, int N, int K) {
     GemmArgs g{}, g2{};
     g.M = rows; g.N = g.n1 = N; g.K = K;
@@ -118,12 +141,12 @@ int gemm_splits(int rows, int rows2, int N, int K) {
     const int slabs = K / 64;
     int best = 1;
     double best_us = 0;
-    for (int parts = 1; parts <= 8 && slabs >= 8 * parts; ++parts) {
+    for (int parts = 1; parts <= 3 && slabs >= 8 * parts; ++parts) {
         gemm_set_split(&g, parts, nullptr);
         if (g.ksplits != parts) continue;
         gemm_set_split(&g2, parts, nullptr);
         double us;
-        best_tile({&g, rows2 > 0 ? &g2 : nullptr}, &us);
+        best_tile({&g, rows2 > 0 ? &g2 : nullptr}, ALL_OF_IT, &us);
         if (parts > 1) us += 6.0 + 2.0 * 4.0 * parts * (double)(rows + rows2) * N / 4e6;
         if (parts == 1 || us < (best == 1 ? 0.95 : 1.0) * best_us) best = parts, best_us = us;
     }
@@ -306,13 +329,17 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(ReduceArgs a) {
 }
 
 // one or two layers; those with a cut sum go through their parts
-hipError_t dispatch(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s) {
-    // the erf form of the activation costs some forty VALU operations per element: it gets kernels
+hipError_t dispatch(const GemmPlan& plan, const GemmArgs& g, const GemmArgs* second, hipStream_t s) {
+    // the erf form of the activation is some seventeen VALU operations per element against the tanh form's four: it gets kernels
     // of its own rather than a run-time choice inside the tanh one
-    if (g.epi != EPI_GATE_RESID) return g.act_erf ? gemm_launch_split_gelu_erf(tile, g, second, s) : gemm_launch_split_gelu(tile, g, second, s);
-    if (g.ksplits <= 1) return gemm_launch_gate_resid(tile, g, second, s);
-    const hipError_t e = gemm_launch_partial(tile, g, second, s);
+    if (g.epi != EPI_GATE_RESID) return g.act_erf ? gemm_launch_split_gelu_erf(plan.tile, g, second, s) : gemm_launch_split_gelu(plan.tile, g, second, s);
+    if (g.ksplits <= 1) return gemm_launch_gate_resid(plan.tile, g, second, s);
+    GemmArgs parts[2] = {g, second ? *second : g};
+    if (plan.last >= 0)
+        for (GemmArgs& p : parts) --p.ksplits;
+    const hipError_t e = gemm_launch_partial(plan.tile, parts[0], second ? &parts[1] : nullptr, s);
     if (e != hipSuccess) return e;
+    if (plan.last >= 0) return gemm_launch_last_part(plan.last, g, second, s);
     auto blocks = [](const GemmArgs& p) { return (uint32_t)(((long)p.M * ((p.n1 - p.n0) / 4) + 255) / 256); };
     ReduceArgs a{};
     a.g[0] = g;
@@ -323,16 +350,14 @@ hipError_t dispatch(int tile, const GemmArgs& g, const GemmArgs* second, hipStre
 }
 }  // namespace
 
-hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) { return dispatch(gemm_tile(g), g, nullptr, s); }
+hipError_t gemm_launch_as(const GemmPlan& plan, const GemmArgs& g, hipStream_t s) { return dispatch(plan, g, nullptr, s); }
+hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) { return gemm_launch_as(gemm_plan(g, nullptr), g, s); }
 
-// Tile shape both problems of a pair run with, or -1 if they cannot share a launch (different epilogues, or only one with
-// its sum in parts).
-int gemm_pair_tile(const GemmArgs& g0, const GemmArgs& g1) {
-    if (g0.epi != g1.epi || g0.act_erf != g1.act_erf || (g0.ksplits > 1) != (g1.ksplits > 1)) return -1;
-    return best_tile({&g0, &g1});
+// two layers share a launch if they have one epilogue and both or neither have their sum in parts
+bool gemm_can_pair(const GemmArgs& g0, const GemmArgs& g1) {
+    return g0.epi == g1.epi && g0.act_erf == g1.act_erf && (g0.ksplits > 1) == (g1.ksplits > 1);
 }
 
 hipError_t gemm_launch_pair(const GemmArgs& g0, const GemmArgs& g1, hipStream_t s) {
-    const int t = gemm_pair_tile(g0, g1);
-    return t < 0 ? hipErrorInvalidValue : dispatch(t, g0, &g1, s);
+    return gemm_can_pair(g0, g1) ? dispatch(gemm_plan(g0, &g1), g0, &g1, s) : hipErrorInvalidValue;
 }

@@ -34,6 +34,7 @@ namespace {
 
 constexpr int EPI_SPLIT_GELU_ERF = 2;  // kernel variant of EPI_SPLIT_GELU with the erf form of the activation
 constexpr int EPI_PARTIAL = 3;         // kernel variant of EPI_GATE_RESID that stores the sums of one part of K, nothing added
+constexpr int EPI_LAST_PART = 4;       // kernel variant of EPI_GATE_RESID for the last part of K, which adds the ones before it from memory
 constexpr int BK = 64;                 // K slab (bf16 elements) = 128 bytes per LDS row
 constexpr int STAGES = 2;              // slabs resident in LDS: one being multiplied, one in flight
 constexpr int ROWB = BK * 2;           // bytes per LDS row
@@ -87,7 +88,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx16 (&acc)
     // register quad.  Bias / GELU / gate are applied there, then each wave transposes its quadrant
     // through its own slice of LDS so that global stores are 16 bytes per lane with 16 (or 8)
     // consecutive lanes covering one contiguous row segment.
-    constexpr bool OUT_BF16 = (EPI != EPI_GATE_RESID && EPI != EPI_PARTIAL);
+    constexpr bool OUT_BF16 = (EPI == EPI_SPLIT_GELU || EPI == EPI_SPLIT_GELU_ERF);
+    constexpr bool CUT = (EPI == EPI_PARTIAL || EPI == EPI_LAST_PART);     // the accumulators hold one part of a sum: no bias yet
     constexpr bool ACT_ERF = (EPI == EPI_SPLIT_GELU_ERF);
     constexpr int PASSES = OUT_BF16 || NT == 1 ? 1 : 2;    // fp32 rows are staged in two column halves
     constexpr int NTP = NT / PASSES;                       // 32-column tiles per pass
@@ -109,7 +111,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx16 (&acc)
         for (int i = 0; i < NT; ++i)
 #pragma unroll
             for (int vb = 0; vb < 4; ++vb) bias_raw[i][vb] = uint32x2{0u, 0u};
-        if (EPI != EPI_PARTIAL && g.has_bias) {
+        if (!CUT && g.has_bias) {
 #pragma unroll
             for (int i = 0; i < NT; ++i)
 #pragma unroll
@@ -182,12 +184,18 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx16 (&acc)
                 // sample.  The residual rows of UB stores are fetched together: taken one by one, each store
                 // would wait out a memory round trip of its own.  Lanes outside the problem read a valid
                 // address (row M-1, column 0) and store nothing.
-                constexpr int UB = WM / RPI < 8 ? WM / RPI : 8;
+                constexpr int UB = EPI == EPI_LAST_PART && BM * BN <= 128 * 128 ? 4 : WM / RPI < 8 ? WM / RPI : 8;    // (two workgroups per CU: 256 registers)
                 static_assert((WM / RPI) % UB == 0, "write-out batches");
                 const bool n_ok = n < g.n1;
                 const int nc = n_ok ? n : 0;
                 const bool has_gate = g.gate != nullptr;
                 const float* const gate_p = has_gate ? g.gate : g.resid;       // a readable address either way
+                floatx4 bias_c = {0.f, 0.f, 0.f, 0.f};
+                if (EPI == EPI_LAST_PART && g.has_bias) {
+                    const uint32x2 bb = *(const uint32x2*)wv_ptr(g.W, g.bias_off + 2ull * nc);
+                    bias_c = floatx4{__uint_as_float(bb.x << 16), __uint_as_float(bb.x & 0xffff0000u), __uint_as_float(bb.y << 16),
+                                     __uint_as_float(bb.y & 0xffff0000u)};
+                }
                 const long gate_bs = has_gate ? g.gate_bs : 0;
                 auto write_out = [&](auto per_sample) {
                     constexpr bool PS = decltype(per_sample)::value;
@@ -196,6 +204,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx16 (&acc)
 #pragma unroll
                     for (int r0 = 0; r0 < WM / RPI; r0 += UB) {
                         floatx4 rr[UB], gt[UB];                // native vectors: arrays of them stay in registers
+                        floatx4 sum[EPI == EPI_LAST_PART ? UB : 1];       // of the parts before, in order
                         size_t y_off[UB];
                         bool ok[UB];
 #pragma unroll
@@ -214,11 +223,26 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx16 (&acc)
                                 gt[u] = gate_c;
                             }
                             y_off[u] = (size_t)b * g.y_bs + (size_t)i * g.ldy + nc;
+                            if constexpr (EPI == EPI_LAST_PART) sum[u] = *(const floatx4*)(g.part + (size_t)mm * g.N + nc);
+                        }
+                        if constexpr (EPI == EPI_LAST_PART) {
+                            for (int p = 1; p < part; ++p)
+#pragma unroll
+                                for (int u = 0; u < UB; ++u) {
+                                    const int mm = min(m0 + wm0 + (r0 + u) * RPI + lane / CPR, g.M - 1);
+                                    const floatx4 t = *(const floatx4*)(g.part + ((size_t)p * g.M + mm) * g.N + nc);
+#pragma unroll
+                                    for (int e = 0; e < 4; ++e) sum[u][e] += t[e];
+                                }
                         }
 #pragma unroll
                         for (int u = 0; u < UB; ++u) {
                             const int row = (r0 + u) * RPI + lane / CPR;
-                            const floatx4 val = *(const floatx4*)(stg + row * PITCH + (lane % CPR) * 16);
+                            floatx4 val = *(const floatx4*)(stg + row * PITCH + (lane % CPR) * 16);
+                            if constexpr (EPI == EPI_LAST_PART) {
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) val[e] = (sum[u][e] + val[e]) + bias_c[e];
+                            }
                             floatx4 o;
 #pragma unroll
                             for (int e = 0; e < 4; ++e) o[e] = __fadd_rn(rr[u][e], __fmul_rn(gt[u][e], val[e]));
@@ -299,8 +323,9 @@ __device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0,
     }
 
     // slabs of this workgroup: all, or those of its part
-    const int kt0 = EPI == EPI_PARTIAL ? part * g.part_slabs : 0;
-    const int KT = EPI == EPI_PARTIAL ? min(g.part_slabs, g.K / BK - kt0) : g.K / BK;
+    constexpr bool CUT = EPI == EPI_PARTIAL || EPI == EPI_LAST_PART;
+    const int kt0 = CUT ? part * g.part_slabs : 0;
+    const int KT = CUT ? min(g.part_slabs, g.K / BK - kt0) : g.K / BK;
     bf16x8 fa[2][MH][KSTEPS], fw[2][NH][KSTEPS];
 
     // Slab kt's copies into stage st.  Past the last slab the resources are empty: the copies of the two slabs that do
@@ -468,8 +493,9 @@ __device__ __forceinline__ void gemm_ring_run(const GemmArgs& g, int m0, int n0,
         w_frag[kk] = (lds_frag*)(smem + BM * ROWB + (wn0 + li) * ROWB + c);
     }
     // slabs of this workgroup: all, or those of its part
-    const int kt0 = EPI == EPI_PARTIAL ? part * g.part_slabs : 0;
-    const int KT = EPI == EPI_PARTIAL ? min(g.part_slabs, g.K / BK - kt0) : g.K / BK;
+    constexpr bool CUT = EPI == EPI_PARTIAL || EPI == EPI_LAST_PART;
+    const int kt0 = CUT ? part * g.part_slabs : 0;
+    const int KT = CUT ? min(g.part_slabs, g.K / BK - kt0) : g.K / BK;
     bf16x8 fa[2][MT][KSTEPS], fw[2][NT][KSTEPS];
 
     struct Src { __amdgpu_buffer_rsrc_t a, w; uint32_t k0; bool on; };
@@ -543,8 +569,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, uint32_t bid, 
     const int tiles_m = (g.M + BM - 1) / BM;
     const int tiles_n = (g.n1 - g.n0 + BN - 1) / BN;
     uint32_t lid = xcd_contiguous_id(bid, nblk);
-    const int part = EPI == EPI_PARTIAL ? lid / (tiles_m * tiles_n) : 0;
+    int part = EPI == EPI_PARTIAL ? lid / (tiles_m * tiles_n) : 0;
     lid -= part * (tiles_m * tiles_n);
+    if (EPI == EPI_LAST_PART) part = g.ksplits - 1;
     // row-tile groups of about 8, all of one size: a short last group would walk every weight tile once more
     const int n_groups = max(1, (tiles_m + 4) / 8);
     const int GM = (tiles_m + n_groups - 1) / n_groups;
@@ -584,7 +611,7 @@ __global__ __launch_bounds__(256) void gemm_pair_kernel(GemmPair p) {
 template <int BM, int BN, int S, int EPI>
 constexpr size_t gemm_smem() {
     constexpr int WM = BM / 2, WN = BN / 2;
-    constexpr int staged_row = EPI != EPI_GATE_RESID && EPI != EPI_PARTIAL ? WN * 2 + 16 : (WN > 32 ? WN * 2 : WN * 4) + 32;     // the epilogue's PITCH
+    constexpr int staged_row = EPI == EPI_SPLIT_GELU || EPI == EPI_SPLIT_GELU_ERF ? WN * 2 + 16 : (WN > 32 ? WN * 2 : WN * 4) + 32;     // the epilogue's PITCH
     constexpr size_t loop = (size_t)(S > 0 ? S : STAGES) * (BM + BN) * ROWB, epi = 4ull * WM * staged_row;
     return loop > epi ? loop : epi;
 }
@@ -605,7 +632,7 @@ hipError_t launch(const GemmArgs& g, const GemmArgs* second, hipStream_t s) {
         if (allowed != hipSuccess) return allowed;
         hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, S, EPI>), dim3(tiles(g)), dim3(256), smem, s, g);
     } else if constexpr (BM * BN == 65536 && EPI == EPI_PARTIAL) {
-        return hipErrorInvalidValue;               // does not fit the registers; gemm_pair_tile never asks for it
+        return hipErrorInvalidValue;               // does not fit the registers; gemm_plan never asks for it
     } else {
         static const hipError_t allowed = allow_smem(gemm_pair_kernel<BM, BN, S, EPI>, smem);
         if (allowed != hipSuccess) return allowed;

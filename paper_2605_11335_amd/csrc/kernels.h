@@ -27,7 +27,7 @@ struct GemmArgs {
     // b*y_bs + i*ldy in y (strides in elements).  rows_per_sample = 0: one sample, strides unused.
     int rows_per_sample; long gate_bs, resid_bs, y_bs;
     // EPI_GATE_RESID with the sum over K cut into ksplits parts of part_slabs 64-wide slabs each (gemm_set_split), computed
-    // by workgroups of their own into part[ksplits][M][N] and put together by a second kernel; 0 or 1 = whole.
+    // by workgroups of their own into part[ksplits][M][N] and put together by a second launch; 0 or 1 = whole.
     int ksplits, part_slabs;
     float* part;
 };
@@ -35,19 +35,25 @@ int gemm_splits(int rows, int rows2, int N, int K);      // parts to cut K into,
 void gemm_set_split(GemmArgs* g, int splits, float* part);
 const char* gemm_check(const GemmArgs& g);
 enum { GEMM_256x256 = 0, GEMM_128x128 = 1, GEMM_128x256 = 2, GEMM_128x64 = 3, GEMM_64x64 = 4, GEMM_192x256 = 5, GEMM_TILES = 6 };     // tokens x features
-int gemm_tile(const GemmArgs& g);      // tile gemm_launch will use
+// How a layer, or two in one launch (`second` not NULL), is launched: its tile; of a cut sum the tile of the parts, and that of
+// the last part where its launch puts the sum together (else -1).
+struct GemmPlan { int tile, last; };
+GemmPlan gemm_plan(const GemmArgs& g, const GemmArgs* second);
+void gemm_tile_shape(int tile, int* tokens, int* features);
 double gemm_fill(int M, int n);        // share of the launched rounds of workgroups that n features x M tokens fill
 hipError_t gemm_launch(const GemmArgs& g, hipStream_t s);
+hipError_t gemm_launch_as(const GemmPlan& plan, const GemmArgs& g, hipStream_t s);     // (diagnostic) as told
 // per epilogue: one problem, or two in one launch (`second` not NULL), with the given tile
 hipError_t gemm_launch_split_gelu(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s);
 hipError_t gemm_launch_split_gelu_erf(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s);
 hipError_t gemm_launch_gate_resid(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s);
 hipError_t gemm_launch_partial(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s);     // the parts of a cut sum only
+hipError_t gemm_launch_last_part(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s);   // its last part, added to the others
 hipError_t mfma_rate_launch(int iters, int random_operands, float* out, hipStream_t s);   // diagnostic: MFMAs on registers only
 // diagnostic: MFMAs sharing the SIMD with LDS fragment reads and VALU work (see gemm.hip for the supported mixes)
 hipError_t mix_rate_launch(int iters, int waves, int reads16, int valu, int exps, float* out, hipStream_t s);
-// two independent problems in one launch; gemm_pair_tile: the tile shape they share (as gemm_tile), -1 = cannot pair
-int gemm_pair_tile(const GemmArgs& g0, const GemmArgs& g1);
+// two independent problems in one launch
+bool gemm_can_pair(const GemmArgs& g0, const GemmArgs& g1);
 hipError_t gemm_launch_pair(const GemmArgs& g0, const GemmArgs& g1, hipStream_t s);
 
 // Positions of this rank's tokens in the joint sequence: up to two contiguous segments

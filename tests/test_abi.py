@@ -275,3 +275,23 @@ def test_block_attention_plans():
         assert lib.cf_op_attention_form(p, p, p, p, H, nq, nk, nk, hd, parts, 0, deal, 0, p, nbytes, None) == B.CF_ERR_ARG
     # a drawn sweep is cut in four pieces of at least a tile, however many there are
     assert all(plan(48, b, nq, nk, 128)[2] != 2 for b in (1, 16, 256) for nq in (4608, 119056) for nk in (1, 64, 128, 192))
+
+
+def test_block_linear_plans():
+    """How a block launches its linear layers: the number of parts of a sum follows from one sample, is at most three (a batch that
+    fills the chip pays for each), and where such a batch puts it together the last part does."""
+    def plan(*shape, **kw):
+        p = B.cf_plan_block_linear(*shape, **kw)
+        return (p.tile_tokens, p.tile_features), p.parts, (p.last_tile_tokens, p.last_tile_features)
+    assert plan(2304, 21504, 3072, False) == ((256, 256), 1, (0, 0))
+    for shape in ((576, 3072, 15360), (1320, 3072, 14336), (2304, 3072, 15360)):
+        alone = plan(*shape, True)
+        assert 1 < alone[1] <= 3 and alone[2] == (0, 0)
+        assert all(plan(*shape, True, batch=b)[1] == alone[1] for b in (2, 4, 8, 64))
+    assert plan(576, 3072, 15360, True, batch=8)[2] == (256, 256) and plan(1320, 3072, 14336, True, batch=4)[2] == (256, 256)
+    for bad in ((0, 64, 64), (64, 0, 64), (64, 64, 0)):
+        with pytest.raises(B.ChunkflowError):
+            B.cf_plan_block_linear(*bad, True)
+    lib, p = B.lib(), C.c_void_p(4096)             # never dereferenced
+    for tile, parts, nbytes in (((256, 64), 1, 0), ((128, 64), 0, 0), ((128, 64), 9, 1 << 30), ((128, 64), 2, 4096)):
+        assert lib.cf_op_linear_residual_form(p, 512, p, 0, -1, 64, 64, 512, p, None, p, tile[0], tile[1], parts, 0, p, nbytes, None) == B.CF_ERR_ARG

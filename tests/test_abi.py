@@ -295,3 +295,16 @@ def test_block_linear_plans():
     lib, p = B.lib(), C.c_void_p(4096)             # never dereferenced
     for tile, parts, nbytes in (((256, 64), 1, 0), ((128, 64), 0, 0), ((128, 64), 9, 1 << 30), ((128, 64), 2, 4096)):
         assert lib.cf_op_linear_residual_form(p, 512, p, 0, -1, 64, 64, 512, p, None, p, tile[0], tile[1], parts, 0, p, nbytes, None) == B.CF_ERR_ARG
+
+
+def test_the_tile_tests_take_every_tile():
+    """The sizes of tests/test_gpu_gemm_tiles.py still reach all tiles: on the longest sum, with few slabs all but 128 x 256, and with
+    two layers in one launch."""
+    from tests import test_gpu_gemm_tiles as t
+
+    def tile(m, k, n=t.N, m2=0):
+        p = B.cf_plan_block_linear(m, n, k, False, rows2=m2)
+        return p.tile_tokens, p.tile_features
+    assert {tile(m, t.KS[-1]) for m in t.FEWER + (t.M,)} == t.TILES
+    assert all({tile(m, k) for m in t.FEWER + (t.M,)} >= t.TILES - {(128, 256)} for k in t.KS)
+    assert {tile(m, 512, 2048, t.TXT) for m in t.IMAGES} == t.TILES

@@ -1,6 +1,7 @@
 """Attention dealt out by the kernel (a sweep that one workgroup begins and another ends), in even shares and as the workgroups
 come for it: against the oracle, and the same bits as sweeps done by one workgroup each -- a batch large enough to be dealt out
-equals its samples run alone, which are too small for it (or, the long ones, are dealt out differently)."""
+equals its samples run alone, which are too small for it (or, the long ones, are dealt out differently).  Sweeps that have to be
+repeated are compared bit for bit in test_gpu_attention_forms.py."""
 import numpy as np
 import pytest
 
@@ -43,5 +44,5 @@ def test_dealt_out_evenly(n, heads, hd, batch, sharp):
         ref = ob.block_forward(one, params, x, rows=rows)["y"]
         print(f"sample {b}: rel_l2={rel_l2(y[b][rows], ref):.3e}", flush=True)
         # a logit of standard deviation 20 moves by 0.05 when q and k are rounded to bf16, and its weight by as many per cent;
-        # tiles then go out of the fast softmax's range, and each part of a sweep is repeated by the workgroup that has it
+        # tiles then go out of the fast softmax's range, and the sweep is repeated by the workgroup with its last piece
         assert rel_l2(y[b][rows], ref) <= (1e-2 if sharp == 1.0 else 5e-2)

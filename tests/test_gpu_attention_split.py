@@ -6,15 +6,18 @@ import pytest
 
 import workload as wl
 from oracle import block as ob
+from paper_2605_11335_amd import binding as B
 from paper_2605_11335_amd.runner import BlockRunner, bits_of
 from tests.util import bits_to_f64, max_abs, rel_l2
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n,heads,hd,sp,sharp", [(256, 8, 64, 1, 1.0), (260, 4, 128, 4, 1.0), (1028, 4, 128, 4, 1.0),
-                                                 (1730, 8, 64, 2, 1.0), (1028, 4, 128, 4, 24.0), (1730, 8, 64, 2, 24.0)])
+@pytest.mark.parametrize("n,heads,hd,sp,sharp", [(1888, 8, 64, 8, 1.0), (2720, 8, 64, 8, 1.0), (1540, 4, 128, 4, 1.0),
+                                                 (2000, 4, 128, 2, 1.0), (1540, 4, 128, 4, 24.0), (2720, 8, 64, 8, 24.0)])
 def test_split_keys_against_the_oracle(n, heads, hd, sp, sharp):
+    plan = B.cf_plan_block_attention(heads // sp, 1, n, n, hd)
+    assert plan.parts > 1 and not plan.all_parts
     cfg = wl.BlockConfig("split", wl.KIND_SINGLE, n_blocks=1, d=512, n_heads=heads, head_dim=hd, f=512, n_total=n, sp_degree=sp,
                          sp_rank=sp - 1, qk_rmsnorm=True, n_chunks=3)
     params, inputs = wl.gen_block_params(cfg, 0), wl.gen_block_inputs(cfg, 0)

@@ -260,11 +260,12 @@ def test_linear_under_one_round_of_tiles():
     assert max_abs(y.cpu().numpy(), resid + g.astype(np.float64) * z) < 1e-3
 
 
-@pytest.mark.parametrize("M,N", [(2304, 4096), (2100, 2056)])
-def test_linear_every_epilogue_on_both_tiles(M, N):
-    """The first shape fills the chip better with 256 x 256 tiles, the second (ragged in both directions)
+@pytest.mark.parametrize("M,N,tile", [(3300, 4096, 256), (2304, 4096, 192), (2100, 2056, 128)])
+def test_linear_every_epilogue_on_large_tiles(M, N, tile):
+    """The first shape fills the chip better with 256 x 256 tiles, the second with 192 x 256, the third (ragged in both directions)
     with 128 x 128 ones; each runs the split epilogue with either activation and the gated residual one."""
     K, n_split = 192, 1024
+    assert B.cf_plan_block_linear(M, N, K, False).tile_tokens == tile
     rng = np.random.default_rng(M + N)
     a, ab = bf16_round(rng.normal(size=(M, K)))
     buf, w, b, w_off, b_off = make_blob(rng, N, K)

@@ -115,7 +115,7 @@ hipError_t modvec_launch(const WView& W, uint64_t w_off, uint64_t b_off, const f
 // xn = LN(x) * (1 + scale) + shift  (fp32 in, bf16 out); with ln_w/ln_b (blob offsets, has_affine)
 // instead: xn = LN(x) * w + b.
 // Row r of a batch is row r % rows_per_sample of sample b = r / rows_per_sample: read at x + b*x_bs, modulated
-// with shift + b*mod_bs, scale + b*mod_bs; written densely to xn + r*ld_out.  rows_per_sample = 0: one sample.
+// with shift + b*mod_bs, scale + b*mod_bs; written densely to xn + r*d.  rows_per_sample = 0: one sample.
 struct LnArgs {
     const float *x, *shift, *scale;
     bf16* xn;

@@ -202,7 +202,8 @@ def test_mixed_block_kinds_are_planned_per_block():
 
 
 def test_attention_launch_shapes():
-    """The launch planner's choices for the shapes they were measured on (one MI355X): 8 waves per
+    """The launch planner's choices by the grid for the shapes they were measured on (one MI355X; a block may deal
+    the sweeps out otherwise, test_block_attention_plans): 8 waves per
     workgroup for the Flux-like and the Hunyuan-like self-attention, 7 for the Wan-like one (7- and 8-wave
     grids take six generations either way, and a 7-wave generation of such a long sweep is shorter), 4 for
     the cross-attention to 512 context tokens (short sweeps: one workgroup's fixed part hides behind the

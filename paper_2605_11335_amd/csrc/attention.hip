@@ -536,7 +536,9 @@ __global__ __launch_bounds__(512, 2) void attn_even_kernel(AttnArgs a) {
                 if (leave >= 0) {
                     store_state<HD>(a.even_state + ((size_t)leave * 32 + j) * STATE, wave, lane, o, mc, l_run);
                     // One release per workgroup, by thread 0 behind the barrier: it writes back the XCD's whole L2.  By every wave
-                    // it cost 57 us.
+                    // it cost 57 us.  Its own wait covers its own wave's stores only, and the barrier waits for none: each wave
+                    // waits for its stores to have reached the L2 that is written back.
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                     __syncthreads();
                     if (threadIdx.x == 0) __hip_atomic_store(a.even_flags + leave * 32 + j, (uint32_t)kStateLeft, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
                 } else {

@@ -80,179 +80,224 @@ __device__ __forceinline__ void handover() {
     asm volatile("" ::: "memory");
 }
 
+// The epilogue's staging: a wave passes its quadrant through a slice of LDS of its own, ROWS tokens (and of fp32 results 64
+// features) at a time, so that global stores are 16 bytes per lane with the lanes of a row on one contiguous segment.
+// 16-byte chunks of the slice's rows are XOR-swizzled like those of the slabs.
+template <int NT, int ELT, int ROWS>
+struct Stage {
+    static constexpr int FP = NT * 32 * ELT <= 256 ? NT * 32 : 256 / ELT;      // features per pass
+    static constexpr int PASSES = NT * 32 / FP, NTP = FP / 32;
+    static constexpr int RB = FP * ELT, CPR = RB / 16;         // bytes and chunks of a staged row
+    static constexpr int RPI = 64 / CPR, ST = ROWS / RPI;      // rows per store, stores per slice
+    static constexpr int BYTES = ROWS * RB;
+    static __device__ __forceinline__ int at(int row, int chunk) { return row * RB + ((chunk ^ (row & (CPR - 1))) << 4); }
+};
+// Activations go out 32 tokens at a time (gemm_epilogue), fp32 results half a quadrant at a time: with nothing to compute between
+// the slices, smaller ones would only add waits.
+template <int BM, int EPI>
+constexpr int slice_rows() { return EPI == EPI_SPLIT_GELU || EPI == EPI_SPLIT_GELU_ERF ? 32 : BM / 2; }
+// orders a wave's LDS accesses before and after it, for the compiler (the LDS itself takes a wave's accesses in order)
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// In the accumulators a lane owns one token row and 4 consecutive features per register quad.  Bias and GELU are applied there,
+// slice by slice, so that the stores of one slice are on their way while the next is computed; bias, gate and residual of fp32
+// results at the write-out, where they need a few registers per lane instead of one per feature, which leaves room to fetch
+// residual rows a batch ahead.  Bound, on a full chip of 256 x 256 tiles, by the VALU (GELU: 9.5 us, 46 operations of 256 values
+// per lane and some) or by the memory that all CUs turn to at once (33 MB of bf16 in 5.2 us, 5.8 before; residual and result,
+// 134 MB, in 21 us, 26.8 with a batch fetched when it was needed).  A Wan-like share of 1320 rows, whose three gated layers end in
+// it: 607 -> 598 us.
 template <int BM, int BN, int EPI>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx16 (&acc)[BN / 64][BM / 64], int m0, int n0, int part, int uw, char* smem) {
     constexpr int WM = BM / 2, WN = BN / 2;        // wave quadrant
     constexpr int MT = WM / 32, NT = WN / 32;      // 32x32 MFMA tiles per wave
-    // ---- epilogue.  In the accumulators a lane owns one token row and 4 consecutive features per
-    // register quad.  Bias / GELU / gate are applied there, then each wave transposes its quadrant
-    // through its own slice of LDS so that global stores are 16 bytes per lane with 16 (or 8)
-    // consecutive lanes covering one contiguous row segment.
     constexpr bool OUT_BF16 = (EPI == EPI_SPLIT_GELU || EPI == EPI_SPLIT_GELU_ERF);
-    constexpr bool CUT = (EPI == EPI_PARTIAL || EPI == EPI_LAST_PART);     // the accumulators hold one part of a sum: no bias yet
     constexpr bool ACT_ERF = (EPI == EPI_SPLIT_GELU_ERF);
-    constexpr int PASSES = OUT_BF16 || NT == 1 ? 1 : 2;    // fp32 rows are staged in two column halves
-    constexpr int NTP = NT / PASSES;                       // 32-column tiles per pass
     constexpr int ELT = OUT_BF16 ? 2 : 4;
-    constexpr int RB = NTP * 32 * ELT;                     // staged row bytes
-    constexpr int PITCH = RB + (OUT_BF16 ? 16 : 32);       // padded: conflict-free quad writes
-    constexpr int CPR = RB / 16, RPI = 64 / CPR;           // 16-byte chunks per row, rows per store
-    static_assert(4 * WM * PITCH <= 160 * 1024, "staging exceeds LDS");
-    {
-        // lane coordinates are derived afresh (lane from the wave's bit count, wave from its scalar copy)
-        // rather than kept in vector registers across the main loop
-        const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), wave = uw;
-        const int wm0 = (wave & 1) * WM, wn0 = (wave >> 1) * WN;
-        const int li = lane & 31, lg = lane >> 5;
-        // Bias of the wave's features, in accumulator order: 4 consecutive features per (feature tile, register
-        // quad).  Fetched in one go: taken one by one in the epilogue, each would cost a memory round trip.
-        uint32x2 bias_raw[NT][4];
+    constexpr int SJ = slice_rows<BM, EPI>() / 32;         // MFMA tiles of tokens per slice
+    using St = Stage<NT, ELT, SJ * 32>;
+    constexpr int ST = St::ST, RPI = St::RPI, CPR = St::CPR;
+    // the same value, of which the compiler knows nothing: what is made from it is made where it is used, and not ahead of the
+    // main loop (lane coordinates) or of the write-out (all its addresses at once), where it would fill the registers
+    auto opaque = [](int v) { asm volatile("" : "+v"(v)); return v; };
+    const int lane = opaque(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u))), wave = uw;
+    const int wm0 = (wave & 1) * WM, wn0 = (wave >> 1) * WN;
+    const int li = lane & 31, lg = lane >> 5;
+    // Bias of the wave's features where the activation needs it, in accumulator order: 4 consecutive features per (feature tile, register
+    // quad).  Fetched in one go: taken one by one in the epilogue, each would cost a memory round trip.
+    uint32x2 bias_raw[NT][4];
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int vb = 0; vb < 4; ++vb) bias_raw[i][vb] = uint32x2{0u, 0u};
+    if (OUT_BF16 && g.has_bias) {
 #pragma unroll
         for (int i = 0; i < NT; ++i)
 #pragma unroll
-            for (int vb = 0; vb < 4; ++vb) bias_raw[i][vb] = uint32x2{0u, 0u};
-        if (!CUT && g.has_bias) {
+            for (int vb = 0; vb < 4; ++vb) {
+                const int n = min(n0 + wn0 + i * 32 + vb * 8 + lg * 4, g.N - 4);
+                bias_raw[i][vb] = *(const uint32x2*)wv_ptr(g.W, g.bias_off + 2ull * n);
+            }
+    }
+    char* const stg = smem + wave * St::BYTES;
+    // slice (p, j): tokens j*32.. and features p*FP.. of the quadrant, computed and written to LDS.  Whether a quadrant's features are
+    // activated is decided once (n_split falls inside at most one column of quadrants): a decision per quad is a branch per quad,
+    // between which nothing overlaps
+    enum { PLAIN, ACTIVATED, MIXED };
+    auto stage = [&](auto act, int p, int j, int row0) __attribute__((always_inline)) {
+        wave_lds_order();
 #pragma unroll
-            for (int i = 0; i < NT; ++i)
+        for (int ii = 0; ii < St::NTP; ++ii) {
+            const int i = p * St::NTP + ii;
+            floatx16 sums = acc[i][j];
+            if constexpr (SJ == 1) asm volatile("" : "+v"(sums));      // from the accumulation registers now, not all tiles' ahead of the first store
 #pragma unroll
-                for (int vb = 0; vb < 4; ++vb) {
-                    const int n = min(n0 + wn0 + i * 32 + vb * 8 + lg * 4, g.N - 4);
-                    bias_raw[i][vb] = *(const uint32x2*)wv_ptr(g.W, g.bias_off + 2ull * n);
+            for (int vb = 0; vb < 4; ++vb) {
+                const uint32x2 bb = bias_raw[i][vb];
+                const float b[4] = {__uint_as_float(bb.x << 16), __uint_as_float(bb.x & 0xffff0000u),
+                                    __uint_as_float(bb.y << 16), __uint_as_float(bb.y & 0xffff0000u)};
+                float v[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = OUT_BF16 ? sums[vb * 4 + e] + b[e] : sums[vb * 4 + e];
+                if constexpr (OUT_BF16) {
+                    if constexpr (decltype(act)::value != PLAIN) {
+                        const bool here = decltype(act)::value == ACTIVATED || n0 + wn0 + i * 32 + vb * 8 + lg * 4 >= g.n_split;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const float a = ACT_ERF ? gelu_erf_f32(v[e]) : gelu_tanh_f32(v[e]);
+                            v[e] = here ? a : v[e];
+                        }
+                    }
+                    bf16x4 o;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e] = (bf16)v[e];
+                    *(bf16x4*)(stg + St::at(row0 + li, ii * 4 + vb) + lg * 8) = o;
+                } else {
+                    *(floatx4*)(stg + St::at(row0 + li, ii * 8 + vb * 2 + lg)) = floatx4{v[0], v[1], v[2], v[3]};
                 }
+            }
         }
+        wave_lds_order();
+    };
+    const int row_l = lane / CPR, chunk_l = lane % CPR;        // a store's row (of RPI) and chunk of this lane
+    if constexpr (OUT_BF16 || EPI == EPI_PARTIAL) {
         slab_handover();                       // every wave is done reading the slabs; the bias loads flew meanwhile
-        char* const stg = smem + wave * (WM * PITCH);
+        auto write_out = [&](auto act) __attribute__((always_inline)) {
+            constexpr int ACT = decltype(act)::value;
 #pragma unroll
-        for (int p = 0; p < PASSES; ++p) {
+            for (int p = 0; p < St::PASSES; ++p) {
+                const int n = n0 + wn0 + p * St::FP + chunk_l * (16 / ELT);        // first column of the lane's chunk
 #pragma unroll
-            for (int ii = 0; ii < NTP; ++ii) {
-                const int i = p * NTP + ii;
+                for (int j0 = 0; j0 < MT; j0 += SJ) {
 #pragma unroll
-                for (int vb = 0; vb < 4; ++vb) {
-                    const int n = min(n0 + wn0 + i * 32 + vb * 8 + lg * 4, g.N - 4);
-                    const uint32x2 bb = bias_raw[i][vb];
-                    const float b[4] = {__uint_as_float(bb.x << 16), __uint_as_float(bb.x & 0xffff0000u),
-                                        __uint_as_float(bb.y << 16), __uint_as_float(bb.y & 0xffff0000u)};
-                    const bool act = OUT_BF16 && n >= g.n_split;
+                    for (int j = 0; j < SJ; ++j) stage(act, p, j0 + j, j * 32);
+                    const int r = opaque(row_l);
+                    uint32x4 val[ST];
 #pragma unroll
-                    for (int j = 0; j < MT; ++j) {
-                        float v[4];
+                    for (int u = 0; u < ST; ++u) val[u] = *(const uint32x4*)(stg + St::at(u * RPI + row_l, chunk_l));
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) v[e] = acc[i][j][vb * 4 + e] + b[e];
-                        char* dst = stg + (j * 32 + li) * PITCH + (ii * 32 + vb * 8 + lg * 4) * ELT;
-                        if (OUT_BF16) {
-                            if (act) {
-#pragma unroll
-                                for (int e = 0; e < 4; ++e) v[e] = ACT_ERF ? gelu_erf_f32(v[e]) : gelu_tanh_f32(v[e]);
-                            }
-                            bf16x4 o;
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) o[e] = (bf16)v[e];
-                            *(bf16x4*)dst = o;
-                        } else {
-                            *(float4*)dst = make_float4(v[0], v[1], v[2], v[3]);
-                        }
-                    }
-                }
-            }
-            // coalesced write-out of this pass
-            const int col = (lane % CPR) * (16 / ELT);                         // first column of the lane's chunk
-            const int n = n0 + wn0 + p * (NTP * 32) + col;
-            if constexpr (OUT_BF16) {
-#pragma unroll
-                for (int r = 0; r < WM / RPI; ++r) {
-                    const int row = r * RPI + lane / CPR;
-                    const int m = m0 + wm0 + row;
-                    const uint4 val = *(const uint4*)(stg + row * PITCH + (lane % CPR) * 16);
-                    if (m < g.M && n < g.n1) {
-                        bf16* dst = n < g.n_split ? g.out0 + (size_t)m * g.ld0 + n
-                                                  : g.out1 + (size_t)m * g.ld1 + g.col1_off + (n - g.n_split);
-                        *(uint4*)dst = val;
-                    }
-                }
-            } else if constexpr (EPI == EPI_PARTIAL) {
-                float* const out = g.part + (size_t)part * g.M * g.N;
-#pragma unroll
-                for (int r = 0; r < WM / RPI; ++r) {
-                    const int row = r * RPI + lane / CPR;
-                    const int m = m0 + wm0 + row;
-                    const floatx4 val = *(const floatx4*)(stg + row * PITCH + (lane % CPR) * 16);
-                    if (m < g.M && n < g.n1) *(floatx4*)(out + (size_t)m * g.N + n) = val;
-                }
-            } else {
-                // y = resid + gate * (...), the product rounded before the sum; the gate belongs to the row's
-                // sample.  The residual rows of UB stores are fetched together: taken one by one, each store
-                // would wait out a memory round trip of its own.  Lanes outside the problem read a valid
-                // address (row M-1, column 0) and store nothing.
-                constexpr int UB = EPI == EPI_LAST_PART && BM * BN <= 128 * 128 ? 4 : WM / RPI < 8 ? WM / RPI : 8;    // (two workgroups per CU: 256 registers)
-                static_assert((WM / RPI) % UB == 0, "write-out batches");
-                const bool n_ok = n < g.n1;
-                const int nc = n_ok ? n : 0;
-                const bool has_gate = g.gate != nullptr;
-                const float* const gate_p = has_gate ? g.gate : g.resid;       // a readable address either way
-                floatx4 bias_c = {0.f, 0.f, 0.f, 0.f};
-                if (EPI == EPI_LAST_PART && g.has_bias) {
-                    const uint32x2 bb = *(const uint32x2*)wv_ptr(g.W, g.bias_off + 2ull * nc);
-                    bias_c = floatx4{__uint_as_float(bb.x << 16), __uint_as_float(bb.x & 0xffff0000u), __uint_as_float(bb.y << 16),
-                                     __uint_as_float(bb.y & 0xffff0000u)};
-                }
-                const long gate_bs = has_gate ? g.gate_bs : 0;
-                auto write_out = [&](auto per_sample) {
-                    constexpr bool PS = decltype(per_sample)::value;
-                    floatx4 gate_c = {1.f, 1.f, 1.f, 1.f};
-                    if (!PS && has_gate) gate_c = *(const floatx4*)(gate_p + nc);
-#pragma unroll
-                    for (int r0 = 0; r0 < WM / RPI; r0 += UB) {
-                        floatx4 rr[UB], gt[UB];                // native vectors: arrays of them stay in registers
-                        floatx4 sum[EPI == EPI_LAST_PART ? UB : 1];       // of the parts before, in order
-                        size_t y_off[UB];
-                        bool ok[UB];
-#pragma unroll
-                        for (int u = 0; u < UB; ++u) {
-                            const int row = (r0 + u) * RPI + lane / CPR;
-                            const int m = m0 + wm0 + row;
-                            ok[u] = n_ok && m < g.M;
-                            const int mm = min(m, g.M - 1);
-                            int b = 0, i = mm;
-                            if (PS) { b = mm / g.rows_per_sample; i = mm - b * g.rows_per_sample; }
-                            rr[u] = *(const floatx4*)(g.resid + (size_t)b * g.resid_bs + (size_t)i * g.ldy + nc);
-                            if (PS) {
-                                const floatx4 t = *(const floatx4*)(gate_p + (size_t)b * gate_bs + nc);
-                                gt[u] = has_gate ? t : gate_c;
+                    for (int u = 0; u < ST; ++u) {
+                        const int m = m0 + wm0 + j0 * 32 + u * RPI + r;
+                        if (m < g.M && n < g.n1) {
+                            if constexpr (OUT_BF16) {
+                                bf16* const dst = ACT == PLAIN || (ACT == MIXED && n < g.n_split) ? g.out0 + (size_t)m * g.ld0 + n
+                                                                                                  : g.out1 + (size_t)m * g.ld1 + g.col1_off + (n - g.n_split);
+                                *(uint32x4*)dst = val[u];
                             } else {
-                                gt[u] = gate_c;
+                                *(uint32x4*)(g.part + (size_t)part * g.M * g.N + (size_t)m * g.N + n) = val[u];
                             }
-                            y_off[u] = (size_t)b * g.y_bs + (size_t)i * g.ldy + nc;
-                            if constexpr (EPI == EPI_LAST_PART) sum[u] = *(const floatx4*)(g.part + (size_t)mm * g.N + nc);
-                        }
-                        if constexpr (EPI == EPI_LAST_PART) {
-                            for (int p = 1; p < part; ++p)
-#pragma unroll
-                                for (int u = 0; u < UB; ++u) {
-                                    const int mm = min(m0 + wm0 + (r0 + u) * RPI + lane / CPR, g.M - 1);
-                                    const floatx4 t = *(const floatx4*)(g.part + ((size_t)p * g.M + mm) * g.N + nc);
-#pragma unroll
-                                    for (int e = 0; e < 4; ++e) sum[u][e] += t[e];
-                                }
-                        }
-#pragma unroll
-                        for (int u = 0; u < UB; ++u) {
-                            const int row = (r0 + u) * RPI + lane / CPR;
-                            floatx4 val = *(const floatx4*)(stg + row * PITCH + (lane % CPR) * 16);
-                            if constexpr (EPI == EPI_LAST_PART) {
-#pragma unroll
-                                for (int e = 0; e < 4; ++e) val[e] = (sum[u][e] + val[e]) + bias_c[e];
-                            }
-                            floatx4 o;
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) o[e] = __fadd_rn(rr[u][e], __fmul_rn(gt[u][e], val[e]));
-                            if (ok[u]) *(floatx4*)(g.y + y_off[u]) = o;
                         }
                     }
-                };
-                if (g.rows_per_sample) write_out(std::true_type{}); else write_out(std::false_type{});
+                }
             }
+        };
+        using Plain = std::integral_constant<int, PLAIN>;
+        if constexpr (!OUT_BF16) {
+            write_out(Plain{});
+        } else {
+            if (n0 + wn0 >= g.n_split) write_out(std::integral_constant<int, ACTIVATED>{});
+            else if (min(n0 + wn0 + WN, g.n1) <= g.n_split) write_out(Plain{});
+            else write_out(std::integral_constant<int, MIXED>{});
         }
+    } else {
+        // y = resid + gate * (...), the product rounded before the sum; the gate belongs to the row's
+        // sample.  The residual rows of UB stores are fetched together and a batch ahead: taken one by one, each store
+        // would wait out a memory round trip of its own.  Lanes outside the problem read a valid
+        // address (row M-1, column 0) and store nothing.
+        const bool has_gate = g.gate != nullptr;
+        const float* const gate_p = has_gate ? g.gate : g.resid;       // a readable address either way
+        const long gate_bs = has_gate ? g.gate_bs : 0;
+        auto write_out = [&](auto per_sample) {
+            constexpr bool PS = decltype(per_sample)::value;
+            constexpr bool LAST = EPI == EPI_LAST_PART;
+            constexpr int AHEAD = LAST ? 0 : 1, UB = BM * BN <= 128 * 128 ? 4 : 8;        // (two workgroups per CU: 256 registers)
+            static_assert(ST % UB == 0, "write-out batches");
+            constexpr int HB = ST / UB, NB = St::PASSES * HB;          // batches of a slice (a pass), of the quadrant
+            floatx4 rr[1 + AHEAD][UB], gt[1 + AHEAD][PS ? UB : 1], sum[LAST ? UB : 1];      // native vectors: arrays of them stay in registers
+            floatx4 gate_c = {1.f, 1.f, 1.f, 1.f}, bias_c = {0.f, 0.f, 0.f, 0.f};
+            auto col = [&](int p) { return n0 + wn0 + p * St::FP + chunk_l * 4; };
+            auto token = [&](int b, int u, int r) { return m0 + wm0 + (b % HB * UB + u) * RPI + r; };
+            auto fetch = [&](int b, int buf) __attribute__((always_inline)) {
+                const int nc = col(b / HB) < g.n1 ? col(b / HB) : 0, r = opaque(row_l);
+#pragma unroll
+                for (int u = 0; u < UB; ++u) {
+                    const int mm = min(token(b, u, r), g.M - 1);
+                    int sm = 0, i = mm;
+                    if (PS) { sm = mm / g.rows_per_sample; i = mm - sm * g.rows_per_sample; }
+                    rr[buf][u] = *(const floatx4*)(g.resid + (size_t)sm * g.resid_bs + (size_t)i * g.ldy + nc);
+                    if constexpr (PS) gt[buf][u] = *(const floatx4*)(gate_p + (size_t)sm * gate_bs + nc);
+                    if constexpr (LAST) sum[u] = *(const floatx4*)(g.part + (size_t)mm * g.N + nc);       // of the parts before, in order
+                }
+            };
+            if (AHEAD) fetch(0, 0);
+            slab_handover();                   // every wave is done reading the slabs; these loads flew meanwhile
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const int p = b / HB, buf = AHEAD ? b & 1 : 0, r = opaque(row_l);
+                const int n = col(p), nc = n < g.n1 ? n : 0;
+                __builtin_amdgcn_sched_barrier(0);         // (batches kept apart, for the registers' sake)
+                if (b + AHEAD < NB) fetch(b + AHEAD, AHEAD ? buf ^ 1 : 0);
+                if (b % HB == 0) {
+                    if (!PS && has_gate) gate_c = *(const floatx4*)(gate_p + nc);
+                    if (g.has_bias) {
+                        const uint32x2 bb = *(const uint32x2*)wv_ptr(g.W, g.bias_off + 2ull * nc);
+                        bias_c = floatx4{__uint_as_float(bb.x << 16), __uint_as_float(bb.x & 0xffff0000u), __uint_as_float(bb.y << 16),
+                                         __uint_as_float(bb.y & 0xffff0000u)};
+                    }
+                }
+                if (b % HB == 0) {
+#pragma unroll
+                    for (int j = 0; j < MT; ++j) stage(std::integral_constant<int, PLAIN>{}, p, j, j * 32);
+                }
+                if constexpr (LAST) {
+                    for (int q = 1; q < part; ++q)
+#pragma unroll
+                        for (int u = 0; u < UB; ++u) {
+                            const floatx4 t = *(const floatx4*)(g.part + ((size_t)q * g.M + min(token(b, u, r), g.M - 1)) * g.N + nc);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) sum[u][e] += t[e];
+                        }
+                }
+#pragma unroll
+                for (int u = 0; u < UB; ++u) {
+                    const int m = token(b, u, r);
+                    floatx4 val = *(const floatx4*)(stg + St::at((b % HB * UB + u) * RPI + row_l, chunk_l)), o;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) val[e] = (LAST ? sum[LAST ? u : 0][e] + val[e] : val[e]) + bias_c[e];
+                    const floatx4 gq = PS && has_gate ? gt[buf][PS ? u : 0] : gate_c;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e] = __fadd_rn(rr[buf][u][e], __fmul_rn(gq[e], val[e]));
+                    if (m < g.M && n < g.n1) {
+                        int sm = 0, i = m;
+                        if (PS) { sm = m / g.rows_per_sample; i = m - sm * g.rows_per_sample; }
+                        *(floatx4*)(g.y + (size_t)sm * g.y_bs + (size_t)i * g.ldy + n) = o;
+                    }
+                }
+            }
+        };
+        if (g.rows_per_sample) write_out(std::true_type{}); else write_out(std::false_type{});
     }
 }
 
@@ -589,8 +634,12 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, uint32_t bid, 
     }
 }
 
+// two workgroups per CU: 256 registers
+template <int BM, int BN>
+constexpr int min_waves() { return BM * BN <= 128 * 128 ? 2 : 1; }
+
 template <int BM, int BN, int S, int EPI>
-__global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgs g) {
+__global__ __launch_bounds__(256, (min_waves<BM, BN>())) void gemm_bf16_kernel(GemmArgs g) {
     gemm_tile_body<BM, BN, S, EPI>(g, blockIdx.x, gridDim.x);
 }
 
@@ -603,16 +652,15 @@ struct GemmPair {
     uint32_t tiles0, tiles0_pad;
 };
 template <int BM, int BN, int S, int EPI>
-__global__ __launch_bounds__(256) void gemm_pair_kernel(GemmPair p) {
+__global__ __launch_bounds__(256, (min_waves<BM, BN>())) void gemm_pair_kernel(GemmPair p) {
     if (blockIdx.x < p.tiles0) gemm_tile_body<BM, BN, S, EPI>(p.g[0], blockIdx.x, p.tiles0);
     else if (blockIdx.x >= p.tiles0_pad) gemm_tile_body<BM, BN, S, EPI>(p.g[1], blockIdx.x - p.tiles0_pad, gridDim.x - p.tiles0_pad);
 }
 
 template <int BM, int BN, int S, int EPI>
 constexpr size_t gemm_smem() {
-    constexpr int WM = BM / 2, WN = BN / 2;
-    constexpr int staged_row = EPI == EPI_SPLIT_GELU || EPI == EPI_SPLIT_GELU_ERF ? WN * 2 + 16 : (WN > 32 ? WN * 2 : WN * 4) + 32;     // the epilogue's PITCH
-    constexpr size_t loop = (size_t)(S > 0 ? S : STAGES) * (BM + BN) * ROWB, epi = 4ull * WM * staged_row;
+    constexpr size_t loop = (size_t)(S > 0 ? S : STAGES) * (BM + BN) * ROWB;
+    constexpr size_t epi = 4 * Stage<BN / 64, EPI == EPI_SPLIT_GELU || EPI == EPI_SPLIT_GELU_ERF ? 2 : 4, slice_rows<BM, EPI>()>::BYTES;
     return loop > epi ? loop : epi;
 }
 

@@ -25,6 +25,8 @@
 // 8192-cubed 837 -> 762 us, 13640 x 9216 x 3072 651 -> 603 us, 13640 x 3072 x 14336 1169 -> 971 us
 // (the time per slab of a full chip 1.52 -> 1.33 us).
 #pragma once
+#include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "common.h"
@@ -194,19 +196,23 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx16 (&acc)
 #pragma unroll
                     for (int j = 0; j < SJ; ++j) stage(act, p, j0 + j, j * 32);
                     const int r = opaque(row_l);
-                    uint32x4 val[ST];
+                    constexpr int UB = ST > 4 && MT == 3 ? 4 : ST;     // (as the register allocator has it without spills)
 #pragma unroll
-                    for (int u = 0; u < ST; ++u) val[u] = *(const uint32x4*)(stg + St::at(u * RPI + row_l, chunk_l));
+                    for (int u0 = 0; u0 < ST; u0 += UB) {
+                        uint32x4 val[UB];
 #pragma unroll
-                    for (int u = 0; u < ST; ++u) {
-                        const int m = m0 + wm0 + j0 * 32 + u * RPI + r;
-                        if (m < g.M && n < g.n1) {
-                            if constexpr (OUT_BF16) {
-                                bf16* const dst = ACT == PLAIN || (ACT == MIXED && n < g.n_split) ? g.out0 + (size_t)m * g.ld0 + n
-                                                                                                  : g.out1 + (size_t)m * g.ld1 + g.col1_off + (n - g.n_split);
-                                *(uint32x4*)dst = val[u];
-                            } else {
-                                *(uint32x4*)(g.part + (size_t)part * g.M * g.N + (size_t)m * g.N + n) = val[u];
+                        for (int u = 0; u < UB; ++u) val[u] = *(const uint32x4*)(stg + St::at((u0 + u) * RPI + row_l, chunk_l));
+#pragma unroll
+                        for (int u = 0; u < UB; ++u) {
+                            const int m = m0 + wm0 + j0 * 32 + (u0 + u) * RPI + r;
+                            if (m < g.M && n < g.n1) {
+                                if constexpr (OUT_BF16) {
+                                    bf16* const dst = ACT == PLAIN || (ACT == MIXED && n < g.n_split) ? g.out0 + (size_t)m * g.ld0 + n
+                                                                                                      : g.out1 + (size_t)m * g.ld1 + g.col1_off + (n - g.n_split);
+                                    *(uint32x4*)dst = val[u];
+                                } else {
+                                    *(uint32x4*)(g.part + (size_t)part * g.M * g.N + (size_t)m * g.N + n) = val[u];
+                                }
                             }
                         }
                     }
@@ -607,24 +613,38 @@ __device__ __forceinline__ void gemm_ring_run(const GemmArgs& g, int m0, int n0,
     gemm_epilogue<BM, BN, EPI>(g, acc, m0, n0, part, uw, smem);
 }
 
+// A problem's tiles in the order of their logical ids: groups of about 8 row-tiles, all of one size (a short last group would walk
+// every weight tile once more), walked feature-tile-major.
+template <int BM, int BN>
+struct TileWalk {
+    int tiles_m, tiles_n, GM;
+    __device__ __forceinline__ explicit TileWalk(const GemmArgs& g) {
+        tiles_m = (g.M + BM - 1) / BM;
+        tiles_n = (g.n1 - g.n0 + BN - 1) / BN;
+        const int n_groups = max(1, (tiles_m + 4) / 8);
+        GM = (tiles_m + n_groups - 1) / n_groups;
+    }
+    struct Tile { int m0, n0, above, gsz; };       // first token and feature; row-tiles of its group before it, in all
+    __device__ __forceinline__ Tile at(const GemmArgs& g, uint32_t lid) const {
+        const int group = lid / (GM * tiles_n), in = lid % (GM * tiles_n);
+        const int first_m = group * GM;
+        const int gsz = min(tiles_m - first_m, GM);
+        return Tile{(first_m + in % gsz) * BM, g.n0 + in / gsz * BN, in % gsz, gsz};
+    }
+};
+
 // Workgroup `bid` of the `nblk` that problem owns.  S: stages of the ring loop, 0 = the quadrant-phase loop (two stages).
 template <int BM, int BN, int S, int EPI>
 __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, uint32_t bid, uint32_t nblk) {
-    // logical tile: XCD-contiguous id, then (part of K by part of K) groups of GM row-tiles walked feature-tile-major
-    const int tiles_m = (g.M + BM - 1) / BM;
-    const int tiles_n = (g.n1 - g.n0 + BN - 1) / BN;
+    // logical tile: XCD-contiguous id, then (part of K by part of K) the walk over the tiles
+    const TileWalk<BM, BN> walk(g);
+    const int tiles_m = walk.tiles_m, tiles_n = walk.tiles_n;
     uint32_t lid = xcd_contiguous_id(bid, nblk);
     int part = EPI == EPI_PARTIAL ? lid / (tiles_m * tiles_n) : 0;
     lid -= part * (tiles_m * tiles_n);
     if (EPI == EPI_LAST_PART) part = g.ksplits - 1;
-    // row-tile groups of about 8, all of one size: a short last group would walk every weight tile once more
-    const int n_groups = max(1, (tiles_m + 4) / 8);
-    const int GM = (tiles_m + n_groups - 1) / n_groups;
-    const int group = lid / (GM * tiles_n);
-    const int first_m = group * GM;
-    const int gsz = min(tiles_m - first_m, GM);
-    const int m0 = (first_m + (lid % (GM * tiles_n)) % gsz) * BM;
-    const int n0 = g.n0 + (lid % (GM * tiles_n)) / gsz * BN;
+    const auto tile = walk.at(g, lid);
+    const int m0 = tile.m0, n0 = tile.n0;
     if constexpr (S > 0) {
         gemm_ring_run<BM, BN, S, EPI>(g, m0, n0, part);
     } else {
@@ -638,23 +658,104 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, uint32_t bid, 
 template <int BM, int BN>
 constexpr int min_waves() { return BM * BN <= 128 * 128 ? 2 : 1; }
 
-template <int BM, int BN, int S, int EPI>
-__global__ __launch_bounds__(256, (min_waves<BM, BN>())) void gemm_bf16_kernel(GemmArgs g) {
-    gemm_tile_body<BM, BN, S, EPI>(g, blockIdx.x, gridDim.x);
-}
-
 // Two independent problems of one tile shape and epilogue in one launch (the text and image streams
 // of a double-stream block, App. B): a small problem's workgroups ride along with the large one's
 // instead of holding the chip for the length of their K loop.  The first problem's share of the grid
 // is padded to a multiple of 8 so that both keep the block-index-to-XCD correspondence.
 struct GemmPair {
     GemmArgs g[2];
-    uint32_t tiles0, tiles0_pad;
+    uint32_t tiles0, tiles0_pad, tiles;        // workgroups of the first problem, with padding, of both
 };
+
+// The last round of workgroups leaves CUs without a tile.  There the grid goes on with workgroups that fetch, for the tiles of that
+// round, what their CU's copies are about to ask for, into the L2 of the XCD they share (`idle_fetch` is their number and pace).
+// A CU's loads return in order, so that a copy that misses L2 holds up all behind it: with operands from HBM a lone 128x256
+// workgroup takes 0.83 us per slab, from L2 0.50, whatever share of them misses; waves of its own workgroup or of its CU
+// fetching ahead wait in the same queue and gain nothing.  No result depends on it; a workgroup that is late, or on another XCD
+// than thought, only fetches in vain, and stops when the round should be over.
+// 512 x 9216 x 3072 (144 tiles of 128x256): 49.3 -> 40.0 us; 1320 x 3072 x 3072 (132): 50.2 -> 42.5;
+// 2304 x 3072 x 12288 (216): 173.8 -> 163.8; 1531 x 12288 x 3072 (384 of 192x256): 125.8 -> 119.7.
+struct IdleFetch {
+    uint32_t workgroups;                       // behind the tiles'; 0 = none
+    uint32_t ticks_per_chunk, deadline;        // of 10 ns
+    int stride, with_a;                        // every stride-th chunk; the activations too
+};
+constexpr uint32_t IDLE_MOST = 224;            // tiles of a last round beside which fetching still pays
+constexpr int FETCH_SLABS = 4, FETCH_LEAD = 2; // a chunk is 512 bytes of a row; the first ones are asked for before a fetch could help
+
+struct Panel { uint64_t base; uint32_t bytes, row_bytes; };
+// The panels of one problem's tiles among them, the lane's tile (if any) being `lid`: in each problem the logical ids of an XCD's
+// last tiles follow one another.  -> panels listed so far
+template <int BM, int BN, int EPI>
+__device__ __forceinline__ int list_panels(const GemmArgs& g, Panel* panels, int n, bool on, uint32_t lid, bool with_a) {
+    constexpr bool CUT = EPI == EPI_PARTIAL;
+    const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    const TileWalk<BM, BN> walk(g);
+    lid = on ? lid : 0;
+    const uint32_t whole = walk.tiles_m * walk.tiles_n, part = CUT ? lid / whole : 0;
+    const auto t = walk.at(g, lid - part * whole);
+    const uint64_t k0 = CUT ? (uint64_t)part * g.part_slabs * (BK * 2) : 0;
+    const uint64_t w0 = g.w_off + (uint64_t)t.n0 * g.K * 2, w_end = g.w_off + (uint64_t)min(t.n0 + BN, g.n1) * g.K * 2;
+    const uint64_t w1 = g.W.split > w0 && g.W.split < w_end ? g.W.split : w_end;       // what lies in one buffer
+    const int lane0 = __ffsll((unsigned long long)__ballot(on)) - 1;
+    const bool new_w = on && (lane == lane0 || t.above == 0), new_a = on && with_a && lane - lane0 < t.gsz;
+    const uint64_t wm = __ballot(new_w), am = __ballot(new_a), below = (1ull << lane) - 1;
+    if (new_w) panels[n + __popcll(wm & below)] = Panel{(uint64_t)(uintptr_t)wv_ptr(g.W, w0) + k0, rsrc_bytes(w1 > w0 + k0 ? w1 - w0 - k0 : 0), (uint32_t)g.K * 2u};
+    n += __popcll(wm);
+    if (new_a) panels[n + __popcll(am & below)] =
+        Panel{(uint64_t)(uintptr_t)(g.A + (size_t)t.m0 * g.lda) + k0, rsrc_bytes(((uint64_t)(min(g.M - t.m0, BM) - 1) * g.lda + g.K) * 2 - k0), (uint32_t)g.lda * 2u};
+    return n + __popcll(am);
+}
+// tiles0, tiles0_pad, tiles: as in GemmPair; one problem: all three alike
+template <int BM, int BN, int EPI>
+__device__ __forceinline__ void gemm_idle_fetch(const GemmArgs& g0, const GemmArgs& g1, uint32_t tiles0, uint32_t tiles0_pad, uint32_t tiles, const IdleFetch& f, uint32_t bid) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    Panel* const panels = (Panel*)smem;                        // at most 2 x 32
+    int* const count = (int*)(smem + 64 * sizeof(Panel));
+    const int lane = threadIdx.x & 63, uw = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (uw == 0) {
+        const uint32_t b = (tiles & ~255u) + (bid & 7u) + 8u * lane;       // a lane per tile of the round on this XCD
+        int n = list_panels<BM, BN, EPI>(g0, panels, 0, b < tiles0, xcd_contiguous_id(b, tiles0), f.with_a);
+        if (tiles > tiles0_pad) n = list_panels<BM, BN, EPI>(g1, panels, n, b >= tiles0_pad && b < tiles, xcd_contiguous_id(b - tiles0_pad, tiles - tiles0_pad), f.with_a);
+        if (lane == 0) *count = n;
+    }
+    __syncthreads();
+    // the waves of all fetching workgroups of this XCD, two rows of a chunk each at a time
+    const uint32_t before = (tiles + 7u - (bid & 7u)) >> 3, helpers = ((tiles + f.workgroups + 7u - (bid & 7u)) >> 3) - before;
+    const uint32_t waves = helpers * 4, mine = ((bid >> 3) - before) * 4 + uw;
+    constexpr uint32_t PAIRS = (BN > BM ? BN : BM) / 2;
+    const uint32_t slabs = EPI == EPI_PARTIAL ? g0.part_slabs : g0.K / BK, pairs = (uint32_t)*count * PAIRS, chunks = (slabs + FETCH_SLABS - 1) / FETCH_SLABS;
+    const unsigned long long begin = __builtin_amdgcn_s_memrealtime();
+    for (uint32_t c = FETCH_LEAD; c < chunks; c += f.stride) {
+        unsigned long long t;
+        while ((t = __builtin_amdgcn_s_memrealtime() - begin) < (c - FETCH_LEAD) * f.ticks_per_chunk) __builtin_amdgcn_s_sleep(2);
+        if (t > f.deadline) break;
+        for (uint32_t i = mine; i < pairs; i += waves) {
+            const Panel q = panels[i / PAIRS];
+            const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)q.base), hi = __builtin_amdgcn_readfirstlane((uint32_t)(q.base >> 32));
+            const __amdgpu_buffer_rsrc_t rs = make_rsrc((const void*)(uintptr_t)((uint64_t)hi << 32 | lo), __builtin_amdgcn_readfirstlane(q.bytes));
+            const uint32_t row = (i % PAIRS) * 2 + (lane >> 5);
+            lds_bload16(rs, row * q.row_bytes + c * (FETCH_SLABS * ROWB) + (lane & 31) * 16, 0, smem + 2048 + uw * 1024);      // kept nowhere
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // before the LDS is another workgroup's
+}
+// one workgroup per CU; two problems of the largest tile take all registers as it is
+template <int BM, int BN, int S, int EPI, bool PAIR>
+constexpr bool has_idle_fetch() { return S == 0 && BM * BN > 128 * 128 && EPI != EPI_LAST_PART && !(PAIR && BM * BN == 256 * 256); }
+
 template <int BM, int BN, int S, int EPI>
-__global__ __launch_bounds__(256, (min_waves<BM, BN>())) void gemm_pair_kernel(GemmPair p) {
+__global__ __launch_bounds__(256, (min_waves<BM, BN>())) void gemm_bf16_kernel(GemmArgs g, uint32_t tiles, IdleFetch f) {
+    if (!has_idle_fetch<BM, BN, S, EPI, false>() || blockIdx.x < tiles) gemm_tile_body<BM, BN, S, EPI>(g, blockIdx.x, tiles);
+    else gemm_idle_fetch<BM, BN, EPI>(g, g, tiles, tiles, tiles, f, blockIdx.x);
+}
+template <int BM, int BN, int S, int EPI>
+__global__ __launch_bounds__(256, (min_waves<BM, BN>())) void gemm_pair_kernel(GemmPair p, IdleFetch f) {
+    if constexpr (has_idle_fetch<BM, BN, S, EPI, true>()) {
+        if (blockIdx.x >= p.tiles) { gemm_idle_fetch<BM, BN, EPI>(p.g[0], p.g[1], p.tiles0, p.tiles0_pad, p.tiles, f, blockIdx.x); return; }
+    }
     if (blockIdx.x < p.tiles0) gemm_tile_body<BM, BN, S, EPI>(p.g[0], blockIdx.x, p.tiles0);
-    else if (blockIdx.x >= p.tiles0_pad) gemm_tile_body<BM, BN, S, EPI>(p.g[1], blockIdx.x - p.tiles0_pad, gridDim.x - p.tiles0_pad);
+    else if (blockIdx.x >= p.tiles0_pad) gemm_tile_body<BM, BN, S, EPI>(p.g[1], blockIdx.x - p.tiles0_pad, p.tiles - p.tiles0_pad);
 }
 
 template <int BM, int BN, int S, int EPI>
@@ -669,6 +770,32 @@ hipError_t allow_smem(Kernel kernel, size_t smem) {
     return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
 }
 
+// A fetching workgroup gets about 50 GB/s of data that misses L2.  Where those of an XCD cannot keep up with its tiles they leave
+// the activations out, and then chunks.  `tiles`: workgroups of the launch, tiles1 of them the second problem's.
+template <int BM, int BN, int EPI>
+IdleFetch idle_fetch(const GemmArgs& g, const GemmArgs* second, uint32_t tiles, uint32_t tiles1) {
+    IdleFetch f{};
+    const uint32_t rest = tiles % 256;
+    const int slabs = EPI == EPI_PARTIAL ? g.part_slabs : g.K / BK;
+    if (rest == 0 || rest > IDLE_MOST || slabs < 4 * FETCH_SLABS) return f;
+    if (second && (g.K != second->K || g.part_slabs != second->part_slabs)) return f;
+    const double slab_us = BM * BN <= 128 * 256 ? 0.45 : BM * BN <= 192 * 256 ? 0.7 : 1.0;
+    double w_bytes = 0, a_bytes = 0;                           // per slab, of an XCD's tiles in the last round
+    for (int i = 0; i < (second ? 2 : 1); ++i) {
+        const double of = (i ? std::min(rest, tiles1) : rest - std::min(rest, tiles1)) / 8.0;
+        const double sharers = std::min(((i ? second->M : g.M) + BM - 1) / BM, 9);       // row-tiles that walk a weight panel together
+        w_bytes += std::ceil(of / sharers) * BN * ROWB;
+        a_bytes += std::min(std::ceil(of), sharers) * BM * ROWB;
+    }
+    const double can = (256 - rest) / 8 * 50e3 * slab_us;
+    f.workgroups = 256 - rest;
+    f.with_a = w_bytes + a_bytes <= can;
+    f.stride = (int)std::ceil(w_bytes / can);
+    f.ticks_per_chunk = (uint32_t)(slab_us * FETCH_SLABS * 100.0);
+    f.deadline = (uint32_t)(slabs * 2.0 * slab_us * 100.0);
+    return f;
+}
+
 template <int BM, int BN, int S, int EPI>
 hipError_t launch(const GemmArgs& g, const GemmArgs* second, hipStream_t s) {
     auto tiles = [](const GemmArgs& p) {
@@ -678,7 +805,8 @@ hipError_t launch(const GemmArgs& g, const GemmArgs* second, hipStream_t s) {
     if (!second) {
         static const hipError_t allowed = allow_smem(gemm_bf16_kernel<BM, BN, S, EPI>, smem);
         if (allowed != hipSuccess) return allowed;
-        hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, S, EPI>), dim3(tiles(g)), dim3(256), smem, s, g);
+        const IdleFetch f = has_idle_fetch<BM, BN, S, EPI, false>() ? idle_fetch<BM, BN, EPI>(g, nullptr, tiles(g), 0) : IdleFetch{};
+        hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, S, EPI>), dim3(tiles(g) + f.workgroups), dim3(256), smem, s, g, tiles(g), f);
     } else if constexpr (BM * BN == 65536 && EPI == EPI_PARTIAL) {
         return hipErrorInvalidValue;               // does not fit the registers; gemm_plan never asks for it
     } else {
@@ -689,7 +817,9 @@ hipError_t launch(const GemmArgs& g, const GemmArgs* second, hipStream_t s) {
         p.g[1] = *second;
         p.tiles0 = tiles(g);
         p.tiles0_pad = (p.tiles0 + 7u) & ~7u;
-        hipLaunchKernelGGL((gemm_pair_kernel<BM, BN, S, EPI>), dim3(p.tiles0_pad + tiles(*second)), dim3(256), smem, s, p);
+        p.tiles = p.tiles0_pad + tiles(*second);
+        const IdleFetch f = has_idle_fetch<BM, BN, S, EPI, true>() ? idle_fetch<BM, BN, EPI>(g, second, p.tiles, p.tiles - p.tiles0_pad) : IdleFetch{};
+        hipLaunchKernelGGL((gemm_pair_kernel<BM, BN, S, EPI>), dim3(p.tiles + f.workgroups), dim3(256), smem, s, p, f);
     }
     return hipGetLastError();
 }

@@ -18,13 +18,13 @@ extern "C" {
  * term): *waves_per_workgroup receives 4 (two workgroups per CU), 7 or 8 (one), each wave owning 32
  * queries.  The choice minimises an estimate of the launch's time: generations of workgroups times the
  * time of one generation, fitted to measurements.  No GPU is touched.  CF_ERR_ARG: non-positive
- * sizes, head_dim other than 64 or 128, NULL result.  cf_op_attention runs as this says; a block's attention
- * may be cut or dealt out instead (cf_plan_block_attention). */
+ * sizes, head_dim other than 64 or 128, NULL result.  cf_op_attention runs as this says, or, with few queries, with its keys in
+ * parts that go to the waves of a workgroup; a block's attention may be cut or dealt out instead (cf_plan_block_attention). */
 int cf_plan_attention(int32_t H, int32_t nq, int32_t nk, int32_t head_dim, int32_t* waves_per_workgroup);
 
 /* Host-only view of how a block launches attention, `heads` heads for each of `batch` samples: with its keys in
- * `parts` parts (1 = whole), computed by workgroups of their own and merged afterwards or (all_parts, where the
- * batch fills the chip) by one workgroup after the other; dealt out by the grid (deal 0), by the kernel in even shares (1) or as
+ * `parts` parts (1 = whole), computed by workgroups of their own and merged afterwards, or (few queries: `waves` is then the
+ * number of parts) by the waves of one workgroup, or (all_parts, where the batch fills the chip) by one workgroup after the other; dealt out by the grid (deal 0), by the kernel in even shares (1) or as
  * workgroups come for the next sweep (2), whole sweeps of 8-wave workgroups in either case; in workgroups of `waves`
  * waves.  The number of parts is a matter of one sample alone, and the bits of the result with it.  No GPU is touched. */
 typedef struct cf_attention_plan {
@@ -69,7 +69,7 @@ int cf_op_linear_residual_form(const uint16_t* A, int32_t lda, const void* blob,
 int cf_op_attention(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O,
                     int32_t H, int32_t nq, int32_t nk, int32_t nk_pad, int32_t hd, void* stream);
 /* The same in a form of the caller's choice, as a block may launch it: keys in `parts` parts, with all_parts those of
- * a query tile in one workgroup, or (parts = 1) dealt out as `deal` says; head width 128 and more than 7 * 32 query tiles of 256 for deal 1 and 2,
+ * a query tile in one workgroup, one after the other (1) or a wave to each (2; up to 8 parts, 4 with 128-wide heads), or (parts = 1) dealt out as `deal` says; head width 128 and more than 7 * 32 query tiles of 256 for deal 1 and 2,
  * more than 192 keys for deal 2.  no_wait: a workgroup that would go on
  * with a sweep begun by another does not find it, as if that one had not run in time.  scratch: 16-byte aligned; none with
  * all_parts, parts * H * ceil(nq / 32) * 32 * (hd + 2) floats, or for a deal 4096 bytes that are ZERO followed by 24 * 32 * 512 * 66 floats. */

@@ -38,28 +38,26 @@ constexpr float kNoRef = -3.402823466e38f;     // reference of a query before it
 
 __device__ __forceinline__ float max3f(float a, float b, float c) { return __builtin_fmaxf(__builtin_fmaxf(a, b), c); }
 
+// Where the output row of query q of head h goes, or NULL.
+template <int HD>
+__device__ __forceinline__ bf16* out_row(const AttnArgs& a, int h, int q) {
+    if (q >= a.nq) return nullptr;
+    const int hps = a.hps ? a.hps : a.H;            // heads per sample of a batch
+    const int b = h / hps, hh = h % hps;
+    if (!a.scatter) return a.O + (size_t)b * a.o_bs + (size_t)hh * a.o_hs + (size_t)q * a.o_qs;
+    // the second exchange by the stores themselves: this rank's positions go to the projection operand,
+    // the others to the send buffer (in ascending position order, as the receiver expects them)
+    const TokenMap& m = a.map;
+    if (q >= m.pos0 && q < m.pos0 + m.len0) return a.dst0 + (size_t)b * a.bs0 + (size_t)(q - m.pos0) * a.ld + (a.h0 + hh) * HD;
+    if (q >= m.pos1 && q < m.pos1 + m.len1) return a.dst1 + (size_t)b * a.bs1 + (size_t)(q - m.pos1) * a.ld + (a.h0 + hh) * HD;
+    const int ri = q - (q >= m.pos0 + m.len0 ? m.len0 : 0) - (q >= m.pos1 + m.len1 ? m.len1 : 0);
+    return a.send ? a.send + (size_t)b * a.send_bs + ((size_t)hh * (m.n_total - m.n_local) + ri) * HD : nullptr;
+}
+
 // Output row of query q of head h, times inv: lane = query, value(d, 4*vb + e) = column d*32 + vb*8 + lg*4 + e.
 template <int HD, class Value>
 __device__ __forceinline__ void store_rows(const AttnArgs& a, int h, int q, int lg, Value&& value, float inv) {
-    if (q >= a.nq) return;
-    const int hps = a.hps ? a.hps : a.H;            // heads per sample of a batch
-    const int b = h / hps, hh = h % hps;
-    bf16* op;
-    if (a.scatter) {
-        // the second exchange by the stores themselves: this rank's positions go to the projection operand,
-        // the others to the send buffer (in ascending position order, as the receiver expects them)
-        const TokenMap& m = a.map;
-        if (q >= m.pos0 && q < m.pos0 + m.len0) {
-            op = a.dst0 + (size_t)b * a.bs0 + (size_t)(q - m.pos0) * a.ld + (a.h0 + hh) * HD;
-        } else if (q >= m.pos1 && q < m.pos1 + m.len1) {
-            op = a.dst1 + (size_t)b * a.bs1 + (size_t)(q - m.pos1) * a.ld + (a.h0 + hh) * HD;
-        } else {
-            const int ri = q - (q >= m.pos0 + m.len0 ? m.len0 : 0) - (q >= m.pos1 + m.len1 ? m.len1 : 0);
-            op = a.send ? a.send + (size_t)b * a.send_bs + ((size_t)hh * (m.n_total - m.n_local) + ri) * HD : nullptr;
-        }
-    } else {
-        op = a.O + (size_t)b * a.o_bs + (size_t)hh * a.o_hs + (size_t)q * a.o_qs;
-    }
+    bf16* const op = out_row<HD>(a, h, q);
     if (!op) return;
 #pragma unroll
     for (int d = 0; d < HD / 32; ++d)
@@ -553,6 +551,195 @@ __global__ __launch_bounds__(512, 2) void attn_even_kernel(AttnArgs a) {
     }
 }
 
+// Keys in parts, a wave to each: the workgroup is 32 queries of a head and as many waves as there are parts, and joins them through
+// LDS in the merge kernel's order and rounding (the same bits).  For launches with so few queries that their workgroups are a few
+// dozen sweeps side by side.  Every wave copies the tiles of its part into LDS of its own and waits for nobody: the next tile's K
+// goes where this one's was as soon as the scores are computed, V after the second contraction.  Bound by the latency of a tile
+// and, from about one workgroup per CU on, by what a CU takes in (16 or 32 KB per tile that nobody shares).  (Fragments straight
+// from memory, 32 rows x 32 bytes per load, took 0.43 us per tile of 64-wide heads, however many waves shared them.)
+// 8 heads x 512 x 64: 5.8 us, whole 9.2; 3 x 2640 x 128: 26.1, whole 44.9, in parts of their own 32.4 (attn_splits has the line).
+constexpr int wave_parts_most(int hd) { return hd == 64 ? 8 : 4; }     // 16 or 32 KB of LDS each
+template <int HD>
+__global__ __launch_bounds__(64 * wave_parts_most(HD)) void attn_wave_parts_kernel(AttnArgs a) {
+    constexpr int DT = HD / 32, KS = HD / 16, QUADS = DT * 4, KCH = HD / 8, KROW = HD * 2;
+    constexpr int KL = BKV * KCH / 64, VL = HD * 8 / 64, K_RPL = 1024 / KROW;
+    constexpr int K_TILE = BKV * KROW, V_TILE = HD * 128;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int lane = threadIdx.x & 63, lj = lane & 31, lg = lane >> 5;
+    const int part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    char* const sK = smem + part * (K_TILE + V_TILE);
+    char* const sV = sK + K_TILE;
+    const int nqt = (a.nq + 31) / 32, NT = (a.nk + BKV - 1) / BKV;
+    const uint32_t lid = xcd_contiguous_id(blockIdx.x, gridDim.x);
+    const int h = lid / nqt, q0 = lid % nqt * 32;
+    const int T0 = part * a.part_tiles, T1 = min(NT, T0 + a.part_tiles);       // every part has a tile (attn_check)
+    const float c2 = a.scale * 1.4426950408889634f;
+    const int krow = (lj & 0x13) | ((lj & 4) << 1) | ((lj & 8) >> 1);
+    auto kswz = [](int key) { return HD == 128 ? (key & 15) : (((key >> 1) & 7) ^ ((key & 1) << 2)); };        // as attn_sweep
+    auto vswz = [](int row) { return ((row >> 1) & 7) ^ ((row & 1) << 2); };
+    const __amdgpu_buffer_rsrc_t k_rsrc = make_rsrc(a.K + (size_t)h * a.nk * HD, (uint64_t)a.nk * KROW);
+    const __amdgpu_buffer_rsrc_t v_rsrc = make_rsrc(a.Vt + (size_t)h * HD * a.nk_pad, (uint64_t)HD * a.nk_pad * 2);
+    auto issue_k = [&](int t) __attribute__((always_inline)) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // this wave's reads of the tile before have returned
+#pragma unroll
+        for (int j = 0; j < KL; ++j) {
+            const int key = j * K_RPL + lane / KCH;
+            lds_bload16(k_rsrc, (uint32_t)key * KROW + (((lane % KCH) ^ kswz(key)) << 4), (uint32_t)t * K_TILE, sK + j * 1024);
+        }
+    };
+    auto issue_v = [&](int t) __attribute__((always_inline)) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int j = 0; j < VL; ++j) {
+            const int row = j * 8 + (lane >> 3);
+            lds_bload16(v_rsrc, (uint32_t)row * (uint32_t)a.nk_pad * 2 + (((lane & 7) ^ vswz(row)) << 4), (uint32_t)t * (BKV * 2), sV + j * 1024);
+        }
+    };
+    auto landed = [](auto younger) __attribute__((always_inline)) {            // all but the `younger` last copies of this wave
+        constexpr int N = decltype(younger)::value;
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+        asm volatile("" ::: "memory");
+    };
+    bf16x8 qf[KS];
+    {
+        const bf16* const qp = a.Q + ((size_t)h * a.nq + min(q0 + lj, a.nq - 1)) * HD + lg * 8;
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) qf[kk] = *(const bf16x8*)(qp + kk * 16);
+    }
+    floatx16 o[DT];
+    float mc, l_run;
+    int out_of_range;
+    // as attn_sweep's tiles: the same products in the same order
+    auto tile = [&](int t, bool more, auto tracking_c) __attribute__((always_inline)) {
+        constexpr bool tracking = decltype(tracking_c)::value;
+        landed(std::integral_constant<int, VL>{});
+        floatx16 s[2];
+#pragma unroll
+        for (int i = 0; i < 2 * KS; ++i) {
+            const int key = (i & 1) * 32 + krow, c = (i >> 1) * 2 + lg;
+            const bf16x8 kf = *(const bf16x8*)(sK + key * KROW + ((c ^ kswz(key)) << 4));
+            if (i < 2) {
+                floatx16 z;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) z[v] = 0.f;
+                s[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[i >> 1], z, 0, 0, 0);
+            } else {
+                s[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[i >> 1], s[i & 1], 0, 0, 0);
+            }
+        }
+        if (more) issue_k(t + 1);
+        if (t * BKV + BKV > a.nk) {
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    if (t * BKV + mt * 32 + 16 * (v >> 3) + 8 * lg + (v & 7) >= a.nk) s[mt][v] = -INFINITY;
+        }
+        if constexpr (tracking) {
+            float mx = s[0][0];
+#pragma unroll
+            for (int v = 1; v < 32; ++v) mx = fmaxf(mx, s[v >> 4][v & 15]);
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float mc_new = fmaxf(mc, mx * c2), alpha = __builtin_amdgcn_exp2f(mc - mc_new);
+            l_run *= alpha;
+#pragma unroll
+            for (int d = 0; d < DT; ++d)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o[d][v] *= alpha;
+            mc = mc_new;
+        }
+        bf16x8 pf[4];
+        float ps[4] = {0.f, 0.f, 0.f, 0.f};
+        bf16x2 ones;
+        ones[0] = (bf16)1.0f;
+        ones[1] = (bf16)1.0f;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+            for (int e = 0; e < 8; e += 2) {
+                bf16x2 pp;
+                pp[0] = (bf16)__builtin_amdgcn_exp2f(fmaf(s[ks >> 1][8 * (ks & 1) + e], c2, -mc));
+                pp[1] = (bf16)__builtin_amdgcn_exp2f(fmaf(s[ks >> 1][8 * (ks & 1) + e + 1], c2, -mc));
+                pf[ks][e] = pp[0];
+                pf[ks][e + 1] = pp[1];
+                ps[(e >> 1) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, ps[(e >> 1) & 3], false);
+            }
+        const float psum = (ps[0] + ps[1]) + (ps[2] + ps[3]);
+        l_run += psum;
+        if (more) landed(std::integral_constant<int, KL>{});
+        else landed(std::integral_constant<int, 0>{});
+#pragma unroll
+        for (int i = 0; i < QUADS; ++i) {
+            const int row = (i % DT) * 32 + lj, c = (i / DT) * 2 + lg;
+            const bf16x8 vf = *(const bf16x8*)(sV + row * 128 + ((c ^ vswz(row)) << 4));
+            o[i % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[i / DT], o[i % DT], 0, 0, 0);
+        }
+        if (more) issue_v(t + 1);
+        if constexpr (!tracking) {
+            const float row = psum + __shfl_xor(psum, 32);
+            if (__any(!(row < 1048576.0f))) {
+                if (__any(!(row < 18446744073709551616.0f))) {
+                    out_of_range = 1;
+                } else {
+                    const int e = row < 1048576.0f ? 0 : (int)(__float_as_uint(row) >> 23) - 127;
+                    const float alpha = __uint_as_float((uint32_t)(127 - e) << 23);
+                    mc += (float)e;
+                    l_run *= alpha;
+#pragma unroll
+                    for (int d = 0; d < DT; ++d)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) o[d][v] *= alpha;
+                }
+            }
+        }
+    };
+    auto sweep = [&](auto tracking_c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int d = 0; d < DT; ++d)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) o[d][v] = 0.f;
+        mc = kNoRef;
+        l_run = 0.f;
+        out_of_range = 0;
+        issue_k(T0);
+        issue_v(T0);
+        tile(T0, T0 + 1 < T1, std::true_type{});
+        for (int t = T0 + 1; t < T1; ++t) tile(t, t + 1 < T1, tracking_c);
+    };
+    sweep(std::false_type{});
+    if (out_of_range) sweep(std::true_type{});
+    // joined in the order of the parts; of the row's QUADS pieces wave w puts together every parts-th
+    auto po = [&](int p) { return (float*)(smem + p * (K_TILE + V_TILE)); };       // of part p, where its tiles were: [QUADS][64 * 4]
+    auto ml = [&](int p) { return po(p) + QUADS * 256; };                          // [64 * 2]
+    static_assert(QUADS * 1024 + 512 <= K_TILE + V_TILE, "a part's result in place of its tiles");
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");         // this wave's last reads of them
+#pragma unroll
+    for (int i = 0; i < QUADS; ++i)
+        *(floatx4*)(po(part) + i * 256 + lane * 4) = floatx4{o[i / 4][i % 4 * 4], o[i / 4][i % 4 * 4 + 1], o[i / 4][i % 4 * 4 + 2], o[i / 4][i % 4 * 4 + 3]};
+    *(float2*)(ml(part) + lane * 2) = make_float2(mc, l_run + __shfl_xor(l_run, 32));
+    __syncthreads();
+    bf16* const op = out_row<HD>(a, h, q0 + lj);
+    for (int i = part; i < QUADS; i += a.splits) {
+        float m = kNoRef, l = 0.f;
+        floatx4 sum = {0.f, 0.f, 0.f, 0.f};
+        for (int p = 0; p < a.splits; ++p) {
+            const float2 mp = *(const float2*)(ml(p) + lane * 2);
+            const floatx4 v = *(const floatx4*)(po(p) + i * 256 + lane * 4);
+            const Joint f = join_part(m, l, mp.x, mp.y);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) sum[c] = f.join(sum[c], v[c]);
+        }
+        const float inv = 1.0f / l;
+        if (op) {
+            bf16x4 w;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) w[c] = (bf16)(sum[c] * inv);
+            *(bf16x4*)(op + i / 4 * 32 + i % 4 * 8 + lg * 4) = w;
+        }
+    }
+}
+
 // Puts the parts of the keys together: a wave per 32 queries of a head, lanes as in attn_fwd_kernel, parts in order.
 // Bound by the partial results it reads (3 heads x 4608 queries in four parts: 28 MB).
 template <int HD>
@@ -644,6 +831,7 @@ const char* attn_check(const AttnArgs& a) {
         return "attention: bad split of the keys";
     if (a.splits > 1 && !a.all_parts && (!a.part_o || !a.part_ml || (((uintptr_t)a.part_o | (uintptr_t)a.part_ml) % 16)))
         return "attention: no scratch for the parts of the keys";
+    if (a.all_parts == ALL_PARTS_WAVES && (a.splits > wave_parts_most(a.hd) || (long)((a.nq + 31) / 32) * a.H > 0x7fffffffL)) return "attention: too many parts for the waves of a workgroup";
     if (a.all_parts && a.splits < 2) return "attention: no parts for a workgroup to have all of";
     if (a.even_state && (a.splits > 1 || !a.even_flags || ((uintptr_t)a.even_state % 16) || a.hd != 128 || (long)((a.nq + 255) / 256) * a.H <= 7 * 32))
         return "attention: launch cannot be dealt out by the kernel";
@@ -693,46 +881,64 @@ int attn_waves(const AttnArgs& a) {
 // Key tiles of a part: an even number, so that every part begins in the same one of the two tile buffers.
 static int tiles_per_part(int tiles, int parts) { return parts > 1 ? ((tiles + parts - 1) / parts + 1) & ~1 : tiles; }
 
-// Parts the keys of a launch are cut into.  Few heads over a short sequence (a Ulysses rank's share at degree 4 or 8)
+// Estimated time in us, past the launch itself, of parts of `per` tiles with a wave to each, `items` = 32-query tiles of all heads.
+// A wave's step takes 0.5 us and 0.135 for each wave of its CU with 64-wide heads, of which a CU holds eight, 0.92 and 0.2 with
+// 128-wide ones (four; one workgroup per CU).
+static double wave_parts_us(long items, int per, int parts, int hd) {
+    const long per_cu = hd == 64 ? std::min((items + 255) / 256, (long)std::max(1, 8 / parts)) : 1;
+    const double gens = (double)((items + 256 * per_cu - 1) / (256 * per_cu));
+    return hd == 64 ? gens * (per * (0.5 + 0.135 * parts * per_cu) + 2.0) - 1.4 : gens * (per * (0.92 + 0.2 * parts) + 2.0) + 0.5;
+}
+
+// Parts the keys of a launch are cut into.  Few heads over a short sequence (a Ulysses rank's share at degree 4 or 8, the toy model)
 // are a few dozen workgroups that each sweep all keys; cut into parts they fill the chip, at the price of writing the
-// partial results and merging them.  Estimated time in us for 128-wide heads: a tile takes a 4-wave workgroup 0.97 alone
+// partial results and merging them, or, where there are fewer queries still, the parts go to the waves of one workgroup, which costs
+// neither.  Estimated time in us for 128-wide heads: a tile takes a 4-wave workgroup 0.97 alone
 // on its CU and 1.7 beside another, the merge 10 us and one pass over the partial results at 4 TB/s (3 heads x 4608: 72 us
-// whole, 51 in two or four parts; 12 heads x 2640: 51 us whole, 58 in two).  A function of one sample's heads and lengths
-// only, so that a sample's result does not depend on the batch it is part of; parts of at least 6 tiles (8 with 64-wide heads),
-// so that a batch that fills the chip, and whose workgroups have all parts, loses no more than a few per cent by joining them.
+// whole, 51 in two or four parts; 12 heads x 2640: 51 us whole, 58 in two).  A wave to each part (whole / parts and merge / waves):
+// 8 x 512 x 64 9.2 / 11.1 / 5.8, 8 x 1024 x 64 14.7 / 14.8 / 7.8, 2 x 2048 x 64 24 / 16.2 / 11.8, 3 x 1000 x 128 20.5 / 20.2 / 12.4,
+// 3 x 2640 x 128 44.9 / 32.4 / 26.1, 3 x 4608 x 128 72 / 51.6 / 67.6, 1 x 6000 x 128 92 / 42.0 / 47.1.  A function of one sample's
+// heads and lengths only, so that a sample's result does not depend on the batch it is part of; parts of at least 6 tiles (8 with
+// 64-wide heads) where they are workgroups, so that a batch that fills the chip, and whose workgroups have all parts, loses no more
+// than a few per cent by joining them, and of 2 where they are waves (64 heads x 512 x 64: 11.0 us whole, 11.5 in four parts).
 int attn_splits(int heads, int nq, int nk, int hd) {
-    const long items = (long)((nq + 127) / 128) * heads;
+    const long items = (long)((nq + 127) / 128) * heads, items32 = (long)((nq + 31) / 32) * heads;
     const int tiles = (nk + BKV - 1) / BKV, least = hd == 64 ? 8 : 6;
     int best = 1;
     double best_us = 0;
     for (int s = 1; s <= 8; ++s) {
         const int per = tiles_per_part(tiles, s);
-        if (s > 1 && (per < least || (tiles + per - 1) / per != s)) continue;
+        if (s > 1 && (per < 2 || (tiles + per - 1) / per != s)) continue;
         const long wgs = items * s;
-        if (s > 1 && wgs > 512) break;
-        double us = (wgs <= 256 ? 0.97 * per : 1.7 * per * (double)((wgs + 511) / 512)) * (hd == 64 ? 0.55 : 1.0) + 3.0;
-        if (s > 1) us += 10.0 + 4.0 * s * (double)heads * nq * hd / 4e6;
+        double us = 1e30;
+        if (s == 1 || (per >= least && wgs <= 512)) {
+            us = (wgs <= 256 ? 0.97 * per : 1.7 * per * (double)((wgs + 511) / 512)) * (hd == 64 ? 0.55 : 1.0) + 3.0;
+            if (s > 1) us += 10.0 + 4.0 * s * (double)heads * nq * hd / 4e6;
+        }
+        if (s > 1 && s <= wave_parts_most(hd)) us = std::min(us, 3.0 + wave_parts_us(items32, per, s, hd));
         if (s == 1 || us < 0.95 * best_us) best = s, best_us = us;
     }
     return best;
 }
 
-// Whether a workgroup has all parts of its queries, for the heads of all samples together: where the query tiles alone fill the
-// chip, the parts only cost (12 heads x 4608 x 128, four samples: 115 us in one sweep, 136 in two parts and their merge, 115 with
+// Whether a workgroup has all parts of its queries, for the heads of all samples together, and how: where the query tiles alone fill the
+// chip, parts that are workgroups only cost (12 heads x 4608 x 128, four samples: 115 us in one sweep, 136 in two parts and their merge, 115 with
 // both in one workgroup).  Estimated in us, n = 4-wave workgroups per CU: a tile takes each CU 0.97 + 0.25 n up to one of them and
 // 0.25 + 0.97 n from there on with 128-wide heads, 0.45 + 0.48 n and at least 0.68 with 64-wide ones; joining a part costs
 // half a tile, the merge 6 us and a pass over the partial results at 4 TB/s.  (3 heads x 4608 for 1, 2, 3, 4, 8 samples, in parts /
 // in one workgroup: 55/74, 78/81, 126/108, 146/126, 286/248; 3 x 2640: 34/46, 44/47, -, 65/54, 119/95; 2 x 4696 x 64 for 1, 4, 16:
-// 29/51, 64/75, 210/199.)
-bool attn_all_parts(int heads, int nq, int nk, int hd, int splits) {
-    if (splits <= 1) return false;
+// 29/51, 64/75, 210/199.)  With a wave to each part: wave_parts_us.
+int attn_all_parts(int heads, int nq, int nk, int hd, int splits) {
+    if (splits <= 1) return 0;
     const double tiles = (nk + BKV - 1) / BKV, items = (double)((nq + 127) / 128) * heads;
     auto sweeps = [&](double wgs, double t) {
         const double n = wgs / 256.0;
         return t * (hd == 64 ? std::max(0.68, 0.45 + 0.48 * n) : n <= 1.0 ? 0.97 + 0.25 * n : 0.25 + 0.97 * n);
     };
-    const double parts = sweeps(items * splits, tiles_per_part((int)tiles, splits)) + 6.0 + 4.0 * splits * (double)heads * nq * hd / 4e6;
-    return sweeps(items, tiles + 0.5 * (splits - 1)) < parts;
+    const int per = tiles_per_part((int)tiles, splits);
+    const double parts = sweeps(items * splits, per) + 6.0 + 4.0 * splits * (double)heads * nq * hd / 4e6, in_turn = sweeps(items, tiles + 0.5 * (splits - 1));
+    if (splits <= wave_parts_most(hd) && wave_parts_us((long)((nq + 31) / 32) * heads, per, splits, hd) < std::min(parts, in_turn)) return ALL_PARTS_WAVES;
+    return in_turn < parts ? ALL_PARTS_IN_TURN : 0;
 }
 
 uint64_t attn_part_floats(int heads, int nq, int hd, int splits) {
@@ -797,8 +1003,18 @@ static hipError_t launch_even(const AttnArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <int HD>
+static hipError_t launch_wave_parts(const AttnArgs& a, hipStream_t s) {
+    const size_t smem = (size_t)a.splits * (BKV * HD * 2 + HD * 128);
+    static const hipError_t allowed = hipFuncSetAttribute((const void*)attn_wave_parts_kernel<HD>, hipFuncAttributeMaxDynamicSharedMemorySize, wave_parts_most(HD) * (BKV * HD * 2 + HD * 128));
+    if (allowed != hipSuccess) return allowed;
+    hipLaunchKernelGGL(attn_wave_parts_kernel<HD>, dim3((a.nq + 31) / 32 * a.H), dim3(64 * a.splits), smem, s, a);
+    return hipGetLastError();
+}
+
 hipError_t attn_launch(const AttnArgs& a, hipStream_t s) {
     if (a.even_state) return launch_even(a, s);
+    if (a.all_parts == ALL_PARTS_WAVES) return a.hd == 128 ? launch_wave_parts<128>(a, s) : launch_wave_parts<64>(a, s);
     const int nw = attn_waves(a);
     const hipError_t e = a.hd == 128 ? launch_nw<128>(nw, a, s) : launch_nw<64>(nw, a, s);
     if (e != hipSuccess || a.splits <= 1 || a.all_parts) return e;

@@ -1003,9 +1003,10 @@ int cf_plan_block_attention(int32_t heads, int32_t batch, int32_t nq, int32_t nk
     a.H = heads * batch; a.nq = nq; a.nk = nk; a.hd = head_dim;
     attn_set_split(&a, attn_splits(heads, nq, nk, head_dim), nullptr);
     plan->parts = a.splits;
-    plan->all_parts = a.all_parts = attn_all_parts(a.H, nq, nk, head_dim, a.splits);
+    a.all_parts = attn_all_parts(a.H, nq, nk, head_dim, a.splits);
+    plan->all_parts = a.all_parts == ALL_PARTS_IN_TURN;
     plan->deal = attn_deal(a.H, nq, nk, head_dim, a.splits);
-    plan->waves = plan->deal ? 8 : attn_waves(a);
+    plan->waves = plan->deal ? 8 : a.all_parts == ALL_PARTS_WAVES ? a.splits : attn_waves(a);
     return CF_OK;
 }
 
@@ -1456,6 +1457,13 @@ int cf_op_attention(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, ui
     a.scale = 1.0f / sqrtf((float)hd);
     attn_set_split(&a, 1, nullptr);
     if (const char* msg = attn_check(a)) return cf_fail(nullptr, CF_ERR_ARG, "%s", msg);
+    // no scratch here: whole sweeps, or parts that are a workgroup's waves
+    const int parts = attn_splits(H, nq, nk, hd);
+    if (attn_all_parts(H, nq, nk, hd, parts) == ALL_PARTS_WAVES) {
+        attn_set_split(&a, parts, nullptr);
+        a.all_parts = ALL_PARTS_WAVES;
+        if (const char* msg = attn_check(a)) return cf_fail(nullptr, CF_ERR_ARG, "%s", msg);
+    }
     hipError_t e = attn_launch(a, (hipStream_t)stream);
     return e == hipSuccess ? CF_OK : cf_fail(nullptr, CF_ERR_HIP, "attention launch: %s", hipGetErrorString(e));
 }
@@ -1472,7 +1480,7 @@ int cf_op_attention_form(const uint16_t* Q, const uint16_t* K, const uint16_t* V
     const uint64_t need = 4 * (deal ? ATTN_FLAGS + attn_deal_floats(deal) : (all_parts ? 0 : attn_part_floats(H, nq, hd, parts)));
     if (need && (!scratch || scratch_bytes < need)) return cf_fail(nullptr, CF_ERR_ARG, "attention: this form needs %llu bytes of scratch", (unsigned long long)need);
     attn_set_split(&a, parts, (float*)scratch);
-    a.all_parts = all_parts != 0;
+    a.all_parts = all_parts == ALL_PARTS_WAVES ? ALL_PARTS_WAVES : all_parts != 0;
     attn_set_deal(&a, deal, (float*)scratch + ATTN_FLAGS, (uint32_t*)scratch);
     a.even_wait = !no_wait;
     if (const char* msg = attn_check(a)) return cf_fail(nullptr, CF_ERR_ARG, "%s", msg);

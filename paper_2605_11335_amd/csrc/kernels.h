@@ -84,7 +84,8 @@ struct AttnArgs {
     long bs0, bs1, send_bs;
     // The keys in `splits` parts of part_tiles 64-key tiles each (attn_set_split), merged by a second kernel; 1 = whole.
     // Scratch, float: part_o [splits][H][ceil(nq/32)][32 * hd] in register order, part_ml [..][32] (reference, row sum).
-    // all_parts: a workgroup has all parts of its queries, one after the other, and merges them itself: same bits, no scratch.
+    // all_parts: a workgroup has all parts of its queries, one after the other or a wave to each, and merges them itself: same bits,
+    // no scratch.
     int splits, part_tiles, all_parts;
     float *part_o, *part_ml;
     // Sweeps dealt out by the kernel (attn_set_deal) instead of one workgroup per query tile; state NULL = no.  Scratch: the
@@ -94,8 +95,9 @@ struct AttnArgs {
     uint32_t* even_flags;
     int even_units, even_last, even_cuts, even_wait;
 };
+enum { ALL_PARTS_IN_TURN = 1, ALL_PARTS_WAVES = 2 };      // AttnArgs::all_parts
 int attn_splits(int heads, int nq, int nk, int hd);      // parts to cut the keys into, for one sample's heads
-bool attn_all_parts(int heads, int nq, int nk, int hd, int splits);    // for all samples' heads: a workgroup has all parts of its queries
+int attn_all_parts(int heads, int nq, int nk, int hd, int splits);     // for all samples' heads: AttnArgs::all_parts
 uint64_t attn_part_floats(int heads, int nq, int hd, int splits);      // scratch for all samples' heads, parts apart; 0 if splits is 1
 void attn_set_split(AttnArgs* a, int splits, float* scratch);          // after H, nq, nk and hd are set
 int attn_deal(int H, int nq, int nk, int hd, int splits);              // how the sweeps of all samples' heads are dealt out: 0 by the grid, 1 even, 2 drawn

@@ -26,7 +26,8 @@ int cf_plan_attention(int32_t H, int32_t nq, int32_t nk, int32_t head_dim, int32
  * `parts` parts (1 = whole), computed by workgroups of their own and merged afterwards, or (few queries: `waves` is then the
  * number of parts) by the waves of one workgroup, or (all_parts, where the batch fills the chip) by one workgroup after the other; dealt out by the grid (deal 0), by the kernel in even shares (1) or as
  * workgroups come for the next sweep (2), whole sweeps of 8-wave workgroups in either case; in workgroups of `waves`
- * waves.  The number of parts is a matter of one sample alone, and the bits of the result with it.  No GPU is touched. */
+ * waves.  The number of parts is a matter of one sample alone, and the bits of the result with it (whatever the scores: also
+ * where those of 32 queries make their sweep start over, see attention.hip).  No GPU is touched. */
 typedef struct cf_attention_plan {
     int32_t waves, parts, all_parts, deal;
 } cf_attention_plan;

@@ -113,9 +113,11 @@ __device__ __forceinline__ Joint join_part(float& m, float& l, float mc, float l
 // One sweep of a workgroup (NW waves of 32 queries each, the wave's first at q0) over the key tiles [T0, T1) of head h.
 // `from`: not NULL = go on from the state another workgroup left there after the tiles before T0 (store_state).
 // repeat() is asked where a tile was out of the fast softmax's range: whether the sweep is to be repeated here; if not, finish
-// is not called.  finish(o, mc, l) gets O^T, the reference it is taken against and the lane's row sum.
+// is not called.  In a repeated sweep the waves that were in range compute what they did before: a query's bits depend on the 32
+// queries of its wave, and not on how many waves a workgroup has or whose keys are in parts.  finish(o, mc, l) gets O^T, the reference it is taken against and the lane's row sum.
 // ALL_PARTS: the tiles are parts of a.part_tiles (an even number) one after the other, each swept as by a workgroup of its own
 // and joined to the ones before (join_part) in registers; the copies run on from part to part.
+enum { FIRST, FAST, REPEATED };                 // tiles: of a sweep's beginning, of its rest, of the rest of a repeated one
 template <int HD, int NW, bool ALL_PARTS, class Repeat, class Finish>
 __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int T0, int T1, const float* from, Repeat&& repeat, Finish&& finish) {
     constexpr int KCH = HD / 8;                 // 16-byte chunks per K row
@@ -190,6 +192,7 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
     const int krow = (lj & 0x13) | ((lj & 4) << 1) | ((lj & 8) >> 1);
 
     int out_of_range = 0;                       // wave-uniform: a fast tile met scores it could not take
+    bool tracks = false;                        // of a repeated sweep, wave-uniform: tiles past the first track, too
     const int T_end = T1;                       // of the copies
 
     // One tile.  The LDS buffer is a compile-time constant so that fragment addresses are a per-lane
@@ -198,15 +201,15 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
     // Softmax is invariant to the reference its exponentials are taken against, as long as numerator and
     // denominator share it; magnitudes only have to stay inside the fp32 / bf16 range, whose relative
     // precision does not depend on scale.  A tracking tile does what online softmax usually does: take
-    // the tile's maximum, move the reference there, rescale O^T and the row sum.  A fast tile takes no
+    // the tile's maximum, move the reference there, rescale O^T and the row sum (of the first tile, which always tracks, there is
+    // nothing to rescale).  A fast tile takes no
     // maximum: it forms P^T = exp2(s * c2 - mc) against the reference it inherits (one FMA, one exp2 and
     // half a conversion per score) and looks at the row sums afterwards.  A query whose 64 values add
     // up to 2^20 or more has its reference, O^T and row sum shifted by a whole power of two (exact); if
     // they add up to 2^64 or more, or to no number (exp2 overflowed), the tile is declared out of range:
-    // nothing is repaired on the spot, the workgroup repeats the whole sweep with tracking tiles.
-    auto tile = [&](int t, auto buf_c, auto tracking_c) __attribute__((always_inline)) {
-        constexpr int buf = decltype(buf_c)::value;
-        constexpr bool tracking = decltype(tracking_c)::value;
+    // nothing is repaired on the spot, the workgroup repeats the whole sweep, and this wave its own with tracking tiles.
+    auto tile = [&](int t, auto buf_c, auto mode_c) __attribute__((always_inline)) {
+        constexpr int buf = decltype(buf_c)::value, mode = decltype(mode_c)::value;
         if (t + 1 < T_end) issue_tile(t + 1, buf ^ 1);
         const char* cK = sK + buf * K_TILE;
         const char* cV = sV + buf * V_TILE;
@@ -266,7 +269,8 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
         // the three phases apart and leaving the overlap to the SIMD's other wave.
         __builtin_amdgcn_sched_barrier(0);
 
-        if constexpr (tracking) {
+        float alpha = 1.f;
+        if (mode == FIRST || (mode == REPEATED && tracks)) {
             float mx;                                   // the lane's 32 scores: a tree of three-input maxima
             {
                 float m3[11];
@@ -278,12 +282,13 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
             }
             mx = fmaxf(mx, __shfl_xor(mx, 32));
             const float mc_new = fmaxf(mc, mx * c2);                             // -inf where all scores are: mc stays
-            const float alpha = __builtin_amdgcn_exp2f(mc - mc_new);             // 0 from kNoRef
-            l_run *= alpha;
+            if constexpr (mode == REPEATED) {
+                alpha = __builtin_amdgcn_exp2f(mc - mc_new);                     // 0 from kNoRef
 #pragma unroll
-            for (int d = 0; d < DT; ++d)
+                for (int d = 0; d < DT; ++d)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) o[d][v] *= alpha;
+                    for (int v = 0; v < 16; ++v) o[d][v] *= alpha;
+            }
             mc = mc_new;
         }
 
@@ -310,7 +315,7 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
                 }
             psum = (ps[0] + ps[1]) + (ps[2] + ps[3]);
         }
-        l_run += psum;
+        l_run = mode == REPEATED ? fmaf(l_run, alpha, psum) : l_run + psum;
         __builtin_amdgcn_sched_barrier(0);
 
         // ---- O^T += V^T . P^T: MFMA i handles k-step (i / DT) of 16 keys and d-tile (i % DT);
@@ -329,7 +334,7 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
             __builtin_amdgcn_sched_group_barrier(0x008, 4, 1);
         }
 
-        if constexpr (!tracking) {
+        if (mode == FAST || (mode == REPEATED && !tracks)) {
             const float row = psum + __shfl_xor(psum, 32);
             if (__any(!(row < 1048576.0f))) {
                 if (__any(!(row < 18446744073709551616.0f))) {
@@ -351,7 +356,7 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
         __syncthreads();                        // tile t+1 has landed, tile t may be overwritten
     };
     // One sweep: the first tile tracks (it sets the reference) unless the state is inherited, the others go in pairs.
-    auto sweep = [&](auto tracking_c, bool landed) __attribute__((always_inline)) {
+    auto sweep = [&](auto mode_c, bool landed) __attribute__((always_inline)) {
         int t = T0;
         if (from) {
             load_state<HD>(from, wave, lane, o, mc, l_run);
@@ -368,14 +373,15 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
                 issue_tile(t, 0);
                 __syncthreads();
             }
-            tile(t, std::integral_constant<int, 0>{}, std::true_type{});
+            tile(t, std::integral_constant<int, 0>{}, std::integral_constant<int, FIRST>{});
             ++t;
         }
         for (; t < T1; t += 2) {
-            tile(t, std::integral_constant<int, 1>{}, tracking_c);
-            if (t + 1 < T1) tile(t + 1, std::integral_constant<int, 0>{}, tracking_c);
+            tile(t, std::integral_constant<int, 1>{}, mode_c);
+            if (t + 1 < T1) tile(t + 1, std::integral_constant<int, 0>{}, mode_c);
         }
     };
+    // the K/V tiles are the workgroup's: if any wave met a tile out of range, all of them go again
     if constexpr (ALL_PARTS) {
         floatx16 sum[DT];                       // the parts so far
         float m_sum = kNoRef, l_sum = 0.f;
@@ -383,13 +389,13 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
         for (int d = 0; d < DT; ++d)
 #pragma unroll
             for (int v = 0; v < 16; ++v) sum[d][v] = 0.f;
-        for (int t0 = T0; t0 < T_end; t0 += a.part_tiles) {
-            T0 = t0;
-            T1 = min(T_end, t0 + a.part_tiles);
-            sweep(std::false_type{}, t0 > 0);
+        for (T0 = 0; T0 < T_end; T0 += a.part_tiles) {
+            T1 = min(T_end, T0 + a.part_tiles);
+            sweep(std::integral_constant<int, FAST>{}, T0 > 0);
             if (__syncthreads_or(out_of_range)) {
+                tracks = out_of_range != 0;
+                sweep(std::integral_constant<int, REPEATED>{}, false);
                 out_of_range = 0;
-                sweep(std::true_type{}, false);
             }
             const Joint f = join_part(m_sum, l_sum, mc, l_run + __shfl_xor(l_run, 32));
 #pragma unroll
@@ -399,11 +405,11 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
         }
         finish(sum, m_sum, l_sum);
     } else {
-        sweep(std::false_type{}, false);
-        // the K/V tiles are the workgroup's: if any wave met a tile out of range, all of them go again
+        sweep(std::integral_constant<int, FAST>{}, false);
         if (__syncthreads_or(out_of_range)) {
             if (!repeat()) return;
-            sweep(std::true_type{}, false);
+            tracks = out_of_range != 0;
+            sweep(std::integral_constant<int, REPEATED>{}, false);
         }
         finish(o, mc, l_run);
     }
@@ -412,7 +418,7 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
 // NW waves of 32 queries each per workgroup: 4 (two workgroups per CU), 7 or 8 (one per CU); for 64-wide heads twice as many,
 // held to the 128 registers that takes: at 129 a CU has one 7-wave workgroup and 8 heads x 20892 take 1.11 ms instead of 0.90.
 // PARTS: the keys are cut (a.splits > 1), each part for a workgroup of its own, the results go to scratch.  ALL_PARTS: cut alike,
-// and a workgroup has all parts of its queries, for which it holds a second O^T: 246 to 250 registers with 128-wide heads; 162 with
+// and a workgroup has all parts of its queries, for which it holds a second O^T: 247 to 251 registers with 128-wide heads; 163 with
 // 64-wide ones, where three 4-wave workgroups then share a CU, which costs no time (32 heads x 4696: 198.4 us whole, 198.6).
 enum { WHOLE, PARTS, ALL_PARTS };
 template <int HD, int NW, int FORM>
@@ -610,9 +616,9 @@ __global__ __launch_bounds__(64 * wave_parts_most(HD)) void attn_wave_parts_kern
     floatx16 o[DT];
     float mc, l_run;
     int out_of_range;
-    // as attn_sweep's tiles: the same products in the same order
-    auto tile = [&](int t, bool more, auto tracking_c) __attribute__((always_inline)) {
-        constexpr bool tracking = decltype(tracking_c)::value;
+    // as attn_sweep's tiles: the same products in the same order.  (A repeated sweep is this wave's alone, and tracks.)
+    auto tile = [&](int t, bool more, auto mode_c) __attribute__((always_inline)) {
+        constexpr int mode = decltype(mode_c)::value;
         landed(std::integral_constant<int, VL>{});
         floatx16 s[2];
 #pragma unroll
@@ -636,17 +642,20 @@ __global__ __launch_bounds__(64 * wave_parts_most(HD)) void attn_wave_parts_kern
                 for (int v = 0; v < 16; ++v)
                     if (t * BKV + mt * 32 + 16 * (v >> 3) + 8 * lg + (v & 7) >= a.nk) s[mt][v] = -INFINITY;
         }
-        if constexpr (tracking) {
+        float alpha = 1.f;
+        if constexpr (mode != FAST) {
             float mx = s[0][0];
 #pragma unroll
             for (int v = 1; v < 32; ++v) mx = fmaxf(mx, s[v >> 4][v & 15]);
             mx = fmaxf(mx, __shfl_xor(mx, 32));
-            const float mc_new = fmaxf(mc, mx * c2), alpha = __builtin_amdgcn_exp2f(mc - mc_new);
-            l_run *= alpha;
+            const float mc_new = fmaxf(mc, mx * c2);
+            if constexpr (mode == REPEATED) {
+                alpha = __builtin_amdgcn_exp2f(mc - mc_new);
 #pragma unroll
-            for (int d = 0; d < DT; ++d)
+                for (int d = 0; d < DT; ++d)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) o[d][v] *= alpha;
+                    for (int v = 0; v < 16; ++v) o[d][v] *= alpha;
+            }
             mc = mc_new;
         }
         bf16x8 pf[4];
@@ -666,7 +675,7 @@ __global__ __launch_bounds__(64 * wave_parts_most(HD)) void attn_wave_parts_kern
                 ps[(e >> 1) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, ps[(e >> 1) & 3], false);
             }
         const float psum = (ps[0] + ps[1]) + (ps[2] + ps[3]);
-        l_run += psum;
+        l_run = mode == REPEATED ? fmaf(l_run, alpha, psum) : l_run + psum;
         if (more) landed(std::integral_constant<int, KL>{});
         else landed(std::integral_constant<int, 0>{});
 #pragma unroll
@@ -676,7 +685,7 @@ __global__ __launch_bounds__(64 * wave_parts_most(HD)) void attn_wave_parts_kern
             o[i % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[i / DT], o[i % DT], 0, 0, 0);
         }
         if (more) issue_v(t + 1);
-        if constexpr (!tracking) {
+        if constexpr (mode == FAST) {
             const float row = psum + __shfl_xor(psum, 32);
             if (__any(!(row < 1048576.0f))) {
                 if (__any(!(row < 18446744073709551616.0f))) {
@@ -694,7 +703,7 @@ __global__ __launch_bounds__(64 * wave_parts_most(HD)) void attn_wave_parts_kern
             }
         }
     };
-    auto sweep = [&](auto tracking_c) __attribute__((always_inline)) {
+    auto sweep = [&](auto mode_c) __attribute__((always_inline)) {
 #pragma unroll
         for (int d = 0; d < DT; ++d)
 #pragma unroll
@@ -704,11 +713,11 @@ __global__ __launch_bounds__(64 * wave_parts_most(HD)) void attn_wave_parts_kern
         out_of_range = 0;
         issue_k(T0);
         issue_v(T0);
-        tile(T0, T0 + 1 < T1, std::true_type{});
-        for (int t = T0 + 1; t < T1; ++t) tile(t, t + 1 < T1, tracking_c);
+        tile(T0, T0 + 1 < T1, std::integral_constant<int, FIRST>{});
+        for (int t = T0 + 1; t < T1; ++t) tile(t, t + 1 < T1, mode_c);
     };
-    sweep(std::false_type{});
-    if (out_of_range) sweep(std::true_type{});
+    sweep(std::integral_constant<int, FAST>{});
+    if (out_of_range) sweep(std::integral_constant<int, REPEATED>{});
     // joined in the order of the parts; of the row's QUADS pieces wave w puts together every parts-th
     auto po = [&](int p) { return (float*)(smem + p * (K_TILE + V_TILE)); };       // of part p, where its tiles were: [QUADS][64 * 4]
     auto ml = [&](int p) { return po(p) + QUADS * 256; };                          // [64 * 2]

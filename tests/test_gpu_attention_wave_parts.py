@@ -18,8 +18,7 @@ def test_a_wave_to_each_part(H, nq, nk, hd, parts, sharp):
     q, k, v = (rng.normal(size=(H, n, hd)) for n in (nq, nk, nk))
     ops, values = operands(q * np.sqrt(sharp), k * np.sqrt(sharp), v)
     got = form(ops, parts=parts, all_parts=2)
-    if sharp == 1.0:      # a sweep repeated for scores out of range is a wave's here, a workgroup's there
-        assert np.array_equal(got, form(ops, parts=parts))
+    assert np.array_equal(got, form(ops, parts=parts))         # also where a sweep is repeated for scores out of range
     ref, got = reference(values), bits_to_f64(got)
     assert rel_l2(got, ref) < 6e-3 and max_abs(got, ref) < 2e-2 * max(1.0, np.abs(ref).max())
 

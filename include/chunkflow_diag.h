@@ -23,10 +23,11 @@ extern "C" {
 int cf_plan_attention(int32_t H, int32_t nq, int32_t nk, int32_t head_dim, int32_t* waves_per_workgroup);
 
 /* Host-only view of how a block launches attention, `heads` heads for each of `batch` samples: with its keys in
- * `parts` parts (1 = whole), computed by workgroups of their own and merged afterwards, or (few queries: `waves` is then the
- * number of parts) by the waves of one workgroup, or (all_parts, where the batch fills the chip) by one workgroup after the other; dealt out by the grid (deal 0), by the kernel in even shares (1) or as
- * workgroups come for the next sweep (2), whole sweeps of 8-wave workgroups in either case; in workgroups of `waves`
- * waves.  The number of parts is a matter of one sample alone, and the bits of the result with it (whatever the scores: also
+ * `parts` parts (1 = whole).  all_parts: 0 = parts are computed by workgroups of their own and merged by a kernel afterwards, 1 = a
+ * workgroup has all parts of its queries, one after the other (where the batch fills the chip), 2 = a wave to each (few queries), as in
+ * cf_op_attention_form.  deal: sweeps dealt out by the grid (0), by the kernel in even shares (1) or as
+ * workgroups come for the next sweep (2), whole sweeps of 8-wave workgroups in either case.  `waves`: of a workgroup.
+ * The number of parts is a matter of one sample alone, and the bits of the result with it (whatever the scores: also
  * where those of 32 queries make their sweep start over, see attention.hip).  No GPU is touched. */
 typedef struct cf_attention_plan {
     int32_t waves, parts, all_parts, deal;

@@ -1003,8 +1003,7 @@ int cf_plan_block_attention(int32_t heads, int32_t batch, int32_t nq, int32_t nk
     a.H = heads * batch; a.nq = nq; a.nk = nk; a.hd = head_dim;
     attn_set_split(&a, attn_splits(heads, nq, nk, head_dim), nullptr);
     plan->parts = a.splits;
-    a.all_parts = attn_all_parts(a.H, nq, nk, head_dim, a.splits);
-    plan->all_parts = a.all_parts == ALL_PARTS_IN_TURN;
+    plan->all_parts = a.all_parts = attn_all_parts(a.H, nq, nk, head_dim, a.splits);
     plan->deal = attn_deal(a.H, nq, nk, head_dim, a.splits);
     plan->waves = plan->deal ? 8 : a.all_parts == ALL_PARTS_WAVES ? a.splits : attn_waves(a);
     return CF_OK;

@@ -261,11 +261,13 @@ def test_block_attention_plans():
     assert plan(12, 1, 4608, 4608, 128) == (8, 1, 0)
     assert plan(12, 1, 27280, 27280, 128) == (8, 1, 1)
     assert plan(12, 1, 119056, 119056, 128) == (8, 1, 2)
-    for shape in ((3, 4608, 128), (3, 2640, 128), (1, 4696, 128), (1, 2264, 64)):
+    # merged by a kernel (0) or a wave to each part (2) where one sample runs; a batch that fills the chip has as many parts (the bits
+    # depend on them), but pays for neither: its workgroups have all parts, one after the other (1)
+    for shape, form in (((3, 4608, 128), 0), ((3, 2640, 128), 2), ((1, 4696, 128), 0), ((2, 4696, 64), 0), ((1, 2264, 64), 2), ((8, 512, 64), 2)):
         one = B.cf_plan_block_attention(shape[0], 1, shape[1], shape[1], shape[2])
-        many = B.cf_plan_block_attention(shape[0], 32, shape[1], shape[1], shape[2])
-        # as many parts (the bits depend on them), but a batch that fills the chip does not pay for workgroups of their own
-        assert many.parts == one.parts > 1 and many.all_parts and not one.all_parts, shape
+        many = B.cf_plan_block_attention(shape[0], 64, shape[1], shape[1], shape[2])
+        assert many.parts == one.parts > 1 and (one.all_parts, many.all_parts) == (form, 1), shape
+        assert form != 2 or one.waves == one.parts, shape
     for bad in ((0, 1, 10, 10, 128), (1, 0, 10, 10, 128), (1, 1, 0, 10, 128), (1, 1, 10, 0, 128), (1, 1, 10, 10, 96), (1 << 20, 1 << 20, 10, 10, 64)):
         with pytest.raises(B.ChunkflowError):
             B.cf_plan_block_attention(*bad)

@@ -1,5 +1,5 @@
 """Attention with its keys cut into parts (few heads over a short sequence): what the parts leave is merged by a second
-kernel.  Checked through the block, which owns the scratch memory, against the oracle: part boundaries inside and at the end
+kernel (form 0), or each part is a wave of one workgroup (form 2), as the planner has it.  Checked through the block, which owns the scratch memory, against the oracle: part boundaries inside and at the end
 of a tile, both head widths, ragged queries, and logits large enough that every part but one carries nothing."""
 import numpy as np
 import pytest
@@ -13,11 +13,11 @@ from tests.util import bits_to_f64, max_abs, rel_l2
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n,heads,hd,sp,sharp", [(1888, 8, 64, 8, 1.0), (2720, 8, 64, 8, 1.0), (1540, 4, 128, 4, 1.0),
-                                                 (2000, 4, 128, 2, 1.0), (1540, 4, 128, 4, 24.0), (2720, 8, 64, 8, 24.0)])
-def test_split_keys_against_the_oracle(n, heads, hd, sp, sharp):
+@pytest.mark.parametrize("n,heads,hd,sp,sharp,form", [(1888, 8, 64, 8, 1.0, 2), (2720, 8, 64, 8, 1.0, 2), (4696, 8, 64, 4, 1.0, 0), (1540, 4, 128, 4, 1.0, 0),
+                                                      (2000, 4, 128, 2, 1.0, 2), (1540, 4, 128, 4, 24.0, 0), (2720, 8, 64, 8, 24.0, 2), (4696, 8, 64, 4, 24.0, 0)])
+def test_split_keys_against_the_oracle(n, heads, hd, sp, sharp, form):
     plan = B.cf_plan_block_attention(heads // sp, 1, n, n, hd)
-    assert plan.parts > 1 and not plan.all_parts
+    assert plan.parts > 1 and plan.all_parts == form
     cfg = wl.BlockConfig("split", wl.KIND_SINGLE, n_blocks=1, d=512, n_heads=heads, head_dim=hd, f=512, n_total=n, sp_degree=sp,
                          sp_rank=sp - 1, qk_rmsnorm=True, n_chunks=3)
     params, inputs = wl.gen_block_params(cfg, 0), wl.gen_block_inputs(cfg, 0)

@@ -192,6 +192,8 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
     const int krow = (lj & 0x13) | ((lj & 4) << 1) | ((lj & 8) >> 1);
 
     int out_of_range = 0;                       // wave-uniform: a fast tile met scores it could not take
+    __shared__ int any_out_of_range;            // ... of any wave of the workgroup: written before a tile's barrier, read after it
+    if (tid == 0) any_out_of_range = 0;
     bool tracks = false;                        // of a repeated sweep, wave-uniform: tiles past the first track, too
     const int T_end = T1;                       // of the copies
 
@@ -339,6 +341,7 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
             if (__any(!(row < 1048576.0f))) {
                 if (__any(!(row < 18446744073709551616.0f))) {
                     out_of_range = 1;
+                    any_out_of_range = 1;
                 } else {
                     // queries at or past 2^20: divide by 2^e, e = the sum's binary exponent; the others keep e = 0
                     const int e = row < 1048576.0f ? 0 : (int)(__float_as_uint(row) >> 23) - 127;
@@ -382,6 +385,12 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
         }
     };
     // the K/V tiles are the workgroup's: if any wave met a tile out of range, all of them go again
+    auto again = [&] {
+        if (!__builtin_amdgcn_readfirstlane(any_out_of_range)) return false;
+        __syncthreads();                        // every wave has read it
+        if (tid == 0) any_out_of_range = 0;
+        return true;
+    };
     if constexpr (ALL_PARTS) {
         floatx16 sum[DT];                       // the parts so far
         float m_sum = kNoRef, l_sum = 0.f;
@@ -392,7 +401,7 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
         for (T0 = 0; T0 < T_end; T0 += a.part_tiles) {
             T1 = min(T_end, T0 + a.part_tiles);
             sweep(std::integral_constant<int, FAST>{}, T0 > 0);
-            if (__syncthreads_or(out_of_range)) {
+            if (again()) {
                 tracks = out_of_range != 0;
                 sweep(std::integral_constant<int, REPEATED>{}, false);
                 out_of_range = 0;
@@ -406,7 +415,7 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
         finish(sum, m_sum, l_sum);
     } else {
         sweep(std::integral_constant<int, FAST>{}, false);
-        if (__syncthreads_or(out_of_range)) {
+        if (again()) {
             if (!repeat()) return;
             tracks = out_of_range != 0;
             sweep(std::integral_constant<int, REPEATED>{}, false);
@@ -563,7 +572,7 @@ __global__ __launch_bounds__(512, 2) void attn_even_kernel(AttnArgs a) {
 // goes where this one's was as soon as the scores are computed, V after the second contraction.  Bound by the latency of a tile
 // and, from about one workgroup per CU on, by what a CU takes in (16 or 32 KB per tile that nobody shares).  (Fragments straight
 // from memory, 32 rows x 32 bytes per load, took 0.43 us per tile of 64-wide heads, however many waves shared them.)
-// 8 heads x 512 x 64: 5.8 us, whole 9.2; 3 x 2640 x 128: 26.1, whole 44.9, in parts of their own 32.4 (attn_splits has the line).
+// 8 heads x 512 x 64: 7.6 us in two parts, whole 9.3; 3 x 2640 x 128 in three: 29.8, whole 44.8, in parts of their own 33.3 (attn_splits has the line).
 constexpr int wave_parts_most(int hd) { return hd == 64 ? 8 : 4; }     // 16 or 32 KB of LDS each
 template <int HD>
 __global__ __launch_bounds__(64 * wave_parts_most(HD)) void attn_wave_parts_kernel(AttnArgs a) {
@@ -890,63 +899,86 @@ int attn_waves(const AttnArgs& a) {
 // Key tiles of a part: an even number, so that every part begins in the same one of the two tile buffers.
 static int tiles_per_part(int tiles, int parts) { return parts > 1 ? ((tiles + parts - 1) / parts + 1) & ~1 : tiles; }
 
-// Estimated time in us, past the launch itself, of parts of `per` tiles with a wave to each, `items` = 32-query tiles of all heads.
-// A wave's step takes 0.5 us and 0.135 for each wave of its CU with 64-wide heads, of which a CU holds eight, 0.92 and 0.2 with
-// 128-wide ones (four; one workgroup per CU).
-static double wave_parts_us(long items, int per, int parts, int hd) {
-    const long per_cu = hd == 64 ? std::min((items + 255) / 256, (long)std::max(1, 8 / parts)) : 1;
-    const double gens = (double)((items + 256 * per_cu - 1) / (256 * per_cu));
-    return hd == 64 ? gens * (per * (0.5 + 0.135 * parts * per_cu) + 2.0) - 1.4 : gens * (per * (0.92 + 0.2 * parts) + 2.0) + 0.5;
+// Estimated times in us, past the launch itself.  Sweeps of `tiles` by `wgs` 4-wave workgroups, n to a CU: a tile takes each CU
+// 0.97 + 0.25 n up to one of them and 0.25 + 0.97 n from there on with 128-wide heads, 0.68 and 0.45 + 0.48 n with 64-wide ones.
+static double sweeps_us(double wgs, double tiles, int hd) {
+    const double n = wgs / 256.0;
+    return tiles * (hd == 64 ? (n <= 1.0 ? 0.68 : 0.45 + 0.48 * n) : n <= 1.0 ? 0.97 + 0.25 * n : 0.25 + 0.97 * n);
+}
+// The same, their parts merged by a kernel: 6 us and a pass over the partial results at 4 TB/s.
+static double merged_us(int heads, int nq, int tiles, int hd, int parts) {
+    return sweeps_us((double)((nq + 127) / 128) * heads * parts, tiles_per_part(tiles, parts), hd) + 6.0 + 4.0 * parts * (double)heads * nq * hd / 4e6;
+}
+// The same, a workgroup with all parts one after the other: joining one costs 0.4 of a tile (0.3 us, 64-wide, or 0.4).
+static double in_turn_us(int heads, int nq, int tiles, int hd, int parts) {
+    return sweeps_us((double)((nq + 127) / 128) * heads, tiles + 0.4 * (parts - 1), hd);
+}
+// A wave to each part, 32 queries to a workgroup, of which a CU holds 9 waves with 64-wide heads (8 in two parts) or 4 with 128-wide ones.
+// Fitted to 286 launches of each width, 1 to 128 heads x 320 to 3584 in 2 to 4 parts: off by 6 and 4 % in the mean.
+static double wave_parts_us(int heads, int nq, int tiles, int hd, int parts) {
+    const long items = (long)((nq + 31) / 32) * heads;
+    const long per_cu = hd == 64 ? (parts == 2 ? 4 : std::max(1, 9 / parts)) : std::max(1, 4 / parts), slots = 256 * per_cu;
+    auto generation = [&](long n) {            // n workgroups to a CU
+        return hd == 64 ? tiles_per_part(tiles, parts) * (0.6 + 0.085 * parts * n + (n > 1 ? 0.33 : 0.0)) + 2.0
+                        : tiles_per_part(tiles, parts) * (1.03 + 0.16 * parts * n + (n > 1 ? 0.17 : 0.0)) + 3.7;
+    };
+    const long rest = items % slots;
+    return (double)(items / slots) * generation(per_cu) + (rest ? generation((rest + 255) / 256) : 0.0) - (hd == 64 ? 1.3 : 2.5);
 }
 
 // Parts the keys of a launch are cut into.  Few heads over a short sequence (a Ulysses rank's share at degree 4 or 8, the toy model)
 // are a few dozen workgroups that each sweep all keys; cut into parts they fill the chip, at the price of writing the
 // partial results and merging them, or, where there are fewer queries still, the parts go to the waves of one workgroup, which costs
-// neither.  Estimated time in us for 128-wide heads: a tile takes a 4-wave workgroup 0.97 alone
-// on its CU and 1.7 beside another, the merge 10 us and one pass over the partial results at 4 TB/s (3 heads x 4608: 72 us
-// whole, 51 in two or four parts; 12 heads x 2640: 51 us whole, 58 in two).  A wave to each part (whole / parts and merge / waves):
-// 8 x 512 x 64 9.2 / 11.1 / 5.8, 8 x 1024 x 64 14.7 / 14.8 / 7.8, 2 x 2048 x 64 24 / 16.2 / 11.8, 3 x 1000 x 128 20.5 / 20.2 / 12.4,
-// 3 x 2640 x 128 44.9 / 32.4 / 26.1, 3 x 4608 x 128 72 / 51.6 / 67.6, 1 x 6000 x 128 92 / 42.0 / 47.1.  A function of one sample's
-// heads and lengths only, so that a sample's result does not depend on the batch it is part of; parts of at least 6 tiles (8 with
-// 64-wide heads) where they are workgroups, so that a batch that fills the chip, and whose workgroups have all parts, loses no more
-// than a few per cent by joining them, and of 2 where they are waves (64 heads x 512 x 64: 11.0 us whole, 11.5 in four parts).
+// neither.  A function of one sample's heads and lengths only, so that a sample's result does not depend on the batch it is part of;
+// a batch that fills the chip, whose workgroups have all parts, pays for joining them and gains nothing, which sets a bound on
+// their number.
+// Parts that are workgroups: at least 6 tiles each (8 with 64-wide heads).  Estimated time in us for 128-wide heads: a tile takes a
+// 4-wave workgroup 0.97 alone on its CU and 1.7 beside another, the merge 10 us and one pass over the partial results at 4 TB/s (3 heads
+// x 4608: 72 us whole, 51 in two or four parts; 12 heads x 2640: 51 us whole, 58 in two).  Not where the planner would then give one
+// sample's workgroups all parts.
+// Parts that are waves: two to four (five to eight are no faster: 8 x 1000 x 64 in 2, 3, 4, 8 parts 11.3, 9.8, 8.3, 8.9 us), where they take
+// at least 15 % off and a batch with a workgroup per CU joins them in a twenty-fifth of its time.  One sample whole or merged / so, and
+// eight samples whole / all parts in turn: 8 x 512 x 64 9.3 / 7.6 and 10.2 / 10.4; 8 x 800 x 64 12.6 / 10.7 and 19.8 / 20.4; 8 x 1000 x 64 14.4 / 11.3 and
+// 24.4 / 25.3; 3 x 2048 x 64 17.0 / 12.2 and 36.8 / 38.2; 8 x 512 x 128 13.1 / 11.5 and 15.8 / 16.7; 8 x 1000 x 128 20.9 / 15.4 and 40.9 / 41.6; 3 x 2048 x 128 28.7 / 20.5
+// and 53.5 / 54.4.  (Four parts of 8 x 512 x 64: 6.1 us, and eight samples 11.2.)  Over 380 batches of 320 to 3584
+// tokens whose samples are cut for their own sake, the median is even with whole sweeps, and the worst 7 % behind (one, 4 x 1280 x 128 of two samples,
+// 24.4 against 27.2, merged where in turn would be better).
 int attn_splits(int heads, int nq, int nk, int hd) {
-    const long items = (long)((nq + 127) / 128) * heads, items32 = (long)((nq + 31) / 32) * heads;
+    const long items = (long)((nq + 127) / 128) * heads;
     const int tiles = (nk + BKV - 1) / BKV, least = hd == 64 ? 8 : 6;
+    auto cuts = [&](int s) { const int per = tiles_per_part(tiles, s); return (tiles + per - 1) / per == s; };
     int best = 1;
     double best_us = 0;
     for (int s = 1; s <= 8; ++s) {
         const int per = tiles_per_part(tiles, s);
-        if (s > 1 && (per < 2 || (tiles + per - 1) / per != s)) continue;
+        if (s > 1 && (per < least || !cuts(s))) continue;
         const long wgs = items * s;
-        double us = 1e30;
-        if (s == 1 || (per >= least && wgs <= 512)) {
-            us = (wgs <= 256 ? 0.97 * per : 1.7 * per * (double)((wgs + 511) / 512)) * (hd == 64 ? 0.55 : 1.0) + 3.0;
-            if (s > 1) us += 10.0 + 4.0 * s * (double)heads * nq * hd / 4e6;
-        }
-        if (s > 1 && s <= wave_parts_most(hd)) us = std::min(us, 3.0 + wave_parts_us(items32, per, s, hd));
+        if (s > 1 && wgs > 512) break;
+        double us = (wgs <= 256 ? 0.97 * per : 1.7 * per * (double)((wgs + 511) / 512)) * (hd == 64 ? 0.55 : 1.0) + 3.0;
+        if (s > 1) us += 10.0 + 4.0 * s * (double)heads * nq * hd / 4e6;
         if (s == 1 || us < 0.95 * best_us) best = s, best_us = us;
+    }
+    if (best > 1 && attn_all_parts(heads, nq, nk, hd, best) == ALL_PARTS_IN_TURN) best = 1;
+    best_us = best > 1 ? merged_us(heads, nq, tiles, hd, best) : sweeps_us(items, tiles, hd);
+    const double join = hd == 64 ? 0.3 : 0.4, batch = sweeps_us(256, tiles, hd) + 4.0;
+    bool waves = false;
+    for (int s = 2; s <= 4 && (s - 1) * join <= 0.04 * batch; ++s) {
+        const double us = wave_parts_us(heads, nq, tiles, hd, s);
+        if (cuts(s) && attn_all_parts(heads, nq, nk, hd, s) == ALL_PARTS_WAVES && us < (waves ? 0.95 : 0.85) * best_us) best = s, best_us = us, waves = true;
     }
     return best;
 }
 
 // Whether a workgroup has all parts of its queries, for the heads of all samples together, and how: where the query tiles alone fill the
 // chip, parts that are workgroups only cost (12 heads x 4608 x 128, four samples: 115 us in one sweep, 136 in two parts and their merge, 115 with
-// both in one workgroup).  Estimated in us, n = 4-wave workgroups per CU: a tile takes each CU 0.97 + 0.25 n up to one of them and
-// 0.25 + 0.97 n from there on with 128-wide heads, 0.45 + 0.48 n and at least 0.68 with 64-wide ones; joining a part costs
-// half a tile, the merge 6 us and a pass over the partial results at 4 TB/s.  (3 heads x 4608 for 1, 2, 3, 4, 8 samples, in parts /
+// both in one workgroup).  (3 heads x 4608 for 1, 2, 3, 4, 8 samples, in parts /
 // in one workgroup: 55/74, 78/81, 126/108, 146/126, 286/248; 3 x 2640: 34/46, 44/47, -, 65/54, 119/95; 2 x 4696 x 64 for 1, 4, 16:
-// 29/51, 64/75, 210/199.)  With a wave to each part: wave_parts_us.
+// 29/51, 64/75, 210/199.)
 int attn_all_parts(int heads, int nq, int nk, int hd, int splits) {
     if (splits <= 1) return 0;
-    const double tiles = (nk + BKV - 1) / BKV, items = (double)((nq + 127) / 128) * heads;
-    auto sweeps = [&](double wgs, double t) {
-        const double n = wgs / 256.0;
-        return t * (hd == 64 ? std::max(0.68, 0.45 + 0.48 * n) : n <= 1.0 ? 0.97 + 0.25 * n : 0.25 + 0.97 * n);
-    };
-    const int per = tiles_per_part((int)tiles, splits);
-    const double parts = sweeps(items * splits, per) + 6.0 + 4.0 * splits * (double)heads * nq * hd / 4e6, in_turn = sweeps(items, tiles + 0.5 * (splits - 1));
-    if (splits <= wave_parts_most(hd) && wave_parts_us((long)((nq + 31) / 32) * heads, per, splits, hd) < std::min(parts, in_turn)) return ALL_PARTS_WAVES;
+    const int tiles = (nk + BKV - 1) / BKV;
+    const double parts = merged_us(heads, nq, tiles, hd, splits), in_turn = in_turn_us(heads, nq, tiles, hd, splits);
+    if (splits <= wave_parts_most(hd) && wave_parts_us(heads, nq, tiles, hd, splits) < std::min(parts, in_turn)) return ALL_PARTS_WAVES;
     return in_turn < parts ? ALL_PARTS_IN_TURN : 0;
 }
 

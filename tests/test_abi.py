@@ -268,6 +268,14 @@ def test_block_attention_plans():
         many = B.cf_plan_block_attention(shape[0], 64, shape[1], shape[1], shape[2])
         assert many.parts == one.parts > 1 and (one.all_parts, many.all_parts) == (form, 1), shape
         assert form != 2 or one.waves == one.parts, shape
+    # One sample's keys are cut where that gives it workgroups or waves, not where its workgroups would have all parts in turn; and for waves
+    # in few parts only, which a batch joins at little cost: no more than one to five tiles of a sweep.
+    for hd in (64, 128):
+        for heads in (1, 2, 3, 4, 6, 8, 12, 14, 16, 24, 25, 33, 64):
+            for n in (64, 200, 320, 512, 640, 800, 1000, 1280, 1536, 1955, 2048, 2565, 2640, 3584, 4639, 9000):
+                p = B.cf_plan_block_attention(heads, 1, n, n, hd)
+                assert p.all_parts != 1, (heads, n, hd)
+                assert p.all_parts != 2 or -(-n // 64) >= 5 * (p.parts - 1), (heads, n, hd, p.parts)
     for bad in ((0, 1, 10, 10, 128), (1, 0, 10, 10, 128), (1, 1, 0, 10, 128), (1, 1, 10, 0, 128), (1, 1, 10, 10, 96), (1 << 20, 1 << 20, 10, 10, 64)):
         with pytest.raises(B.ChunkflowError):
             B.cf_plan_block_attention(*bad)

@@ -51,6 +51,16 @@ typedef struct cf_linear_plan {
 } cf_linear_plan;
 int cf_plan_block_linear(int32_t rows, int32_t rows2, int32_t batch, int32_t n_features, int32_t k, int32_t residual, cf_linear_plan* plan);
 
+/* Host-only view of how that launch (of a cut sum: of its parts) lets CUs without a tile in the last round of workgroups fetch for the others:
+ * `fetching` workgroups (0: none) behind `tiles` with a tile or as padding, which read every stride-th 512 bytes of the listed panels, one slab of 64
+ * features per pace_ns, and stop deadline_ns after they began.  A panel is (XCD, first or second layer, 0 weights or 1 activations, first byte, bytes), of
+ * weights at offset 0 in one buffer and activations of k per row; those of one XCD lie together, 64 at most. */
+typedef struct cf_fetch_plan {
+    int32_t tiles, fetching, with_activations, stride, pace_ns, deadline_ns, panels, pad;
+    int64_t panel[8 * 64][5];
+} cf_fetch_plan;
+int cf_plan_block_fetch(int32_t rows, int32_t rows2, int32_t batch, int32_t n_features, int32_t k, int32_t residual, cf_fetch_plan* plan);
+
 /* ---- single kernels.  `blob` holds W (and bias) at the given byte offsets. */
 /* out[m,n] = A[m,:] . W[n,:] + bias[n]; features < n_split stored bf16 to out0[m*ld0+n], the rest
  * through GELU (tanh form, or erf form if gelu_erf) to out1[m*ld1 + n - n_split] (App. B linear layers). */

@@ -1037,6 +1037,30 @@ int cf_plan_block_linear(int32_t rows, int32_t rows2, int32_t batch, int32_t n_f
     return CF_OK;
 }
 
+int cf_plan_block_fetch(int32_t rows, int32_t rows2, int32_t batch, int32_t n_features, int32_t k, int32_t residual, cf_fetch_plan* plan) {
+    if (rows <= 0 || rows2 < 0 || batch <= 0 || ((int64_t)rows + rows2) * batch > 0x7fffffff || n_features <= 0 || k < 64 || !plan)
+        return cf_fail(nullptr, CF_ERR_ARG, "cf_plan_block_fetch: positive sizes and a result pointer are required");
+    GemmArgs g[2] = {};
+    const int parts = residual ? gemm_splits(rows, rows2, n_features, k) : 1;
+    for (int i = 0; i < 2; ++i) {
+        g[i].M = (i ? rows2 : rows) * batch; g[i].N = g[i].n1 = n_features; g[i].K = g[i].lda = k;
+        g[i].epi = residual ? EPI_GATE_RESID : EPI_SPLIT_GELU;
+        g[i].W.split = ~0ull;
+        gemm_set_split(&g[i], parts, nullptr);
+    }
+    const GemmArgs* const second = rows2 ? &g[1] : nullptr;
+    uint32_t tiles;
+    static_assert(sizeof(FetchPanel) == sizeof plan->panel[0], "a panel as the header has it");
+    const IdleFetch f = gemm_idle_fetch_view(gemm_plan(g[0], second), g[0], second, &tiles, (FetchPanel*)plan->panel, &plan->panels);
+    plan->tiles = (int32_t)tiles;
+    plan->fetching = (int32_t)f.workgroups;
+    plan->with_activations = f.with_a;
+    plan->stride = f.stride;
+    plan->pace_ns = (int32_t)(f.ticks_per_chunk * 10 / 4);
+    plan->deadline_ns = (int32_t)(f.deadline * 10);
+    return CF_OK;
+}
+
 int cf_workspace_bytes(const cf_ctx* c, uint64_t* out) {
     if (!c || !out) return CF_ERR_ARG;
     *out = c->ws_bytes;

@@ -36,7 +36,7 @@ __device__ __forceinline__ float wv_bf16(const WView& w, uint64_t boff_of_tensor
 
 // Workgroup id -> logical tile id such that each XCD (workgroups are dealt round-robin to the
 // 8 XCDs) walks one contiguous range of logical ids and so shares operands in its own L2.
-__device__ __forceinline__ uint32_t xcd_contiguous_id(uint32_t bid, uint32_t nb) {
+__host__ __device__ __forceinline__ uint32_t xcd_contiguous_id(uint32_t bid, uint32_t nb) {
     const uint32_t q = nb >> 3, r = nb & 7u;
     const uint32_t xcd = bid & 7u, idx = bid >> 3;
     return xcd < r ? xcd * (q + 1) + idx : r * (q + 1) + (xcd - r) * q + idx;

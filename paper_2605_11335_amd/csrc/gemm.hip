@@ -2,8 +2,7 @@
 // diagnostics.  The kernels themselves are in gemm_kernel.h.
 #include <algorithm>
 
-#include "common.h"
-#include "kernels.h"
+#include "gemm_kernel.h"
 
 const char* gemm_check(const GemmArgs& g) {
     if (g.M <= 0 || g.N <= 0 || g.K <= 0) return "gemm: empty shape";
@@ -123,6 +122,78 @@ GemmPlan gemm_plan(const GemmArgs& g, const GemmArgs* second) {
 void gemm_tile_shape(int tile, int* tokens, int* features) {
     *tokens = kTileCost[tile].bm;
     *features = kTileCost[tile].bn;
+}
+
+// Which launches fetch ahead for their last round, and how (gemm_kernel.h).  A fetching workgroup gets about 50 GB/s of data that misses
+// L2.  Where those of an XCD cannot keep up with its tiles they leave the activations out, and then chunks.  Up to two rounds of
+// workgroups: behind more of them the last one is too little of a launch, and its CUs begin it too far apart, to gain anything (4608 x 9216 x
+// 3072, 2.5 rounds, none / fetching: 232.0 / 233.5 us; 13640 x 3072 x 14336, 2.5: 959 / 966; 13640 x 9216 x 3072, 7.6: 628 / 633).  The pace is that of
+// a tile whose operands lie in L2.  A workgroup stops at the latest when a round at that pace is over since it began itself: one
+// that gets its CU late, because another stream's work was there, can make the launch longer by as much as it was late, and at most by that.
+IdleFetch gemm_idle_fetch_plan(int bm, int bn, bool cut, const GemmArgs& g, const GemmArgs* second, uint32_t tiles, uint32_t tiles1) {
+    IdleFetch f{};
+    const uint32_t rest = tiles % 256;
+    const int slabs = cut ? g.part_slabs : g.K / BK;
+    if (tiles > 512 || rest == 0 || rest > IDLE_MOST || slabs < 4 * FETCH_SLABS) return f;
+    if (second && (g.K != second->K || g.part_slabs != second->part_slabs)) return f;
+    const double slab_us = bm * bn <= 128 * 256 ? 0.45 : bm * bn <= 192 * 256 ? 0.7 : 1.0;
+    double w_bytes = 0, a_bytes = 0;                           // per slab, of an XCD's tiles in the last round
+    for (int i = 0; i < (second ? 2 : 1); ++i) {
+        const double of = (i ? std::min(rest, tiles1) : rest - std::min(rest, tiles1)) / 8.0;
+        const double sharers = std::min(((i ? second->M : g.M) + bm - 1) / bm, 9);       // row-tiles that walk a weight panel together
+        w_bytes += std::ceil(of / sharers) * bn * ROWB;
+        a_bytes += std::min(std::ceil(of), sharers) * bm * ROWB;
+    }
+    const double can = (256 - rest) / 8 * 50e3 * slab_us;
+    f.workgroups = 256 - rest;
+    f.with_a = w_bytes + a_bytes <= can;
+    f.stride = (int)std::ceil(w_bytes / can);
+    f.ticks_per_chunk = (uint32_t)(slab_us * FETCH_SLABS * 100.0);
+    f.deadline = (uint32_t)(slabs * slab_us * 100.0);
+    return f;
+}
+
+namespace {
+// The panels that list_panels lists on each XCD, by the same arithmetic.
+template <int BM, int BN>
+int panels_of(const GemmArgs& g, const GemmArgs* second, bool cut, uint32_t tiles0, uint32_t tiles0_pad, uint32_t tiles, bool with_a, FetchPanel* out) {
+    int n = 0;
+    for (uint32_t x = 0; x < 8; ++x)
+        for (int i = 0; i < (second ? 2 : 1); ++i) {
+            const GemmArgs& p = i ? *second : g;
+            const uint32_t first = i ? tiles0_pad : 0, count = i ? tiles - tiles0_pad : tiles0;
+            int lane0 = -1;
+            for (int lane = 0; lane < 64; ++lane) {
+                const uint32_t b = (tiles & ~255u) + x + 8u * lane;
+                if (b < first || b >= first + count) continue;
+                if (lane0 < 0) lane0 = lane;
+                const TilePanels<BM, BN> t(p, cut, xcd_contiguous_id(b - first, count));
+                if (t.lists_w(lane, lane0)) out[n++] = FetchPanel{x, i, 0, (int64_t)(t.w_begin + t.k0), (int64_t)t.w_bytes};
+                if (with_a && t.lists_a(lane, lane0)) out[n++] = FetchPanel{x, i, 1, (int64_t)t.a_begin, (int64_t)t.a_bytes};
+            }
+        }
+    return n;
+}
+}  // namespace
+
+IdleFetch gemm_idle_fetch_view(const GemmPlan& plan, const GemmArgs& g, const GemmArgs* second, uint32_t* tiles, FetchPanel* panels, int* n_panels) {
+    const int bm = kTileCost[plan.tile].bm, bn = kTileCost[plan.tile].bn;
+    const bool cut = g.epi == EPI_GATE_RESID && g.ksplits > 1;
+    GemmArgs a[2] = {g, second ? *second : g};
+    if (cut && plan.last >= 0)
+        for (GemmArgs& p : a) --p.ksplits;
+    const uint32_t tiles0 = tile_count(a[0], bm, bn, cut), pad = second ? (tiles0 + 7u) & ~7u : tiles0;
+    *tiles = second ? pad + tile_count(a[1], bm, bn, cut) : tiles0;
+    *n_panels = 0;
+    if (!can_idle_fetch(bm, bn, cut ? EPI_PARTIAL : g.epi, second != nullptr)) return IdleFetch{};
+    const IdleFetch f = gemm_idle_fetch_plan(bm, bn, cut, a[0], second ? &a[1] : nullptr, *tiles, *tiles - pad);
+    if (f.workgroups) {
+        auto list = [&](auto panels_of_tile) { *n_panels = panels_of_tile(a[0], second ? &a[1] : nullptr, cut, tiles0, pad, *tiles, f.with_a != 0, panels); };
+        if (plan.tile == GEMM_256x256) list(panels_of<256, 256>);
+        else if (plan.tile == GEMM_192x256) list(panels_of<192, 256>);
+        else list(panels_of<128, 256>);
+    }
+    return f;
 }
 
 // Parts K is cut into.  A layer with few outputs and a long sum (the MLP-out layers of a short sequence or of a rank at

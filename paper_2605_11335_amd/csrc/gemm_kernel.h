@@ -618,17 +618,17 @@ __device__ __forceinline__ void gemm_ring_run(const GemmArgs& g, int m0, int n0,
 template <int BM, int BN>
 struct TileWalk {
     int tiles_m, tiles_n, GM;
-    __device__ __forceinline__ explicit TileWalk(const GemmArgs& g) {
+    __host__ __device__ __forceinline__ explicit TileWalk(const GemmArgs& g) {
         tiles_m = (g.M + BM - 1) / BM;
         tiles_n = (g.n1 - g.n0 + BN - 1) / BN;
-        const int n_groups = max(1, (tiles_m + 4) / 8);
+        const int n_groups = std::max(1, (tiles_m + 4) / 8);
         GM = (tiles_m + n_groups - 1) / n_groups;
     }
     struct Tile { int m0, n0, above, gsz; };       // first token and feature; row-tiles of its group before it, in all
-    __device__ __forceinline__ Tile at(const GemmArgs& g, uint32_t lid) const {
+    __host__ __device__ __forceinline__ Tile at(const GemmArgs& g, uint32_t lid) const {
         const int group = lid / (GM * tiles_n), in = lid % (GM * tiles_n);
         const int first_m = group * GM;
-        const int gsz = min(tiles_m - first_m, GM);
+        const int gsz = std::min(tiles_m - first_m, GM);
         return Tile{(first_m + in % gsz) * BM, g.n0 + in / gsz * BN, in % gsz, gsz};
     }
 };
@@ -668,42 +668,51 @@ struct GemmPair {
 };
 
 // The last round of workgroups leaves CUs without a tile.  There the grid goes on with workgroups that fetch, for the tiles of that
-// round, what their CU's copies are about to ask for, into the L2 of the XCD they share (`idle_fetch` is their number and pace).
-// A CU's loads return in order, so that a copy that misses L2 holds up all behind it: with operands from HBM a lone 128x256
-// workgroup takes 0.83 us per slab, from L2 0.50, whatever share of them misses; waves of its own workgroup or of its CU
-// fetching ahead wait in the same queue and gain nothing.  No result depends on it; a workgroup that is late, or on another XCD
-// than thought, only fetches in vain, and stops when the round should be over.
-// 512 x 9216 x 3072 (144 tiles of 128x256): 49.3 -> 40.0 us; 1320 x 3072 x 3072 (132): 50.2 -> 42.5;
-// 2304 x 3072 x 12288 (216): 173.8 -> 163.8; 1531 x 12288 x 3072 (384 of 192x256): 125.8 -> 119.7.
-struct IdleFetch {
-    uint32_t workgroups;                       // behind the tiles'; 0 = none
-    uint32_t ticks_per_chunk, deadline;        // of 10 ns
-    int stride, with_a;                        // every stride-th chunk; the activations too
-};
+// round, what their CU's copies are about to ask for, into the L2 of the XCD they share (`IdleFetch` is their number and pace).
+// A CU's loads return in order, so that a copy that misses L2 holds up all behind it; waves of its own workgroup or of its CU
+// fetching ahead wait in the same queue and gain nothing.  No result depends on it: a workgroup that is late, or on another XCD
+// than thought, only fetches in vain.
+// Operands that come from HBM (sets in turn, 1.2 GB; none / fetching): 2304 x 3072 x 12288 (216 tiles of 128x256) 176.6 / 167.1 us, 1531 x
+// 12288 x 3072 (384 of 192x256) 122.9 / 117.1, 512 x 12288 x 3072 52.5 / 50.3.  The same few operands again and again, which the last-level
+// cache holds: 149.4 / 151.6, 118.1 / 120.8, 43.6 / 44.0.  A pace 0.8 to 1.75 times this one gives the same within 2 %.
 constexpr uint32_t IDLE_MOST = 224;            // tiles of a last round beside which fetching still pays
 constexpr int FETCH_SLABS = 4, FETCH_LEAD = 2; // a chunk is 512 bytes of a row; the first ones are asked for before a fetch could help
 
+// What a fetching workgroup reads of the tiles on its XCD in the last round, of which `lane` is one and lane0 the first of its problem:
+// in each problem their logical ids follow one another, so a weight panel begins with every walk over a group's row-tiles, and
+// the row-tiles of the first walk are all there are.
+template <int BM, int BN>
+struct TilePanels {
+    typename TileWalk<BM, BN>::Tile t;
+    uint64_t k0, w_begin, w_bytes, a_begin, a_bytes;   // first byte of the part of K; panels in bytes of the weight blob (before k0) and of A (behind it)
+    __host__ __device__ __forceinline__ TilePanels(const GemmArgs& g, bool cut, uint32_t lid) {
+        const TileWalk<BM, BN> walk(g);
+        const uint32_t whole = walk.tiles_m * walk.tiles_n, part = cut ? lid / whole : 0;
+        t = walk.at(g, lid - part * whole);
+        k0 = cut ? (uint64_t)part * g.part_slabs * (BK * 2) : 0;
+        w_begin = g.w_off + (uint64_t)t.n0 * g.K * 2;
+        const uint64_t w_end = g.w_off + (uint64_t)std::min(t.n0 + BN, g.n1) * g.K * 2;
+        const uint64_t w1 = g.W.split > w_begin && g.W.split < w_end ? g.W.split : w_end;      // what lies in one buffer
+        w_bytes = w1 > w_begin + k0 ? w1 - w_begin - k0 : 0;
+        a_begin = (uint64_t)t.m0 * g.lda * 2 + k0;
+        a_bytes = ((uint64_t)(std::min(g.M - t.m0, BM) - 1) * g.lda + g.K) * 2 - k0;
+    }
+    __host__ __device__ __forceinline__ bool lists_w(int lane, int lane0) const { return lane == lane0 || t.above == 0; }
+    __host__ __device__ __forceinline__ bool lists_a(int lane, int lane0) const { return lane - lane0 < t.gsz; }
+};
+
 struct Panel { uint64_t base; uint32_t bytes, row_bytes; };
-// The panels of one problem's tiles among them, the lane's tile (if any) being `lid`: in each problem the logical ids of an XCD's
-// last tiles follow one another.  -> panels listed so far
+// The panels of one problem's tiles among them, the lane's tile (if any) being `lid`.  -> panels listed so far
 template <int BM, int BN, int EPI>
 __device__ __forceinline__ int list_panels(const GemmArgs& g, Panel* panels, int n, bool on, uint32_t lid, bool with_a) {
-    constexpr bool CUT = EPI == EPI_PARTIAL;
     const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-    const TileWalk<BM, BN> walk(g);
-    lid = on ? lid : 0;
-    const uint32_t whole = walk.tiles_m * walk.tiles_n, part = CUT ? lid / whole : 0;
-    const auto t = walk.at(g, lid - part * whole);
-    const uint64_t k0 = CUT ? (uint64_t)part * g.part_slabs * (BK * 2) : 0;
-    const uint64_t w0 = g.w_off + (uint64_t)t.n0 * g.K * 2, w_end = g.w_off + (uint64_t)min(t.n0 + BN, g.n1) * g.K * 2;
-    const uint64_t w1 = g.W.split > w0 && g.W.split < w_end ? g.W.split : w_end;       // what lies in one buffer
+    const TilePanels<BM, BN> p(g, EPI == EPI_PARTIAL, on ? lid : 0);
     const int lane0 = __ffsll((unsigned long long)__ballot(on)) - 1;
-    const bool new_w = on && (lane == lane0 || t.above == 0), new_a = on && with_a && lane - lane0 < t.gsz;
+    const bool new_w = on && p.lists_w(lane, lane0), new_a = on && with_a && p.lists_a(lane, lane0);
     const uint64_t wm = __ballot(new_w), am = __ballot(new_a), below = (1ull << lane) - 1;
-    if (new_w) panels[n + __popcll(wm & below)] = Panel{(uint64_t)(uintptr_t)wv_ptr(g.W, w0) + k0, rsrc_bytes(w1 > w0 + k0 ? w1 - w0 - k0 : 0), (uint32_t)g.K * 2u};
+    if (new_w) panels[n + __popcll(wm & below)] = Panel{(uint64_t)(uintptr_t)wv_ptr(g.W, p.w_begin) + p.k0, rsrc_bytes(p.w_bytes), (uint32_t)g.K * 2u};
     n += __popcll(wm);
-    if (new_a) panels[n + __popcll(am & below)] =
-        Panel{(uint64_t)(uintptr_t)(g.A + (size_t)t.m0 * g.lda) + k0, rsrc_bytes(((uint64_t)(min(g.M - t.m0, BM) - 1) * g.lda + g.K) * 2 - k0), (uint32_t)g.lda * 2u};
+    if (new_a) panels[n + __popcll(am & below)] = Panel{(uint64_t)(uintptr_t)g.A + p.a_begin, rsrc_bytes(p.a_bytes), (uint32_t)g.lda * 2u};
     return n + __popcll(am);
 }
 // tiles0, tiles0_pad, tiles: as in GemmPair; one problem: all three alike
@@ -740,18 +749,18 @@ __device__ __forceinline__ void gemm_idle_fetch(const GemmArgs& g0, const GemmAr
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // before the LDS is another workgroup's
 }
-// one workgroup per CU; two problems of the largest tile take all registers as it is
-template <int BM, int BN, int S, int EPI, bool PAIR>
-constexpr bool has_idle_fetch() { return S == 0 && BM * BN > 128 * 128 && EPI != EPI_LAST_PART && !(PAIR && BM * BN == 256 * 256); }
+// Tiles with one workgroup per CU; two problems of the largest take all registers as it is, and the last part of a cut sum has a
+// launch of its own only where a batch fills the chip (gemm_plan).
+constexpr bool can_idle_fetch(int bm, int bn, int epi, bool pair) { return bm * bn > 128 * 128 && epi != EPI_LAST_PART && !(pair && bm * bn == 256 * 256); }
 
 template <int BM, int BN, int S, int EPI>
 __global__ __launch_bounds__(256, (min_waves<BM, BN>())) void gemm_bf16_kernel(GemmArgs g, uint32_t tiles, IdleFetch f) {
-    if (!has_idle_fetch<BM, BN, S, EPI, false>() || blockIdx.x < tiles) gemm_tile_body<BM, BN, S, EPI>(g, blockIdx.x, tiles);
+    if (!can_idle_fetch(BM, BN, EPI, false) || blockIdx.x < tiles) gemm_tile_body<BM, BN, S, EPI>(g, blockIdx.x, tiles);
     else gemm_idle_fetch<BM, BN, EPI>(g, g, tiles, tiles, tiles, f, blockIdx.x);
 }
 template <int BM, int BN, int S, int EPI>
 __global__ __launch_bounds__(256, (min_waves<BM, BN>())) void gemm_pair_kernel(GemmPair p, IdleFetch f) {
-    if constexpr (has_idle_fetch<BM, BN, S, EPI, true>()) {
+    if constexpr (can_idle_fetch(BM, BN, EPI, true)) {
         if (blockIdx.x >= p.tiles) { gemm_idle_fetch<BM, BN, EPI>(p.g[0], p.g[1], p.tiles0, p.tiles0_pad, p.tiles, f, blockIdx.x); return; }
     }
     if (blockIdx.x < p.tiles0) gemm_tile_body<BM, BN, S, EPI>(p.g[0], blockIdx.x, p.tiles0);
@@ -770,43 +779,21 @@ hipError_t allow_smem(Kernel kernel, size_t smem) {
     return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
 }
 
-// A fetching workgroup gets about 50 GB/s of data that misses L2.  Where those of an XCD cannot keep up with its tiles they leave
-// the activations out, and then chunks.  `tiles`: workgroups of the launch, tiles1 of them the second problem's.
-template <int BM, int BN, int EPI>
-IdleFetch idle_fetch(const GemmArgs& g, const GemmArgs* second, uint32_t tiles, uint32_t tiles1) {
-    IdleFetch f{};
-    const uint32_t rest = tiles % 256;
-    const int slabs = EPI == EPI_PARTIAL ? g.part_slabs : g.K / BK;
-    if (rest == 0 || rest > IDLE_MOST || slabs < 4 * FETCH_SLABS) return f;
-    if (second && (g.K != second->K || g.part_slabs != second->part_slabs)) return f;
-    const double slab_us = BM * BN <= 128 * 256 ? 0.45 : BM * BN <= 192 * 256 ? 0.7 : 1.0;
-    double w_bytes = 0, a_bytes = 0;                           // per slab, of an XCD's tiles in the last round
-    for (int i = 0; i < (second ? 2 : 1); ++i) {
-        const double of = (i ? std::min(rest, tiles1) : rest - std::min(rest, tiles1)) / 8.0;
-        const double sharers = std::min(((i ? second->M : g.M) + BM - 1) / BM, 9);       // row-tiles that walk a weight panel together
-        w_bytes += std::ceil(of / sharers) * BN * ROWB;
-        a_bytes += std::min(std::ceil(of), sharers) * BM * ROWB;
-    }
-    const double can = (256 - rest) / 8 * 50e3 * slab_us;
-    f.workgroups = 256 - rest;
-    f.with_a = w_bytes + a_bytes <= can;
-    f.stride = (int)std::ceil(w_bytes / can);
-    f.ticks_per_chunk = (uint32_t)(slab_us * FETCH_SLABS * 100.0);
-    f.deadline = (uint32_t)(slabs * 2.0 * slab_us * 100.0);
-    return f;
+// workgroups that the tiles of one problem take
+inline uint32_t tile_count(const GemmArgs& g, int bm, int bn, bool cut) {
+    return (uint32_t)(((g.M + bm - 1) / bm) * ((g.n1 - g.n0 + bn - 1) / bn)) * (cut ? g.ksplits : 1);
 }
 
 template <int BM, int BN, int S, int EPI>
 hipError_t launch(const GemmArgs& g, const GemmArgs* second, hipStream_t s) {
-    auto tiles = [](const GemmArgs& p) {
-        return (uint32_t)(((p.M + BM - 1) / BM) * ((p.n1 - p.n0 + BN - 1) / BN)) * (EPI == EPI_PARTIAL ? p.ksplits : 1);
-    };
+    constexpr bool cut = EPI == EPI_PARTIAL;
+    const uint32_t tiles = tile_count(g, BM, BN, cut);
     constexpr size_t smem = gemm_smem<BM, BN, S, EPI>();
     if (!second) {
         static const hipError_t allowed = allow_smem(gemm_bf16_kernel<BM, BN, S, EPI>, smem);
         if (allowed != hipSuccess) return allowed;
-        const IdleFetch f = has_idle_fetch<BM, BN, S, EPI, false>() ? idle_fetch<BM, BN, EPI>(g, nullptr, tiles(g), 0) : IdleFetch{};
-        hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, S, EPI>), dim3(tiles(g) + f.workgroups), dim3(256), smem, s, g, tiles(g), f);
+        const IdleFetch f = can_idle_fetch(BM, BN, EPI, false) ? gemm_idle_fetch_plan(BM, BN, cut, g, nullptr, tiles, 0) : IdleFetch{};
+        hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, S, EPI>), dim3(tiles + f.workgroups), dim3(256), smem, s, g, tiles, f);
     } else if constexpr (BM * BN == 65536 && EPI == EPI_PARTIAL) {
         return hipErrorInvalidValue;               // does not fit the registers; gemm_plan never asks for it
     } else {
@@ -815,10 +802,10 @@ hipError_t launch(const GemmArgs& g, const GemmArgs* second, hipStream_t s) {
         GemmPair p;
         p.g[0] = g;
         p.g[1] = *second;
-        p.tiles0 = tiles(g);
+        p.tiles0 = tiles;
         p.tiles0_pad = (p.tiles0 + 7u) & ~7u;
-        p.tiles = p.tiles0_pad + tiles(*second);
-        const IdleFetch f = has_idle_fetch<BM, BN, S, EPI, true>() ? idle_fetch<BM, BN, EPI>(g, second, p.tiles, p.tiles - p.tiles0_pad) : IdleFetch{};
+        p.tiles = p.tiles0_pad + tile_count(*second, BM, BN, cut);
+        const IdleFetch f = can_idle_fetch(BM, BN, EPI, true) ? gemm_idle_fetch_plan(BM, BN, cut, g, second, p.tiles, p.tiles - p.tiles0_pad) : IdleFetch{};
         hipLaunchKernelGGL((gemm_pair_kernel<BM, BN, S, EPI>), dim3(p.tiles + f.workgroups), dim3(256), smem, s, p, f);
     }
     return hipGetLastError();

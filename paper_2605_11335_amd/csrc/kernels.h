@@ -43,6 +43,17 @@ void gemm_tile_shape(int tile, int* tokens, int* features);
 double gemm_fill(int M, int n);        // share of the launched rounds of workgroups that n features x M tokens fill
 hipError_t gemm_launch(const GemmArgs& g, hipStream_t s);
 hipError_t gemm_launch_as(const GemmPlan& plan, const GemmArgs& g, hipStream_t s);     // (diagnostic) as told
+// Workgroups behind the tiles of a launch that fetch for its last round (gemm_kernel.h).
+struct IdleFetch {
+    uint32_t workgroups;                       // 0 = none
+    uint32_t ticks_per_chunk, deadline;        // of 10 ns
+    int stride, with_a;                        // every stride-th chunk; the activations too
+};
+// `tiles`: workgroups of the launch, with what pads the first problem's, tiles1 of them the second's; cut: the parts of a cut sum
+IdleFetch gemm_idle_fetch_plan(int bm, int bn, bool cut, const GemmArgs& g, const GemmArgs* second, uint32_t tiles, uint32_t tiles1);
+// (diagnostic) how the launch of a plan's tiles fetches; its panels by XCD, 64 of them at most, as (XCD, problem, 0 weights | 1 activations, first byte, bytes)
+struct FetchPanel { int64_t xcd, problem, activations, begin, bytes; };
+IdleFetch gemm_idle_fetch_view(const GemmPlan& plan, const GemmArgs& g, const GemmArgs* second, uint32_t* tiles, FetchPanel* panels, int* n_panels);
 // per epilogue: one problem, or two in one launch (`second` not NULL), with the given tile
 hipError_t gemm_launch_split_gelu(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s);
 hipError_t gemm_launch_split_gelu_erf(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s);

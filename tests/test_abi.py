@@ -308,6 +308,66 @@ def test_block_linear_plans():
         assert lib.cf_op_linear_residual_form(p, 512, p, 0, -1, 64, 64, 512, p, None, p, tile[0], tile[1], parts, 0, p, nbytes, None) == B.CF_ERR_ARG
 
 
+def _tiles_of_the_last_round(problems, tile, parts):
+    """(XCD, problem, first token, first feature, part) of the tiles past whole rounds of 256 workgroups, in the order in which the kernel
+    walks them: an XCD's ids together, groups of row-tiles of one size, feature-tile-major."""
+    bm, bn = tile
+    first, out = 0, []
+    counts = [-(-m // bm) * -(-n // bn) * parts for m, n in problems]
+    begins = [0, -(-counts[0] // 8) * 8]
+    tiles = begins[len(problems) - 1] + counts[-1]
+    for i, (m, n) in enumerate(problems):
+        tm, tn = -(-m // bm), -(-n // bn)
+        gm = -(-tm // max(1, (tm + 4) // 8))
+        order = [(r, c) for g0 in range(0, tm, gm) for c in range(tn) for r in range(g0, min(tm, g0 + gm))] * parts
+        for b in range(max(0, tiles // 256 * 256 - begins[i]), counts[i]):
+            q, r = divmod(counts[i], 8)
+            lid = b % 8 * q + min(b % 8, r) + b // 8
+            out.append((b % 8, i, order[lid][0] * bm, order[lid][1] * bn, lid // (tm * tn)))
+    return tiles, out
+
+
+def test_idle_fetch_plans():
+    """Which launches let idle CUs fetch, for how long, and what: up to two rounds of workgroups, no longer than a round takes at their
+    pace, and on every XCD the weights (and activations) of its own tiles, whole, once, and nothing past the operands' ends."""
+    seen = set()
+    for rows, rows2, n, k, residual in ((2304, 0, 3072, 12288, True), (1531, 0, 12288, 3072, False), (1320, 0, 14336, 3072, False), (1320, 0, 3072, 14336, True),
+                                        (512, 64, 9216, 3072, False), (1500, 70, 4104, 1088, False), (300, 0, 25000, 1024, False), (2304, 0, 3080, 15360, True),
+                                        (4608, 0, 3072, 12288, True), (2304, 0, 3072, 15360, True), (1500, 0, 3072, 12288, True),
+                                        (900, 512, 2048, 10240, True), (1320, 70, 1536, 6144, True), (6000, 256, 1024, 4096, True), (6000, 256, 1536, 6144, True),
+                                        (2640, 256, 3072, 1024, False), (4608, 0, 9216, 3072, False), (13640, 0, 9216, 3072, False), (5, 0, 8, 4096, False)):
+        p = B.cf_plan_block_linear(rows, n, k, residual, rows2=rows2)
+        f = B.cf_plan_block_fetch(rows, n, k, residual, rows2=rows2)
+        tile, slabs = (p.tile_tokens, p.tile_features), -(-(k // 64) // p.parts)
+        problems = [(m, n) for m in (rows, rows2) if m]
+        tiles, last = _tiles_of_the_last_round(problems, tile, p.parts)
+        assert f.tiles == tiles
+        if not f.fetching:
+            assert f.panels == 0
+            continue
+        seen.add((tile, p.parts > 1, rows2 > 0))
+        assert tile in ((256, 256), (192, 256), (128, 256)) and tiles <= 512 and f.fetching == 256 - tiles % 256
+        assert f.stride >= 1 and f.deadline_ns <= slabs * f.pace_ns
+        for x in range(8):
+            mine = [q for q in f.panel[:f.panels] if q[0] == x]
+            assert len(mine) <= 64
+            for i, (m, _) in enumerate(problems):
+                at = [t for t in last if t[0] == x and t[1] == i]
+                got = [(q[3], q[3] + q[4]) for q in mine if q[1] == i and not q[2]]
+                want = [(2 * (n0 * k + part * slabs * 64), 2 * min(n, n0 + tile[1]) * k) for _, _, _, n0, part in at]
+                assert set(got) == set(want) and len(set(got)) == len(got) and all(0 <= a < b <= 2 * n * k for a, b in got)
+                got = [(q[3], q[3] + q[4]) for q in mine if q[1] == i and q[2]]
+                want = {(2 * (m0 * k + part * slabs * 64), 2 * min(m, m0 + tile[0]) * k) for _, _, m0, _, part in at}
+                # of a second part of the sum on the same XCD the activations are left out
+                assert not f.with_activations or (set(got) <= want and len(set(got)) == len(got) and (p.parts > 1 or set(got) == want))
+                assert f.with_activations or not got
+                assert all(0 <= a < b <= 2 * m * k for a, b in got)
+    assert {t for t, _, _ in seen} == {(256, 256), (192, 256), (128, 256)} and {c for _, c, _ in seen} == {True, False} == {t for _, _, t in seen}, seen
+    for bad in ((0, 64, 64), (64, 0, 64), (64, 64, 32)):
+        with pytest.raises(B.ChunkflowError):
+            B.cf_plan_block_fetch(*bad, False)
+
+
 def test_the_tile_tests_take_every_tile():
     """The sizes of tests/test_gpu_gemm_tiles.py still reach all tiles: on the longest sum, with few slabs all but 128 x 256, and with
     two layers in one launch."""

@@ -1,5 +1,5 @@
-"""Launches whose last round of workgroups leaves CUs idle, on the three largest tiles (one workgroup per CU): from 16 slabs on,
-workgroups without a tile fetch operands ahead there.  One tile and all but one of a round, ragged rows, features and slabs, a sum in
+"""Launches whose last round of workgroups leaves CUs idle, on the three largest tiles (one workgroup per CU): from 16 slabs on and up to
+two rounds, workgroups without a tile fetch operands ahead there (what they read is checked on the host, test_abi.py).  One tile and all but one of a round, ragged rows, features and slabs, a sum in
 parts; and the two streams of a double-stream block in one launch, with the weights in one buffer and split between two."""
 import math
 
@@ -8,17 +8,18 @@ import pytest
 import torch
 
 import workload as wl
+from oracle import block as ob
 from paper_2605_11335_amd import binding as B
 from paper_2605_11335_amd.runner import BlockRunner
 from tests.test_gpu_kernels import make_blob
-from tests.util import bf16_round, dev_bits, max_abs
+from tests.util import bf16_round, dev_bits, max_abs, rel_l2
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("tile", [(256, 256), (192, 256), (128, 256)])
-@pytest.mark.parametrize("M,N,K,parts", [(5, 8, 1024, 1), (300, 520, 1088, 1), (1500, 3080, 1984, 1), (700, 1032, 3968, 2), (3300, 5000, 1152, 1)])
+@pytest.mark.parametrize("M,N,K,parts", [(5, 8, 1024, 1), (300, 520, 1088, 1), (1500, 3080, 1984, 1), (700, 1032, 3968, 2), (3300, 5000, 1152, 1), (3300, 4608, 1152, 1)])
 def test_last_round(tile, M, N, K, parts):
     rng = np.random.default_rng(M + K)
     a, ab = bf16_round(rng.normal(size=(M, K)))
@@ -34,21 +35,56 @@ def test_last_round(tile, M, N, K, parts):
     assert max_abs(y.cpu().numpy(), ref) < 5e-5 * math.sqrt(K)
 
 
-@pytest.mark.parametrize("img", [300, 1500])
-def test_two_streams(img):
-    cfg = wl.BlockConfig("idle_pair", wl.KIND_DOUBLE, n_blocks=1, d=1024, n_heads=8, head_dim=128, f=4096, n_total=img + 70, n_txt=70, qk_rmsnorm=True, n_chunks=9)
+def paired_layers(cfg):
+    """(name, tile, whether idle CUs fetch) of a double-stream block's paired layers, from the planner."""
+    d, f, img, txt = cfg.d, cfg.f, cfg.n_total - cfg.n_txt, cfg.n_txt
+    for name, n, k, residual in (("qkv", 3 * d, d, False), ("out", d, d, True), ("up", f, d, False), ("down", d, f, True)):
+        p = B.cf_plan_block_linear(img, n, k, residual, rows2=txt)
+        yield name, f"{p.tile_tokens}x{p.tile_features}", p.parts, B.cf_plan_block_fetch(img, n, k, residual, rows2=txt).fetching > 0
+
+
+# between them every paired kernel that can fetch: both tiles, plain, either activation, residual, parts of a cut sum
+@pytest.mark.parametrize("d,f,img,txt,erf,fetching", [(1024, 4096, 6000, 256, False, {"qkv 192x256", "out 128x256", "down 128x256"}),
+                                                      (1536, 6144, 1320, 70, False, {"qkv 128x256", "up 192x256", "down 128x256 in 3 parts"}),
+                                                      (1536, 6144, 6000, 256, False, {"out 192x256", "down 192x256"}),
+                                                      (2048, 10240, 1320, 70, True, {"qkv 192x256", "up 128x256", "down 192x256 in 3 parts"})])
+def test_two_streams(d, f, img, txt, erf, fetching):
+    """Both streams of a double-stream block in one launch per layer, as the kernel times say, with the weights in one buffer and cut
+    between two at several places; right against the oracle, and the same bits wherever they are cut."""
+    cfg = wl.BlockConfig("idle_pair", wl.KIND_DOUBLE, n_blocks=2, d=d, n_heads=d // 128, head_dim=128, f=f, n_total=img + txt, n_txt=txt, qk_rmsnorm=True,
+                         n_chunks=9, gelu_erf=erf)
+    layers = list(paired_layers(cfg))
+    assert {f"{n} {t}" + (f" in {p} parts" if p > 1 else "") for n, t, p, on in layers if on} == fetching
     params, inputs = wl.gen_block_params(cfg, 0), wl.gen_block_inputs(cfg, 0)
-    got = []
-    for r in (1.0, 0.5, 0.0):
-        run = BlockRunner(cfg)
-        try:
+    run = BlockRunner(cfg)
+    want = None
+    try:
+        for b in range(2):
+            run.register_params(b, params)
+        t = run.make_io(inputs)
+        io = run.io_struct(t)
+        for r in (1.0, 0.85, 0.6, 0.3):
             run.ctx.set_resident_fraction(r)
-            run.register_params(0, params)
-            t = run.make_io(inputs)
-            run.run_block(0, t)
-            got.append(np.concatenate([t["y_txt"].cpu().numpy(), t["y"].cpu().numpy()]))
-        finally:
-            run.close()
-    assert np.isfinite(got[0]).all()
-    for g in got[1:]:
-        assert np.array_equal(g.view(np.uint8), got[0].view(np.uint8))
+            run.begin(0)
+            for i in range(4):                     # each block's weights land before the one ahead of it runs: from the third on one wait
+                run.begin((i + 1) % 2)             # for all chunks, and every layer is launched whole, its weights partly in either buffer
+                torch.cuda.synchronize()
+                if i == 3:
+                    run.ctx.cf_kernel_times_reset()
+                    run.ctx.cf_set_profiling(True)
+                run.fwd(i % 2, io)
+                run.ctx.cf_sync()
+            times = {k["name"]: k["launches"] for k in run.ctx.cf_kernel_times() if k["launches"]}
+            run.ctx.cf_set_profiling(False)
+            for name, tile, _, _ in layers:
+                assert times.get(f"gemm_{name}/{tile}") == 1 and sum(v for k, v in times.items() if k.startswith(f"gemm_{name}/")) == 1, (r, times)
+            got = np.concatenate([t["y_txt"].cpu().numpy(), t["y"].cpu().numpy()])
+            want = got if want is None else want
+            assert np.array_equal(got.view(np.uint8), want.view(np.uint8)), r
+            run.fwd(0, io)                         # the block that was begun
+            run.ctx.cf_sync()
+    finally:
+        run.close()
+    rows = np.sort(np.random.default_rng(img).choice(img + txt, 150, replace=False))
+    ref = ob.block_forward(cfg, params, inputs, rows=rows)["y_rows"]
+    assert rel_l2(want[rows], ref) <= 1e-2

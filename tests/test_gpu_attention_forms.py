@@ -22,14 +22,6 @@ def operands(q, k, v):
     return (dev_bits(qb), dev_bits(kb), dev_bits(vt), H, q.shape[1], nk, pad, hd), (qf, kf, vf)
 
 
-def whole(ops):
-    q, k, vt, H, nq, nk, pad, hd = ops
-    o = torch.zeros((H, nq, hd), dtype=torch.int16, device=DEV)
-    B.cf_op_attention(q, k, vt, o, H, nq, nk, pad, hd)
-    torch.cuda.synchronize()
-    return host_bits(o)
-
-
 def form(ops, parts=1, all_parts=False, deal=0, no_wait=False):
     q, k, vt, H, nq, nk, pad, hd = ops
     floats = parts * H * ((nq + 31) // 32) * 32 * (hd + 2) if parts > 1 else 24 * 32 * 512 * 66
@@ -39,6 +31,11 @@ def form(ops, parts=1, all_parts=False, deal=0, no_wait=False):
     B.cf_op_attention_form(q, k, vt, o, H, nq, nk, pad, hd, None if all_parts else scratch, parts, all_parts, deal, no_wait)
     torch.cuda.synchronize()
     return host_bits(o)
+
+
+def whole(ops):
+    """Sweeps over all keys by the grid's workgroups, which cf_op_attention need not take (few queries)."""
+    return form(ops)
 
 
 def reference(values):

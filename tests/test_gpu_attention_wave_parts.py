@@ -23,13 +23,14 @@ def test_a_wave_to_each_part(H, nq, nk, hd, parts, sharp):
     assert rel_l2(got, ref) < 6e-3 and max_abs(got, ref) < 2e-2 * max(1.0, np.abs(ref).max())
 
 
-def test_scores_out_of_range():
+@pytest.mark.parametrize("hd", [64, 128])
+def test_scores_out_of_range(hd):
     rng = np.random.default_rng(5)
-    q, k, v = (rng.normal(size=(2, n, 64)) for n in (70, 1000, 1000))
-    u = np.ones(64) / 8.0
+    q, k, v = (rng.normal(size=(2, n, hd)) for n in (70, 1000, 1000))
+    u = np.ones(hd) / np.sqrt(hd)
     q += 4.0 * u
-    k[0, 640:704] += 600.0 * u                                 # 300 nats above the tiles before it, inside a part
-    k[1, :256] = np.where(np.arange(64) == 0, -np.inf, 0.0)    # a whole part of -inf (or +inf: q < 0) scores
+    k[0, 640:704] += 600.0 * u                                 # 300 or 212 nats above the tiles before it, inside a part
+    k[1, :256] = np.where(np.arange(hd) == 0, -np.inf, 0.0)    # a whole part of -inf (or +inf: q < 0) scores
     q[1, :, 0] = np.abs(q[1, :, 0]) + 0.1
     ops, values = operands(q, k, v)
     got = bits_to_f64(form(ops, parts=4, all_parts=2))

@@ -83,7 +83,8 @@ def test_linear_gated_residual(M, N, K, gate):
     assert max_abs(y.cpu().numpy(), ref) < 5e-5 * math.sqrt(K) and rel_l2(y.cpu().numpy(), ref) < 1e-5
 
 
-def run_attention(q, k, v, hd):
+def run_attention(q, k, v, hd, form=None):
+    """form: (parts, all_parts) of the caller's choice (cf_op_attention_form) instead of the planner's."""
     H, nq, _ = q.shape
     nk = k.shape[1]
     nk_pad = (nk + 63) // 64 * 64
@@ -93,7 +94,10 @@ def run_attention(q, k, v, hd):
     vt = np.zeros((H, hd, nk_pad), dtype=np.uint16)
     vt[:, :, :nk] = vb.transpose(0, 2, 1)
     O = torch.zeros((H, nq, hd), dtype=torch.int16, device=DEV)
-    B.cf_op_attention(dev_bits(qb), dev_bits(kb), dev_bits(vt), O, H, nq, nk, nk_pad, hd)
+    if form is None:
+        B.cf_op_attention(dev_bits(qb), dev_bits(kb), dev_bits(vt), O, H, nq, nk, nk_pad, hd)
+    else:
+        B.cf_op_attention_form(dev_bits(qb), dev_bits(kb), dev_bits(vt), O, H, nq, nk, nk_pad, hd, None, *form)
     torch.cuda.synchronize()
     ref = ob.attention(bits_to_f64(qb), bits_to_f64(kb), bits_to_f64(vb))
     return bits_to_f64(host_bits(O)), ref
@@ -127,8 +131,9 @@ def test_attention_uniform_values_and_dominant_key():
     assert np.abs(got[0, 3] - bf16_round(v2[0, 150])[0]).max() < 1e-2
 
 
+@pytest.mark.parametrize("form", [None, (1, 0), (2, 1), (2, 2)])        # the planner's; one long sweep; two parts of six tiles in turn, a wave to each
 @pytest.mark.parametrize("step", [0.7, 3.0, 30.0, 200.0])
-def test_attention_scores_that_keep_rising_along_the_keys(step):
+def test_attention_scores_that_keep_rising_along_the_keys(step, form):
     """Every 64-key tile scores `step` nats above the one before it, for every query: whatever reference
     the kernel's online softmax keeps has to move again and again (by a little, by 43 binary orders per
     tile, and by more than exp2 can represent), and late tiles carry nearly all the weight."""
@@ -141,7 +146,7 @@ def test_attention_scores_that_keep_rising_along_the_keys(step):
     ramp = (np.arange(nk) // 64) * step * np.sqrt(hd) / a
     k = ramp[None, :, None] * u + 0.3 * rng.normal(size=(H, nk, hd))
     v = rng.normal(size=(H, nk, hd))
-    got, ref = run_attention(q, k, v, hd)
+    got, ref = run_attention(q, k, v, hd, form)
     assert np.isfinite(got).all()
     assert rel_l2(got, ref) < 6e-3, rel_l2(got, ref)
     assert max_abs(got, ref) < 2e-2 * max(1.0, np.abs(ref).max()), max_abs(got, ref)

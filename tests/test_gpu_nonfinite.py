@@ -56,6 +56,7 @@ def test_tiles_of_scores_of_minus_infinity(hd, parts, lo, hi):
     ref = reference(values)
     assert np.isfinite(ref).all() and np.isfinite(got).all()
     if parts > 1:
-        assert np.array_equal(form(ops, parts=parts, all_parts=True), form(ops, parts=parts))
+        for all_parts in (1, 2) if parts <= (8 if hd == 64 else 4) else (1,):      # one after the other, a wave to each
+            assert np.array_equal(form(ops, parts=parts, all_parts=all_parts), form(ops, parts=parts)), all_parts
     print(f"rel_l2={rel_l2(got, ref):.3e}", flush=True)
     assert rel_l2(got, ref) < 6e-3 and max_abs(got, ref) < 2e-2 * max(1.0, np.abs(ref).max())

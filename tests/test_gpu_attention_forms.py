@@ -85,7 +85,7 @@ def test_dealt_out_sweeps_have_the_bits_of_whole_ones(H, nq, nk, deal):
 @pytest.mark.parametrize("deal", [1, 2])
 def test_dealt_out_sweeps_that_have_to_be_repeated(H, nq, nk, at, deal):
     """A cut sweep is then repeated from its first tile, as a whole one is, whichever of its pieces found out."""
-    assert B.cf_plan_attention(H, nq, nk, 128) == 8            # a repeated sweep is a workgroup's: the same 256 queries
+    assert B.cf_plan_attention(H, nq, nk, 128) == 8            # the height of the dealt out sweeps
     rng = np.random.default_rng(nk)
     q, k, v = (rng.normal(size=(H, n, 128)) for n in (nq, nk, nk))
     u = rng.normal(size=128)

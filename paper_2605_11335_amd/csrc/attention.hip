@@ -937,7 +937,8 @@ static double wave_parts_us(int heads, int nq, int tiles, int hd, int parts) {
 // x 4608: 72 us whole, 51 in two or four parts; 12 heads x 2640: 51 us whole, 58 in two).  Not where the planner would then give one
 // sample's workgroups all parts.
 // Parts that are waves: two to four (five to eight are no faster: 8 x 1000 x 64 in 2, 3, 4, 8 parts 11.3, 9.8, 8.3, 8.9 us), where they take
-// at least 15 % off and a batch with a workgroup per CU joins them in a twenty-fifth of its time.  One sample whole or merged / so, and
+// at least 15 % off and a batch with a workgroup per CU joins them in a twenty-fifth of its time; or as many as were chosen for workgroups, where
+// waves are the faster with those (1 x 2640 to 4680 x 64 in five to eight: merged 17.0 to 22.0, waves 14.3 to 20.2).  One sample whole or merged / so, and
 // eight samples whole / all parts in turn: 8 x 512 x 64 9.3 / 7.6 and 10.2 / 10.4; 8 x 800 x 64 12.6 / 10.7 and 19.8 / 20.4; 8 x 1000 x 64 14.4 / 11.3 and
 // 24.4 / 25.3; 3 x 2048 x 64 17.0 / 12.2 and 36.8 / 38.2; 8 x 512 x 128 13.1 / 11.5 and 15.8 / 16.7; 8 x 1000 x 128 20.9 / 15.4 and 40.9 / 41.6; 3 x 2048 x 128 28.7 / 20.5
 // and 53.5 / 54.4.  (Four parts of 8 x 512 x 64: 6.1 us, and eight samples 11.2.)  Over 380 batches of 320 to 3584

@@ -635,6 +635,45 @@ int run_linear_pair(Fwd& F, int kid, const std::string (&wname)[2], const std::s
     return CF_OK;
 }
 
+// Whether a projection (n = 2: two in one launch) places its heads itself.  Only as one launch: every chunk of its weights, biases and
+// norms has been waited for.  Otherwise its rows go out panel by panel and pre_attention_launch makes heads of them, with the same bits.
+// What it saves of that pass: reading and writing `rows` vectors of d at 5 TB/s, and where there is nothing else to it (`all`) the launch.
+bool heads_in_launch(const Fwd& F, const GemmArgs* g_in, int n, const std::string* wname, const std::string* bname, const std::vector<std::string>& norms,
+                     double rows, bool all) {
+    const cf_ctx* c = F.c;
+    // (32-bit offsets within a sample's heads)
+    if ((uint64_t)c->d.d * (n_pad_of(c->d.n_total) + n_pad_of(c->d.l_ctx)) * 2 >= (1ull << 32)) return false;
+    const int have = std::max(c->waited_upto, c->P(F.block).n_res_chunks - 1);
+    auto landed = [&](const TensorDesc& t) { return (int)((t.off + t.bytes() - 1) / c->chunk_bytes) <= have; };
+    GemmArgs g[2];
+    for (int i = 0; i < n; ++i) {
+        const TensorDesc& w = T(F, wname[i]);
+        if (g_in[i].M <= 0 || !landed(w) || !landed(T(F, bname[i]))) return false;
+        // v goes out eight tokens to a store, a slice of 32 with one address: where samples and segments begin on eight positions and are not
+        // tiny (4 x 593 tokens of a rank, whose v goes out element by element: 23 us of the launch become 39, 9 of 36 in the pass are saved)
+        const HeadsOut& h = g_in[i].heads;
+        const TokenMap& t = h.r.map;
+        const bool has_v = h.first + (int)w.rows / c->d.d > 2;
+        if ((has_v && (t.pos0 % 8 || (t.len1 > 0 && (t.len0 % 8 || t.pos1 % 8)) || h.rps % 8)) || (h.rps && h.rps < 64)) return false;
+        g[i] = g_in[i];
+        g[i].n0 = 0;
+        g[i].N = g[i].n1 = (int)w.rows;
+        g[i].K = (int)w.cols;
+        g[i].heads.on = 1;
+    }
+    if (c->d.qk_rmsnorm)
+        for (const std::string& t : norms)
+            if (!landed(T(F, t))) return false;
+    return gemm_heads_pay(g[0], n > 1 ? &g[1] : nullptr, (all ? 5.0 : 1.0) + 4.0 * rows * c->d.d / 5e6);
+}
+
+// r of the first sample; op_bs, vt_bs, send_bs: strides to the next one
+HeadsOut heads_to(const RelayoutArgs& r, int first, int rps, size_t op_bs, size_t vt_bs, size_t send_bs) {
+    HeadsOut h{};
+    h.first = first; h.rps = rps; h.op_bs = (long)op_bs; h.vt_bs = (long)vt_bs; h.send_bs = (long)send_bs; h.r = r;
+    return h;
+}
+
 TokenMap token_map(const cf_model_desc& m) {
     TokenMap t;
     t.n_total = m.n_total;
@@ -676,9 +715,9 @@ struct AttnOut {
 };
 
 // q/k/v of the local rows (already in ws.qkv) -> attention over the joint sequence -> rows of all
-// heads for the local tokens.  `parts` describe sample 0; sample b's rows follow densely
+// heads for the local tokens.  placed: the projection has made heads of the local rows already (HeadsOut).  `parts` describe sample 0; sample b's rows follow densely
 // (b * rows * ld further), its operands and peer/send buffers one sample further each.
-int run_joint_attention(Fwd& F, const RelayoutArgs* parts, int n_parts, const AttnOut& out) {
+int run_joint_attention(Fwd& F, const RelayoutArgs* parts, int n_parts, const AttnOut& out, bool placed) {
     cf_ctx* c = F.c;
     const cf_model_desc& m = c->d;
     const int P = m.sp_degree, hl = m.n_heads / P, h0 = m.sp_rank * hl, hd = m.head_dim, B = batch_of(m);
@@ -692,13 +731,14 @@ int run_joint_attention(Fwd& F, const RelayoutArgs* parts, int n_parts, const At
     const size_t peer_bs = (size_t)hl * n_rem * hd, send_bs = (size_t)(m.n_heads - hl) * map.n_local * hd;
     const bool direct = P == 1 && !out.dst1;        // attention writes the projection operand row by row itself
     const size_t pa_bs = (size_t)map.n_local * (m.n_heads - hl) * hd;
-    for (int b = 0; b < B; ++b) {
+    for (int b = 0; b < B && !(placed && P == 1 && !F.ws.flags); ++b) {
         RelayoutArgs pb[2];
         double bytes = 0;
         for (int i = 0; i < n_parts; ++i) {
             RelayoutArgs& r = pb[i];
             r = parts[i];
             r.src += (size_t)b * r.rows * r.ld;
+            if (placed) r.rows = 0;
             r.Q += b * op_bs; r.K += b * op_bs; r.Vt += b * vt_bs;
             if (r.send_q) r.send_q += b * send_bs;
             if (r.send_k) r.send_k += b * send_bs;
@@ -770,6 +810,12 @@ RelayoutArgs relayout_for(Fwd& F, const bf16* src, int rows, int row0, const std
     return r;
 }
 
+HeadsOut joint_heads(const Fwd& F, const RelayoutArgs& r) {
+    const cf_model_desc& m = F.c->d;
+    const size_t hl = m.n_heads / m.sp_degree, nl = m.n_total / m.sp_degree, hd = m.head_dim;
+    return heads_to(r, 0, batch_of(m) > 1 ? r.rows : 0, hl * m.n_total * hd, hl * hd * n_pad_of(m.n_total), (m.n_heads - hl) * nl * hd);
+}
+
 // sample strides of the caller's residual streams (elements); 0 in the io struct = dense
 long x_stride(const cf_block_io* io, long dense) { return io->x_sample_stride ? (long)io->x_sample_stride : dense; }
 long x_txt_stride(const cf_block_io* io, long dense) { return io->x_txt_sample_stride ? (long)io->x_txt_sample_stride : dense; }
@@ -795,9 +841,12 @@ int fwd_single(Fwd& F) {
     g.A = F.ws.xn; g.lda = d; g.M = rows; g.epi = EPI_SPLIT_GELU;
     g.out0 = F.ws.qkv; g.ld0 = 3 * d; g.n_split = 3 * d;
     g.out1 = F.ws.c; g.ld1 = d + f; g.col1_off = d;
-    CF_TRY(run_linear(F, K_LIN1, "w1", "b1", g));
-    RelayoutArgs r = relayout_for(F, F.ws.qkv, nl, 0, "q_norm", "k_norm");
-    CF_TRY(run_joint_attention(F, &r, 1, AttnOut{F.ws.c, nullptr, d + f, (long)nl * (d + f), 0}));
+    const RelayoutArgs r = relayout_for(F, F.ws.qkv, nl, 0, "q_norm", "k_norm");
+    g.heads = joint_heads(F, r);
+    const std::string w1 = "w1", b1 = "b1";
+    g.heads.on = heads_in_launch(F, &g, 1, &w1, &b1, {"q_norm", "k_norm"}, 3.0 * rows, m.sp_degree == 1);
+    CF_TRY(run_linear(F, K_LIN1, w1, b1, g));
+    CF_TRY(run_joint_attention(F, &r, 1, AttnOut{F.ws.c, nullptr, d + f, (long)nl * (d + f), 0}, g.heads.on));
     GemmArgs h{};
     h.A = F.ws.c; h.lda = d + f; h.M = rows; h.epi = EPI_GATE_RESID;
     h.resid = io->x; h.gate = gate; h.y = io->y; h.ldy = d;
@@ -1629,9 +1678,13 @@ int fwd_dit(Fwd& F) {
     // self-attention
     CF_TRY(run_ln_mod(F, LnArgs{io->x, sh1, sc1, w.xn, rows, rps, xs, mod_bs}));
     if (m.qk_rmsnorm) { CF_TRY(need(F, T(F, "q_norm"))); CF_TRY(need(F, T(F, "k_norm"))); }
-    CF_TRY(run_linear(F, K_QKV, "w_qkv", "b_qkv", plain_linear(w.xn, d, rows, w.qkv, 3 * d)));
-    RelayoutArgs r = relayout_for(F, w.qkv, nl, 0, "q_norm", "k_norm");
-    CF_TRY(run_joint_attention(F, &r, 1, AttnOut{w.c, nullptr, d, dense, 0}));
+    const RelayoutArgs r = relayout_for(F, w.qkv, nl, 0, "q_norm", "k_norm");
+    GemmArgs qkv = plain_linear(w.xn, d, rows, w.qkv, 3 * d);
+    const std::string wqkv = "w_qkv", bqkv = "b_qkv";
+    qkv.heads = joint_heads(F, r);
+    qkv.heads.on = heads_in_launch(F, &qkv, 1, &wqkv, &bqkv, {"q_norm", "k_norm"}, 3.0 * rows, m.sp_degree == 1);
+    CF_TRY(run_linear(F, K_QKV, wqkv, bqkv, qkv));
+    CF_TRY(run_joint_attention(F, &r, 1, AttnOut{w.c, nullptr, d, dense, 0}, qkv.heads.on));
     CF_TRY(run_linear(F, K_OUT, "w_o", "b_o", batched(resid_linear(w.c, d, rows, io->x, g1, w.x1, d), B, nl, mod_bs, xs, dense)));
     // cross-attention: queries from the local tokens (all heads), keys/values from the context
     CF_TRY(need(F, T(F, "ln_c_w")));
@@ -1641,25 +1694,32 @@ int fwd_dit(Fwd& F) {
         CF_HIP(c, ln_affine_launch(w.x1, F.W, T(F, "ln_c_w").off, T(F, "ln_c_b").off, w.xn, rows, d, F.s));
     }
     if (m.qk_rmsnorm) { CF_TRY(need(F, T(F, "cq_norm"))); CF_TRY(need(F, T(F, "ck_norm"))); }
+    const int lpad = n_pad_of(lc);
+    RelayoutArgs rq{};
+    rq.src = w.qkv; rq.ld = d; rq.rows = nl; rq.col_q = 0; rq.col_k = -1; rq.col_v = -1;
+    rq.n_heads = H; rq.h0 = 0; rq.h_local = H; rq.hd = hd; rq.W = F.W; rq.has_norm = m.qk_rmsnorm;
+    if (m.qk_rmsnorm) { rq.qn_off = T(F, "cq_norm").off; rq.kn_off = T(F, "ck_norm").off; }
+    rq.map = identity_map(nl); rq.row0 = 0; rq.Q = w.cQ; rq.K = nullptr; rq.Vt = nullptr; rq.n_pad = 0;
+    RelayoutArgs rk = rq;
+    rk.src = w.ckv; rk.ld = 2 * d; rk.rows = lc; rk.col_q = -1; rk.col_k = 0; rk.col_v = d;
+    rk.map = identity_map(lc); rk.Q = nullptr; rk.K = w.cK; rk.Vt = w.cVt;
+    rk.n_pad = lpad;
+    bool placed;
     {
         // the query projection of the local tokens and the K/V projection of the context are independent
         const std::string wn[2] = {"w_cq", "w_ckv"}, bn[2] = {"b_cq", "b_ckv"};
-        const GemmArgs g[2] = {plain_linear(w.xn, d, rows, w.qkv, d), plain_linear((const bf16*)io->ctx, d, B * lc, w.ckv, 2 * d)};
+        GemmArgs g[2] = {plain_linear(w.xn, d, rows, w.qkv, d), plain_linear((const bf16*)io->ctx, d, B * lc, w.ckv, 2 * d)};
+        g[0].heads = heads_to(rq, 0, rps, (size_t)nl * d, 0, 0);
+        g[1].heads = heads_to(rk, 1, B > 1 ? lc : 0, (size_t)lc * d, (size_t)d * lpad, 0);
+        placed = heads_in_launch(F, g, 2, wn, bn, {"cq_norm", "ck_norm"}, rows + 2.0 * B * lc, true);
+        g[0].heads.on = g[1].heads.on = placed;
         CF_TRY(run_linear_pair(F, K_CROSS_Q, wn, bn, g));
     }
-    const int lpad = n_pad_of(lc);
-    for (int b = 0; b < B; ++b) {
-        RelayoutArgs rq{};
-        rq.src = w.qkv + (size_t)b * nl * d; rq.ld = d; rq.rows = nl; rq.col_q = 0; rq.col_k = -1; rq.col_v = -1;
-        rq.n_heads = H; rq.h0 = 0; rq.h_local = H; rq.hd = hd; rq.W = F.W; rq.has_norm = m.qk_rmsnorm;
-        if (m.qk_rmsnorm) { rq.qn_off = T(F, "cq_norm").off; rq.kn_off = T(F, "ck_norm").off; }
-        rq.map = identity_map(nl); rq.row0 = 0; rq.Q = w.cQ + (size_t)b * nl * d; rq.K = nullptr; rq.Vt = nullptr; rq.n_pad = 0;
-        RelayoutArgs rk = rq;
-        rk.src = w.ckv + (size_t)b * lc * 2 * d; rk.ld = 2 * d; rk.rows = lc; rk.col_q = -1; rk.col_k = 0; rk.col_v = d;
-        rk.map = identity_map(lc); rk.Q = nullptr; rk.K = w.cK + (size_t)b * lc * d; rk.Vt = w.cVt + (size_t)b * d * lpad;
-        rk.n_pad = lpad;
+    for (int b = 0; b < B && !placed; ++b) {
+        RelayoutArgs both[2] = {rq, rk};
+        both[0].src += (size_t)b * nl * d; both[0].Q += (size_t)b * nl * d;
+        both[1].src += (size_t)b * lc * 2 * d; both[1].K += (size_t)b * lc * d; both[1].Vt += (size_t)b * d * lpad;
         ProfScope ps(c, F.s, K_RELAYOUT, 0, 2.0 * 2 * ((double)nl * d + 2.0 * lc * d));
-        const RelayoutArgs both[2] = {rq, rk};
         CF_HIP(c, pre_attention_launch(both, 2, nullptr, nullptr, nullptr, PeerAttnArgs{}, nullptr, F.s));
     }
     {
@@ -1710,19 +1770,24 @@ int fwd_double(Fwd& F) {
     RelayoutArgs parts[2];
     auto names = [&](const char* t, std::string (&out)[2]) { out[0] = nm(st[0], t); out[1] = nm(st[1], t); };
     std::string wn[2], bn[2];
+    for (int s = 0; s < 2; ++s) parts[s] = relayout_for(F, w.qkv + (size_t)row0[s] * 3 * d, per[s], s ? tl : 0, nm(st[s], "q_norm"), nm(st[s], "k_norm"));
+    bool placed;
     {
-        const GemmArgs g[2] = {plain_linear(w.xn + (size_t)row0[0] * d, d, rows[0], w.qkv + (size_t)row0[0] * 3 * d, 3 * d),
-                               plain_linear(w.xn + (size_t)row0[1] * d, d, rows[1], w.qkv + (size_t)row0[1] * 3 * d, 3 * d)};
+        GemmArgs g[2];
         names("w_qkv", wn); names("b_qkv", bn);
+        for (int s = 0; s < 2; ++s) {
+            g[s] = plain_linear(w.xn + (size_t)row0[s] * d, d, rows[s], w.qkv + (size_t)row0[s] * 3 * d, 3 * d);
+            g[s].heads = joint_heads(F, parts[s]);
+        }
+        placed = heads_in_launch(F, g, 2, wn, bn, {"txt_q_norm", "txt_k_norm", "img_q_norm", "img_k_norm"}, 3.0 * B * nl, m.sp_degree == 1);
+        g[0].heads.on = g[1].heads.on = placed;
         CF_TRY(run_linear_pair(F, K_QKV, wn, bn, g));
     }
-    for (int s = 0; s < 2; ++s) {
+    for (int s = 0; s < 2; ++s)
         if (m.qk_rmsnorm) { CF_TRY(need(F, T(F, nm(st[s], "q_norm")))); CF_TRY(need(F, T(F, nm(st[s], "k_norm")))); }
-        parts[s] = relayout_for(F, w.qkv + (size_t)row0[s] * 3 * d, per[s], s ? tl : 0, nm(st[s], "q_norm"), nm(st[s], "k_norm"));
-    }
     // one sample: its image rows follow its text rows in w.c; a batch: the streams' regions are apart
     CF_TRY(run_joint_attention(F, parts, 2, B > 1 ? AttnOut{w.c, w.c + (size_t)row0[1] * d, d, dense[0], dense[1]}
-                                                  : AttnOut{w.c, nullptr, d, (long)nl * d, 0}));
+                                                  : AttnOut{w.c, nullptr, d, (long)nl * d, 0}, placed));
     {
         GemmArgs g[2];
         for (int s = 0; s < 2; ++s)

@@ -4,6 +4,7 @@
 // streamed-bytes checksum.  All accesses are 8- or 16-byte per lane and
 // consecutive lanes touch consecutive addresses.
 #include "common.h"
+#include "heads.h"
 #include "kernels.h"
 
 namespace {
@@ -12,30 +13,6 @@ __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     return v;
-}
-
-__device__ __forceinline__ void unpack8(const uint32x4& u, float* f) {
-    f[0] = __uint_as_float(u.x << 16); f[1] = __uint_as_float(u.x & 0xffff0000u);
-    f[2] = __uint_as_float(u.y << 16); f[3] = __uint_as_float(u.y & 0xffff0000u);
-    f[4] = __uint_as_float(u.z << 16); f[5] = __uint_as_float(u.z & 0xffff0000u);
-    f[6] = __uint_as_float(u.w << 16); f[7] = __uint_as_float(u.w & 0xffff0000u);
-}
-__device__ __forceinline__ void unpack8(const uint4& u, float* f) {
-    f[0] = __uint_as_float(u.x << 16); f[1] = __uint_as_float(u.x & 0xffff0000u);
-    f[2] = __uint_as_float(u.y << 16); f[3] = __uint_as_float(u.y & 0xffff0000u);
-    f[4] = __uint_as_float(u.z << 16); f[5] = __uint_as_float(u.z & 0xffff0000u);
-    f[6] = __uint_as_float(u.w << 16); f[7] = __uint_as_float(u.w & 0xffff0000u);
-}
-
-__device__ __forceinline__ int local_pos(const TokenMap& m, int i) {
-    return i < m.len0 ? m.pos0 + i : m.pos1 + (i - m.len0);
-}
-// i-th position (ascending) that is NOT local
-__device__ __forceinline__ int remote_pos(const TokenMap& m, int i) {
-    if (i < m.pos0) return i;
-    i += m.len0;
-    if (m.len1 == 0 || i < m.pos1) return i;
-    return i + m.len1;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -197,7 +174,7 @@ __device__ __forceinline__ void qk_relayout_part(const RelayoutArgs& r, int bid,
     const int lane = threadIdx.x & 63;
     const int lph = r.hd / 8, lsh = r.hd == 128 ? 4 : 3;        // lanes per head vector
     const int vpw = 64 >> lsh, grp = lane >> lsh, sub = lane & (lph - 1);
-    float w[2][8];
+    float w[2][8] = {};
     if (r.has_norm) {
 #pragma unroll
         for (int t = 0; t < 2; ++t) unpack8(*(const uint32x4*)wv_ptr(r.W, (t ? r.kn_off : r.qn_off) + sub * 16), w[t]);
@@ -214,11 +191,11 @@ __device__ __forceinline__ void qk_relayout_part(const RelayoutArgs& r, int bid,
         bf16* const send_dst = send + (size_t)lrow * r.hd + sub * 8;
         const bf16* const src = r.src + (size_t)row * r.ld + col + sub * 8;
         const bool turn = r.rope_cos && tns < 2;
-        float4 cs = make_float4(1.f, 1.f, 1.f, 1.f), sn = make_float4(0.f, 0.f, 0.f, 0.f);
+        floatx4 cs = {1.f, 1.f, 1.f, 1.f}, sn = {0.f, 0.f, 0.f, 0.f};
         if (turn) {          // this lane's 8 elements are pairs sub*4 .. sub*4+3 of the head vector, for every head
             const size_t ro = (size_t)lrow * (r.hd / 2) + sub * 4;
-            cs = *(const float4*)(r.rope_cos + ro);
-            sn = *(const float4*)(r.rope_sin + ro);
+            cs = *(const floatx4*)(r.rope_cos + ro);
+            sn = *(const floatx4*)(r.rope_sin + ro);
         }
         for (int h4 = 0; h4 < r.n_heads; h4 += 4 * vpw) {        // four vectors of a lane group in flight
             uint32x4 u[4];
@@ -237,30 +214,10 @@ __device__ __forceinline__ void qk_relayout_part(const RelayoutArgs& r, int bid,
                     *(uint32x4*)dst = u[q];
                     continue;
                 }
-                float f[8];
-                unpack8(u[q], f);
-                if (r.has_norm) {
-                    float ss = 0.f;
+                float wt[8];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) ss += f[e] * f[e];
-                    for (int o = lph >> 1; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
-                    const float rs = rsqrtf(ss / r.hd + 1e-6f);
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) f[e] = f[e] * rs * (tns ? w[1][e] : w[0][e]);
-                }
-                if (turn) {
-                    const float c[4] = {cs.x, cs.y, cs.z, cs.w}, s4[4] = {sn.x, sn.y, sn.z, sn.w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float a = f[2 * e], b = f[2 * e + 1];
-                        f[2 * e] = a * c[e] - b * s4[e];
-                        f[2 * e + 1] = a * s4[e] + b * c[e];
-                    }
-                }
-                bf16x8 o8;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) o8[e] = (bf16)f[e];
-                *(bf16x8*)dst = o8;
+                for (int e = 0; e < 8; ++e) wt[e] = tns ? w[1][e] : w[0][e];
+                *(uint32x4*)dst = head_piece<false>(u[q], r.hd, r.has_norm, wt, turn, cs, sn);
             }
         }
     }
@@ -283,31 +240,8 @@ __device__ __forceinline__ void v_transpose_part(int bx, int h, const bf16* __re
         const bf16* const p = src + (size_t)h * src_hs + (size_t)i0 * src_rs + c * 8;
 #pragma unroll
         for (int k = 0; k < 8; ++k) u[k] = *(const uint32x4*)(p + (size_t)min(k, cnt - 1) * src_rs);
-        const int i_first = row0 + i0, i_last = i_first + cnt - 1;
-        const int p_first = remote ? remote_pos(map, i_first) : local_pos(map, i_first);
-        const int p_last = remote ? remote_pos(map, i_last) : local_pos(map, i_last);
-        const bool line = cnt == 8 && p_last - p_first == 7 && (p_first & 7) == 0;
-        uint16_t* const vh = (uint16_t*)Vt + (size_t)h * hd * n_pad;         // a head's rows: 32-bit offsets from here
-        const uint32_t o0 = (uint32_t)(c * 8) * (uint32_t)n_pad;
-        if (line) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {                        // element c*8 + e of the eight tokens
-                uint32x4 t;
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    t[k] = __builtin_amdgcn_perm(u[2 * k + 1][e >> 1], u[2 * k][e >> 1], e & 1 ? 0x07060302u : 0x05040100u);
-                *(uint32x4*)(vh + (o0 + (uint32_t)e * (uint32_t)n_pad + (uint32_t)p_first)) = t;
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                if (k >= cnt) break;
-                const uint32_t pos = remote ? remote_pos(map, i_first + k) : local_pos(map, i_first + k);
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    vh[o0 + (uint32_t)e * (uint32_t)n_pad + pos] = (uint16_t)(u[k][e >> 1] >> (16 * (e & 1)));
-            }
-        }
+        uint16_t* const vh = (uint16_t*)Vt + (size_t)h * hd * n_pad + (size_t)(c * 8) * n_pad;
+        v_turned(u, cnt, n_pad, [&](int k) { const int i = row0 + i0 + k; return vh + (remote ? remote_pos(map, i) : local_pos(map, i)); });
     }
     // zero the pad columns once per (head, d) row
     if (bx == 0 && !remote) {
@@ -359,7 +293,8 @@ __device__ __forceinline__ void peer_attn_part(int bid, const PeerAttnArgs& p) {
     }
 }
 
-// Everything between the QKV projection and attention in ONE launch: per part (one per stream)
+// Everything between the QKV projection and attention in ONE launch: per part (one per stream; none where the projection has placed
+// its heads itself)
 // the q/k RMSNorm + head-major relayout and the transposition of the own heads' v, then the peer
 // rows (q, k copied, v transposed).  Workgroups are dealt to the sub-tasks by index range.
 struct PreAttnArgs {
@@ -500,7 +435,8 @@ hipError_t pre_attention_launch(const RelayoutArgs* parts, int n_parts, const bf
         end += (int)((pieces + PEER_PIECES - 1) / PEER_PIECES);
     }
     a.seg[6] = end;
-    if (end == 0) return hipSuccess;
+    if (end == 0 && !zero) return hipSuccess;
+    if (end == 0) end = 1;                      // (nothing but words to clear)
     hipLaunchKernelGGL(pre_attention_kernel, dim3(end), dim3(256), 0, s, a);
     return hipGetLastError();
 }

@@ -16,7 +16,12 @@ const char* gemm_check(const GemmArgs& g) {
     if (((uintptr_t)g.A) % 16) return "gemm: A must be 16-byte aligned";
     if (g.epi == EPI_SPLIT_GELU) {
         if (g.n_split % 8) return "gemm: n_split must be a multiple of 8";
-        if (g.n_split > 0 && (!g.out0 || (g.ld0 % 8) || ((uintptr_t)g.out0 % 16))) return "gemm: out0 must be 16-byte aligned with ld0 a multiple of 8";
+        const HeadsOut& h = g.heads;
+        const int section = h.r.n_heads * h.r.hd;
+        if (h.on && ((h.r.hd != 64 && h.r.hd != 128) || section <= 0 || section % 256 || g.n_split % section || g.n_split / section > 3 - h.first || g.n0 % 256 ||
+                     h.first < 0 || h.rps < 0 || (h.rps && g.M % h.rps)))
+            return "gemm: heads must be whole tensors of 64 or 128 wide heads";
+        if (g.n_split > 0 && !h.on && (!g.out0 || (g.ld0 % 8) || ((uintptr_t)g.out0 % 16))) return "gemm: out0 must be 16-byte aligned with ld0 a multiple of 8";
         if (g.n_split < g.N && (!g.out1 || (g.ld1 % 8) || (g.col1_off % 8) || ((uintptr_t)g.out1 % 16)))
             return "gemm: out1 must be 16-byte aligned with ld1 and col1_off multiples of 8";
     } else if (g.epi == EPI_GATE_RESID) {
@@ -80,6 +85,11 @@ double tile_time(const TileCost& t, long tiles, int K) {
     }
     return us;
 }
+// Whether a tile's epilogue has whole heads where they are normed: a quadrant's half of the features, or on small tiles all of them
+// (gemm_epilogue).
+bool heads_fit(const TileCost& t, const GemmArgs& g) {
+    return !g.heads.on || !g.heads.r.has_norm || (t.bn < 256 ? t.bn : t.bn / 2) >= g.heads.r.hd;
+}
 // What a launch covers of a cut sum: all its parts, all but the last, the last
 enum Share { ALL_OF_IT, BEFORE_LAST, LAST };
 int best_tile(const GemmArgs* const (&g)[2], Share share = ALL_OF_IT, double* time = nullptr) {
@@ -87,6 +97,7 @@ int best_tile(const GemmArgs* const (&g)[2], Share share = ALL_OF_IT, double* ti
     double best_us = 0;
     for (int i = 0; i < GEMM_TILES; ++i) {
         if (i == GEMM_256x256 && g[1] && g[1]->ksplits > 1 && share != LAST) continue;        // not built: registers
+        if (!heads_fit(kTileCost[i], *g[0]) || (g[1] && !heads_fit(kTileCost[i], *g[1]))) continue;
         const TileCost& t = kTileCost[i];
         long tiles = 0;
         int K = 0;                       // the longest walk
@@ -403,6 +414,7 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(ReduceArgs a) {
 hipError_t dispatch(const GemmPlan& plan, const GemmArgs& g, const GemmArgs* second, hipStream_t s) {
     // the erf form of the activation is some seventeen VALU operations per element against the tanh form's four: it gets kernels
     // of its own rather than a run-time choice inside the tanh one
+    if (g.epi != EPI_GATE_RESID && g.heads.on) return g.act_erf ? gemm_launch_heads_erf(plan.tile, g, second, s) : gemm_launch_heads(plan.tile, g, second, s);
     if (g.epi != EPI_GATE_RESID) return g.act_erf ? gemm_launch_split_gelu_erf(plan.tile, g, second, s) : gemm_launch_split_gelu(plan.tile, g, second, s);
     if (g.ksplits <= 1) return gemm_launch_gate_resid(plan.tile, g, second, s);
     GemmArgs parts[2] = {g, second ? *second : g};
@@ -425,8 +437,28 @@ hipError_t gemm_launch_as(const GemmPlan& plan, const GemmArgs& g, hipStream_t s
 hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) { return gemm_launch_as(gemm_plan(g, nullptr), g, s); }
 
 // two layers share a launch if they have one epilogue and both or neither have their sum in parts
+// Whether a launch had better place its heads itself (`second`: two layers at once) than leave them to a pass that takes separate_us.
+// What it costs there: the tile may have to be another (heads_fit), and a quadrant's slices of 32 tokens take 1.2 us each longer than
+// plain rows, 2 where they are normed and 3 where they are rotated, in every round, or in as many as there are tiles of heads if there are
+// several (even_step).  1320 x 9216 x 3072, normed, one round of 192x256 tiles: 67.6 us and 9.1 of the pass, or 73; 2304 x 21504 x 3072,
+// three rounds: 265.4 and 17, or 266.  Rotated, 512 + 64 rows: 51 and 6, or 58.
+bool gemm_heads_pay(const GemmArgs& g, const GemmArgs* second, double separate_us) {
+    const GemmArgs* const with[2] = {&g, second};
+    GemmArgs plain[2] = {g, second ? *second : g};
+    for (GemmArgs& p : plain) p.heads.on = 0;
+    double placed, apart;
+    best_tile({&plain[0], second ? &plain[1] : nullptr}, ALL_OF_IT, &apart);
+    const TileCost& t = kTileCost[best_tile(with, ALL_OF_IT, &placed)];
+    long tiles = 0;
+    for (const GemmArgs* p : with)
+        if (p) tiles += (long)((p->M + t.bm - 1) / t.bm) * ((p->N + t.bn - 1) / t.bn);
+    const double slices = t.bn < 256 ? 0.5 : t.bm / 64, slice_us = g.heads.r.rope_cos ? 3.0 : g.heads.r.has_norm ? 2.0 : 1.2;
+    const double rounds = std::ceil((double)tiles / (256 * t.per_cu));
+    return placed + slices * slice_us * std::max(1.0, rounds * std::min(g.n_split, g.N) / g.N) <= apart + separate_us;
+}
+
 bool gemm_can_pair(const GemmArgs& g0, const GemmArgs& g1) {
-    return g0.epi == g1.epi && g0.act_erf == g1.act_erf && (g0.ksplits > 1) == (g1.ksplits > 1);
+    return g0.epi == g1.epi && g0.act_erf == g1.act_erf && g0.heads.on == g1.heads.on && (g0.ksplits > 1) == (g1.ksplits > 1);
 }
 
 hipError_t gemm_launch_pair(const GemmArgs& g0, const GemmArgs& g1, hipStream_t s) {

@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "heads.h"
 #include "kernels.h"
 
 namespace {
@@ -37,6 +38,8 @@ namespace {
 constexpr int EPI_SPLIT_GELU_ERF = 2;  // kernel variant of EPI_SPLIT_GELU with the erf form of the activation
 constexpr int EPI_PARTIAL = 3;         // kernel variant of EPI_GATE_RESID that stores the sums of one part of K, nothing added
 constexpr int EPI_LAST_PART = 4;       // kernel variant of EPI_GATE_RESID for the last part of K, which adds the ones before it from memory
+constexpr int EPI_HEADS = 5;           // kernel variant of EPI_SPLIT_GELU whose plain features are heads (HeadsOut)
+constexpr int EPI_HEADS_ERF = 6;       // and with the erf form of the activation
 constexpr int BK = 64;                 // K slab (bf16 elements) = 128 bytes per LDS row
 constexpr int STAGES = 2;              // slabs resident in LDS: one being multiplied, one in flight
 constexpr int ROWB = BK * 2;           // bytes per LDS row
@@ -82,6 +85,13 @@ __device__ __forceinline__ void handover() {
     asm volatile("" ::: "memory");
 }
 
+// The lane's number, computed here: the compiler does not keep the register from where it was asked for before.
+__device__ __forceinline__ int lane_here() {
+    uint32_t zero = 0u;
+    asm volatile("" : "+v"(zero));
+    return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
+}
+
 // The epilogue's staging: a wave passes its quadrant through a slice of LDS of its own, ROWS tokens (and of fp32 results 64
 // features) at a time, so that global stores are 16 bytes per lane with the lanes of a row on one contiguous segment.
 // 16-byte chunks of the slice's rows are XOR-swizzled like those of the slabs.
@@ -95,9 +105,15 @@ struct Stage {
     static __device__ __forceinline__ int at(int row, int chunk) { return row * RB + ((chunk ^ (row & (CPR - 1))) << 4); }
 };
 // Activations go out 32 tokens at a time (gemm_epilogue), fp32 results half a quadrant at a time: with nothing to compute between
-// the slices, smaller ones would only add waits.
-template <int BM, int EPI>
-constexpr int slice_rows() { return EPI == EPI_SPLIT_GELU || EPI == EPI_SPLIT_GELU_ERF ? 32 : BM / 2; }
+// the slices, smaller ones would only add waits.  Where heads are placed (EPI_HEADS) on tiles of 64 and 128 features, the two waves of the
+// same tokens share a slice of all of them, which has the heads whole (elsewhere the barrier costs 0.4 us of a launch).
+constexpr bool heads_out(int epi) { return epi == EPI_HEADS || epi == EPI_HEADS_ERF; }
+constexpr bool bf16_out(int epi) { return epi == EPI_SPLIT_GELU || epi == EPI_SPLIT_GELU_ERF || heads_out(epi); }
+constexpr bool joint_slices(int bn, int epi) { return heads_out(epi) && bn < 256; }
+template <int BM, int BN, int EPI>
+constexpr int slice_rows() { return bf16_out(EPI) && !joint_slices(BN, EPI) ? 32 : BM / 2; }
+template <int BM, int BN, int EPI>
+using StageOf = Stage<joint_slices(BN, EPI) ? BN / 32 : BN / 64, bf16_out(EPI) ? 2 : 4, slice_rows<BM, BN, EPI>()>;
 // orders a wave's LDS accesses before and after it, for the compiler (the LDS itself takes a wave's accesses in order)
 __device__ __forceinline__ void wave_lds_order() {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -115,16 +131,16 @@ template <int BM, int BN, int EPI>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx16 (&acc)[BN / 64][BM / 64], int m0, int n0, int part, int uw, char* smem) {
     constexpr int WM = BM / 2, WN = BN / 2;        // wave quadrant
     constexpr int MT = WM / 32, NT = WN / 32;      // 32x32 MFMA tiles per wave
-    constexpr bool OUT_BF16 = (EPI == EPI_SPLIT_GELU || EPI == EPI_SPLIT_GELU_ERF);
-    constexpr bool ACT_ERF = (EPI == EPI_SPLIT_GELU_ERF);
+    constexpr bool OUT_BF16 = bf16_out(EPI), JOINT = joint_slices(BN, EPI);
+    constexpr bool ACT_ERF = (EPI == EPI_SPLIT_GELU_ERF || EPI == EPI_HEADS_ERF);
     constexpr int ELT = OUT_BF16 ? 2 : 4;
-    constexpr int SJ = slice_rows<BM, EPI>() / 32;         // MFMA tiles of tokens per slice
-    using St = Stage<NT, ELT, SJ * 32>;
+    constexpr int SJ = slice_rows<BM, BN, EPI>() / 32;     // MFMA tiles of tokens per slice
+    using St = StageOf<BM, BN, EPI>;
     constexpr int ST = St::ST, RPI = St::RPI, CPR = St::CPR;
     // the same value, of which the compiler knows nothing: what is made from it is made where it is used, and not ahead of the
     // main loop (lane coordinates) or of the write-out (all its addresses at once), where it would fill the registers
     auto opaque = [](int v) { asm volatile("" : "+v"(v)); return v; };
-    const int lane = opaque(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u))), wave = uw;
+    const int lane = lane_here(), wave = uw;
     const int wm0 = (wave & 1) * WM, wn0 = (wave >> 1) * WN;
     const int li = lane & 31, lg = lane >> 5;
     // Bias of the wave's features where the activation needs it, in accumulator order: 4 consecutive features per (feature tile, register
@@ -143,15 +159,16 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx16 (&acc)
                 bias_raw[i][vb] = *(const uint32x2*)wv_ptr(g.W, g.bias_off + 2ull * n);
             }
     }
-    char* const stg = smem + wave * St::BYTES;
+    char* const stg = smem + (JOINT ? wave & 1 : wave) * St::BYTES;
+    const int cofs = JOINT ? (wave >> 1) * NT * 4 : 0;     // the wave's first chunk of a staged row
     // slice (p, j): tokens j*32.. and features p*FP.. of the quadrant, computed and written to LDS.  Whether a quadrant's features are
     // activated is decided once (n_split falls inside at most one column of quadrants): a decision per quad is a branch per quad,
     // between which nothing overlaps
     enum { PLAIN, ACTIVATED, MIXED };
-    auto stage = [&](auto act, int p, int j, int row0) __attribute__((always_inline)) {
+    auto stage = [&](auto act, int p, int j, int row0, char* stg) __attribute__((always_inline)) {
         wave_lds_order();
 #pragma unroll
-        for (int ii = 0; ii < St::NTP; ++ii) {
+        for (int ii = 0; ii < (JOINT ? NT : St::NTP); ++ii) {
             const int i = p * St::NTP + ii;
             floatx16 sums = acc[i][j];
             if constexpr (SJ == 1) asm volatile("" : "+v"(sums));      // from the accumulation registers now, not all tiles' ahead of the first store
@@ -175,7 +192,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx16 (&acc)
                     bf16x4 o;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) o[e] = (bf16)v[e];
-                    *(bf16x4*)(stg + St::at(row0 + li, ii * 4 + vb) + lg * 8) = o;
+                    *(bf16x4*)(stg + St::at(row0 + li, cofs + ii * 4 + vb) + lg * 8) = o;
                 } else {
                     *(floatx4*)(stg + St::at(row0 + li, ii * 8 + vb * 2 + lg)) = floatx4{v[0], v[1], v[2], v[3]};
                 }
@@ -186,25 +203,176 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx16 (&acc)
     const int row_l = lane / CPR, chunk_l = lane % CPR;        // a store's row (of RPI) and chunk of this lane
     if constexpr (OUT_BF16 || EPI == EPI_PARTIAL) {
         slab_handover();                       // every wave is done reading the slabs; the bias loads flew meanwhile
+        // the staged rows that the wave writes out, and the first feature of a staged row
+        constexpr int RW = JOINT ? WM / 2 : SJ * 32, STW = RW / RPI;
+        const int r0 = JOINT ? (wave >> 1) * RW : 0, nb = n0 + (JOINT ? 0 : wn0);
+        if constexpr (heads_out(EPI)) {
+            if (nb < g.n_split) {              // (whole tiles of either sort: gemm_check)
+                // Heads of q, k or v (a tile lies in one of the three), a vector in hd / 8 neighbouring lanes, to where attention reads them.  The
+                // whole quadrant is staged first: its registers are free then for a loop over the slices in which nothing waits for memory
+                // but the first rows of the rotary tables.  Bound by the VALU: the norm and the rotation are some 8 operations per value, 0.9 us of a
+                // slice.  What it replaces, a pass over rows in memory: toy 45 -> 41 us a block, Wan-like 1320 rows 603 -> 588 (two passes), Flux-like
+                // 2304 rows 620 -> 607.
+                const HeadsOut& h = g.heads;
+                const RelayoutArgs& r = h.r;
+                const int lsh = r.hd == 128 ? 4 : 3, D = r.n_heads * r.hd, sec = nb / D, tns = h.first + sec;
+                const bool norm = r.has_norm && tns < 2, turn = r.rope_cos && tns < 2;
+                uint32x4 w_raw = {0u, 0u, 0u, 0u};
+                if (norm) w_raw = *(const uint32x4*)wv_ptr(g.W, (tns ? r.kn_off : r.qn_off) + ((nb / 8 + lane_here() % CPR) & ((1 << lsh) - 1)) * 16);
+                // slices of RW tokens: of the wave's quadrant, one after the other, or (JOINT) its share of one
+                constexpr int SLICES = JOINT ? 1 : MT, NEXT = JOINT ? 32 * St::RB : 4 * St::BYTES;
+                const int m_first = m0 + wm0 + r0;
+#pragma unroll
+                for (int j = 0; j < MT; ++j) { __builtin_amdgcn_sched_barrier(0); stage(std::integral_constant<int, PLAIN>{}, 0, j, 0, stg + j * NEXT); }
+                if (JOINT) __syncthreads();
+                const int here = lane_here(), chunk = here % CPR, row = here / CPR, hh_c = nb - sec * D + chunk * 8, hh = hh_c >> (lsh + 3), sub = (hh_c >> 3) & ((1 << lsh) - 1);
+                const bool own = hh >= r.h0 && hh < r.h0 + r.h_local;
+                // sample of the token o tokens behind token i of sample b (o < 32); its number there
+                auto sample = [&](int b, int i, int o, int& io) __attribute__((always_inline)) {
+                    io = i + o;
+                    if (!h.rps) return b;
+                    if (h.rps >= 32) {
+                        const bool next = io >= h.rps;
+                        io -= next ? h.rps : 0;
+                        return b + next;
+                    }
+                    const int n = io / h.rps;
+                    io -= n * h.rps;
+                    return b + n;
+                };
+                // Most slices lie in one sample and one segment of the joint sequence: then a lane's addresses are one offset from a scalar
+                // base, and its rows a constant apart.  (With an address made for each row the slices took twice as long.)
+                struct Slice { bool whole; int b, i, pos; };       // sample, its token, position of the first token
+                auto slice = [&](int m) __attribute__((always_inline)) {
+                    const int b = h.rps ? m / h.rps : 0, i = m - b * h.rps, last = i + RW - 1, lrow = r.row0 + i;
+                    const bool whole = m + RW <= g.M && (!h.rps || last < h.rps) && ((lrow < r.map.len0) == (r.row0 + last < r.map.len0));
+                    return Slice{whole, b, i, local_pos(r.map, lrow)};
+                };
+                auto vectors = [&](auto norm_c, auto turn_c) __attribute__((always_inline)) {
+                    constexpr bool NORM = decltype(norm_c)::value, TURN = decltype(turn_c)::value;
+                    bf16* const send = tns == 0 ? r.send_q : tns == 1 ? r.send_k : r.send_v;
+                    bf16* const to_own = tns ? r.K : r.Q;
+                    const bool store = own ? tns < 2 : send != nullptr;
+                    float w[8];
+                    unpack8(w_raw, w);
+                    const int rows = own ? r.map.n_total : r.map.n_local, head = own ? hh - r.h0 : hh < r.h0 ? hh : hh - r.h_local;
+                    const uint32_t off = ((uint32_t)(head * rows + row) * r.hd + sub * 8) * 2u;
+                    floatx4 cs[TURN ? STW : 1], sn[TURN ? STW : 1], cs1[TURN ? STW : 1], sn1[TURN ? STW : 1];
+                    auto tables = [&](int m_in, auto& c, auto& s) __attribute__((always_inline)) {
+                        if constexpr (TURN) {
+                            const int m = m_in < g.M ? m_in : 0;           // (of a slice behind the end: some rows)
+                            const Slice first = slice(m);
+#pragma unroll
+                            for (int u = 0; u < STW; ++u) {
+                                int i;
+                                sample(first.b, first.i, m + u * RPI + row < g.M ? u * RPI + row : 0, i);
+                                const uint32_t at = (uint32_t)(r.row0 + i) * (r.hd / 2) + sub * 4;
+                                c[u] = *(const floatx4*)(r.rope_cos + at);
+                                s[u] = *(const floatx4*)(r.rope_sin + at);
+                            }
+                        }
+                    };
+                    tables(m_first, cs, sn);
+#pragma unroll 1
+                    for (int j = 0; j < SLICES; ++j) {
+                        const int mw = m_first + j * 32;
+                        if (SLICES > 1) tables(mw + 32, cs1, sn1);
+                        uint32x4 val[STW];
+#pragma unroll
+                        for (int u = 0; u < STW; ++u) val[u] = *(const uint32x4*)(stg + j * NEXT + St::at(r0 + u * RPI + row, chunk));
+                        if constexpr (NORM || TURN)
+#pragma unroll
+                            for (int u = 0; u < STW; ++u) val[u] = head_piece<true>(val[u], r.hd, NORM, w, TURN, cs[TURN ? u : 0], sn[TURN ? u : 0]);
+                        const Slice at = slice(mw);
+                        if (at.whole) {
+                            auto put = [&](bf16* to) __attribute__((always_inline)) {
+#pragma unroll
+                                for (int u = 0; u < STW; ++u) *(uint32x4*)((char*)to + off + u * RPI * r.hd * 2) = val[u];
+                            };
+                            if (own && tns < 2) put(to_own + at.b * h.op_bs + (size_t)at.pos * r.hd);
+                            if (!own && send) put(send + at.b * h.send_bs + (size_t)(r.row0 + at.i) * r.hd);
+                        } else if (store) {
+                            bf16* const base = (own ? to_own : send) + (size_t)(head * (long)rows) * r.hd + sub * 8;
+#pragma unroll
+                            for (int u = 0; u < STW; ++u) {
+                                int i;
+                                const int b = sample(at.b, at.i, u * RPI + row, i);
+                                if (mw + u * RPI + row < g.M) *(uint32x4*)(base + b * (own ? h.op_bs : h.send_bs) + (size_t)(own ? local_pos(r.map, r.row0 + i) : r.row0 + i) * r.hd) = val[u];
+                            }
+                        }
+                        if constexpr (TURN && SLICES > 1)
+#pragma unroll
+                            for (int u = 0; u < STW; ++u) cs[u] = cs1[u], sn[u] = sn1[u];
+                    }
+                };
+                using Yes = std::true_type;
+                using No = std::false_type;
+                if (norm && turn) vectors(Yes{}, Yes{});
+                else if (norm) vectors(Yes{}, No{});
+                else if (turn) vectors(No{}, Yes{});
+                else if (tns < 2 || __any(!own)) vectors(No{}, No{});
+                if (tns < 2) return;
+                // own v: a lane has 8 tokens of one chunk, neighbouring lanes the 8 tokens that follow
+                constexpr int TG = RW / 8;
+                static_assert(TG * CPR <= 64, "a lane per 8 tokens of a chunk");
+                const int grp = here % TG, c = here / TG;
+                const int vc = nb - sec * D + c * 8, vh = vc >> (lsh + 3);
+                const uint32_t v_row = (uint32_t)((vh - r.h0) * r.hd + (vc & (r.hd - 1))) * r.n_pad;
+                if (c < CPR && vh >= r.h0 && vh < r.h0 + r.h_local) {
+#pragma unroll 1
+                    for (int j = 0; j < SLICES; ++j) {
+                        const int mw = m_first + j * 32, cnt = min(8, g.M - mw - grp * 8);
+                        uint32x4 u[8];
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) u[k] = *(const uint32x4*)(stg + j * NEXT + St::at(r0 + grp * 8 + k, c));
+                        const Slice at = slice(mw);
+                        if (at.whole && (at.pos & 7) == 0) {
+                            v_turned_line(u, (char*)(r.Vt + at.b * h.vt_bs + at.pos), (v_row + grp * 8) * 2u, r.n_pad);
+                        } else if (cnt > 0) {
+                            v_turned(u, cnt, r.n_pad, [&](int k) __attribute__((always_inline)) {
+                                int i;
+                                const int b = sample(at.b, at.i, grp * 8 + k, i);
+                                return (uint16_t*)r.Vt + b * h.vt_bs + v_row + local_pos(r.map, r.row0 + i);
+                            });
+                        }
+                    }
+                }
+                // The columns of Vt behind the last position, a lane per row of it: by the wave that has local row 0 of the sample.
+                if (r.row0 == 0 && r.n_pad > r.map.n_total) {
+                    const int rps = h.rps ? h.rps : g.M, end = min(m_first + (SLICES - 1) * 32 + RW, g.M);
+                    for (int b = (m_first + rps - 1) / rps; b * rps < end; ++b)
+                        for (int f = here; f < St::FP; f += 64) {
+                            const int vc = nb - sec * D + f - r.h0 * r.hd;
+                            if (vc < 0 || vc >= r.h_local * r.hd) continue;
+                            uint16_t* const col = (uint16_t*)r.Vt + b * h.vt_bs + (size_t)vc * r.n_pad;
+                            int p = r.map.n_total;
+                            for (; p & 7; ++p) col[p] = 0;
+                            for (; p < r.n_pad; p += 8) *(uint32x4*)(col + p) = uint32x4{0u, 0u, 0u, 0u};
+                        }
+                }
+                return;
+            }
+        }
         auto write_out = [&](auto act) __attribute__((always_inline)) {
             constexpr int ACT = decltype(act)::value;
 #pragma unroll
             for (int p = 0; p < St::PASSES; ++p) {
-                const int n = n0 + wn0 + p * St::FP + chunk_l * (16 / ELT);        // first column of the lane's chunk
+                const int n = nb + p * St::FP + chunk_l * (16 / ELT);          // first column of the lane's chunk
 #pragma unroll
                 for (int j0 = 0; j0 < MT; j0 += SJ) {
 #pragma unroll
-                    for (int j = 0; j < SJ; ++j) stage(act, p, j0 + j, j * 32);
+                    for (int j = 0; j < SJ; ++j) stage(act, p, j0 + j, j * 32, stg);
+                    if (JOINT) __syncthreads();
                     const int r = opaque(row_l);
-                    constexpr int UB = ST > 4 && MT == 3 ? 4 : ST;     // (as the register allocator has it without spills)
+                    constexpr int UB = STW > 4 && MT == 3 ? 4 : STW;   // (as the register allocator has it without spills)
 #pragma unroll
-                    for (int u0 = 0; u0 < ST; u0 += UB) {
+                    for (int u0 = 0; u0 < STW; u0 += UB) {
                         uint32x4 val[UB];
 #pragma unroll
-                        for (int u = 0; u < UB; ++u) val[u] = *(const uint32x4*)(stg + St::at((u0 + u) * RPI + row_l, chunk_l));
+                        for (int u = 0; u < UB; ++u) val[u] = *(const uint32x4*)(stg + St::at(r0 + (u0 + u) * RPI + row_l, chunk_l));
 #pragma unroll
                         for (int u = 0; u < UB; ++u) {
-                            const int m = m0 + wm0 + j0 * 32 + (u0 + u) * RPI + r;
+                            const int m = m0 + wm0 + j0 * 32 + r0 + (u0 + u) * RPI + r;
                             if (m < g.M && n < g.n1) {
                                 if constexpr (OUT_BF16) {
                                     bf16* const dst = ACT == PLAIN || (ACT == MIXED && n < g.n_split) ? g.out0 + (size_t)m * g.ld0 + n
@@ -222,9 +390,11 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx16 (&acc)
         using Plain = std::integral_constant<int, PLAIN>;
         if constexpr (!OUT_BF16) {
             write_out(Plain{});
+        } else if constexpr (heads_out(EPI)) {
+            write_out(std::integral_constant<int, ACTIVATED>{});
         } else {
-            if (n0 + wn0 >= g.n_split) write_out(std::integral_constant<int, ACTIVATED>{});
-            else if (min(n0 + wn0 + WN, g.n1) <= g.n_split) write_out(Plain{});
+            if (nb >= g.n_split) write_out(std::integral_constant<int, ACTIVATED>{});
+            else if (min(nb + St::FP, g.n1) <= g.n_split) write_out(Plain{});
             else write_out(std::integral_constant<int, MIXED>{});
         }
     } else {
@@ -275,7 +445,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx16 (&acc)
                 }
                 if (b % HB == 0) {
 #pragma unroll
-                    for (int j = 0; j < MT; ++j) stage(std::integral_constant<int, PLAIN>{}, p, j, j * 32);
+                    for (int j = 0; j < MT; ++j) stage(std::integral_constant<int, PLAIN>{}, p, j, j * 32, stg);
                 }
                 if constexpr (LAST) {
                     for (int q = 1; q < part; ++q)
@@ -310,7 +480,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx16 (&acc)
 // One tile of one problem: tokens m0.., features n0...  STRADDLE: the byte where the blob switches buffers falls
 // inside the tile's weight rows (at most one tile column of a launch), so each lane picks its base.
 template <int BM, int BN, int EPI, bool STRADDLE>
-__device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0, int part) {
+__device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0, int part, int uw) {
     constexpr int WM = BM / 2, WN = BN / 2;        // wave quadrant
     constexpr int MT = WM / 32, NT = WN / 32;      // 32x32 MFMA tiles per wave
     constexpr int PA = MT % 2 ? 3 : 2;             // the activations go in thirds or halves, the weights in halves
@@ -324,16 +494,16 @@ __device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0,
     char* const sA = smem;                         // [STAGES][BM][ROWB] activations
     char* const sW = smem + STAGES * A_STAGE;      // [STAGES][BN][ROWB] weights
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wm0 = (wave & 1) * WM, wn0 = (wave >> 1) * WN;
+    // (the lane made here, the wave's number in a scalar register: of two variants of this in a kernel, the first would otherwise
+    // keep registers for the second)
+    const int lane = lane_here();
+    const int wm0 = (uw & 1) * WM, wn0 = (uw >> 1) * WN;
     const int li = lane & 31, lg = lane >> 5;
 
     // Slab copies go global -> LDS directly (no register staging).  One such load writes the
     // wave's 64 x 16 bytes to consecutive LDS addresses, i.e. 8 rows (a unit); which 16-byte chunk of
     // its row a lane fetches is chosen so that the chunk lands in its swizzled slot.  Part h of an operand is the
     // rows that the h-th parts of the waves' quadrants cover: unit (j*4 + wave) of it is unit `unit(..)` of the tile.
-    const int uw = __builtin_amdgcn_readfirstlane(wave);
     auto unit = [](int G, int parts, int h, int idx) { return (idx / G) * parts * G + h * G + idx % G; };
     uint32_t a_voff[PA][LA], w_voff[2][LW];        // byte offsets from the tile's first row
 #pragma unroll
@@ -498,16 +668,14 @@ __device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0,
 // 576 x 3072 x 12288: 164 us with the former loop, 111 with the 128x128 tile above, 85 with 128x64 (240 workgroups);
 // 64 x 3072 x 12288: 166, 102, 63 with 64x64; 512 x 512 x 2560: 31.4, 20.5, 12.2.
 template <int BM, int BN, int S, int EPI>
-__device__ __forceinline__ void gemm_ring_run(const GemmArgs& g, int m0, int n0, int part) {
+__device__ __forceinline__ void gemm_ring_run(const GemmArgs& g, int m0, int n0, int part, int uw) {
     constexpr int WM = BM / 2, WN = BN / 2;        // wave quadrant
     constexpr int MT = WM / 32, NT = WN / 32;      // 32x32 MFMA tiles per wave
     constexpr int LA = BM / 32, LW = BN / 32, L = LA + LW;     // wave-loads (8 rows each) per wave and slab
     constexpr int STAGE = (BM + BN) * ROWB;
 
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int uw = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     const int li = lane & 31, lg = lane >> 5;
     const int wm0 = (uw & 1) * WM, wn0 = (uw >> 1) * WN;
 
@@ -629,13 +797,15 @@ struct TileWalk {
         const int group = lid / (GM * tiles_n), in = lid % (GM * tiles_n);
         const int first_m = group * GM;
         const int gsz = std::min(tiles_m - first_m, GM);
-        return Tile{(first_m + in % gsz) * BM, g.n0 + in / gsz * BN, in % gsz, gsz};
+        int col = in / gsz;
+        if (g.col_step > 1) col = col * g.col_step % tiles_n;
+        return Tile{(first_m + in % gsz) * BM, g.n0 + col * BN, in % gsz, gsz};
     }
 };
 
 // Workgroup `bid` of the `nblk` that problem owns.  S: stages of the ring loop, 0 = the quadrant-phase loop (two stages).
 template <int BM, int BN, int S, int EPI>
-__device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, uint32_t bid, uint32_t nblk) {
+__device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, uint32_t bid, uint32_t nblk, int uw) {
     // logical tile: XCD-contiguous id, then (part of K by part of K) the walk over the tiles
     const TileWalk<BM, BN> walk(g);
     const int tiles_m = walk.tiles_m, tiles_n = walk.tiles_n;
@@ -646,11 +816,11 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, uint32_t bid, 
     const auto tile = walk.at(g, lid);
     const int m0 = tile.m0, n0 = tile.n0;
     if constexpr (S > 0) {
-        gemm_ring_run<BM, BN, S, EPI>(g, m0, n0, part);
+        gemm_ring_run<BM, BN, S, EPI>(g, m0, n0, part, uw);
     } else {
         const uint64_t t_begin = g.w_off + (uint64_t)n0 * g.K * 2, t_end = g.w_off + (uint64_t)min(n0 + BN, g.N) * g.K * 2;
-        if (g.W.split > t_begin && g.W.split < t_end) gemm_tile_run<BM, BN, EPI, true>(g, m0, n0, part);
-        else gemm_tile_run<BM, BN, EPI, false>(g, m0, n0, part);
+        if (g.W.split > t_begin && g.W.split < t_end) gemm_tile_run<BM, BN, EPI, true>(g, m0, n0, part, uw);
+        else gemm_tile_run<BM, BN, EPI, false>(g, m0, n0, part, uw);
     }
 }
 
@@ -717,11 +887,11 @@ __device__ __forceinline__ int list_panels(const GemmArgs& g, Panel* panels, int
 }
 // tiles0, tiles0_pad, tiles: as in GemmPair; one problem: all three alike
 template <int BM, int BN, int EPI>
-__device__ __forceinline__ void gemm_idle_fetch(const GemmArgs& g0, const GemmArgs& g1, uint32_t tiles0, uint32_t tiles0_pad, uint32_t tiles, const IdleFetch& f, uint32_t bid) {
+__device__ __forceinline__ void gemm_idle_fetch(const GemmArgs& g0, const GemmArgs& g1, uint32_t tiles0, uint32_t tiles0_pad, uint32_t tiles, const IdleFetch& f, uint32_t bid, int uw) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     Panel* const panels = (Panel*)smem;                        // at most 2 x 32
     int* const count = (int*)(smem + 64 * sizeof(Panel));
-    const int lane = threadIdx.x & 63, uw = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     if (uw == 0) {
         const uint32_t b = (tiles & ~255u) + (bid & 7u) + 8u * lane;       // a lane per tile of the round on this XCD
         int n = list_panels<BM, BN, EPI>(g0, panels, 0, b < tiles0, xcd_contiguous_id(b, tiles0), f.with_a);
@@ -755,22 +925,32 @@ constexpr bool can_idle_fetch(int bm, int bn, int epi, bool pair) { return bm * 
 
 template <int BM, int BN, int S, int EPI>
 __global__ __launch_bounds__(256, (min_waves<BM, BN>())) void gemm_bf16_kernel(GemmArgs g, uint32_t tiles, IdleFetch f) {
-    if (!can_idle_fetch(BM, BN, EPI, false) || blockIdx.x < tiles) gemm_tile_body<BM, BN, S, EPI>(g, blockIdx.x, tiles);
-    else gemm_idle_fetch<BM, BN, EPI>(g, g, tiles, tiles, tiles, f, blockIdx.x);
+    const int uw = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (!can_idle_fetch(BM, BN, EPI, false) || blockIdx.x < tiles) gemm_tile_body<BM, BN, S, EPI>(g, blockIdx.x, tiles, uw);
+    else gemm_idle_fetch<BM, BN, EPI>(g, g, tiles, tiles, tiles, f, blockIdx.x, uw);
 }
 template <int BM, int BN, int S, int EPI>
 __global__ __launch_bounds__(256, (min_waves<BM, BN>())) void gemm_pair_kernel(GemmPair p, IdleFetch f) {
+    const int uw = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if constexpr (can_idle_fetch(BM, BN, EPI, true)) {
-        if (blockIdx.x >= p.tiles) { gemm_idle_fetch<BM, BN, EPI>(p.g[0], p.g[1], p.tiles0, p.tiles0_pad, p.tiles, f, blockIdx.x); return; }
+        if (blockIdx.x >= p.tiles) { gemm_idle_fetch<BM, BN, EPI>(p.g[0], p.g[1], p.tiles0, p.tiles0_pad, p.tiles, f, blockIdx.x, uw); return; }
     }
-    if (blockIdx.x < p.tiles0) gemm_tile_body<BM, BN, S, EPI>(p.g[0], blockIdx.x, p.tiles0);
-    else if (blockIdx.x >= p.tiles0_pad) gemm_tile_body<BM, BN, S, EPI>(p.g[1], blockIdx.x - p.tiles0_pad, p.tiles - p.tiles0_pad);
+    const uint32_t tiles1 = p.tiles - p.tiles0_pad;
+    if constexpr (heads_out(EPI)) {            // one body for both problems: two of them cost registers across each other
+        const uint32_t second = blockIdx.x >= p.tiles0_pad;
+        if (second || blockIdx.x < p.tiles0)
+            gemm_tile_body<BM, BN, S, EPI>(p.g[second], blockIdx.x - (second ? p.tiles0_pad : 0), second ? tiles1 : p.tiles0, uw);
+    } else {
+        if (blockIdx.x < p.tiles0) gemm_tile_body<BM, BN, S, EPI>(p.g[0], blockIdx.x, p.tiles0, uw);
+        else if (blockIdx.x >= p.tiles0_pad) gemm_tile_body<BM, BN, S, EPI>(p.g[1], blockIdx.x - p.tiles0_pad, tiles1, uw);
+    }
 }
 
 template <int BM, int BN, int S, int EPI>
 constexpr size_t gemm_smem() {
     constexpr size_t loop = (size_t)(S > 0 ? S : STAGES) * (BM + BN) * ROWB;
-    constexpr size_t epi = 4 * Stage<BN / 64, EPI == EPI_SPLIT_GELU || EPI == EPI_SPLIT_GELU_ERF ? 2 : 4, slice_rows<BM, EPI>()>::BYTES;
+    static_assert(!heads_out(EPI) || (size_t)BM * BN * 2 <= loop, "a tile of heads is staged whole");
+    constexpr size_t epi = (joint_slices(BN, EPI) ? 2 : 4) * StageOf<BM, BN, EPI>::BYTES;
     return loop > epi ? loop : epi;
 }
 
@@ -784,9 +964,20 @@ inline uint32_t tile_count(const GemmArgs& g, int bm, int bn, bool cut) {
     return (uint32_t)(((g.M + bm - 1) / bm) * ((g.n1 - g.n0 + bn - 1) / bn)) * (cut ? g.ksplits : 1);
 }
 
+// The order in which the feature-tiles of a launch whose tiles are not alike (heads, activated) are walked, so that each XCD, which has a
+// range of them, gets its share of either sort: every step-th, a golden section of them.  For launches of more than two rounds.
+inline int even_step(int tiles_n) {
+    int step = std::max(1, (int)(0.618 * tiles_n + 0.5));
+    auto common = [&](int a, int b) { while (b) { const int t = a % b; a = b; b = t; } return a; };
+    while (common(step, tiles_n) != 1) ++step;
+    return step;
+}
+
 template <int BM, int BN, int S, int EPI>
-hipError_t launch(const GemmArgs& g, const GemmArgs* second, hipStream_t s) {
+hipError_t launch(const GemmArgs& g_in, const GemmArgs* second, hipStream_t s) {
     constexpr bool cut = EPI == EPI_PARTIAL;
+    GemmArgs g = g_in;
+    if (heads_out(EPI) && !second && tile_count(g, BM, BN, cut) > 512) g.col_step = even_step((g.n1 - g.n0 + BN - 1) / BN);
     const uint32_t tiles = tile_count(g, BM, BN, cut);
     constexpr size_t smem = gemm_smem<BM, BN, S, EPI>();
     if (!second) {

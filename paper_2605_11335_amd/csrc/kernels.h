@@ -5,6 +5,38 @@
 
 enum { EPI_SPLIT_GELU = 0, EPI_GATE_RESID = 1 };
 
+// Positions of this rank's tokens in the joint sequence: up to two contiguous segments
+// (text rows, image rows).  Local row i < len0 sits at pos0 + i, else at pos1 + (i - len0).
+struct TokenMap {
+    int n_total, n_local;
+    int pos0, len0, pos1, len1;
+};
+
+// Split a projection output into head-major attention operands, with optional per-head RMSNorm.
+struct RelayoutArgs {
+    const bf16* src;        // [rows, ld] ; head h of tensor t at column col0[t] + h*hd
+    int ld, rows;
+    int col_q, col_k, col_v;          // -1 = tensor absent
+    int n_heads;                      // heads present in src (H)
+    int h0, h_local;                  // heads kept for attention: [h0, h0 + h_local)
+    int hd;
+    WView W; uint64_t qn_off, kn_off; int has_norm;
+    const float *rope_cos, *rope_sin; // [n_local, hd/2] by local row, or NULL: rotate q,k pairs (2i, 2i+1) after the norm
+    TokenMap map; int row0;           // src row i is local row row0 + i
+    bf16 *Q, *K, *Vt;                 // [h_local, n_total, hd] x2, [h_local, hd, n_pad]
+    int n_pad;
+    bf16 *send_q, *send_k, *send_v;   // [n_heads - h_local, n_local, hd] (may be NULL)
+};
+
+// A projection whose features are heads of q, k and v, placed as attention reads them by the launch that computes them (`on`),
+// instead of going out as rows that a pass of their own relays: q, k normed and rotated, own v turned round, other heads to the send buffers.
+struct HeadsOut {
+    int on, first;                    // tensor of the first n_heads * hd features (0 q, 1 k, 2 v); the next ones follow
+    int rps;                          // tokens of a sample of a batch (0 = one sample); sample strides:
+    long op_bs, vt_bs, send_bs;       // of Q and K, of Vt, of the send buffers
+    RelayoutArgs r;                   // (src, ld, rows and columns unused)
+};
+
 struct GemmArgs {
     const bf16* A;      // [M, lda] activations
     int lda;
@@ -30,6 +62,8 @@ struct GemmArgs {
     // by workgroups of their own into part[ksplits][M][N] and put together by a second launch; 0 or 1 = whole.
     int ksplits, part_slabs;
     float* part;
+    int col_step;       // > 1: feature-tiles are walked in steps of so many (set by the launch)
+    HeadsOut heads;     // EPI_SPLIT_GELU: where features [0, n_split) go instead of out0
 };
 int gemm_splits(int rows, int rows2, int N, int K);      // parts to cut K into, for one sample's tokens (rows2: of a second layer in the launch)
 void gemm_set_split(GemmArgs* g, int splits, float* part);
@@ -57,6 +91,8 @@ IdleFetch gemm_idle_fetch_view(const GemmPlan& plan, const GemmArgs& g, const Ge
 // per epilogue: one problem, or two in one launch (`second` not NULL), with the given tile
 hipError_t gemm_launch_split_gelu(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s);
 hipError_t gemm_launch_split_gelu_erf(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s);
+hipError_t gemm_launch_heads(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s);           // features [0, n_split) are heads
+hipError_t gemm_launch_heads_erf(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s);
 hipError_t gemm_launch_gate_resid(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s);
 hipError_t gemm_launch_partial(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s);     // the parts of a cut sum only
 hipError_t gemm_launch_last_part(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s);   // its last part, added to the others
@@ -65,14 +101,8 @@ hipError_t mfma_rate_launch(int iters, int random_operands, float* out, hipStrea
 hipError_t mix_rate_launch(int iters, int waves, int reads16, int valu, int exps, float* out, hipStream_t s);
 // two independent problems in one launch
 bool gemm_can_pair(const GemmArgs& g0, const GemmArgs& g1);
+bool gemm_heads_pay(const GemmArgs& g, const GemmArgs* second, double separate_us);      // HeadsOut, or rows and a pass over them
 hipError_t gemm_launch_pair(const GemmArgs& g0, const GemmArgs& g1, hipStream_t s);
-
-// Positions of this rank's tokens in the joint sequence: up to two contiguous segments
-// (text rows, image rows).  Local row i < len0 sits at pos0 + i, else at pos1 + (i - len0).
-struct TokenMap {
-    int n_total, n_local;
-    int pos0, len0, pos1, len1;
-};
 
 struct AttnArgs {
     const bf16* Q;      // [H, nq, hd] head-major
@@ -139,22 +169,6 @@ struct LnArgs {
 hipError_t ln_modulate_launch(const LnArgs* parts, int n_parts, int d, hipStream_t s);
 hipError_t ln_affine_launch(const float* x, const WView& W, uint64_t w_off, uint64_t b_off, bf16* xn,
                             int rows, int d, hipStream_t s);
-
-// Split a projection output into head-major attention operands, with optional per-head RMSNorm.
-struct RelayoutArgs {
-    const bf16* src;        // [rows, ld] ; head h of tensor t at column col0[t] + h*hd
-    int ld, rows;
-    int col_q, col_k, col_v;          // -1 = tensor absent
-    int n_heads;                      // heads present in src (H)
-    int h0, h_local;                  // heads kept for attention: [h0, h0 + h_local)
-    int hd;
-    WView W; uint64_t qn_off, kn_off; int has_norm;
-    const float *rope_cos, *rope_sin; // [n_local, hd/2] by local row, or NULL: rotate q,k pairs (2i, 2i+1) after the norm
-    TokenMap map; int row0;           // src row i is local row row0 + i
-    bf16 *Q, *K, *Vt;                 // [h_local, n_total, hd] x2, [h_local, hd, n_pad]
-    int n_pad;
-    bf16 *send_q, *send_k, *send_v;   // [n_heads - h_local, n_local, hd] (may be NULL)
-};
 
 // What this rank receives from the second exchange (Sec. 2.1): the attention output of the other ranks' heads for
 // its own tokens, peer_attn [n_local, n_heads - h_local, hd], copied into the columns of those heads in the

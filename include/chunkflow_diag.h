@@ -72,7 +72,8 @@ int cf_op_linear_residual(const uint16_t* A, int32_t lda, const void* blob, uint
                           int32_t M, int32_t N, int32_t K, const float* resid, const float* gate,
                           float* y, void* stream);
 /* The same on tiles of the caller's choice (those of cf_plan_block_linear), with the sum over K in `parts` parts, put together by
- * a kernel of its own or (last_joins) by the launch of the last part.  scratch: parts * M * N floats, 16-byte aligned. */
+ * a kernel of its own, (last_joins 1) by the launch of the last part or (2, up to three parts) by the workgroups of all parts in one
+ * launch.  scratch, 16-byte aligned: parts * M * N floats; for 2, four words per tile that are ZERO and parts floats per output of whole tiles. */
 int cf_op_linear_residual_form(const uint16_t* A, int32_t lda, const void* blob, uint64_t w_off, int64_t bias_off, int32_t M, int32_t N,
                                int32_t K, const float* resid, const float* gate, float* y, int32_t tile_tokens, int32_t tile_features,
                                int32_t parts, int32_t last_joins, void* scratch, uint64_t scratch_bytes, void* stream);

@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libchunkflow.so")
 SOURCES = ["chunkflow.hip", "simulate.hip", "gemm.hip", "gemm_split_gelu.hip", "gemm_split_gelu_erf.hip", "gemm_heads.hip", "gemm_heads_erf.hip",
-           "gemm_gate_resid.hip", "gemm_partial.hip", "gemm_last_part.hip", "attention.hip", "elementwise.hip", "checksum_noalloc.hip"]
+           "gemm_gate_resid.hip", "gemm_partial.hip", "gemm_last_part.hip", "gemm_meet.hip", "attention.hip", "elementwise.hip", "checksum_noalloc.hip"]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared", "-pthread",
          # packed-fp32 VALU forms are kept out of every kernel
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

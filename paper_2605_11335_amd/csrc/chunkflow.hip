@@ -116,6 +116,7 @@ struct Ws {
     bf16* up = nullptr;        // [n_local, f]
     bf16 *ckv = nullptr, *cQ = nullptr, *cK = nullptr, *cVt = nullptr;
     uint32_t* flags = nullptr; // ATTN_FLAGS words
+    uint32_t* words = nullptr; // Plan::meet_words words by which the parts of layers cut along their sum meet
     float* part = nullptr;     // partial results of layers cut along their sum, live between two launches only
     uint64_t total = 0;
 };
@@ -142,7 +143,14 @@ void plan_cuts(Plan* p, const cf_model_desc& m) {
     p->sum_splits_d = gemm_splits(nl - tl, tl, m.d, m.d);
     p->sum_splits_mlp = gemm_splits(nl - tl, tl, m.d, k_mlp);
     const int most = std::max(p->sum_splits_d, p->sum_splits_mlp);
-    if (most > 1) part = std::max(part, (uint64_t)most * B * nl * m.d);
+    p->meet_words = 0;
+    if (most > 1) {
+        part = std::max(part, gemm_meet_floats(most, (uint64_t)B * nl, tl > 0 ? 2 : 1, m.d));
+        // four to a tile of any size in each of the cut layers' launches (panels end on whole tiles)
+        const uint64_t tiles = ((uint64_t)B * nl / 64 + 2) * (m.d / 64);
+        const uint64_t layers = (p->sum_splits_mlp > 1) + (p->sum_splits_d > 1) * (p->kind == CF_SINGLE_STREAM ? 0 : p->kind == CF_DIT_CROSS ? 2 : 1);
+        p->meet_words = (uint32_t)(4 * tiles * layers);
+    }
     p->part_floats = part;
 }
 
@@ -174,6 +182,7 @@ Ws carve(const cf_model_desc& m, const Plan& p, char* base) {
         w.cK = (bf16*)take(2ull * lc * d);
         w.cVt = (bf16*)take(2ull * B * d * n_pad_of(m.l_ctx));
     }
+    if (p.meet_words) w.words = (uint32_t*)take(4ull * p.meet_words);
     if (p.self_deal) w.flags = (uint32_t*)take(4 * ATTN_FLAGS);
     w.part = (float*)take(4 * p.part_floats);
     w.total = off;
@@ -440,6 +449,7 @@ struct Fwd {
     WView W;
     const cf_block_io* io;
     Ws ws;
+    uint32_t words_used = 0;   // of ws.words
 };
 
 const TensorDesc& T(const Fwd& F, const std::string& name) {
@@ -521,6 +531,8 @@ int panels(Fwd& F, const TensorDesc& t, int m_rows, Fn&& fn) {
     return CF_OK;
 }
 
+uint32_t c_words(const Fwd& F) { return F.c->P(F.block).meet_words; }
+
 // modulation vectors of every sample: t is [batch, d], out + b*out_bs receives sample b's
 int run_modvec(Fwd& F, const std::string& wname, const std::string& bname, const float* t, float* out, long out_bs) {
     const TensorDesc &w = T(F, wname), &b = T(F, bname);
@@ -528,7 +540,7 @@ int run_modvec(Fwd& F, const std::string& wname, const std::string& bname, const
     const int B = batch_of(F.c->d);
     return panels(F, w, 0, [&](int r0, int r1) -> int {
         ProfScope ps(F.c, F.s, K_MODVEC, 2.0 * B * (r1 - r0) * w.cols, 2.0 * (r1 - r0) * w.cols);
-        CF_HIP(F.c, modvec_launch(F.W, w.off, b.off, t, out, r0, r1, (int)w.cols, B, out_bs, F.s));
+        CF_HIP(F.c, modvec_launch(F.W, w.off, b.off, t, out, r0, r1, (int)w.cols, B, out_bs, F.s, 0, 0, nullptr, F.ws.words, c_words(F)));
         return CF_OK;
     });
 }
@@ -551,7 +563,7 @@ int run_modvec_pair(Fwd& F, const std::string (&wname)[2], const std::string (&b
     }
     const int B = batch_of(c->d), n = (int)w[0]->rows, K = (int)w[0]->cols;
     ProfScope ps(c, F.s, K_MODVEC, 4.0 * B * n * K, 4.0 * n * K);
-    CF_HIP(c, modvec_launch(F.W, w[0]->off, b[0]->off, t, out[0], 0, n, K, B, out_bs, F.s, w[1]->off, b[1]->off, out[1]));
+    CF_HIP(c, modvec_launch(F.W, w[0]->off, b[0]->off, t, out[0], 0, n, K, B, out_bs, F.s, w[1]->off, b[1]->off, out[1], F.ws.words, c_words(F)));
     return CF_OK;
 }
 
@@ -570,6 +582,14 @@ int sum_splits(const Fwd& F, int K) {
     return K == F.c->d.d ? p.sum_splits_d : p.sum_splits_mlp;
 }
 
+// Each launch whose parts meet has words of its own, cleared by the forward's first launch.
+int take_words(Fwd& F, const GemmPlan& plan, const GemmArgs& g, const GemmArgs* second) {
+    const uint32_t n = gemm_meet_words(plan, g, second);
+    if (n > c_words(F) - F.words_used) return cf_fail(F.c, CF_ERR_STATE, "linear: no words left to meet by");
+    F.words_used += n;
+    return CF_OK;
+}
+
 // out-feature panels of one linear layer; `g` carries everything but the panel and the weights
 int run_linear(Fwd& F, int kid, const std::string& wname, const std::string& bname, GemmArgs g) {
     if (g.M <= 0) return CF_OK;
@@ -584,13 +604,17 @@ int run_linear(Fwd& F, int kid, const std::string& wname, const std::string& bna
     g.K = (int)w.cols;
     if (g.epi == EPI_SPLIT_GELU && g.n_split > g.N) g.n_split = g.N;
     if (g.epi == EPI_GATE_RESID) gemm_set_split(&g, sum_splits(F, g.K), F.ws.part);
+    g.may_meet = g.ksplits > 1;
     return panels(F, w, g.M, [&](int r0, int r1) -> int {
         GemmArgs p = g;
         p.n0 = r0;
         p.n1 = r1;
+        p.words = F.ws.words + F.words_used;
         if (const char* msg = gemm_check(p)) return cf_fail(F.c, CF_ERR_ARG, "%s (%s)", msg, wname.c_str());
-        ProfScope ps(F.c, F.s, kid, 2.0 * p.M * (r1 - r0) * p.K, 0, gemm_plan(p, nullptr).tile);
-        CF_HIP(F.c, gemm_launch(p, F.s));
+        const GemmPlan plan = gemm_plan(p, nullptr);
+        CF_TRY(take_words(F, plan, p, nullptr));
+        ProfScope ps(F.c, F.s, kid, 2.0 * p.M * (r1 - r0) * p.K, 0, plan.tile);
+        CF_HIP(F.c, gemm_launch_as(plan, p, F.s));
         return CF_OK;
     });
 }
@@ -623,6 +647,8 @@ int run_linear_pair(Fwd& F, int kid, const std::string (&wname)[2], const std::s
         if (g[i].epi == EPI_GATE_RESID)      // both are in flight together: the second's parts follow the first's
             gemm_set_split(&g[i], sum_splits(F, g[i].K),
                            F.ws.part + (i ? (size_t)g[0].ksplits * g[0].M * g[0].N : 0));
+        g[i].may_meet = g[i].ksplits > 1;
+        g[i].words = F.ws.words + F.words_used;
     }
     if (!pair || !gemm_can_pair(g[0], g[1])) {
         CF_TRY(run_linear(F, kid, wname[0], bname[0], g_in[0]));
@@ -630,8 +656,10 @@ int run_linear_pair(Fwd& F, int kid, const std::string (&wname)[2], const std::s
     }
     for (int i = 0; i < 2; ++i)
         if (const char* msg = gemm_check(g[i])) return cf_fail(c, CF_ERR_ARG, "%s (%s)", msg, wname[i].c_str());
-    ProfScope ps(c, F.s, kid, 2.0 * g[0].M * g[0].N * g[0].K + 2.0 * g[1].M * g[1].N * g[1].K, 0, gemm_plan(g[0], &g[1]).tile);
-    CF_HIP(c, gemm_launch_pair(g[0], g[1], F.s));
+    const GemmPlan plan = gemm_plan(g[0], &g[1]);
+    CF_TRY(take_words(F, plan, g[0], &g[1]));
+    ProfScope ps(c, F.s, kid, 2.0 * g[0].M * g[0].N * g[0].K + 2.0 * g[1].M * g[1].N * g[1].K, 0, plan.tile);
+    CF_HIP(c, gemm_launch_pair(plan, g[0], g[1], F.s));
     return CF_OK;
 }
 
@@ -1077,6 +1105,7 @@ int cf_plan_block_linear(int32_t rows, int32_t rows2, int32_t batch, int32_t n_f
     for (int i = 0; i < 2; ++i) {
         g[i].M = (i ? rows2 : rows) * batch; g[i].N = g[i].n1 = n_features; g[i].K = k;
         gemm_set_split(&g[i], parts, nullptr);
+        g[i].may_meet = parts > 1;
     }
     const GemmPlan p = gemm_plan(g[0], rows2 ? &g[1] : nullptr);
     plan->parts = g[0].ksplits;
@@ -1096,6 +1125,7 @@ int cf_plan_block_fetch(int32_t rows, int32_t rows2, int32_t batch, int32_t n_fe
         g[i].epi = residual ? EPI_GATE_RESID : EPI_SPLIT_GELU;
         g[i].W.split = ~0ull;
         gemm_set_split(&g[i], parts, nullptr);
+        g[i].may_meet = parts > 1;
     }
     const GemmArgs* const second = rows2 ? &g[1] : nullptr;
     uint32_t tiles;
@@ -1515,9 +1545,18 @@ int cf_op_linear_residual_form(const uint16_t* A, int32_t lda, const void* blob,
     if (tile == GEMM_TILES) return cf_fail(nullptr, CF_ERR_ARG, "linear: no tile of %d tokens x %d features", tile_tokens, tile_features);
     if (parts < 1 || parts > K / 64) return cf_fail(nullptr, CF_ERR_ARG, "linear: 1 to K / 64 parts");
     gemm_set_split(&g, parts, (float*)scratch);
-    if (g.ksplits > 1 && (!scratch || scratch_bytes < 4ull * g.ksplits * M * N)) return cf_fail(nullptr, CF_ERR_ARG, "linear: too little scratch for the parts");
+    uint64_t need = 4ull * g.ksplits * M * N;
+    const GemmPlan plan = {tile, g.ksplits > 1 && last_joins == 1 ? tile : -1, g.ksplits > 1 && last_joins == 2};
+    if (plan.meet) {
+        const uint64_t words = gemm_meet_words(plan, g, nullptr);
+        need = 4 * words + words * g.ksplits * tokens * features;      // four words to a tile
+        g.may_meet = 1;
+        g.words = (uint32_t*)scratch;
+        g.part = (float*)scratch + words;
+    }
+    if (g.ksplits > 1 && (!scratch || scratch_bytes < need)) return cf_fail(nullptr, CF_ERR_ARG, "linear: too little scratch for the parts");
     if (const char* msg = gemm_check(g)) return cf_fail(nullptr, CF_ERR_ARG, "%s", msg);
-    hipError_t e = gemm_launch_as(GemmPlan{tile, g.ksplits > 1 && last_joins ? tile : -1}, g, (hipStream_t)stream);
+    hipError_t e = gemm_launch_as(plan, g, (hipStream_t)stream);
     return e == hipSuccess ? CF_OK : cf_fail(nullptr, CF_ERR_HIP, "linear launch: %s", hipGetErrorString(e));
 }
 

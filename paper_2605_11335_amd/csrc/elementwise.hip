@@ -27,7 +27,9 @@ constexpr int MV_ROWS = 4;
 template <int U>
 __global__ __launch_bounds__(256) void modvec_kernel(WView W, uint64_t w_off, uint64_t b_off, uint64_t w_off2, uint64_t b_off2,
                                                      const float* __restrict__ t, float* __restrict__ m, float* __restrict__ m2,
-                                                     int n0, int n1, int K, long m_bs) {
+                                                     int n0, int n1, int K, long m_bs, uint32x4* zero, uint32_t zeros) {
+    for (uint32_t i = ((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 256 + threadIdx.x; i < zeros; i += gridDim.x * gridDim.y * gridDim.z * 256)
+        zero[i] = uint32x4{0u, 0u, 0u, 0u};
     if (blockIdx.z) { w_off = w_off2; b_off = b_off2; m = m2; }      // the second matrix of a launch
     t += (size_t)blockIdx.y * K;                 // one sample of the batch per grid row
     m += (size_t)blockIdx.y * m_bs;
@@ -368,12 +370,13 @@ inline int grid_for(long items, int per_block, int cap = 256 * 16) {
 }  // namespace
 
 hipError_t modvec_launch(const WView& W, uint64_t w_off, uint64_t b_off, const float* t, float* m, int n0, int n1,
-                         int K, int batch, long m_bs, hipStream_t s, uint64_t w_off2, uint64_t b_off2, float* m2) {
+                         int K, int batch, long m_bs, hipStream_t s, uint64_t w_off2, uint64_t b_off2, float* m2,
+                         uint32_t* zero, uint32_t zero_words) {
     if (n1 <= n0) return hipSuccess;
     if (K % 8 || batch < 1 || batch > 65535) return hipErrorInvalidValue;
     const dim3 grid((n1 - n0 + 4 * MV_ROWS - 1) / (4 * MV_ROWS), batch, w_off2 ? 2 : 1);
     const int steps = (K / 8 + 63) / 64;         // steps of a lane's walk over K; taken 3 or 4 at a time
-#define CF_MV_CASE(U) hipLaunchKernelGGL(modvec_kernel<U>, grid, dim3(256), 0, s, W, w_off, b_off, w_off2, b_off2, t, m, m2, n0, n1, K, m_bs)
+#define CF_MV_CASE(U) hipLaunchKernelGGL(modvec_kernel<U>, grid, dim3(256), 0, s, W, w_off, b_off, w_off2, b_off2, t, m, m2, n0, n1, K, m_bs, (uint32x4*)zero, zero_words / 4)
     if (steps == 1) CF_MV_CASE(1);
     else if (steps == 2) CF_MV_CASE(2);
     else if (steps % 3 == 0) CF_MV_CASE(3);

@@ -31,6 +31,7 @@ const char* gemm_check(const GemmArgs& g) {
         if (g.ksplits > 1 && (!g.part || ((uintptr_t)g.part % 16) || g.part_slabs < 1 || (g.ksplits - 1) * g.part_slabs >= g.K / 64 ||
                               g.ksplits * g.part_slabs < g.K / 64))
             return "gemm: bad split of K";
+        if (g.may_meet && g.ksplits > 1 && (!g.words || g.ksplits > 3)) return "gemm: two or three parts can meet, with words to meet by";
         if (g.rows_per_sample && ((g.gate_bs % 4) || (g.resid_bs % 4) || (g.y_bs % 4) || g.gate_bs < 0 || g.resid_bs < 0 || g.y_bs < 0))
             return "gemm: sample strides must be non-negative multiples of 4 elements";
     } else {
@@ -92,7 +93,7 @@ bool heads_fit(const TileCost& t, const GemmArgs& g) {
 }
 // What a launch covers of a cut sum: all its parts, all but the last, the last
 enum Share { ALL_OF_IT, BEFORE_LAST, LAST };
-int best_tile(const GemmArgs* const (&g)[2], Share share = ALL_OF_IT, double* time = nullptr) {
+int best_tile(const GemmArgs* const (&g)[2], Share share = ALL_OF_IT, double* time = nullptr, long* workgroups = nullptr) {
     int best = -1;
     double best_us = 0;
     for (int i = 0; i < GEMM_TILES; ++i) {
@@ -108,11 +109,19 @@ int best_tile(const GemmArgs* const (&g)[2], Share share = ALL_OF_IT, double* ti
                 K = std::max(K, p->ksplits > 1 ? p->part_slabs * 64 : p->K);
             }
         const double us = tile_time(t, tiles, K);
-        if (best < 0 || us < best_us) best = i, best_us = us;
+        if (best < 0 || us < best_us) {
+            best = i, best_us = us;
+            if (workgroups) *workgroups = tiles;
+        }
     }
     if (time) *time = best_us;
     return best;
 }
+// Parts meet where the chip holds all their workgroups at once.
+bool can_meet(int tile, long workgroups) { return workgroups <= 256L * kTileCost[tile].per_cu; }
+// What that costs a launch besides their share of K: four trips to memory one after the other, and all but one part of the sums out and in again at
+// 3 TB/s (2304 x 3072 x 15360 in two: 24 us; 512 x 512 x 2560 in three 64x64 tiles: 7 us, 14.5 in all and 13.1 whole).
+double meet_us(int parts, double sums) { return 6.5 + 8.0 * (parts - 1) * sums / 3e6; }
 }  // namespace
 
 // How a cut sum is put together: by a kernel of its own that reads all parts, or by the launch of its last part, which
@@ -122,11 +131,16 @@ int best_tile(const GemmArgs* const (&g)[2], Share share = ALL_OF_IT, double* ti
 GemmPlan gemm_plan(const GemmArgs& g, const GemmArgs* second) {
     const GemmArgs* const both[2] = {&g, second};
     double all, before, last, bytes = 0;
-    const GemmPlan one = {best_tile(both, ALL_OF_IT, &all), -1};
+    long workgroups;
+    GemmPlan one = {best_tile(both, ALL_OF_IT, &all, &workgroups), -1, 0};
     if (g.ksplits <= 1) return one;
-    const GemmPlan two = {best_tile(both, BEFORE_LAST, &before), best_tile(both, LAST, &last)};
+    const GemmPlan two = {best_tile(both, BEFORE_LAST, &before), best_tile(both, LAST, &last), 0};
     for (const GemmArgs* p : both)
         if (p) bytes += 4.0 * p->M * (p->n1 - p->n0);
+    if (g.may_meet && can_meet(one.tile, workgroups)) {
+        one.meet = 1;
+        return one;
+    }
     return before + last + 3.0 + (g.ksplits + 1) * bytes / 3.5e6 < all + 6.0 + (g.ksplits + 2) * bytes / 3.5e6 ? two : one;
 }
 
@@ -209,8 +223,8 @@ IdleFetch gemm_idle_fetch_view(const GemmPlan& plan, const GemmArgs& g, const Ge
 
 // Parts K is cut into.  A layer with few outputs and a long sum (the MLP-out layers of a short sequence or of a rank at
 // degree 4 or 8) has few tiles whatever their shape: cut, its workgroups multiply, each with a share of the walk.  The price
-// is writing the partial sums and a second kernel that adds them, in the order of the parts, and applies the epilogue:
-// 6 us and two passes over them at 4 TB/s.  Taken where the estimate promises a twentieth (2304 x 3072 x 15360 in two parts:
+// is that of the parts meeting (meet_us) or, where the chip does not hold them at once, of writing the partial sums and a second kernel
+// that adds them, in the order of the parts, and applies the epilogue: 6 us and two passes over them at 4 TB/s.  Taken where the estimate promises a twentieth (2304 x 3072 x 15360 in two parts:
 // a Flux-like single-stream block 660 -> 645 us).  A function of one sample's tokens and
 // the whole layer only, so that results depend neither on the batch nor on the panels a streamed layer is cut into.
 // At most three parts, because a batch that fills the chip pays for each and gains nothing (576 tokens x 3072 x 15360 per sample,
@@ -228,12 +242,20 @@ int gemm_splits(int rows, int rows2, int N, int K) {
         if (g.ksplits != parts) continue;
         gemm_set_split(&g2, parts, nullptr);
         double us;
-        best_tile({&g, rows2 > 0 ? &g2 : nullptr}, ALL_OF_IT, &us);
-        if (parts > 1) us += 6.0 + 2.0 * 4.0 * parts * (double)(rows + rows2) * N / 4e6;
+        long workgroups;
+        const int tile = best_tile({&g, rows2 > 0 ? &g2 : nullptr}, ALL_OF_IT, &us, &workgroups);
+        const double sums = (double)(rows + rows2) * N;
+        if (parts > 1) us += can_meet(tile, workgroups) ? meet_us(parts, sums) : 6.0 + 2.0 * 4.0 * parts * sums / 4e6;
         if (parts == 1 || us < (best == 1 ? 0.95 : 1.0) * best_us) best = parts, best_us = us;
     }
     return best;
 }
+
+uint32_t gemm_meet_words(const GemmPlan& plan, const GemmArgs& g, const GemmArgs* second) {
+    const TileCost& t = kTileCost[plan.tile];
+    return plan.meet ? 4 * (tile_count(g, t.bm, t.bn, false) + (second ? tile_count(*second, t.bm, t.bn, false) : 0)) : 0;
+}
+uint64_t gemm_meet_floats(int parts, uint64_t rows, int problems, int N) { return parts * (rows + 255ull * problems) * N; }
 
 void gemm_set_split(GemmArgs* g, int splits, float* part) {
     const int slabs = g->K / 64;
@@ -417,6 +439,15 @@ hipError_t dispatch(const GemmPlan& plan, const GemmArgs& g, const GemmArgs* sec
     if (g.epi != EPI_GATE_RESID && g.heads.on) return g.act_erf ? gemm_launch_heads_erf(plan.tile, g, second, s) : gemm_launch_heads(plan.tile, g, second, s);
     if (g.epi != EPI_GATE_RESID) return g.act_erf ? gemm_launch_split_gelu_erf(plan.tile, g, second, s) : gemm_launch_split_gelu(plan.tile, g, second, s);
     if (g.ksplits <= 1) return gemm_launch_gate_resid(plan.tile, g, second, s);
+    if (plan.meet) {
+        if (!second) return gemm_launch_meet(plan.tile, g, nullptr, s);
+        GemmArgs g2 = *second;                 // its words and sums follow the first's
+        const TileCost& t = kTileCost[plan.tile];
+        const uint32_t tiles = tile_count(g, t.bm, t.bn, false);
+        g2.words = g.words + 4 * tiles;
+        g2.part = g.part + (size_t)tiles * g.ksplits * t.bm * t.bn;
+        return gemm_launch_meet(plan.tile, g, &g2, s);
+    }
     GemmArgs parts[2] = {g, second ? *second : g};
     if (plan.last >= 0)
         for (GemmArgs& p : parts) --p.ksplits;
@@ -461,6 +492,6 @@ bool gemm_can_pair(const GemmArgs& g0, const GemmArgs& g1) {
     return g0.epi == g1.epi && g0.act_erf == g1.act_erf && g0.heads.on == g1.heads.on && (g0.ksplits > 1) == (g1.ksplits > 1);
 }
 
-hipError_t gemm_launch_pair(const GemmArgs& g0, const GemmArgs& g1, hipStream_t s) {
-    return gemm_can_pair(g0, g1) ? dispatch(gemm_plan(g0, &g1), g0, &g1, s) : hipErrorInvalidValue;
+hipError_t gemm_launch_pair(const GemmPlan& plan, const GemmArgs& g0, const GemmArgs& g1, hipStream_t s) {
+    return gemm_can_pair(g0, g1) ? dispatch(plan, g0, &g1, s) : hipErrorInvalidValue;
 }

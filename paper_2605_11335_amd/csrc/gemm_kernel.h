@@ -40,6 +40,8 @@ constexpr int EPI_PARTIAL = 3;         // kernel variant of EPI_GATE_RESID that 
 constexpr int EPI_LAST_PART = 4;       // kernel variant of EPI_GATE_RESID for the last part of K, which adds the ones before it from memory
 constexpr int EPI_HEADS = 5;           // kernel variant of EPI_SPLIT_GELU whose plain features are heads (HeadsOut)
 constexpr int EPI_HEADS_ERF = 6;       // and with the erf form of the activation
+constexpr int EPI_MEET = 7;            // kernel variant of EPI_GATE_RESID for all parts of K, whose workgroups put the sum together (gemm_meet)
+constexpr bool cut_sum(int epi) { return epi == EPI_PARTIAL || epi == EPI_MEET; }      // a launch's workgroups: tiles, part by part
 constexpr int BK = 64;                 // K slab (bf16 elements) = 128 bytes per LDS row
 constexpr int STAGES = 2;              // slabs resident in LDS: one being multiplied, one in flight
 constexpr int ROWB = BK * 2;           // bytes per LDS row
@@ -477,10 +479,196 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx16 (&acc)
     }
 }
 
+// The parts of a cut sum, put together by the workgroups that computed them: each sends the others what it does not finish itself
+// and finishes its share of the tile, in units of 32 tokens x 64 (32) features that the parts of a wave's quadrant take turns in.  A
+// wave deals with the waves of the same quadrant only; a word of memory per tile and wave has their state.  Nobody waits for a workgroup
+// that may not be running: each counts itself in when it begins, and the one that is done first looks whether all are there.  If so, they
+// exchange; if not (the grid is more than the chip holds, or another stream's work is on it), all send everything, and the one
+// that is done last, which is then waiting for others' stores at most, finishes the tile alone.  The sum is in the order of the parts either way.
+// Data and words go past the XCDs' L2 (stores and loads of agent scope), so that no cache has to be written back or cleared.
+// Bound by the memory the chip turns to at once: two thirds of what the parts and a kernel that adds them up moved.  2304 x 3072 x 15360 in two
+// parts 202.7 -> 189.4 us, 1320 x 3072 x 14336 in three 113.6 -> 108.3, 512 + 64 rows x 3072 x 12288 in two 77.8 -> 76.1 (their blocks: 614 -> 599,
+// 588 -> 569 with the heads above, 329 -> 324 us).
+enum : uint32_t { MEET_DONE_FIRST = 1u << 8, MEET_EXCHANGE = 1u << 16, MEET_ALONE = 1u << 17, MEET_SENT = 1u << 24 };   // low byte: begun
+constexpr int AGENT_SCOPE = 16;                // cache policy of a buffer access: sc1
+template <int BM, int BN>
+struct Meet {
+    using St = Stage<BN / 64, 4, 32>;
+    static constexpr int MT = BM / 64, UNITS = St::PASSES * MT, SLOTS = (UNITS + 1) / 2;       // units of a quadrant, at most so many its own
+    static constexpr int QUADS = St::NTP * 4;                                                  // 16-byte pieces of a lane in a unit
+    static constexpr int BYTES = 4 * SLOTS * St::BYTES;
+};
+__device__ __forceinline__ uint32_t meet_word(const uint32_t* w) { return __builtin_amdgcn_readfirstlane(__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)); }
+template <int BM, int BN>
+__device__ __forceinline__ void gemm_meet(const GemmArgs& g, floatx16 (&acc)[BN / 64][BM / 64], int m0, int n0, int part, uint32_t tile, int uw, char* smem) {
+    using Mt = Meet<BM, BN>;
+    using St = typename Mt::St;
+    constexpr int MT = Mt::MT, UNITS = Mt::UNITS, QUADS = Mt::QUADS, ST = St::ST, RPI = St::RPI, CPR = St::CPR;
+    const int lane = lane_here(), wave = uw, P = g.ksplits;
+    const int m_q = m0 + (wave & 1) * (BM / 2), n_q = n0 + (wave >> 1) * (BN / 2);             // of the wave's quadrant
+    const int li = lane & 31, lg = lane >> 5;
+    uint32_t* const word = g.words + tile * 4 + wave;
+    char* const slots = smem + wave * (Mt::SLOTS * St::BYTES);
+    const __amdgpu_buffer_rsrc_t sums = make_rsrc(g.part + (size_t)tile * P * (BM * BN), (uint32_t)P * (BM * BN * 4));
+    auto sum_at = [&](int q, int u) { return (uint32_t)(((q * 4 + wave) * UNITS + u) * St::BYTES); };
+    auto inside = [&](int u) { return m_q + u % MT * 32 < g.M && n_q + u / MT * St::FP < g.n1; };
+    const int first = (part + P - wave % P) % P;               // the wave's own units: first, first + P, ...
+
+    slab_handover();                           // every wave is done reading the slabs
+    uint32_t seen = 0;
+    if (lane == 0) seen = __hip_atomic_fetch_add(word, MEET_DONE_FIRST, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int next = first, slot = 0;
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
+        const int p = u / MT, j = u % MT;
+        const bool own = u == next;
+        if (own) next += P;
+        if (own || inside(u)) {
+#pragma unroll
+            for (int t = 0; t < QUADS; ++t) {
+                const floatx16& a = acc[p * St::NTP + t / 4][j];
+                const floatx4 v = {a[t % 4 * 4], a[t % 4 * 4 + 1], a[t % 4 * 4 + 2], a[t % 4 * 4 + 3]};
+                if (own) *(floatx4*)(slots + slot * St::BYTES + t * 1024 + lane * 16) = v;
+                else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint32x4, v), sums, t * 1024 + lane * 16, sum_at(part, u), AGENT_SCOPE);
+            }
+        }
+        if (own) ++slot;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // what was sent is there for all to see
+    seen = __builtin_amdgcn_readfirstlane(seen);
+    const int rank = (seen >> 8) & 0xff;                       // parts that were done before
+    uint32_t say = MEET_SENT;
+    if (rank == 0) {
+        seen = (int)(seen & 0xff) == P ? MEET_EXCHANGE : MEET_ALONE;
+        say += seen;
+    } else {
+        while (!(seen & (MEET_EXCHANGE | MEET_ALONE))) {
+            __builtin_amdgcn_s_sleep(1);
+            seen = meet_word(word);
+        }
+    }
+    const bool exchange = seen & MEET_EXCHANGE;
+    wave_lds_order();
+    if (!exchange) {
+        for (int u = first, k = 0; u < UNITS; u += P, ++k)
+#pragma unroll
+            for (int t = 0; t < QUADS; ++t)
+                __builtin_amdgcn_raw_buffer_store_b128(*(const uint32x4*)(slots + k * St::BYTES + t * 1024 + lane * 16), sums, t * 1024 + lane * 16, sum_at(part, u), AGENT_SCOPE);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    if (lane == 0) __hip_atomic_fetch_add(word, say, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!exchange && rank != P - 1) return;
+
+    // the units this wave finishes: its own, or all of the quadrant
+    const int u0 = exchange ? first : 0, step = exchange ? P : 1;
+    const int r_l = lane / CPR, c_l = lane % CPR;              // a store's row (of RPI) and chunk of this lane
+    const int other1 = part == 0 ? 1 : 0, other2 = part == 2 ? 1 : 2;      // the other parts, in order (the second: P = 3)
+    const bool has_gate = g.gate != nullptr;
+    const float* const gate_p = has_gate ? g.gate : g.resid;   // a readable address either way
+    const long gate_bs = has_gate ? g.gate_bs : 0;
+    struct Rows { floatx4 resid[ST], gate[ST], bias; };
+    struct Sums { floatx4 a[QUADS], b[QUADS], own[QUADS]; };
+    auto finish = [&](auto per_sample, auto three) __attribute__((always_inline)) {
+        constexpr bool PS = decltype(per_sample)::value, THREE = decltype(three)::value;
+        // (lanes outside the problem read a valid address, row M-1 or column 0, and store nothing)
+        auto place = [&](int u, int s, int& sm, int& i) {
+            i = min(m_q + u % MT * 32 + s * RPI + r_l, g.M - 1);
+            sm = 0;
+            if (PS) { sm = i / g.rows_per_sample; i -= sm * g.rows_per_sample; }
+        };
+        auto column = [&](int u) { return n_q + u / MT * St::FP + c_l * 4; };
+        auto fetch_rows = [&](int u, Rows& r) __attribute__((always_inline)) {
+            const int n = column(u), nc = n < g.n1 ? n : 0;
+            r.gate[0] = floatx4{1.f, 1.f, 1.f, 1.f};
+            if (!PS && has_gate) r.gate[0] = *(const floatx4*)(gate_p + nc);
+            r.bias = floatx4{0.f, 0.f, 0.f, 0.f};
+            if (g.has_bias) {
+                const uint32x2 bb = *(const uint32x2*)wv_ptr(g.W, g.bias_off + 2ull * nc);
+                r.bias = floatx4{__uint_as_float(bb.x << 16), __uint_as_float(bb.x & 0xffff0000u), __uint_as_float(bb.y << 16), __uint_as_float(bb.y & 0xffff0000u)};
+            }
+#pragma unroll
+            for (int s = 0; s < ST; ++s) {
+                int sm, i;
+                place(u, s, sm, i);
+                r.resid[s] = *(const floatx4*)(g.resid + (size_t)sm * g.resid_bs + (size_t)i * g.ldy + nc);
+                if constexpr (PS) r.gate[s] = *(const floatx4*)(gate_p + (size_t)sm * gate_bs + nc);
+            }
+        };
+        auto fetch_sums = [&](int u, Sums& x) __attribute__((always_inline)) {
+            auto get = [&](int q, floatx4 (&to)[QUADS]) __attribute__((always_inline)) {
+#pragma unroll
+                for (int t = 0; t < QUADS; ++t) to[t] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(sums, t * 1024 + lane * 16, sum_at(q, u), AGENT_SCOPE));
+            };
+            get(other1, x.a);
+            if (THREE) get(other2, x.b);
+            if (!exchange) get(part, x.own);
+        };
+        auto put_out = [&](int u, int k, const Sums& x, const Rows& r) __attribute__((always_inline)) {
+            char* const stg = slots + k * St::BYTES;
+            floatx4 v[QUADS];
+#pragma unroll
+            for (int t = 0; t < QUADS; ++t) {
+                const floatx4 own = exchange ? *(const floatx4*)(stg + t * 1024 + lane * 16) : x.own[t];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if constexpr (THREE) v[t][e] = part == 2 ? (x.a[t][e] + x.b[t][e]) + own[e] : (x.a[t][e] + own[e]) + x.b[t][e];
+                    else v[t][e] = x.a[t][e] + own[e];
+                }
+            }
+            wave_lds_order();
+#pragma unroll
+            for (int t = 0; t < QUADS; ++t) *(floatx4*)(stg + St::at(li, t / 4 * 8 + t % 4 * 2 + lg)) = v[t];
+            wave_lds_order();
+            const int n = column(u);
+#pragma unroll
+            for (int s = 0; s < ST; ++s) {
+                const floatx4 val = *(const floatx4*)(stg + St::at(s * RPI + r_l, c_l)), gq = PS && !has_gate ? floatx4{1.f, 1.f, 1.f, 1.f} : r.gate[PS ? s : 0];
+                floatx4 o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = __fadd_rn(r.resid[s][e], __fmul_rn(gq[e], val[e] + r.bias[e]));
+                if (m_q + u % MT * 32 + s * RPI + r_l < g.M && n < g.n1) {
+                    int sm, i;
+                    place(u, s, sm, i);
+                    *(floatx4*)(g.y + (size_t)sm * g.y_bs + (size_t)i * g.ldy + n) = o;
+                }
+            }
+            wave_lds_order();
+        };
+        Rows rows;
+        Sums sums_of;
+        // rows are the caller's and come while the others are waited for; a unit that is not there (its quadrant ends before) reads row M-1
+        if (u0 < UNITS) fetch_rows(u0, rows);
+        while ((int)(meet_word(word) >> 24) < P) __builtin_amdgcn_s_sleep(1);
+        asm volatile("" ::: "memory");
+        if (u0 >= UNITS) return;
+        fetch_sums(u0, sums_of);
+#pragma unroll 1
+        for (int u = u0, k = 0; u < UNITS; u += step, k += exchange) {
+            if constexpr (UNITS > 2) {         // the next unit's operands ahead
+                Rows rows1;
+                Sums sums1;
+                const int un = u + step < UNITS ? u + step : u;
+                fetch_rows(un, rows1);
+                fetch_sums(un, sums1);
+                if (inside(u)) put_out(u, k, sums_of, rows);
+                rows = rows1;
+                sums_of = sums1;
+            } else {
+                if (inside(u)) put_out(u, k, sums_of, rows);
+                if (u + step < UNITS) { fetch_rows(u + step, rows); fetch_sums(u + step, sums_of); }
+            }
+        }
+    };
+    using Yes = std::true_type;
+    using No = std::false_type;
+    if (g.rows_per_sample) { if (P == 3) finish(Yes{}, Yes{}); else finish(Yes{}, No{}); }
+    else { if (P == 3) finish(No{}, Yes{}); else finish(No{}, No{}); }
+}
+
 // One tile of one problem: tokens m0.., features n0...  STRADDLE: the byte where the blob switches buffers falls
 // inside the tile's weight rows (at most one tile column of a launch), so each lane picks its base.
 template <int BM, int BN, int EPI, bool STRADDLE>
-__device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0, int part, int uw) {
+__device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0, int part, uint32_t tile, int uw) {
     constexpr int WM = BM / 2, WN = BN / 2;        // wave quadrant
     constexpr int MT = WM / 32, NT = WN / 32;      // 32x32 MFMA tiles per wave
     constexpr int PA = MT % 2 ? 3 : 2;             // the activations go in thirds or halves, the weights in halves
@@ -544,7 +732,7 @@ __device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0,
     }
 
     // slabs of this workgroup: all, or those of its part
-    constexpr bool CUT = EPI == EPI_PARTIAL || EPI == EPI_LAST_PART;
+    constexpr bool CUT = cut_sum(EPI) || EPI == EPI_LAST_PART;
     const int kt0 = CUT ? part * g.part_slabs : 0;
     const int KT = CUT ? min(g.part_slabs, g.K / BK - kt0) : g.K / BK;
     bf16x8 fa[2][MH][KSTEPS], fw[2][NH][KSTEPS];
@@ -657,7 +845,8 @@ __device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0,
         slab(I1{}, kt + 1);
     }
 
-    gemm_epilogue<BM, BN, EPI>(g, acc, m0, n0, part, uw, smem);
+    if constexpr (EPI == EPI_MEET) gemm_meet<BM, BN>(g, acc, m0, n0, part, tile, uw, smem);
+    else gemm_epilogue<BM, BN, EPI>(g, acc, m0, n0, part, uw, smem);
 }
 
 // The same for small tiles, which are for layers with too few large ones to give every CU a workgroup: there the time is
@@ -668,7 +857,7 @@ __device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0,
 // 576 x 3072 x 12288: 164 us with the former loop, 111 with the 128x128 tile above, 85 with 128x64 (240 workgroups);
 // 64 x 3072 x 12288: 166, 102, 63 with 64x64; 512 x 512 x 2560: 31.4, 20.5, 12.2.
 template <int BM, int BN, int S, int EPI>
-__device__ __forceinline__ void gemm_ring_run(const GemmArgs& g, int m0, int n0, int part, int uw) {
+__device__ __forceinline__ void gemm_ring_run(const GemmArgs& g, int m0, int n0, int part, uint32_t tile, int uw) {
     constexpr int WM = BM / 2, WN = BN / 2;        // wave quadrant
     constexpr int MT = WM / 32, NT = WN / 32;      // 32x32 MFMA tiles per wave
     constexpr int LA = BM / 32, LW = BN / 32, L = LA + LW;     // wave-loads (8 rows each) per wave and slab
@@ -712,7 +901,7 @@ __device__ __forceinline__ void gemm_ring_run(const GemmArgs& g, int m0, int n0,
         w_frag[kk] = (lds_frag*)(smem + BM * ROWB + (wn0 + li) * ROWB + c);
     }
     // slabs of this workgroup: all, or those of its part
-    constexpr bool CUT = EPI == EPI_PARTIAL || EPI == EPI_LAST_PART;
+    constexpr bool CUT = cut_sum(EPI) || EPI == EPI_LAST_PART;
     const int kt0 = CUT ? part * g.part_slabs : 0;
     const int KT = CUT ? min(g.part_slabs, g.K / BK - kt0) : g.K / BK;
     bf16x8 fa[2][MT][KSTEPS], fw[2][NT][KSTEPS];
@@ -778,7 +967,8 @@ __device__ __forceinline__ void gemm_ring_run(const GemmArgs& g, int m0, int n0,
         slab(I1{}, kt + 1, here, next);
         here = next;
     }
-    gemm_epilogue<BM, BN, EPI>(g, acc, m0, n0, part, uw, smem);
+    if constexpr (EPI == EPI_MEET) gemm_meet<BM, BN>(g, acc, m0, n0, part, tile, uw, smem);
+    else gemm_epilogue<BM, BN, EPI>(g, acc, m0, n0, part, uw, smem);
 }
 
 // A problem's tiles in the order of their logical ids: groups of about 8 row-tiles, all of one size (a short last group would walk
@@ -810,17 +1000,18 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, uint32_t bid, 
     const TileWalk<BM, BN> walk(g);
     const int tiles_m = walk.tiles_m, tiles_n = walk.tiles_n;
     uint32_t lid = xcd_contiguous_id(bid, nblk);
-    int part = EPI == EPI_PARTIAL ? lid / (tiles_m * tiles_n) : 0;
+    int part = cut_sum(EPI) ? lid / (tiles_m * tiles_n) : 0;
     lid -= part * (tiles_m * tiles_n);
     if (EPI == EPI_LAST_PART) part = g.ksplits - 1;
+    if (EPI == EPI_MEET && lane_here() == 0) __hip_atomic_fetch_add(g.words + lid * 4 + uw, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const auto tile = walk.at(g, lid);
     const int m0 = tile.m0, n0 = tile.n0;
     if constexpr (S > 0) {
-        gemm_ring_run<BM, BN, S, EPI>(g, m0, n0, part, uw);
+        gemm_ring_run<BM, BN, S, EPI>(g, m0, n0, part, lid, uw);
     } else {
         const uint64_t t_begin = g.w_off + (uint64_t)n0 * g.K * 2, t_end = g.w_off + (uint64_t)min(n0 + BN, g.N) * g.K * 2;
-        if (g.W.split > t_begin && g.W.split < t_end) gemm_tile_run<BM, BN, EPI, true>(g, m0, n0, part, uw);
-        else gemm_tile_run<BM, BN, EPI, false>(g, m0, n0, part, uw);
+        if (g.W.split > t_begin && g.W.split < t_end) gemm_tile_run<BM, BN, EPI, true>(g, m0, n0, part, lid, uw);
+        else gemm_tile_run<BM, BN, EPI, false>(g, m0, n0, part, lid, uw);
     }
 }
 
@@ -876,7 +1067,7 @@ struct Panel { uint64_t base; uint32_t bytes, row_bytes; };
 template <int BM, int BN, int EPI>
 __device__ __forceinline__ int list_panels(const GemmArgs& g, Panel* panels, int n, bool on, uint32_t lid, bool with_a) {
     const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-    const TilePanels<BM, BN> p(g, EPI == EPI_PARTIAL, on ? lid : 0);
+    const TilePanels<BM, BN> p(g, cut_sum(EPI), on ? lid : 0);
     const int lane0 = __ffsll((unsigned long long)__ballot(on)) - 1;
     const bool new_w = on && p.lists_w(lane, lane0), new_a = on && with_a && p.lists_a(lane, lane0);
     const uint64_t wm = __ballot(new_w), am = __ballot(new_a), below = (1ull << lane) - 1;
@@ -903,7 +1094,7 @@ __device__ __forceinline__ void gemm_idle_fetch(const GemmArgs& g0, const GemmAr
     const uint32_t before = (tiles + 7u - (bid & 7u)) >> 3, helpers = ((tiles + f.workgroups + 7u - (bid & 7u)) >> 3) - before;
     const uint32_t waves = helpers * 4, mine = ((bid >> 3) - before) * 4 + uw;
     constexpr uint32_t PAIRS = (BN > BM ? BN : BM) / 2;
-    const uint32_t slabs = EPI == EPI_PARTIAL ? g0.part_slabs : g0.K / BK, pairs = (uint32_t)*count * PAIRS, chunks = (slabs + FETCH_SLABS - 1) / FETCH_SLABS;
+    const uint32_t slabs = cut_sum(EPI) ? g0.part_slabs : g0.K / BK, pairs = (uint32_t)*count * PAIRS, chunks = (slabs + FETCH_SLABS - 1) / FETCH_SLABS;
     const unsigned long long begin = __builtin_amdgcn_s_memrealtime();
     for (uint32_t c = FETCH_LEAD; c < chunks; c += f.stride) {
         unsigned long long t;
@@ -936,7 +1127,7 @@ __global__ __launch_bounds__(256, (min_waves<BM, BN>())) void gemm_pair_kernel(G
         if (blockIdx.x >= p.tiles) { gemm_idle_fetch<BM, BN, EPI>(p.g[0], p.g[1], p.tiles0, p.tiles0_pad, p.tiles, f, blockIdx.x, uw); return; }
     }
     const uint32_t tiles1 = p.tiles - p.tiles0_pad;
-    if constexpr (heads_out(EPI)) {            // one body for both problems: two of them cost registers across each other
+    if constexpr (heads_out(EPI) || EPI == EPI_MEET) {         // one body for both problems: two of them cost registers across each other
         const uint32_t second = blockIdx.x >= p.tiles0_pad;
         if (second || blockIdx.x < p.tiles0)
             gemm_tile_body<BM, BN, S, EPI>(p.g[second], blockIdx.x - (second ? p.tiles0_pad : 0), second ? tiles1 : p.tiles0, uw);
@@ -950,7 +1141,7 @@ template <int BM, int BN, int S, int EPI>
 constexpr size_t gemm_smem() {
     constexpr size_t loop = (size_t)(S > 0 ? S : STAGES) * (BM + BN) * ROWB;
     static_assert(!heads_out(EPI) || (size_t)BM * BN * 2 <= loop, "a tile of heads is staged whole");
-    constexpr size_t epi = (joint_slices(BN, EPI) ? 2 : 4) * StageOf<BM, BN, EPI>::BYTES;
+    constexpr size_t epi = EPI == EPI_MEET ? Meet<BM, BN>::BYTES : (joint_slices(BN, EPI) ? 2 : 4) * StageOf<BM, BN, EPI>::BYTES;
     return loop > epi ? loop : epi;
 }
 
@@ -975,7 +1166,7 @@ inline int even_step(int tiles_n) {
 
 template <int BM, int BN, int S, int EPI>
 hipError_t launch(const GemmArgs& g_in, const GemmArgs* second, hipStream_t s) {
-    constexpr bool cut = EPI == EPI_PARTIAL;
+    constexpr bool cut = cut_sum(EPI);
     GemmArgs g = g_in;
     if (heads_out(EPI) && !second && tile_count(g, BM, BN, cut) > 512) g.col_step = even_step((g.n1 - g.n0 + BN - 1) / BN);
     const uint32_t tiles = tile_count(g, BM, BN, cut);
@@ -985,7 +1176,7 @@ hipError_t launch(const GemmArgs& g_in, const GemmArgs* second, hipStream_t s) {
         if (allowed != hipSuccess) return allowed;
         const IdleFetch f = can_idle_fetch(BM, BN, EPI, false) ? gemm_idle_fetch_plan(BM, BN, cut, g, nullptr, tiles, 0) : IdleFetch{};
         hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, S, EPI>), dim3(tiles + f.workgroups), dim3(256), smem, s, g, tiles, f);
-    } else if constexpr (BM * BN == 65536 && EPI == EPI_PARTIAL) {
+    } else if constexpr (BM * BN == 65536 && cut_sum(EPI)) {
         return hipErrorInvalidValue;               // does not fit the registers; gemm_plan never asks for it
     } else {
         static const hipError_t allowed = allow_smem(gemm_pair_kernel<BM, BN, S, EPI>, smem);

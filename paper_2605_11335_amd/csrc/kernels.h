@@ -62,6 +62,10 @@ struct GemmArgs {
     // by workgroups of their own into part[ksplits][M][N] and put together by a second launch; 0 or 1 = whole.
     int ksplits, part_slabs;
     float* part;
+    // Where the parts' workgroups put the sum together themselves (GemmPlan::meet): part holds gemm_meet_floats floats, words
+    // gemm_meet_words words that must be zero when the launch starts.
+    int may_meet;
+    uint32_t* words;
     int col_step;       // > 1: feature-tiles are walked in steps of so many (set by the launch)
     HeadsOut heads;     // EPI_SPLIT_GELU: where features [0, n_split) go instead of out0
 };
@@ -71,7 +75,10 @@ const char* gemm_check(const GemmArgs& g);
 enum { GEMM_256x256 = 0, GEMM_128x128 = 1, GEMM_128x256 = 2, GEMM_128x64 = 3, GEMM_64x64 = 4, GEMM_192x256 = 5, GEMM_TILES = 6 };     // tokens x features
 // How a layer, or two in one launch (`second` not NULL), is launched: its tile; of a cut sum the tile of the parts, and that of
 // the last part where its launch puts the sum together (else -1).
-struct GemmPlan { int tile, last; };
+// meet: the workgroups of the parts put the sum together.
+struct GemmPlan { int tile, last, meet; };
+uint32_t gemm_meet_words(const GemmPlan& plan, const GemmArgs& g, const GemmArgs* second);     // 0 unless plan.meet
+uint64_t gemm_meet_floats(int parts, uint64_t rows, int problems, int N);      // scratch for any tile, N a multiple of 256
 GemmPlan gemm_plan(const GemmArgs& g, const GemmArgs* second);
 void gemm_tile_shape(int tile, int* tokens, int* features);
 double gemm_fill(int M, int n);        // share of the launched rounds of workgroups that n features x M tokens fill
@@ -96,13 +103,14 @@ hipError_t gemm_launch_heads_erf(int tile, const GemmArgs& g, const GemmArgs* se
 hipError_t gemm_launch_gate_resid(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s);
 hipError_t gemm_launch_partial(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s);     // the parts of a cut sum only
 hipError_t gemm_launch_last_part(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s);   // its last part, added to the others
+hipError_t gemm_launch_meet(int tile, const GemmArgs& g, const GemmArgs* second, hipStream_t s);        // all parts, which put it together
 hipError_t mfma_rate_launch(int iters, int random_operands, float* out, hipStream_t s);   // diagnostic: MFMAs on registers only
 // diagnostic: MFMAs sharing the SIMD with LDS fragment reads and VALU work (see gemm.hip for the supported mixes)
 hipError_t mix_rate_launch(int iters, int waves, int reads16, int valu, int exps, float* out, hipStream_t s);
 // two independent problems in one launch
 bool gemm_can_pair(const GemmArgs& g0, const GemmArgs& g1);
 bool gemm_heads_pay(const GemmArgs& g, const GemmArgs* second, double separate_us);      // HeadsOut, or rows and a pass over them
-hipError_t gemm_launch_pair(const GemmArgs& g0, const GemmArgs& g1, hipStream_t s);
+hipError_t gemm_launch_pair(const GemmPlan& plan, const GemmArgs& g0, const GemmArgs& g1, hipStream_t s);
 
 struct AttnArgs {
     const bf16* Q;      // [H, nq, hd] head-major
@@ -151,9 +159,10 @@ int attn_waves(const AttnArgs& a);      // waves per workgroup attn_launch takes
 
 // m[b][n] = sum_k W[n,k] t[b][k] + bias[n]  (fp32 out), rows [n0, n1), for `batch` vectors t + b*K -> m + b*m_bs.
 // w_off2 != 0: a second matrix of the same shape (bias at b_off2) in the same launch, its result at m2.
+// zero: so many words to clear for the launches that follow (a multiple of 4, 16-byte aligned), or NULL.
 hipError_t modvec_launch(const WView& W, uint64_t w_off, uint64_t b_off, const float* t, float* m,
                          int n0, int n1, int K, int batch, long m_bs, hipStream_t s, uint64_t w_off2 = 0, uint64_t b_off2 = 0,
-                         float* m2 = nullptr);
+                         float* m2 = nullptr, uint32_t* zero = nullptr, uint32_t zero_words = 0);
 
 // xn = LN(x) * (1 + scale) + shift  (fp32 in, bf16 out); with ln_w/ln_b (blob offsets, has_affine)
 // instead: xn = LN(x) * w + b.

@@ -117,11 +117,15 @@ int best_tile(const GemmArgs* const (&g)[2], Share share = ALL_OF_IT, double* ti
     if (time) *time = best_us;
     return best;
 }
-// Parts meet where the chip holds all their workgroups at once.
-bool can_meet(int tile, long workgroups) { return workgroups <= 256L * kTileCost[tile].per_cu; }
-// What that costs a launch besides their share of K: four trips to memory one after the other, and all but one part of the sums out and in again at
-// 3 TB/s (2304 x 3072 x 15360 in two: 24 us; 512 x 512 x 2560 in three 64x64 tiles: 7 us, 14.5 in all and 13.1 whole).
-double meet_us(int parts, double sums) { return 6.5 + 8.0 * (parts - 1) * sums / 3e6; }
+// Parts meet where every one of their workgroups has a CU and it costs less than a kernel that reads them all: meeting is some 3 us
+// (two parts) or 7 (three) and a third of a microsecond per MB of sums, on tiles of 64 features 10 and more; the kernel 5.5 and 0.5 or 0.6 per MB.
+// Apart / meeting, with weights from HBM: 576 x 3072 x 12288 in two 64.2 / 62.4 us, 1600 x 3072 x 12288 in two 120.7 / 114.0, 1000 x 2048 x 10240 in three
+// 51.4 / 52.6, 1152 x 3072 x 12288 in three 97.5 / 95.5, 1320 x 3072 x 14336 in three 111.0 / 108.6; 64x64 tiles: 150 x 3072 x 13376 in three 43.9 / 51.7.
+bool can_meet(int tile, long workgroups, int parts, double sums) {
+    return workgroups <= 256 && kTileCost[tile].bn >= 128 && (parts == 2 || sums >= 2.5e6);
+}
+// What it adds to the estimate of a launch whose workgroups end with their share of K (2304 x 3072 x 15360 in two: 24 us).
+double meet_us(int parts, double sums) { return 4.5 + 8.0 * (parts - 1) * sums / 3.5e6; }
 }  // namespace
 
 // How a cut sum is put together: by a kernel of its own that reads all parts, or by the launch of its last part, which
@@ -137,7 +141,7 @@ GemmPlan gemm_plan(const GemmArgs& g, const GemmArgs* second) {
     const GemmPlan two = {best_tile(both, BEFORE_LAST, &before), best_tile(both, LAST, &last), 0};
     for (const GemmArgs* p : both)
         if (p) bytes += 4.0 * p->M * (p->n1 - p->n0);
-    if (g.may_meet && can_meet(one.tile, workgroups)) {
+    if (g.may_meet && can_meet(one.tile, workgroups, g.ksplits, bytes / 4)) {
         one.meet = 1;
         return one;
     }
@@ -245,7 +249,7 @@ int gemm_splits(int rows, int rows2, int N, int K) {
         long workgroups;
         const int tile = best_tile({&g, rows2 > 0 ? &g2 : nullptr}, ALL_OF_IT, &us, &workgroups);
         const double sums = (double)(rows + rows2) * N;
-        if (parts > 1) us += can_meet(tile, workgroups) ? meet_us(parts, sums) : 6.0 + 2.0 * 4.0 * parts * sums / 4e6;
+        if (parts > 1) us += can_meet(tile, workgroups, parts, sums) ? meet_us(parts, sums) : 6.0 + 2.0 * 4.0 * parts * sums / 4e6;
         if (parts == 1 || us < (best == 1 ? 0.95 : 1.0) * best_us) best = parts, best_us = us;
     }
     return best;

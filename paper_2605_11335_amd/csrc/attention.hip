@@ -19,6 +19,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "modvec.h"
 
 namespace {
 
@@ -424,6 +425,17 @@ __device__ __forceinline__ void attn_sweep(const AttnArgs& a, int h, int q0, int
     }
 }
 
+// The workgroups behind the sweeps: modulation rows that nothing needs before attention is over.  They stream weights while the matrix
+// cores work, on CUs without a sweep or beside one that leaves half of its CU free.
+// What remains of their time is what they slow the sweeps by (their own loads in flight, and whether they go past L2 or behind the sweeps'
+// waves in the issue order, changed nothing): double-stream block at degree 8, 27 of 40 us of the product gone for 11 us of attention, 326 -> 311 us;
+// Wan-like short clip 569 -> 564.
+template <int NW>
+__device__ __forceinline__ void attn_mod_rows(const AttnArgs& a, uint32_t b) {
+    const uint32_t per = (a.mod.n1 - a.mod.n0 + NW * MV_ROWS - 1) / (NW * MV_ROWS), of = b / per;
+    modvec_rows<3>(a.mod, of % a.mod.mats, of / a.mod.mats, a.mod.n0 + ((b - of * per) * NW + (threadIdx.x >> 6)) * MV_ROWS);
+}
+
 // NW waves of 32 queries each per workgroup: 4 (two workgroups per CU), 7 or 8 (one per CU); for 64-wide heads twice as many,
 // held to the 128 registers that takes: at 129 a CU has one 7-wave workgroup and 8 heads x 20892 take 1.11 ms instead of 0.90.
 // PARTS: the keys are cut (a.splits > 1), each part for a workgroup of its own, the results go to scratch.  ALL_PARTS: cut alike,
@@ -433,8 +445,13 @@ enum { WHOLE, PARTS, ALL_PARTS };
 template <int HD, int NW, int FORM>
 __global__ __launch_bounds__(64 * NW, HD == 64 ? (FORM == ALL_PARTS ? 3 : 4) : 2) void attn_fwd_kernel(AttnArgs a) {
     constexpr int BQ = 32 * NW, DT = HD / 32;
+    const uint32_t sweeps = gridDim.x - a.mod_blocks;
+    if (blockIdx.x >= sweeps) {
+        attn_mod_rows<NW>(a, blockIdx.x - sweeps);
+        return;
+    }
     const int nqt = (a.nq + BQ - 1) / BQ;
-    const uint32_t lid = xcd_contiguous_id(blockIdx.x, gridDim.x);
+    const uint32_t lid = xcd_contiguous_id(blockIdx.x, sweeps);
     const int hs = lid / nqt, qt = lid % nqt;
     const int h = FORM == PARTS ? hs / a.splits : hs, part = FORM == PARTS ? hs % a.splits : 0;       // head, and which part of the keys
     const int q0 = qt * BQ + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 32;
@@ -799,7 +816,9 @@ hipError_t launch(const AttnArgs& a, hipStream_t s) {
         attr_set = true;
     }
     const int nqt = (a.nq + 32 * NW - 1) / (32 * NW);
-    hipLaunchKernelGGL((attn_fwd_kernel<HD, NW, FORM>), dim3(nqt * a.H * (FORM == PARTS ? a.splits : 1)), dim3(64 * NW), smem, s, a);
+    AttnArgs b = a;
+    b.mod_blocks = a.mod.n1 > a.mod.n0 ? (a.mod.n1 - a.mod.n0 + NW * MV_ROWS - 1) / (NW * MV_ROWS) * a.mod.mats * a.mod.batch : 0;
+    hipLaunchKernelGGL((attn_fwd_kernel<HD, NW, FORM>), dim3(nqt * a.H * (FORM == PARTS ? a.splits : 1) + b.mod_blocks), dim3(64 * NW), smem, s, b);
     return hipGetLastError();
 }
 
@@ -1054,7 +1073,21 @@ static hipError_t launch_wave_parts(const AttnArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+// One generation of workgroups that leaves an eighth of the chip's places free, so that what streams there does not wait for a sweep to end;
+// and sweeps that last (1.35 us a tile of 128-wide heads, half of that for 64-wide ones) as long as the rows take to be read at 5 TB/s,
+// or the launch would end with a product that a launch of its own, with more of it in flight, does faster.  3 heads x 4608 x 128 in two parts, 50 us:
+// 151 MB beside it, 27 us of a launch of their own, make it 61.
+bool attn_takes_mod(const AttnArgs& a) {
+    if (a.even_state || a.all_parts == ALL_PARTS_WAVES) return false;
+    const int nw = attn_waves(a), own = a.splits > 1 && !a.all_parts ? a.splits : 1;
+    const long groups = (long)((a.nq + 32 * nw - 1) / (32 * nw)) * a.H * own;
+    const double sweep_us = (a.hd == 128 ? 1.35 : 0.68) * (own > 1 ? a.part_tiles : (a.nk + BKV - 1) / BKV);
+    const double read_us = 2.0 * (a.mod.n1 - a.mod.n0) * a.mod.K * a.mod.mats * a.mod.batch / 5e6;
+    return groups <= 7 * 32 * (nw == 4 ? 2 : 1) * (a.hd == 64 ? 2 : 1) && read_us <= sweep_us;
+}
+
 hipError_t attn_launch(const AttnArgs& a, hipStream_t s) {
+    if (a.mod.n1 > a.mod.n0 && (!attn_takes_mod(a) || a.mod.K % 8 || a.mod.mats < 1 || a.mod.mats > 2 || a.mod.batch < 1)) return hipErrorInvalidValue;
     if (a.even_state) return launch_even(a, s);
     if (a.all_parts == ALL_PARTS_WAVES) return a.hd == 128 ? launch_wave_parts<128>(a, s) : launch_wave_parts<64>(a, s);
     const int nw = attn_waves(a);

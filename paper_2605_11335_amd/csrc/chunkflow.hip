@@ -152,6 +152,13 @@ void plan_cuts(Plan* p, const cf_model_desc& m) {
         p->meet_words = (uint32_t)(4 * tiles * layers);
     }
     p->part_floats = part;
+    AttnArgs a{};
+    a.H = B * hl; a.nq = a.nk = m.n_total; a.hd = hd;
+    attn_set_split(&a, p->self_splits, nullptr);
+    a.all_parts = p->self_all_parts;
+    a.mod.n1 = (p->kind == CF_SINGLE_STREAM ? 1 : 4) * m.d;       // behind the first shift and scale
+    a.mod.K = m.d; a.mod.batch = B; a.mod.mats = p->kind == CF_DOUBLE_STREAM ? 2 : 1;
+    p->mod_in_attention = !p->self_deal && attn_takes_mod(a);
 }
 
 // every per-token buffer holds the whole batch, sample after sample
@@ -450,6 +457,7 @@ struct Fwd {
     const cf_block_io* io;
     Ws ws;
     uint32_t words_used = 0;   // of ws.words
+    ModRows later{};           // modulation rows left to the joint attention's launch (n1 = 0: none)
 };
 
 const TensorDesc& T(const Fwd& F, const std::string& name) {
@@ -533,37 +541,43 @@ int panels(Fwd& F, const TensorDesc& t, int m_rows, Fn&& fn) {
 
 uint32_t c_words(const Fwd& F) { return F.c->P(F.block).meet_words; }
 
-// modulation vectors of every sample: t is [batch, d], out + b*out_bs receives sample b's
-int run_modvec(Fwd& F, const std::string& wname, const std::string& bname, const float* t, float* out, long out_bs) {
-    const TensorDesc &w = T(F, wname), &b = T(F, bname);
-    CF_TRY(need(F, b));
-    const int B = batch_of(F.c->d);
-    return panels(F, w, 0, [&](int r0, int r1) -> int {
-        ProfScope ps(F.c, F.s, K_MODVEC, 2.0 * B * (r1 - r0) * w.cols, 2.0 * (r1 - r0) * w.cols);
-        CF_HIP(F.c, modvec_launch(F.W, w.off, b.off, t, out, r0, r1, (int)w.cols, B, out_bs, F.s, 0, 0, nullptr, F.ws.words, c_words(F)));
-        return CF_OK;
-    });
-}
-
-// Two modulation matrices of one shape (the streams of a double-stream block): one launch when neither needs a chunk that has
-// not been waited for yet, otherwise each in its own panels.
-int run_modvec_pair(Fwd& F, const std::string (&wname)[2], const std::string (&bname)[2], const float* t, float* const (&out)[2], long out_bs) {
+// Modulation vectors of every sample, of one matrix or of two of one shape (the streams of a double-stream block): t is [batch, d],
+// out[i] + b*out_bs receives matrix i's of sample b.  Two go out in one launch when neither needs a chunk that has not been waited for yet,
+// otherwise each in its own panels.  Of matrices that are there whole only the first two vectors, the shift and scale that the block begins with,
+// are computed here if the joint attention's launch has room for the others.
+int run_modvec(Fwd& F, const std::string* wname, const std::string* bname, int n, float* const* out, long out_bs) {
     cf_ctx* c = F.c;
-    const TensorDesc *w[2], *b[2];
-    const int have = std::max(c->waited_upto, c->P(F.block).n_res_chunks - 1);
-    bool pair = true;
-    for (int i = 0; i < 2; ++i) {
-        w[i] = &T(F, wname[i]);
-        b[i] = &T(F, bname[i]);
-        if ((int)((std::max(w[i]->off + w[i]->bytes(), b[i]->off + b[i]->bytes()) - 1) / c->chunk_bytes) > have) pair = false;
+    const int B = batch_of(c->d), have = std::max(c->waited_upto, c->P(F.block).n_res_chunks - 1);
+    ModRows r{};
+    r.W = F.W; r.t = F.io->temb; r.batch = B; r.mats = n; r.m_bs = out_bs;
+    bool there = true;
+    for (int i = 0; i < n; ++i) {
+        const TensorDesc &w = T(F, wname[i]), &b = T(F, bname[i]);
+        r.w_off[i] = w.off; r.b_off[i] = b.off; r.m[i] = out[i];
+        r.n1 = (int)w.rows; r.K = (int)w.cols;
+        if ((int)((std::max(w.off + w.bytes(), b.off + b.bytes()) - 1) / c->chunk_bytes) > have) there = false;
     }
-    if (!pair) {
-        for (int i = 0; i < 2; ++i) CF_TRY(run_modvec(F, wname[i], bname[i], t, out[i], out_bs));
+    if (!there) {
+        for (int i = 0; i < n; ++i) {
+            const TensorDesc &w = T(F, wname[i]), &b = T(F, bname[i]);
+            CF_TRY(need(F, b));
+            ModRows one = r;
+            one.mats = 1; one.w_off[0] = w.off; one.b_off[0] = b.off; one.m[0] = out[i];
+            CF_TRY(panels(F, w, 0, [&](int r0, int r1) -> int {
+                one.n0 = r0; one.n1 = r1;
+                ProfScope ps(c, F.s, K_MODVEC, 2.0 * B * (r1 - r0) * r.K, 2.0 * (r1 - r0) * r.K);
+                CF_HIP(c, modvec_launch(one, F.s, F.ws.words, c_words(F)));
+                return CF_OK;
+            }));
+        }
         return CF_OK;
     }
-    const int B = batch_of(c->d), n = (int)w[0]->rows, K = (int)w[0]->cols;
-    ProfScope ps(c, F.s, K_MODVEC, 4.0 * B * n * K, 4.0 * n * K);
-    CF_HIP(c, modvec_launch(F.W, w[0]->off, b[0]->off, t, out[0], 0, n, K, B, out_bs, F.s, w[1]->off, b[1]->off, out[1], F.ws.words, c_words(F)));
+    if (c->P(F.block).mod_in_attention) {
+        F.later = r;
+        F.later.n0 = r.n1 = 2 * c->d.d;
+    }
+    ProfScope ps(c, F.s, K_MODVEC, 2.0 * n * B * r.n1 * r.K, 2.0 * n * r.n1 * r.K);
+    CF_HIP(c, modvec_launch(r, F.s, F.ws.words, c_words(F)));
     return CF_OK;
 }
 
@@ -809,6 +823,7 @@ int run_joint_attention(Fwd& F, const RelayoutArgs* parts, int n_parts, const At
     attn_set_split(&a, c->P(F.block).self_splits, F.ws.part);
     a.all_parts = c->P(F.block).self_all_parts;
     attn_set_deal(&a, c->P(F.block).self_deal, F.ws.part, F.ws.flags);
+    a.mod = F.later;
     if (const char* msg = attn_check(a)) return cf_fail(c, CF_ERR_ARG, "%s", msg);
     {
         ProfScope ps(c, F.s, K_ATTN, 4.0 * B * hl * (double)m.n_total * m.n_total * hd, 0);
@@ -861,7 +876,8 @@ int fwd_single(Fwd& F) {
     const int d = m.d, f = m.f, nl = m.n_total / m.sp_degree, B = batch_of(m), rows = B * nl, rps = B > 1 ? nl : 0;
     const cf_block_io* io = F.io;
     const long mod_bs = 3L * d, xs = x_stride(io, (long)nl * d);
-    CF_TRY(run_modvec(F, "w_mod", "b_mod", io->temb, F.ws.mod, mod_bs));
+    const std::string w_mod = "w_mod", b_mod = "b_mod";
+    CF_TRY(run_modvec(F, &w_mod, &b_mod, 1, &F.ws.mod, mod_bs));
     const float *shift = F.ws.mod, *scale = F.ws.mod + d, *gate = F.ws.mod + 2 * d;
     CF_TRY(run_ln_mod(F, LnArgs{io->x, shift, scale, F.ws.xn, rows, rps, xs, mod_bs}));
     if (m.qk_rmsnorm) { CF_TRY(need(F, T(F, "q_norm"))); CF_TRY(need(F, T(F, "k_norm"))); }
@@ -1610,7 +1626,9 @@ int cf_op_ln_modulate(const float* x, const float* shift, const float* scale, ui
 int cf_op_modvec(const void* blob, uint64_t w_off, uint64_t b_off, const float* t, float* m, int32_t n, int32_t K,
                  void* stream) {
     if (!blob || !t || !m || (w_off % 16) || (K % 8)) return cf_fail(nullptr, CF_ERR_ARG, "bad modvec operands");
-    hipError_t e = modvec_launch(flat_view(blob), w_off, b_off, t, m, 0, n, K, 1, 0, (hipStream_t)stream);
+    ModRows r{};
+    r.W = flat_view(blob); r.w_off[0] = w_off; r.b_off[0] = b_off; r.t = t; r.m[0] = m; r.n1 = n; r.K = K; r.batch = r.mats = 1;
+    hipError_t e = modvec_launch(r, (hipStream_t)stream);
     return e == hipSuccess ? CF_OK : cf_fail(nullptr, CF_ERR_HIP, "modvec: %s", hipGetErrorString(e));
 }
 
@@ -1711,7 +1729,8 @@ int fwd_dit(Fwd& F) {
     const cf_block_io* io = F.io;
     Ws& w = F.ws;
     const long mod_bs = 6L * d, xs = x_stride(io, (long)nl * d), dense = (long)nl * d;
-    CF_TRY(run_modvec(F, "w_mod", "b_mod", io->temb, w.mod, mod_bs));
+    const std::string w_mod = "w_mod", b_mod = "b_mod";
+    CF_TRY(run_modvec(F, &w_mod, &b_mod, 1, &w.mod, mod_bs));
     const float *sh1 = w.mod, *sc1 = w.mod + d, *g1 = w.mod + 2 * d, *sh2 = w.mod + 3 * d, *sc2 = w.mod + 4 * d,
                 *g2 = w.mod + 5 * d;
     // self-attention
@@ -1800,7 +1819,7 @@ int fwd_double(Fwd& F) {
     {
         const std::string wn[2] = {nm(st[0], "w_mod"), nm(st[1], "w_mod")}, bn[2] = {nm(st[0], "b_mod"), nm(st[1], "b_mod")};
         float* const out[2] = {w.mod, w.mod + 6 * d};
-        CF_TRY(run_modvec_pair(F, wn, bn, io->temb, out, mod_bs));
+        CF_TRY(run_modvec(F, wn, bn, 2, out, mod_bs));
     }
     auto mod = [&](int s, int i) { return w.mod + 6 * d * s + i * d; };
     LnArgs ln[2];

@@ -59,7 +59,8 @@ struct Plan {
     // cross-attention, how the joint attention's sweeps are dealt out (attn_deal), parts of K in residual layers with K = d and
     // with the MLP-out layer's K; scratch for them in floats
     int self_splits = 1, cross_splits = 1, self_deal = 0, sum_splits_d = 1, sum_splits_mlp = 1;
-    uint32_t meet_words = 0;
+    uint32_t meet_words = 0;                                  // words by which the parts of cut sums meet, of a whole forward
+    bool mod_in_attention = false;                            // the joint attention's launch has room for modulation rows (attn_takes_mod)
     int self_all_parts = 0, cross_all_parts = 0;              // whether and how the parts of a query tile's keys go to one workgroup (attn_all_parts)
     uint64_t part_floats = 0;
 };

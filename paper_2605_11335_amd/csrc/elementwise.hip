@@ -6,75 +6,17 @@
 #include "common.h"
 #include "heads.h"
 #include "kernels.h"
+#include "modvec.h"
 
 namespace {
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
-
 // ---------------------------------------------------------------------------------------------
-// m[n] = W[n,:] . t + b[n]; a wave owns MV_ROWS consecutive rows so that each slice of t is read
-// once per MV_ROWS weight vectors and that many 16-byte loads are in flight per lane.  A row's sum
-// is accumulated in the same lane order whatever rows share its wave.
-constexpr int MV_ROWS = 4;
-// U steps of the walk over K are fetched together (U * (MV_ROWS + 2) loads in flight per lane): with one
-// step per round trip to memory the kernel ran at the latency of K / 512 + MV_ROWS dependent loads, not
-// at the bandwidth of the weight matrix.  A lane whose step lies past the end re-reads the row's last
-// chunk and adds nothing.
+// modulation vectors (modvec.h): a workgroup per MV_ROWS rows of each of its waves, grid rows are samples, grid planes matrices
 template <int U>
-__global__ __launch_bounds__(256) void modvec_kernel(WView W, uint64_t w_off, uint64_t b_off, uint64_t w_off2, uint64_t b_off2,
-                                                     const float* __restrict__ t, float* __restrict__ m, float* __restrict__ m2,
-                                                     int n0, int n1, int K, long m_bs, uint32x4* zero, uint32_t zeros) {
+__global__ __launch_bounds__(256) void modvec_kernel(ModRows j, uint32x4* zero, uint32_t zeros) {
     for (uint32_t i = ((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 256 + threadIdx.x; i < zeros; i += gridDim.x * gridDim.y * gridDim.z * 256)
         zero[i] = uint32x4{0u, 0u, 0u, 0u};
-    if (blockIdx.z) { w_off = w_off2; b_off = b_off2; m = m2; }      // the second matrix of a launch
-    t += (size_t)blockIdx.y * K;                 // one sample of the batch per grid row
-    m += (size_t)blockIdx.y * m_bs;
-    const int lane = threadIdx.x & 63;
-    const int n = n0 + (blockIdx.x * 4 + (threadIdx.x >> 6)) * MV_ROWS;
-    if (n >= n1) return;
-    float acc[MV_ROWS];
-#pragma unroll
-    for (int r = 0; r < MV_ROWS; ++r) acc[r] = 0.f;
-    const int nc = K / 8;                        // 16-byte chunks per row
-    for (int c0 = lane; c0 < nc; c0 += 64 * U) {
-        uint32x4 u[U][MV_ROWS];
-        floatx4 t0[U], t1[U];
-#pragma unroll
-        for (int q = 0; q < U; ++q) {
-            const int c = min(c0 + 64 * q, nc - 1);
-#pragma unroll
-            for (int r = 0; r < MV_ROWS; ++r) {
-                const int nr = min(n + r, n1 - 1);
-                u[q][r] = *(const uint32x4*)wv_ptr(W, w_off + ((uint64_t)nr * K + (uint64_t)c * 8) * 2);
-            }
-            t0[q] = *(const floatx4*)(t + c * 8);
-            t1[q] = *(const floatx4*)(t + c * 8 + 4);
-        }
-#pragma unroll
-        for (int q = 0; q < U; ++q) {
-            if (c0 + 64 * q < nc) {
-#pragma unroll
-                for (int r = 0; r < MV_ROWS; ++r) {
-                    float w[8];
-                    unpack8(u[q][r], w);
-                    acc[r] += w[0] * t0[q].x + w[1] * t0[q].y + w[2] * t0[q].z + w[3] * t0[q].w + w[4] * t1[q].x + w[5] * t1[q].y +
-                              w[6] * t1[q].z + w[7] * t1[q].w;
-                }
-            }
-        }
-    }
-    // lane r adds the bias of row r and writes it: the MV_ROWS bias loads go out side by side
-    float mine = 0.f;
-#pragma unroll
-    for (int r = 0; r < MV_ROWS; ++r) {
-        const float v = wave_sum(acc[r]);
-        if (lane == r) mine = v;
-    }
-    if (lane < MV_ROWS && n + lane < n1) m[n + lane] = mine + wv_bf16(W, b_off, n + lane);
+    modvec_rows<U>(j, blockIdx.z, blockIdx.y, j.n0 + (blockIdx.x * 4 + (threadIdx.x >> 6)) * MV_ROWS);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -369,14 +311,12 @@ inline int grid_for(long items, int per_block, int cap = 256 * 16) {
 
 }  // namespace
 
-hipError_t modvec_launch(const WView& W, uint64_t w_off, uint64_t b_off, const float* t, float* m, int n0, int n1,
-                         int K, int batch, long m_bs, hipStream_t s, uint64_t w_off2, uint64_t b_off2, float* m2,
-                         uint32_t* zero, uint32_t zero_words) {
-    if (n1 <= n0) return hipSuccess;
-    if (K % 8 || batch < 1 || batch > 65535) return hipErrorInvalidValue;
-    const dim3 grid((n1 - n0 + 4 * MV_ROWS - 1) / (4 * MV_ROWS), batch, w_off2 ? 2 : 1);
-    const int steps = (K / 8 + 63) / 64;         // steps of a lane's walk over K; taken 3 or 4 at a time
-#define CF_MV_CASE(U) hipLaunchKernelGGL(modvec_kernel<U>, grid, dim3(256), 0, s, W, w_off, b_off, w_off2, b_off2, t, m, m2, n0, n1, K, m_bs, (uint32x4*)zero, zero_words / 4)
+hipError_t modvec_launch(const ModRows& j, hipStream_t s, uint32_t* zero, uint32_t zero_words) {
+    if (j.n1 <= j.n0) return hipSuccess;
+    if (j.K % 8 || j.batch < 1 || j.batch > 65535 || j.mats < 1 || j.mats > 2) return hipErrorInvalidValue;
+    const dim3 grid((j.n1 - j.n0 + 4 * MV_ROWS - 1) / (4 * MV_ROWS), j.batch, j.mats);
+    const int steps = (j.K / 8 + 63) / 64;       // steps of a lane's walk over K; taken 3 or 4 at a time
+#define CF_MV_CASE(U) hipLaunchKernelGGL(modvec_kernel<U>, grid, dim3(256), 0, s, j, (uint32x4*)zero, zero_words / 4)
     if (steps == 1) CF_MV_CASE(1);
     else if (steps == 2) CF_MV_CASE(2);
     else if (steps % 3 == 0) CF_MV_CASE(3);

@@ -112,6 +112,19 @@ bool gemm_can_pair(const GemmArgs& g0, const GemmArgs& g1);
 bool gemm_heads_pay(const GemmArgs& g, const GemmArgs* second, double separate_us);      // HeadsOut, or rows and a pass over them
 hipError_t gemm_launch_pair(const GemmPlan& plan, const GemmArgs& g0, const GemmArgs& g1, hipStream_t s);
 
+// m[b][n] = sum_k W[n,k] t[b][k] + bias[n]  (fp32 out), rows [n0, n1), for `batch` vectors t + b*K -> m + b*m_bs;
+// mats = 2: a second matrix of the same shape (w_off[1], b_off[1]), its result at m[1].
+struct ModRows {
+    WView W;
+    uint64_t w_off[2], b_off[2];
+    const float* t;
+    float* m[2];
+    int n0, n1, K, batch, mats;
+    long m_bs;
+};
+// zero: so many words to clear for the launches that follow (a multiple of 4, 16-byte aligned), or NULL.
+hipError_t modvec_launch(const ModRows& j, hipStream_t s, uint32_t* zero = nullptr, uint32_t zero_words = 0);
+
 struct AttnArgs {
     const bf16* Q;      // [H, nq, hd] head-major
     const bf16* K;      // [H, nk, hd]
@@ -143,6 +156,9 @@ struct AttnArgs {
     float* even_state;
     uint32_t* even_flags;
     int even_units, even_last, even_cuts, even_wait;
+    // Modulation rows that workgroups behind those of attention compute (attn_takes_mod); n1 = 0: none.
+    ModRows mod;
+    int mod_blocks;            // of them (set by the launch)
 };
 enum { ALL_PARTS_IN_TURN = 1, ALL_PARTS_WAVES = 2 };      // AttnArgs::all_parts
 int attn_splits(int heads, int nq, int nk, int hd);      // parts to cut the keys into, for one sample's heads
@@ -153,16 +169,10 @@ int attn_deal(int H, int nq, int nk, int hd, int splits);              // how th
 uint64_t attn_deal_floats(int deal);                                   // scratch for the states of cut sweeps
 void attn_set_deal(AttnArgs* a, int deal, float* state, uint32_t* flags);      // after attn_set_split
 constexpr int ATTN_FLAGS = 1024;
+bool attn_takes_mod(const AttnArgs& a);        // whether its launch has room for a.mod (host arithmetic only; after the set calls)
 const char* attn_check(const AttnArgs& a);
 hipError_t attn_launch(const AttnArgs& a, hipStream_t s);
 int attn_waves(const AttnArgs& a);      // waves per workgroup attn_launch takes (host arithmetic only)
-
-// m[b][n] = sum_k W[n,k] t[b][k] + bias[n]  (fp32 out), rows [n0, n1), for `batch` vectors t + b*K -> m + b*m_bs.
-// w_off2 != 0: a second matrix of the same shape (bias at b_off2) in the same launch, its result at m2.
-// zero: so many words to clear for the launches that follow (a multiple of 4, 16-byte aligned), or NULL.
-hipError_t modvec_launch(const WView& W, uint64_t w_off, uint64_t b_off, const float* t, float* m,
-                         int n0, int n1, int K, int batch, long m_bs, hipStream_t s, uint64_t w_off2 = 0, uint64_t b_off2 = 0,
-                         float* m2 = nullptr, uint32_t* zero = nullptr, uint32_t zero_words = 0);
 
 // xn = LN(x) * (1 + scale) + shift  (fp32 in, bf16 out); with ln_w/ln_b (blob offsets, has_affine)
 // instead: xn = LN(x) * w + b.

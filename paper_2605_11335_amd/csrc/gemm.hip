@@ -124,8 +124,6 @@ int best_tile(const GemmArgs* const (&g)[2], Share share = ALL_OF_IT, double* ti
 bool can_meet(int tile, long workgroups, int parts, double sums) {
     return workgroups <= 256 && kTileCost[tile].bn >= 128 && (parts == 2 || sums >= 2.5e6);
 }
-// What it adds to the estimate of a launch whose workgroups end with their share of K (2304 x 3072 x 15360 in two: 24 us).
-double meet_us(int parts, double sums) { return 4.5 + 8.0 * (parts - 1) * sums / 3.5e6; }
 }  // namespace
 
 // How a cut sum is put together: by a kernel of its own that reads all parts, or by the launch of its last part, which
@@ -227,10 +225,14 @@ IdleFetch gemm_idle_fetch_view(const GemmPlan& plan, const GemmArgs& g, const Ge
 
 // Parts K is cut into.  A layer with few outputs and a long sum (the MLP-out layers of a short sequence or of a rank at
 // degree 4 or 8) has few tiles whatever their shape: cut, its workgroups multiply, each with a share of the walk.  The price
-// is that of the parts meeting (meet_us) or, where the chip does not hold them at once, of writing the partial sums and a second kernel
-// that adds them, in the order of the parts, and applies the epilogue: 6 us and two passes over them at 4 TB/s.  Taken where the estimate promises a twentieth (2304 x 3072 x 15360 in two parts:
-// a Flux-like single-stream block 660 -> 645 us).  A function of one sample's tokens and
+// is writing the partial sums and a second kernel that adds them, in the order of the parts, and applies the epilogue: 6 us and two
+// passes over them at 4 TB/s.  Taken where the estimate promises a twentieth (2304 x 3072 x 15360 in two parts: a Flux-like
+// single-stream block 660 -> 645 us).  A function of one sample's tokens and
 // the whole layer only, so that results depend neither on the batch nor on the panels a streamed layer is cut into.
+// Priced so also where one sample's parts meet within the launch for less: a batch does not fit the chip at once, and of the layers that
+// the lower price would cut besides, it pays for the sums in memory.  30 such, blocks of one / two / four samples, whole and cut: cut 2.2 % faster / 1.4 %
+// slower / 1.8 % slower in the mean (2760 x 1536 x 7232 in two: 292 -> 259, 484 -> 509, 882 -> 889 us; 1671 x 2048 x 10176 in three: 357 -> 360,
+// 586 -> 590, 1009 -> 1080).
 // At most three parts, because a batch that fills the chip pays for each and gains nothing (576 tokens x 3072 x 15360 per sample,
 // one sample / eight of them in 1, 2, 3, 4, 5 parts: 103/347, 79/363, 83/395, 69/442, 72/485 us).
 int gemm_splits(int rows, int rows2, int N, int K) {
@@ -246,10 +248,8 @@ int gemm_splits(int rows, int rows2, int N, int K) {
         if (g.ksplits != parts) continue;
         gemm_set_split(&g2, parts, nullptr);
         double us;
-        long workgroups;
-        const int tile = best_tile({&g, rows2 > 0 ? &g2 : nullptr}, ALL_OF_IT, &us, &workgroups);
-        const double sums = (double)(rows + rows2) * N;
-        if (parts > 1) us += can_meet(tile, workgroups, parts, sums) ? meet_us(parts, sums) : 6.0 + 2.0 * 4.0 * parts * sums / 4e6;
+        best_tile({&g, rows2 > 0 ? &g2 : nullptr}, ALL_OF_IT, &us);
+        if (parts > 1) us += 6.0 + 2.0 * 4.0 * parts * (double)(rows + rows2) * N / 4e6;
         if (parts == 1 || us < (best == 1 ? 0.95 : 1.0) * best_us) best = parts, best_us = us;
     }
     return best;

@@ -308,6 +308,15 @@ def test_block_linear_plans():
         assert lib.cf_op_linear_residual_form(p, 512, p, 0, -1, 64, 64, 512, p, None, p, tile[0], tile[1], parts, 0, p, nbytes, None) == B.CF_ERR_ARG
 
 
+def test_sums_that_a_batch_would_pay_for_stay_whole():
+    """A layer whose sum only one sample gains from cutting, because its parts meet within a launch that holds no more of them, is not cut:
+    the parts are those of every batch, which would put them together through memory."""
+    for rows, rows2, n, k in ((2760, 0, 1536, 7232), (2444, 400, 1536, 5952), (5485, 0, 1024, 4608), (1865, 0, 2048, 9408), (1591, 80, 2048, 10176), (2783, 64, 2048, 6336),
+                              (1131, 26, 3072, 11264), (2472, 0, 3072, 10560), (2000, 0, 3072, 9216), (4000, 0, 1536, 4608), (996, 0, 4096, 18176)):
+        assert B.cf_plan_block_linear(rows, n, k, True, rows2=rows2).parts == 1, (rows, rows2, n, k)
+    assert [B.cf_plan_block_linear(*shape, True).parts for shape in ((2304, 3072, 15360), (1320, 3072, 14336), (576, 3072, 15360))] == [2, 3, 2]
+
+
 def _tiles_of_the_last_round(problems, tile, parts):
     """(XCD, problem, first token, first feature, part) of the tiles past whole rounds of 256 workgroups, in the order in which the kernel
     walks them: an XCD's ids together, groups of row-tiles of one size, feature-tile-major."""

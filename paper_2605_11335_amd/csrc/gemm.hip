@@ -405,10 +405,10 @@ hipError_t mix_rate_launch(int iters, int waves, int reads16, int valu, int exps
 // The parts of one or two cut layers added up in order, and the epilogue of gemm_kernel.h: y = resid + gate * (sum + bias).
 // A thread per 4 features of a token.  Bound by the partial sums it reads (1320 x 3072 in three parts: 49 MB).
 namespace {
-struct ReduceArgs { GemmArgs g[2]; uint32_t blocks0; };
+struct ReduceArgs { GemmCore g[2]; uint32_t blocks0; };
 __global__ __launch_bounds__(256) void gemm_reduce_kernel(ReduceArgs a) {
     const bool second = blockIdx.x >= a.blocks0;
-    const GemmArgs& g = a.g[second];
+    const GemmCore& g = a.g[second];
     const int quads = (g.n1 - g.n0) / 4;
     const long q = (long)(blockIdx.x - (second ? a.blocks0 : 0)) * 256 + threadIdx.x;
     if (q >= (long)g.M * quads) return;

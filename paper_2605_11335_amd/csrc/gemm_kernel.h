@@ -110,6 +110,10 @@ struct Stage {
 // the slices, smaller ones would only add waits.  Where heads are placed (EPI_HEADS) on tiles of 64 and 128 features, the two waves of the
 // same tokens share a slice of all of them, which has the heads whole (elsewhere the barrier costs 0.4 us of a launch).
 constexpr bool heads_out(int epi) { return epi == EPI_HEADS || epi == EPI_HEADS_ERF; }
+// the arguments of a variant's kernels
+template <int EPI>
+using KernelArgs = std::conditional_t<heads_out(EPI), GemmArgs, GemmCore>;
+static_assert(sizeof(GemmCore) <= 216, "what only some variants read goes to those alone");
 constexpr bool bf16_out(int epi) { return epi == EPI_SPLIT_GELU || epi == EPI_SPLIT_GELU_ERF || heads_out(epi); }
 constexpr bool joint_slices(int bn, int epi) { return heads_out(epi) && bn < 256; }
 template <int BM, int BN, int EPI>
@@ -130,7 +134,7 @@ __device__ __forceinline__ void wave_lds_order() {
 // 134 MB, in 21 us, 26.8 with a batch fetched when it was needed).  A Wan-like share of 1320 rows, whose three gated layers end in
 // it: 607 -> 598 us.
 template <int BM, int BN, int EPI>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, floatx16 (&acc)[BN / 64][BM / 64], int m0, int n0, int part, int uw, char* smem) {
+__device__ __forceinline__ void gemm_epilogue(const KernelArgs<EPI>& g, floatx16 (&acc)[BN / 64][BM / 64], int m0, int n0, int part, int uw, char* smem) {
     constexpr int WM = BM / 2, WN = BN / 2;        // wave quadrant
     constexpr int MT = WM / 32, NT = WN / 32;      // 32x32 MFMA tiles per wave
     constexpr bool OUT_BF16 = bf16_out(EPI), JOINT = joint_slices(BN, EPI);
@@ -500,7 +504,7 @@ struct Meet {
 };
 __device__ __forceinline__ uint32_t meet_word(const uint32_t* w) { return __builtin_amdgcn_readfirstlane(__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)); }
 template <int BM, int BN>
-__device__ __forceinline__ void gemm_meet(const GemmArgs& g, floatx16 (&acc)[BN / 64][BM / 64], int m0, int n0, int part, uint32_t tile, int uw, char* smem) {
+__device__ __forceinline__ void gemm_meet(const GemmCore& g, floatx16 (&acc)[BN / 64][BM / 64], int m0, int n0, int part, uint32_t tile, int uw, char* smem) {
     using Mt = Meet<BM, BN>;
     using St = typename Mt::St;
     constexpr int MT = Mt::MT, UNITS = Mt::UNITS, QUADS = Mt::QUADS, ST = St::ST, RPI = St::RPI, CPR = St::CPR;
@@ -668,7 +672,7 @@ __device__ __forceinline__ void gemm_meet(const GemmArgs& g, floatx16 (&acc)[BN 
 // One tile of one problem: tokens m0.., features n0...  STRADDLE: the byte where the blob switches buffers falls
 // inside the tile's weight rows (at most one tile column of a launch), so each lane picks its base.
 template <int BM, int BN, int EPI, bool STRADDLE>
-__device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0, int part, uint32_t tile, int uw) {
+__device__ __forceinline__ void gemm_tile_run(const KernelArgs<EPI>& g, int m0, int n0, int part, uint32_t tile, int uw) {
     constexpr int WM = BM / 2, WN = BN / 2;        // wave quadrant
     constexpr int MT = WM / 32, NT = WN / 32;      // 32x32 MFMA tiles per wave
     constexpr int PA = MT % 2 ? 3 : 2;             // the activations go in thirds or halves, the weights in halves
@@ -857,7 +861,7 @@ __device__ __forceinline__ void gemm_tile_run(const GemmArgs& g, int m0, int n0,
 // 576 x 3072 x 12288: 164 us with the former loop, 111 with the 128x128 tile above, 85 with 128x64 (240 workgroups);
 // 64 x 3072 x 12288: 166, 102, 63 with 64x64; 512 x 512 x 2560: 31.4, 20.5, 12.2.
 template <int BM, int BN, int S, int EPI>
-__device__ __forceinline__ void gemm_ring_run(const GemmArgs& g, int m0, int n0, int part, uint32_t tile, int uw) {
+__device__ __forceinline__ void gemm_ring_run(const KernelArgs<EPI>& g, int m0, int n0, int part, uint32_t tile, int uw) {
     constexpr int WM = BM / 2, WN = BN / 2;        // wave quadrant
     constexpr int MT = WM / 32, NT = WN / 32;      // 32x32 MFMA tiles per wave
     constexpr int LA = BM / 32, LW = BN / 32, L = LA + LW;     // wave-loads (8 rows each) per wave and slab
@@ -976,26 +980,26 @@ __device__ __forceinline__ void gemm_ring_run(const GemmArgs& g, int m0, int n0,
 template <int BM, int BN>
 struct TileWalk {
     int tiles_m, tiles_n, GM;
-    __host__ __device__ __forceinline__ explicit TileWalk(const GemmArgs& g) {
+    __host__ __device__ __forceinline__ explicit TileWalk(const GemmCore& g) {
         tiles_m = (g.M + BM - 1) / BM;
         tiles_n = (g.n1 - g.n0 + BN - 1) / BN;
         const int n_groups = std::max(1, (tiles_m + 4) / 8);
         GM = (tiles_m + n_groups - 1) / n_groups;
     }
     struct Tile { int m0, n0, above, gsz; };       // first token and feature; row-tiles of its group before it, in all
-    __host__ __device__ __forceinline__ Tile at(const GemmArgs& g, uint32_t lid) const {
+    __host__ __device__ __forceinline__ Tile at(const GemmCore& g, uint32_t lid, int col_step = 1) const {
         const int group = lid / (GM * tiles_n), in = lid % (GM * tiles_n);
         const int first_m = group * GM;
         const int gsz = std::min(tiles_m - first_m, GM);
         int col = in / gsz;
-        if (g.col_step > 1) col = col * g.col_step % tiles_n;
+        if (col_step > 1) col = col * col_step % tiles_n;
         return Tile{(first_m + in % gsz) * BM, g.n0 + col * BN, in % gsz, gsz};
     }
 };
 
 // Workgroup `bid` of the `nblk` that problem owns.  S: stages of the ring loop, 0 = the quadrant-phase loop (two stages).
 template <int BM, int BN, int S, int EPI>
-__device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, uint32_t bid, uint32_t nblk, int uw) {
+__device__ __forceinline__ void gemm_tile_body(const KernelArgs<EPI>& g, uint32_t bid, uint32_t nblk, int uw) {
     // logical tile: XCD-contiguous id, then (part of K by part of K) the walk over the tiles
     const TileWalk<BM, BN> walk(g);
     const int tiles_m = walk.tiles_m, tiles_n = walk.tiles_n;
@@ -1004,7 +1008,9 @@ __device__ __forceinline__ void gemm_tile_body(const GemmArgs& g, uint32_t bid, 
     lid -= part * (tiles_m * tiles_n);
     if (EPI == EPI_LAST_PART) part = g.ksplits - 1;
     if (EPI == EPI_MEET && lane_here() == 0) __hip_atomic_fetch_add(g.words + lid * 4 + uw, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const auto tile = walk.at(g, lid);
+    int step = 1;
+    if constexpr (heads_out(EPI)) step = g.col_step;
+    const auto tile = walk.at(g, lid, step);
     const int m0 = tile.m0, n0 = tile.n0;
     if constexpr (S > 0) {
         gemm_ring_run<BM, BN, S, EPI>(g, m0, n0, part, lid, uw);
@@ -1023,8 +1029,9 @@ constexpr int min_waves() { return BM * BN <= 128 * 128 ? 2 : 1; }
 // of a double-stream block, App. B): a small problem's workgroups ride along with the large one's
 // instead of holding the chip for the length of their K loop.  The first problem's share of the grid
 // is padded to a multiple of 8 so that both keep the block-index-to-XCD correspondence.
+template <int EPI>
 struct GemmPair {
-    GemmArgs g[2];
+    KernelArgs<EPI> g[2];
     uint32_t tiles0, tiles0_pad, tiles;        // workgroups of the first problem, with padding, of both
 };
 
@@ -1046,7 +1053,7 @@ template <int BM, int BN>
 struct TilePanels {
     typename TileWalk<BM, BN>::Tile t;
     uint64_t k0, w_begin, w_bytes, a_begin, a_bytes;   // first byte of the part of K; panels in bytes of the weight blob (before k0) and of A (behind it)
-    __host__ __device__ __forceinline__ TilePanels(const GemmArgs& g, bool cut, uint32_t lid) {
+    __host__ __device__ __forceinline__ TilePanels(const GemmCore& g, bool cut, uint32_t lid) {
         const TileWalk<BM, BN> walk(g);
         const uint32_t whole = walk.tiles_m * walk.tiles_n, part = cut ? lid / whole : 0;
         t = walk.at(g, lid - part * whole);
@@ -1065,7 +1072,7 @@ struct TilePanels {
 struct Panel { uint64_t base; uint32_t bytes, row_bytes; };
 // The panels of one problem's tiles among them, the lane's tile (if any) being `lid`.  -> panels listed so far
 template <int BM, int BN, int EPI>
-__device__ __forceinline__ int list_panels(const GemmArgs& g, Panel* panels, int n, bool on, uint32_t lid, bool with_a) {
+__device__ __forceinline__ int list_panels(const GemmCore& g, Panel* panels, int n, bool on, uint32_t lid, bool with_a) {
     const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     const TilePanels<BM, BN> p(g, cut_sum(EPI), on ? lid : 0);
     const int lane0 = __ffsll((unsigned long long)__ballot(on)) - 1;
@@ -1078,7 +1085,7 @@ __device__ __forceinline__ int list_panels(const GemmArgs& g, Panel* panels, int
 }
 // tiles0, tiles0_pad, tiles: as in GemmPair; one problem: all three alike
 template <int BM, int BN, int EPI>
-__device__ __forceinline__ void gemm_idle_fetch(const GemmArgs& g0, const GemmArgs& g1, uint32_t tiles0, uint32_t tiles0_pad, uint32_t tiles, const IdleFetch& f, uint32_t bid, int uw) {
+__device__ __forceinline__ void gemm_idle_fetch(const GemmCore& g0, const GemmCore& g1, uint32_t tiles0, uint32_t tiles0_pad, uint32_t tiles, const IdleFetch& f, uint32_t bid, int uw) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     Panel* const panels = (Panel*)smem;                        // at most 2 x 32
     int* const count = (int*)(smem + 64 * sizeof(Panel));
@@ -1115,13 +1122,13 @@ __device__ __forceinline__ void gemm_idle_fetch(const GemmArgs& g0, const GemmAr
 constexpr bool can_idle_fetch(int bm, int bn, int epi, bool pair) { return bm * bn > 128 * 128 && epi != EPI_LAST_PART && !(pair && bm * bn == 256 * 256); }
 
 template <int BM, int BN, int S, int EPI>
-__global__ __launch_bounds__(256, (min_waves<BM, BN>())) void gemm_bf16_kernel(GemmArgs g, uint32_t tiles, IdleFetch f) {
+__global__ __launch_bounds__(256, (min_waves<BM, BN>())) void gemm_bf16_kernel(KernelArgs<EPI> g, uint32_t tiles, IdleFetch f) {
     const int uw = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (!can_idle_fetch(BM, BN, EPI, false) || blockIdx.x < tiles) gemm_tile_body<BM, BN, S, EPI>(g, blockIdx.x, tiles, uw);
     else gemm_idle_fetch<BM, BN, EPI>(g, g, tiles, tiles, tiles, f, blockIdx.x, uw);
 }
 template <int BM, int BN, int S, int EPI>
-__global__ __launch_bounds__(256, (min_waves<BM, BN>())) void gemm_pair_kernel(GemmPair p, IdleFetch f) {
+__global__ __launch_bounds__(256, (min_waves<BM, BN>())) void gemm_pair_kernel(GemmPair<EPI> p, IdleFetch f) {
     const int uw = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if constexpr (can_idle_fetch(BM, BN, EPI, true)) {
         if (blockIdx.x >= p.tiles) { gemm_idle_fetch<BM, BN, EPI>(p.g[0], p.g[1], p.tiles0, p.tiles0_pad, p.tiles, f, blockIdx.x, uw); return; }
@@ -1175,13 +1182,13 @@ hipError_t launch(const GemmArgs& g_in, const GemmArgs* second, hipStream_t s) {
         static const hipError_t allowed = allow_smem(gemm_bf16_kernel<BM, BN, S, EPI>, smem);
         if (allowed != hipSuccess) return allowed;
         const IdleFetch f = can_idle_fetch(BM, BN, EPI, false) ? gemm_idle_fetch_plan(BM, BN, cut, g, nullptr, tiles, 0) : IdleFetch{};
-        hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, S, EPI>), dim3(tiles + f.workgroups), dim3(256), smem, s, g, tiles, f);
+        hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, S, EPI>), dim3(tiles + f.workgroups), dim3(256), smem, s, (const KernelArgs<EPI>&)g, tiles, f);
     } else if constexpr (BM * BN == 65536 && cut_sum(EPI)) {
         return hipErrorInvalidValue;               // does not fit the registers; gemm_plan never asks for it
     } else {
         static const hipError_t allowed = allow_smem(gemm_pair_kernel<BM, BN, S, EPI>, smem);
         if (allowed != hipSuccess) return allowed;
-        GemmPair p;
+        GemmPair<EPI> p;
         p.g[0] = g;
         p.g[1] = *second;
         p.tiles0 = tiles;

@@ -118,10 +118,10 @@ __device__ __forceinline__ void qk_relayout_part(const RelayoutArgs& r, int bid,
     const int lane = threadIdx.x & 63;
     const int lph = r.hd / 8, lsh = r.hd == 128 ? 4 : 3;        // lanes per head vector
     const int vpw = 64 >> lsh, grp = lane >> lsh, sub = lane & (lph - 1);
-    float w[2][8] = {};
+    uint32x4 w_raw[2] = {};            // (as they are in memory, for the registers' sake)
     if (r.has_norm) {
 #pragma unroll
-        for (int t = 0; t < 2; ++t) unpack8(*(const uint32x4*)wv_ptr(r.W, (t ? r.kn_off : r.qn_off) + sub * 16), w[t]);
+        for (int t = 0; t < 2; ++t) w_raw[t] = *(const uint32x4*)wv_ptr(r.W, (t ? r.kn_off : r.qn_off) + sub * 16);
     }
     const int n_other = r.n_heads - r.h_local;
     for (uint32_t item = (uint32_t)bid * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); item < (uint32_t)r.rows * 3u; item += (uint32_t)nblk * 4u) {
@@ -141,6 +141,8 @@ __device__ __forceinline__ void qk_relayout_part(const RelayoutArgs& r, int bid,
             cs = *(const floatx4*)(r.rope_cos + ro);
             sn = *(const floatx4*)(r.rope_sin + ro);
         }
+        float w[8];
+        unpack8(tns ? w_raw[1] : w_raw[0], w);
         for (int h4 = 0; h4 < r.n_heads; h4 += 4 * vpw) {        // four vectors of a lane group in flight
             uint32x4 u[4];
 #pragma unroll
@@ -158,10 +160,7 @@ __device__ __forceinline__ void qk_relayout_part(const RelayoutArgs& r, int bid,
                     *(uint32x4*)dst = u[q];
                     continue;
                 }
-                float wt[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) wt[e] = tns ? w[1][e] : w[0][e];
-                *(uint32x4*)dst = head_piece<false>(u[q], r.hd, r.has_norm, wt, turn, cs, sn);
+                *(uint32x4*)dst = head_piece<false>(u[q], r.hd, r.has_norm, w, turn, cs, sn);
             }
         }
     }
@@ -250,7 +249,9 @@ struct PreAttnArgs {
     int seg[7];                                // end of each segment: qk0, vt0, qk1, vt1, peer_qk, peer_vt, peer_attn
 };
 
-__global__ __launch_bounds__(256) void pre_attention_kernel(PreAttnArgs a) {
+// Six workgroups on a CU at least: with five, which 81 registers leave, 1422 + 60 rows of 12 heads, two ranks, took 24 us instead of 17 (the
+// double-stream block at batch 4 729 instead of 699), 1155 rows of 24 heads in blocks of two samples 529 to 532 instead of 521.
+__global__ __launch_bounds__(256, 6) void pre_attention_kernel(PreAttnArgs a) {
     const int b = blockIdx.x;
     if (b == 0 && a.zero)
         for (int i = threadIdx.x; i < ATTN_FLAGS; i += 256) a.zero[i] = 0;

@@ -471,12 +471,15 @@ hipError_t dispatch(const GemmPlan& plan, const GemmArgs& g, const GemmArgs* sec
 hipError_t gemm_launch_as(const GemmPlan& plan, const GemmArgs& g, hipStream_t s) { return dispatch(plan, g, nullptr, s); }
 hipError_t gemm_launch(const GemmArgs& g, hipStream_t s) { return gemm_launch_as(gemm_plan(g, nullptr), g, s); }
 
-// two layers share a launch if they have one epilogue and both or neither have their sum in parts
 // Whether a launch had better place its heads itself (`second`: two layers at once) than leave them to a pass that takes separate_us.
 // What it costs there: the tile may have to be another (heads_fit), and a quadrant's slices of 32 tokens take 1.2 us each longer than
 // plain rows, 2 where they are normed and 3 where they are rotated, in every round, or in as many as there are tiles of heads if there are
 // several (even_step).  1320 x 9216 x 3072, normed, one round of 192x256 tiles: 67.6 us and 9.1 of the pass, or 73; 2304 x 21504 x 3072,
 // three rounds: 265.4 and 17, or 266.  Rotated, 512 + 64 rows: 51 and 6, or 58.
+// On tiles of up to 128 features (one slice a wave, nothing to hide the first loads of tables and weights behind) that is 1.5 us and more, a
+// 128x128 tile a whole slice: 32 + 604 x 3072 x 1024, rotated, 15.0 us and 9.9 of the pass that moves the peers' rows besides, or 20.1 and 8.4;
+// 180 x 3968 x 512 6.7 and 6.3, or 8.6 and 6.2.  Beside 128-feature tiles that apply the activation half a slice's time is left of it (blocks of 128 to
+// 1600 rows and 512 to 3072 features -0.8 to +2.6 us of 50 to 160).
 bool gemm_heads_pay(const GemmArgs& g, const GemmArgs* second, double separate_us) {
     const GemmArgs* const with[2] = {&g, second};
     GemmArgs plain[2] = {g, second ? *second : g};
@@ -487,11 +490,14 @@ bool gemm_heads_pay(const GemmArgs& g, const GemmArgs* second, double separate_u
     long tiles = 0;
     for (const GemmArgs* p : with)
         if (p) tiles += (long)((p->M + t.bm - 1) / t.bm) * ((p->N + t.bn - 1) / t.bn);
-    const double slices = t.bn < 256 ? 0.5 : t.bm / 64, slice_us = g.heads.r.rope_cos ? 3.0 : g.heads.r.has_norm ? 2.0 : 1.2;
+    const double slice_us = g.heads.r.rope_cos ? 3.0 : g.heads.r.has_norm ? 2.0 : 1.2;
     const double rounds = std::ceil((double)tiles / (256 * t.per_cu));
-    return placed + slices * slice_us * std::max(1.0, rounds * std::min(g.n_split, g.N) / g.N) <= apart + separate_us;
+    double extra = (t.bn < 256 ? 0.5 : t.bm / 64) * slice_us * std::max(1.0, rounds * std::min(g.n_split, g.N) / g.N);
+    if (t.bn < 128 || (t.bn < 256 && g.n_split >= g.N)) extra = 1.5 + t.bm * t.bn / 16384.0 * (0.5 + slice_us);
+    return placed + extra <= apart + separate_us;
 }
 
+// two layers share a launch if they have one epilogue, both or neither have their sum in parts and both or neither place heads
 bool gemm_can_pair(const GemmArgs& g0, const GemmArgs& g1) {
     return g0.epi == g1.epi && g0.act_erf == g1.act_erf && g0.heads.on == g1.heads.on && (g0.ksplits > 1) == (g1.ksplits > 1);
 }

@@ -37,6 +37,14 @@ def _resource_usage(lines):
     return usage
 
 
+def _check_usage(src, usage):
+    # a kernel that touches scratch memory has lost its register arrays, and one with spilled vector registers copies them to and from
+    # accumulation registers in its loops: both are build errors
+    for kname, u in usage.items():
+        if u.get("ScratchSize [bytes/lane]", 0) or u.get("VGPRs Spill", 0):
+            raise RuntimeError(f"{src}: kernel {kname} spills registers: {u}")
+
+
 def build_library(verbose: bool = True) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objs = []
@@ -55,11 +63,7 @@ def build_library(verbose: bool = True) -> str:
         out = "\n".join(l for l in lines if "warning:" in l or "error:" in l)
         if p.returncode != 0:
             raise RuntimeError(f"hipcc failed on {src}:\n" + "\n".join(lines))
-        for kname, u in usage.items():
-            # a kernel that touches scratch memory has lost its register arrays: treat as a build error (a register
-            # "spilled" without scratch is one copied to an accumulation register)
-            if u.get("ScratchSize [bytes/lane]", 0):
-                raise RuntimeError(f"{src}: kernel {kname} uses scratch memory: {u}")
+        _check_usage(src, usage)
         if verbose and out.strip():
             print(out, file=sys.stderr)
     link = [hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", "-pthread", "-o", LIB] + objs

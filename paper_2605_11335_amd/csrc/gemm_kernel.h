@@ -514,9 +514,9 @@ __device__ __forceinline__ void gemm_meet(const GemmCore& g, floatx16 (&acc)[BN 
     uint32_t* const word = g.words + tile * 4 + wave;
     char* const slots = smem + wave * (Mt::SLOTS * St::BYTES);
     const __amdgpu_buffer_rsrc_t sums = make_rsrc(g.part + (size_t)tile * P * (BM * BN), (uint32_t)P * (BM * BN * 4));
-    auto sum_at = [&](int q, int u) { return (uint32_t)(((q * 4 + wave) * UNITS + u) * St::BYTES); };
+    auto sum_at = [&](int q, int u) { return (uint32_t)__builtin_amdgcn_readfirstlane(((q * 4 + wave) * UNITS + u) * St::BYTES); };
     auto inside = [&](int u) { return m_q + u % MT * 32 < g.M && n_q + u / MT * St::FP < g.n1; };
-    const int first = (part + P - wave % P) % P;               // the wave's own units: first, first + P, ...
+    const int first = __builtin_amdgcn_readfirstlane((part + P - wave % P) % P);       // the wave's own units: first, first + P, ...
 
     slab_handover();                           // every wave is done reading the slabs
     uint32_t seen = 0;
@@ -1011,7 +1011,13 @@ __device__ __forceinline__ void gemm_tile_body(const KernelArgs<EPI>& g, uint32_
     int step = 1;
     if constexpr (heads_out(EPI)) step = g.col_step;
     const auto tile = walk.at(g, lid, step);
-    const int m0 = tile.m0, n0 = tile.n0;
+    int m0 = tile.m0, n0 = tile.n0;
+    if constexpr (EPI == EPI_MEET) {           // scalars that the compiler would keep in vector registers, and loop over at every copy
+        m0 = __builtin_amdgcn_readfirstlane(m0);
+        n0 = __builtin_amdgcn_readfirstlane(n0);
+        part = __builtin_amdgcn_readfirstlane(part);
+        lid = __builtin_amdgcn_readfirstlane(lid);
+    }
     if constexpr (S > 0) {
         gemm_ring_run<BM, BN, S, EPI>(g, m0, n0, part, lid, uw);
     } else {
@@ -1183,7 +1189,7 @@ hipError_t launch(const GemmArgs& g_in, const GemmArgs* second, hipStream_t s) {
         if (allowed != hipSuccess) return allowed;
         const IdleFetch f = can_idle_fetch(BM, BN, EPI, false) ? gemm_idle_fetch_plan(BM, BN, cut, g, nullptr, tiles, 0) : IdleFetch{};
         hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, S, EPI>), dim3(tiles + f.workgroups), dim3(256), smem, s, (const KernelArgs<EPI>&)g, tiles, f);
-    } else if constexpr (BM * BN == 65536 && cut_sum(EPI)) {
+    } else if constexpr ((BM * BN == 65536 && cut_sum(EPI)) || (BN < 128 && EPI == EPI_MEET)) {
         return hipErrorInvalidValue;               // does not fit the registers; gemm_plan never asks for it
     } else {
         static const hipError_t allowed = allow_smem(gemm_pair_kernel<BM, BN, S, EPI>, smem);

@@ -51,6 +51,10 @@ typedef struct cf_linear_plan {
 } cf_linear_plan;
 int cf_plan_block_linear(int32_t rows, int32_t rows2, int32_t batch, int32_t n_features, int32_t k, int32_t residual, cf_linear_plan* plan);
 
+/* Whether the workgroups of the parts of such a cut sum put it together themselves, within one launch: *meet 1 or 0 (a kernel of its
+ * own does it, or the last part's launch; no cut sum).  Arguments and errors as above. */
+int cf_plan_block_meet(int32_t rows, int32_t rows2, int32_t batch, int32_t n_features, int32_t k, int32_t* meet);
+
 /* Host-only view of how that launch (of a cut sum: of its parts) lets CUs without a tile in the last round of workgroups fetch for the others:
  * `fetching` workgroups (0: none) behind `tiles` with a tile or as padding, which read every stride-th 512 bytes of the listed panels, one slab of 64
  * features per pace_ns, and stop deadline_ns after they began.  A panel is (XCD, first or second layer, 0 weights or 1 activations, first byte, bytes), of

@@ -89,7 +89,7 @@ CORE_EXPORTS = ["cf_create", "cf_destroy", "cf_last_error", "cf_blob_bytes", "cf
                 "cf_stats_reset", "cf_set_profiling", "cf_set_adaptive_waits", "cf_kernel_times", "cf_kernel_times_reset",
                 "cf_sync", "cf_op_checksum", "cf_op_checksum_noalloc"]
 #: what include/chunkflow_diag.h declares: single-kernel hooks, planner views, the matrix-core rate probe
-DIAG_EXPORTS = ["cf_plan_attention", "cf_plan_block_attention", "cf_plan_linear", "cf_plan_block_linear", "cf_plan_block_fetch", "cf_op_linear", "cf_op_linear_residual", "cf_op_linear_residual_form",
+DIAG_EXPORTS = ["cf_plan_attention", "cf_plan_block_attention", "cf_plan_linear", "cf_plan_block_linear", "cf_plan_block_meet", "cf_plan_block_fetch", "cf_op_linear", "cf_op_linear_residual", "cf_op_linear_residual_form",
                 "cf_op_attention", "cf_op_attention_form", "cf_op_ln_modulate", "cf_op_modvec", "cf_op_mfma_rate", "cf_op_mix_rate"]
 EXPORTS = CORE_EXPORTS + DIAG_EXPORTS
 
@@ -126,6 +126,7 @@ def lib() -> C.CDLL:
         _lib.cf_plan_attention.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)]
         _lib.cf_plan_block_attention.argtypes = [C.c_int32] * 5 + [C.POINTER(cf_attention_plan)]
         _lib.cf_plan_linear.argtypes = [C.c_int32, C.c_int32, C.POINTER(C.c_int32)]
+        _lib.cf_plan_block_meet.argtypes = [C.c_int32] * 5 + [C.POINTER(C.c_int32)]
         _lib.cf_plan_block_linear.argtypes = [C.c_int32] * 6 + [C.POINTER(cf_linear_plan)]
         _lib.cf_plan_block_fetch.argtypes = [C.c_int32] * 6 + [C.POINTER(cf_fetch_plan)]
         _lib.cf_register_block.argtypes = [C.c_void_p, C.c_int32, C.c_void_p, C.c_uint64]
@@ -410,6 +411,13 @@ def cf_plan_block_linear(rows: int, n_features: int, k: int, residual: bool, row
     out = cf_linear_plan()
     _check(lib().cf_plan_block_linear(rows, rows2, batch, n_features, k, int(residual), C.byref(out)))
     return out
+
+
+def cf_plan_block_meet(rows: int, n_features: int, k: int, rows2: int = 0, batch: int = 1) -> bool:
+    """Whether the parts of such a residual layer's sum, if it is cut, put it together within their launch (host arithmetic only)."""
+    out = C.c_int32()
+    _check(lib().cf_plan_block_meet(rows, rows2, batch, n_features, k, C.byref(out)))
+    return bool(out.value)
 
 
 def cf_plan_block_fetch(rows: int, n_features: int, k: int, residual: bool, rows2: int = 0, batch: int = 1) -> cf_fetch_plan:

@@ -1113,28 +1113,9 @@ int cf_plan_linear(int32_t m_rows, int32_t n_features, int32_t* tile_rows) {
     return CF_OK;
 }
 
-int cf_plan_block_linear(int32_t rows, int32_t rows2, int32_t batch, int32_t n_features, int32_t k, int32_t residual, cf_linear_plan* plan) {
-    if (rows <= 0 || rows2 < 0 || batch <= 0 || ((int64_t)rows + rows2) * batch > 0x7fffffff || n_features <= 0 || k <= 0 || !plan)
-        return cf_fail(nullptr, CF_ERR_ARG, "cf_plan_block_linear: positive sizes and a result pointer are required");
-    GemmArgs g[2] = {};
-    const int parts = residual ? gemm_splits(rows, rows2, n_features, k) : 1;
-    for (int i = 0; i < 2; ++i) {
-        g[i].M = (i ? rows2 : rows) * batch; g[i].N = g[i].n1 = n_features; g[i].K = k;
-        gemm_set_split(&g[i], parts, nullptr);
-        g[i].may_meet = parts > 1;
-    }
-    const GemmPlan p = gemm_plan(g[0], rows2 ? &g[1] : nullptr);
-    plan->parts = g[0].ksplits;
-    gemm_tile_shape(p.tile, &plan->tile_tokens, &plan->tile_features);
-    plan->last_tile_tokens = plan->last_tile_features = 0;
-    if (p.last >= 0) gemm_tile_shape(p.last, &plan->last_tile_tokens, &plan->last_tile_features);
-    return CF_OK;
-}
-
-int cf_plan_block_fetch(int32_t rows, int32_t rows2, int32_t batch, int32_t n_features, int32_t k, int32_t residual, cf_fetch_plan* plan) {
-    if (rows <= 0 || rows2 < 0 || batch <= 0 || ((int64_t)rows + rows2) * batch > 0x7fffffff || n_features <= 0 || k < 64 || !plan)
-        return cf_fail(nullptr, CF_ERR_ARG, "cf_plan_block_fetch: positive sizes and a result pointer are required");
-    GemmArgs g[2] = {};
+// A layer, or two in one launch, over `batch` samples as the plan calls describe them.
+namespace {
+GemmPlan plan_layers(int rows, int rows2, int batch, int n_features, int k, bool residual, GemmArgs (&g)[2]) {
     const int parts = residual ? gemm_splits(rows, rows2, n_features, k) : 1;
     for (int i = 0; i < 2; ++i) {
         g[i].M = (i ? rows2 : rows) * batch; g[i].N = g[i].n1 = n_features; g[i].K = g[i].lda = k;
@@ -1143,10 +1124,42 @@ int cf_plan_block_fetch(int32_t rows, int32_t rows2, int32_t batch, int32_t n_fe
         gemm_set_split(&g[i], parts, nullptr);
         g[i].may_meet = parts > 1;
     }
+    return gemm_plan(g[0], rows2 ? &g[1] : nullptr);
+}
+bool layers_ok(int rows, int rows2, int batch, int n_features, int k, const void* result) {
+    return rows > 0 && rows2 >= 0 && batch > 0 && ((int64_t)rows + rows2) * batch <= 0x7fffffff && n_features > 0 && k > 0 && result;
+}
+}  // namespace
+
+int cf_plan_block_linear(int32_t rows, int32_t rows2, int32_t batch, int32_t n_features, int32_t k, int32_t residual, cf_linear_plan* plan) {
+    if (!layers_ok(rows, rows2, batch, n_features, k, plan))
+        return cf_fail(nullptr, CF_ERR_ARG, "cf_plan_block_linear: positive sizes and a result pointer are required");
+    GemmArgs g[2] = {};
+    const GemmPlan p = plan_layers(rows, rows2, batch, n_features, k, residual != 0, g);
+    plan->parts = g[0].ksplits;
+    gemm_tile_shape(p.tile, &plan->tile_tokens, &plan->tile_features);
+    plan->last_tile_tokens = plan->last_tile_features = 0;
+    if (p.last >= 0) gemm_tile_shape(p.last, &plan->last_tile_tokens, &plan->last_tile_features);
+    return CF_OK;
+}
+
+int cf_plan_block_meet(int32_t rows, int32_t rows2, int32_t batch, int32_t n_features, int32_t k, int32_t* meet) {
+    if (!layers_ok(rows, rows2, batch, n_features, k, meet))
+        return cf_fail(nullptr, CF_ERR_ARG, "cf_plan_block_meet: positive sizes and a result pointer are required");
+    GemmArgs g[2] = {};
+    *meet = plan_layers(rows, rows2, batch, n_features, k, true, g).meet;
+    return CF_OK;
+}
+
+int cf_plan_block_fetch(int32_t rows, int32_t rows2, int32_t batch, int32_t n_features, int32_t k, int32_t residual, cf_fetch_plan* plan) {
+    if (!layers_ok(rows, rows2, batch, n_features, k, plan) || k < 64)
+        return cf_fail(nullptr, CF_ERR_ARG, "cf_plan_block_fetch: positive sizes and a result pointer are required");
+    GemmArgs g[2] = {};
+    const GemmPlan p = plan_layers(rows, rows2, batch, n_features, k, residual != 0, g);
     const GemmArgs* const second = rows2 ? &g[1] : nullptr;
     uint32_t tiles;
     static_assert(sizeof(FetchPanel) == sizeof plan->panel[0], "a panel as the header has it");
-    const IdleFetch f = gemm_idle_fetch_view(gemm_plan(g[0], second), g[0], second, &tiles, (FetchPanel*)plan->panel, &plan->panels);
+    const IdleFetch f = gemm_idle_fetch_view(p, g[0], second, &tiles, (FetchPanel*)plan->panel, &plan->panels);
     plan->tiles = (int32_t)tiles;
     plan->fetching = (int32_t)f.workgroups;
     plan->with_activations = f.with_a;

@@ -93,7 +93,7 @@ bool heads_fit(const TileCost& t, const GemmArgs& g) {
 }
 // What a launch covers of a cut sum: all its parts, all but the last, the last
 enum Share { ALL_OF_IT, BEFORE_LAST, LAST };
-int best_tile(const GemmArgs* const (&g)[2], Share share = ALL_OF_IT, double* time = nullptr, long* workgroups = nullptr) {
+int best_tile(const GemmArgs* const (&g)[2], Share share = ALL_OF_IT, double* time = nullptr) {
     int best = -1;
     double best_us = 0;
     for (int i = 0; i < GEMM_TILES; ++i) {
@@ -109,19 +109,17 @@ int best_tile(const GemmArgs* const (&g)[2], Share share = ALL_OF_IT, double* ti
                 K = std::max(K, p->ksplits > 1 ? p->part_slabs * 64 : p->K);
             }
         const double us = tile_time(t, tiles, K);
-        if (best < 0 || us < best_us) {
-            best = i, best_us = us;
-            if (workgroups) *workgroups = tiles;
-        }
+        if (best < 0 || us < best_us) best = i, best_us = us;
     }
     if (time) *time = best_us;
     return best;
 }
-// Parts meet where every one of their workgroups has a CU and it costs less than a kernel that reads them all: meeting is some 3 us
+// Parts meet where every one of their workgroups has a CU (of two layers with the padding between them, behind which the last ones would wait for
+// a whole round on CUs of their XCD: 1653 + 16 x 1536 x 7232 in three, 258, 92 us instead of 67 and 12) and it costs less than a kernel that reads them all: meeting is some 3 us
 // (two parts) or 7 (three) and a third of a microsecond per MB of sums, on tiles of 64 features 10 and more; the kernel 5.5 and 0.5 or 0.6 per MB.
 // Apart / meeting, with weights from HBM: 576 x 3072 x 12288 in two 64.2 / 62.4 us, 1600 x 3072 x 12288 in two 120.7 / 114.0, 1000 x 2048 x 10240 in three
 // 51.4 / 52.6, 1152 x 3072 x 12288 in three 97.5 / 95.5, 1320 x 3072 x 14336 in three 111.0 / 108.6; 64x64 tiles: 150 x 3072 x 13376 in three 43.9 / 51.7.
-bool can_meet(int tile, long workgroups, int parts, double sums) {
+bool can_meet(int tile, uint32_t workgroups, int parts, double sums) {
     return workgroups <= 256 && kTileCost[tile].bn >= 128 && (parts == 2 || sums >= 2.5e6);
 }
 }  // namespace
@@ -133,9 +131,10 @@ bool can_meet(int tile, long workgroups, int parts, double sums) {
 GemmPlan gemm_plan(const GemmArgs& g, const GemmArgs* second) {
     const GemmArgs* const both[2] = {&g, second};
     double all, before, last, bytes = 0;
-    long workgroups;
-    GemmPlan one = {best_tile(both, ALL_OF_IT, &all, &workgroups), -1, 0};
+    GemmPlan one = {best_tile(both, ALL_OF_IT, &all), -1, 0};
     if (g.ksplits <= 1) return one;
+    const TileCost& t = kTileCost[one.tile];
+    const uint32_t tiles = tile_count(g, t.bm, t.bn, true), workgroups = second ? pad_tiles(tiles) + tile_count(*second, t.bm, t.bn, true) : tiles;
     const GemmPlan two = {best_tile(both, BEFORE_LAST, &before), best_tile(both, LAST, &last), 0};
     for (const GemmArgs* p : both)
         if (p) bytes += 4.0 * p->M * (p->n1 - p->n0);
@@ -209,7 +208,7 @@ IdleFetch gemm_idle_fetch_view(const GemmPlan& plan, const GemmArgs& g, const Ge
     GemmArgs a[2] = {g, second ? *second : g};
     if (cut && plan.last >= 0)
         for (GemmArgs& p : a) --p.ksplits;
-    const uint32_t tiles0 = tile_count(a[0], bm, bn, cut), pad = second ? (tiles0 + 7u) & ~7u : tiles0;
+    const uint32_t tiles0 = tile_count(a[0], bm, bn, cut), pad = second ? pad_tiles(tiles0) : tiles0;
     *tiles = second ? pad + tile_count(a[1], bm, bn, cut) : tiles0;
     *n_panels = 0;
     if (!can_idle_fetch(bm, bn, cut ? EPI_PARTIAL : g.epi, second != nullptr)) return IdleFetch{};

@@ -1168,6 +1168,9 @@ inline uint32_t tile_count(const GemmArgs& g, int bm, int bn, bool cut) {
     return (uint32_t)(((g.M + bm - 1) / bm) * ((g.n1 - g.n0 + bn - 1) / bn)) * (cut ? g.ksplits : 1);
 }
 
+// the first problem's share of a launch of two
+inline uint32_t pad_tiles(uint32_t tiles) { return (tiles + 7u) & ~7u; }
+
 // The order in which the feature-tiles of a launch whose tiles are not alike (heads, activated) are walked, so that each XCD, which has a
 // range of them, gets its share of either sort: every step-th, a golden section of them.  For launches of more than two rounds.
 inline int even_step(int tiles_n) {
@@ -1198,7 +1201,7 @@ hipError_t launch(const GemmArgs& g_in, const GemmArgs* second, hipStream_t s) {
         p.g[0] = g;
         p.g[1] = *second;
         p.tiles0 = tiles;
-        p.tiles0_pad = (p.tiles0 + 7u) & ~7u;
+        p.tiles0_pad = pad_tiles(p.tiles0);
         p.tiles = p.tiles0_pad + tile_count(*second, BM, BN, cut);
         const IdleFetch f = can_idle_fetch(BM, BN, EPI, true) ? gemm_idle_fetch_plan(BM, BN, cut, g, second, p.tiles, p.tiles - p.tiles0_pad) : IdleFetch{};
         hipLaunchKernelGGL((gemm_pair_kernel<BM, BN, S, EPI>), dim3(p.tiles + f.workgroups), dim3(256), smem, s, p, f);

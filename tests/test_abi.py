@@ -317,6 +317,19 @@ def test_sums_that_a_batch_would_pay_for_stay_whole():
     assert [B.cf_plan_block_linear(*shape, True).parts for shape in ((2304, 3072, 15360), (1320, 3072, 14336), (576, 3072, 15360))] == [2, 3, 2]
 
 
+def test_parts_meet_where_all_their_workgroups_have_a_cu():
+    """Of two layers in one launch with the padding to eight workgroups between them: 18 + 6 + 234 do not."""
+    assert B.cf_plan_block_meet(2304, 3072, 15360) and B.cf_plan_block_meet(1320, 3072, 14336) and B.cf_plan_block_meet(512, 3072, 12288, rows2=64)
+    for rows, rows2 in ((1653, 16), (1659, 32)):
+        p = B.cf_plan_block_linear(rows, 1536, 7232, True, rows2=rows2)
+        assert (p.parts, p.tile_tokens, p.tile_features) == (3, 128, 256) and not B.cf_plan_block_meet(rows, 1536, 7232, rows2=rows2)
+    assert B.cf_plan_block_meet(1653 - 128, 1536, 7232, rows2=128)                        # 18 + 6 + 216
+    assert not B.cf_plan_block_meet(2304, 3072, 15360, batch=4) and not B.cf_plan_block_meet(40000, 512, 512)
+    for bad in ((0, 64, 64), (64, 0, 64), (64, 64, 0)):
+        with pytest.raises(B.ChunkflowError):
+            B.cf_plan_block_meet(*bad)
+
+
 def _tiles_of_the_last_round(problems, tile, parts):
     """(XCD, problem, first token, first feature, part) of the tiles past whole rounds of 256 workgroups, in the order in which the kernel
     walks them: an XCD's ids together, groups of row-tiles of one size, feature-tile-major."""

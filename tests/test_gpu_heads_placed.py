@@ -77,3 +77,20 @@ def test_few_rows_beside_the_peers_go_through_the_pass(kind, d, hd, n, txt):
     _, moved_streamed, _, _ = outputs(cfg, params, inputs, 0.0)
     print(cfg, tiles, moved, flush=True)
     assert tiles in (["64x64"], ["128x64"], ["128x128"]) and moved == moved_streamed > 0
+
+
+# ranks' shares, with own and other heads side by side in a tile: staged whole by the waves of the same tokens, or (256 features) quadrant by quadrant
+@pytest.mark.parametrize("kind,d,hd,n,txt,rank,norm,rope,tile",
+                         [(DOUBLE, 512, 64, 2080, 80, 1, True, False, "64x64"), (DOUBLE, 512, 64, 2288, 80, 1, False, False, "128x64"), (DOUBLE, 1024, 128, 3488, 80, 1, True, True, "128x128"),
+                          (DOUBLE, 1024, 64, 4080, 80, 0, True, False, "128x256"), (SINGLE, 1536, 128, 5008, 0, 1, True, False, "192x256"), (SINGLE, 1024, 128, 9248, 0, 1, True, True, "192x256"),
+                          (SINGLE, 2048, 128, 9248, 0, 0, True, True, "256x256"), (SINGLE, 2048, 128, 9248, 0, 1, True, False, "256x256"),
+                          (DOUBLE, 1024, 64, 8064, 80, 1, True, False, "256x256")])
+def test_ranks_place_their_heads_on_every_tile(kind, d, hd, n, txt, rank, norm, rope, tile):
+    cfg = block(kind, d, hd, n, txt, 2, rank, 1, norm, rope)
+    params, inputs = wl.gen_block_params(cfg, 0), wl.gen_block_inputs(cfg, 0)
+    _, moved, tiles, placed = outputs(cfg, params, inputs, 1.0)
+    _, moved_rows, _, rows = outputs(cfg, params, inputs, 0.0)
+    print(cfg, tiles, moved, moved_rows, flush=True)
+    assert tiles == [tile] and moved == moved_rows - 4.0 * cfg.n_local * 3 * d        # the rows' part of the pass
+    for k in placed:
+        assert np.array_equal(placed[k].view(np.uint8), rows[k].view(np.uint8)), k

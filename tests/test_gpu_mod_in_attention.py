@@ -22,13 +22,17 @@ CASES = {
 
 
 def outputs(cfg, params, inputs, r):
+    """-> operations of the product launched ahead of the block, outputs"""
     run = BlockRunner(cfg)
     try:
         run.ctx.set_resident_fraction(r)
         run.register_params(0, params)
         t = run.make_io(inputs)
+        run.ctx.cf_set_profiling(True)
         run.run_block(0, t)
-        return {k: t[k].cpu().numpy() for k in ("y", "y_txt") if k in t}
+        run.ctx.cf_sync()
+        ahead = sum(k["flops"] for k in run.ctx.cf_kernel_times() if k["name"] == "modvec")
+        return ahead, {k: t[k].cpu().numpy() for k in ("y", "y_txt") if k in t}
     finally:
         run.close()
 
@@ -42,8 +46,13 @@ def test_vectors_computed_beside_attention(name):
     print(name, p.parts, p.all_parts, p.deal, p.waves, groups, flush=True)
     assert p.deal == 0 and p.all_parts != 2 and groups <= 224 * (2 if p.waves == 4 else 1) * (2 if cfg.head_dim == 64 else 1)
     params, inputs = wl.gen_block_params(cfg, 0), wl.gen_block_inputs(cfg, 0)
-    got = outputs(cfg, params, inputs, 1.0)
-    for k, v in outputs(cfg, params, inputs, 0.0).items():
+    ahead, got = outputs(cfg, params, inputs, 1.0)
+    whole, streamed = outputs(cfg, params, inputs, 0.0)
+    # two of three vectors (of six, of each stream's six) go ahead, the others beside attention; while weights stream all of them
+    vectors = {wl.KIND_SINGLE: 3, wl.KIND_DIT: 6, wl.KIND_DOUBLE: 12}[cfg.kind]
+    first = 4 if cfg.kind == wl.KIND_DOUBLE else 2
+    assert (ahead, whole) == tuple(2.0 * batch * v * cfg.d * cfg.d for v in (first, vectors))
+    for k, v in streamed.items():
         assert np.array_equal(v.view(np.uint8), got[k].view(np.uint8)), k
     if batch == 1:
         ref = ob.block_forward(cfg, params, inputs)

@@ -19,8 +19,8 @@ const char* gemm_check(const GemmArgs& g) {
         const HeadsOut& h = g.heads;
         const int section = h.r.n_heads * h.r.hd;
         if (h.on && ((h.r.hd != 64 && h.r.hd != 128) || section <= 0 || section % 256 || g.n_split % section || g.n_split / section > 3 - h.first || g.n0 % 256 ||
-                     h.first < 0 || h.rps < 0 || (h.rps && g.M % h.rps)))
-            return "gemm: heads must be whole tensors of 64 or 128 wide heads";
+                     h.first < 0 || h.rps < 0 || (h.rps && (h.rps < 32 || g.M % h.rps))))
+            return "gemm: heads must be whole tensors of 64 or 128 wide heads, of samples of 32 tokens and more";
         if (g.n_split > 0 && !h.on && (!g.out0 || (g.ld0 % 8) || ((uintptr_t)g.out0 % 16))) return "gemm: out0 must be 16-byte aligned with ld0 a multiple of 8";
         if (g.n_split < g.N && (!g.out1 || (g.ld1 % 8) || (g.col1_off % 8) || ((uintptr_t)g.out1 % 16)))
             return "gemm: out1 must be 16-byte aligned with ld1 and col1_off multiples of 8";

@@ -233,18 +233,12 @@ __device__ __forceinline__ void gemm_epilogue(const KernelArgs<EPI>& g, floatx16
                 if (JOINT) __syncthreads();
                 const int here = lane_here(), chunk = here % CPR, row = here / CPR, hh_c = nb - sec * D + chunk * 8, hh = hh_c >> (lsh + 3), sub = (hh_c >> 3) & ((1 << lsh) - 1);
                 const bool own = hh >= r.h0 && hh < r.h0 + r.h_local;
-                // sample of the token o tokens behind token i of sample b (o < 32); its number there
+                // sample of the token o tokens behind token i of sample b (o < 32, and samples are no shorter: gemm_check); its number there
                 auto sample = [&](int b, int i, int o, int& io) __attribute__((always_inline)) {
                     io = i + o;
-                    if (!h.rps) return b;
-                    if (h.rps >= 32) {
-                        const bool next = io >= h.rps;
-                        io -= next ? h.rps : 0;
-                        return b + next;
-                    }
-                    const int n = io / h.rps;
-                    io -= n * h.rps;
-                    return b + n;
+                    const bool next = h.rps && io >= h.rps;
+                    io -= next ? h.rps : 0;
+                    return b + next;
                 };
                 // Most slices lie in one sample and one segment of the joint sequence: then a lane's addresses are one offset from a scalar
                 // base, and its rows a constant apart.  (With an address made for each row the slices took twice as long.)

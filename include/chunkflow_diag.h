@@ -43,7 +43,8 @@ int cf_plan_linear(int32_t m_rows, int32_t n_features, int32_t* tile_rows);
 
 /* Host-only view of how a block launches a linear layer of k input features over `rows` tokens of each of `batch`
  * samples (rows2 > 0: with a second layer over rows2 tokens in the same launch, as the streams of a double-stream block): its
- * tile of tokens x features exactly.  residual: with the gated fp32 residual, whose sum over k may be cut into `parts` parts
+ * tile of tokens x features exactly (of a q, k, v projection: where it leaves rows; one that places its heads needs whole ones in a tile's half,
+ * and may take another).  residual: with the gated fp32 residual, whose sum over k may be cut into `parts` parts
  * (a matter of one sample alone, and the bits with it); the tile is then that of the parts, and last_tile_* is not zero where
  * the last part has a launch of its own, which puts the sum together.  No GPU is touched. */
 typedef struct cf_linear_plan {

@@ -66,7 +66,7 @@ struct GemmCore {
     uint32_t* words;    // where the parts' workgroups put the sum together themselves (GemmPlan::meet): gemm_meet_words words that are zero
 };
 // A layer as the host describes it.  Only launches that place heads take it all along: 264 bytes more cost a launch 0.2 us, whatever it
-// does (307 x 1024 x 4224 24.9 us / 24.8 without, 1024 x 1024 x 300 11.5 / 11.3, 512 x 2048 x 512 9.24 / 9.08).
+// does (307 x 1024 x 4224 24.9 us / 24.8 without, 300 x 1024 x 1024 11.5 / 11.3, 512 x 2048 x 512 9.24 / 9.08).
 struct GemmArgs : GemmCore {
     int may_meet;       // the parts' workgroups may put the sum together: part holds gemm_meet_floats floats and words is set
     int col_step;       // > 1: feature-tiles are walked in steps of so many (set by the launch)
